@@ -34,12 +34,6 @@ struct GranRec { GranEntry e[REC_SLOTS]; };
 
 // Tokens of rollout space one advantage workgroup owns.
 constexpr int ADV_TILE = 8192;
-// Segment descriptors staged in LDS per pass over a tile, plus look-ahead so a
-// 16-token chunk that starts in the last owned segment can be finished.
-constexpr int SEG_BATCH = 256;
-constexpr int SEG_AHEAD = 16;
-
-
 // Workspace carved by dc_plan for dc_gather: per-slot source descriptors
 // (validated, clamped) and, for every granule boundary g * GATHER_GRAN of the
 // destination token axis, the first slot that ends after it.

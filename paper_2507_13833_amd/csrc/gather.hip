@@ -18,12 +18,13 @@
 //     traffic in the vector memory pipeline; when one slot covers all 64 chunks of a wave
 //     instruction the source address is scalar arithmetic, else every lane selects its
 //     slot with a few compares against scalar registers.  No LDS, no barrier;
-//   dense tiles (many short sequences) - the tile's slots are staged in LDS and each
-//     lane finds its chunk's slot by binary search.
+//   dense granules (more slots than that: short sequences) - the wave stages the granule's slots in
+//     LDS words of its own, every lane finds its chunks' slots by bisection, and what is left of the
+//     slots' edges is dealt out again, one element per lane.  No barrier here either.
 // A chunk inside one slot takes one (mis)aligned 16-byte source load (plus one dword
 // and a byte funnel shift for 1- and 2-byte fields) and one aligned 16-byte store;
 // a chunk that touches a slot boundary, padding or the arena end is copied element
-// by element.
+// by element, all its elements in flight together.
 #include <hip/hip_ext.h>
 #include "dc_device.h"
 #include "dc_internal.h"
@@ -31,7 +32,6 @@
 namespace dc {
 
 constexpr int GATHER_BLOCK = 256;
-constexpr int NSEG = SEG_BATCH + SEG_AHEAD;
 static_assert(GRAN_PER_TILE == GATHER_BLOCK / WAVE, "one granule per wave");
 constexpr int64_t GATHER_RIDE_MIN_WGS = 8192;                         // ~4 workgroups per wave slot of the chip
 constexpr int32_t LEN_MASK = (1 << LENSH_SHIFT) - 1;
@@ -39,7 +39,6 @@ static_assert(GATHER_GRAN == WAVE * 16, "a wave covers its granule with 1, 2 or 
 static_assert(GRAN_PER_TILE + 1 <= 8, "the tile's slice of the granule table is one 8-dword scalar load");
 static_assert(GRAN_TABLE_PAD >= 8, "that load never leaves the table");
 static_assert(sizeof(GranEntry) == 16, "one 16-byte load per record entry");
-static_assert(SEG_BATCH == GATHER_BLOCK, "one descriptor per lane plus the look-ahead");
 
 struct GatherArgs {
     int32_t        n_seq;
@@ -53,23 +52,6 @@ struct GatherArgs {
     uint32_t       tiles;                        // tiles per field
     uint32_t       n_carriers, n_riders;         // fields the grid walks (first in the field table), fields riding along
 };
-
-// Slot descriptors of the tile being moved, relative to the tile's first token.
-struct SegLds {
-    int32_t start[NSEG];           // first destination token of the slot (REL_FAR: none)
-    int32_t end[NSEG];             // one past its last token
-    int64_t addr[NSEG];            // source byte address of tile-relative token 0 (may lie before the buffer)
-};
-
-// Largest k in [0, n) with start[k] <= tok, or -1.
-__device__ __forceinline__ int find_seg(const int32_t* start, int n, int32_t tok) {
-    int lo = 0, hi = n;                       // first k with start[k] > tok
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (start[mid] <= tok) lo = mid + 1; else hi = mid;
-    }
-    return lo - 1;
-}
 
 // Payload pointers are rebuilt from integers (base + offset arithmetic in scalar registers
 // or LDS); typing them as global-address-space pointers keeps the accesses global_load /
@@ -123,81 +105,7 @@ __device__ __forceinline__ u32x4 realign(u32x4 v, uint32_t x, uint32_t sh) {
     return o;
 }
 
-// Stage descriptors of slots seg_base + lane and (lanes < SEG_AHEAD) seg_base + SEG_BATCH + lane,
-// up to slot seg_last, for the field whose rollout buffers are src[] and the tile that
-// starts at token tile_begin.
-__device__ __forceinline__ void stage_slots(const GatherArgs& a, SegLds& sg, const char* const* src, int lg,
-                                            int seg_base, int seg_last, int64_t tile_begin) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int k = q * SEG_BATCH + (int)threadIdx.x;
-        const int j = seg_base + k;
-        if (q == 0 || threadIdx.x < SEG_AHEAD) {
-            int32_t st = REL_FAR, en = REL_FAR;
-            int64_t ad = 0;
-            if (j <= seg_last) {
-                const int64_t d = a.dst_tok_off[j] - tile_begin;
-                st = (int32_t)max((int64_t)-REL_FAR, min((int64_t)REL_FAR, d));
-                en = st + a.slot_len[j];
-                ad = reinterpret_cast<int64_t>(src[a.slot_shard[j]]) + ((a.slot_src_off[j] - d) << lg);
-            }
-            sg.start[k] = st; sg.end[k] = en; sg.addr[k] = ad;
-        }
-    }
-}
-
-// One destination tile of one field with element size 1 << lg, slots staged in LDS (whole
-// workgroup, barriers inside).  On return every lane has passed a barrier after its last LDS read.
-__device__ __forceinline__ void move_tile_dense(const GatherArgs& a, SegLds& sg, const char* const* src, int lg,
-                                                char* dst_field, int seg_first, int seg_last, int64_t tile_begin,
-                                                int32_t tile_len) {
-    const int tpc = 16 >> lg;                              // tokens per 16-byte chunk
-    const int tid = threadIdx.x;
-    gptr_w dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(dst_field) + (tile_begin << lg));
-    int seg_base = seg_first;
-    int32_t pass_begin = 0;
-    for (;;) {
-        stage_slots(a, sg, src, lg, seg_base, seg_last, tile_begin);
-        __syncthreads();
-        const int n_left = seg_last - seg_base + 1;
-        const int n_all = min(n_left, NSEG);
-        // more than SEG_BATCH slots left and the next batch's first slot starts inside the tile
-        const bool more = n_left > SEG_BATCH && sg.start[SEG_BATCH] < tile_len;
-        const int32_t pass_end = more ? sg.start[SEG_BATCH] : tile_len;
-
-#pragma unroll 1
-        for (int u = 0; u < (1 << lg); ++u) {              // 1 << lg chunks per lane, one at a time: this path
-            const int32_t c0 = (tid + u * GATHER_BLOCK) * tpc;   // is the rare one and must not cost registers
-            if (c0 < pass_begin || c0 >= pass_end) continue;
-            int k = find_seg(sg.start, n_all, c0);
-            if (k >= 0 && c0 + tpc <= sg.end[k] && c0 + tpc <= tile_len) {
-                // inside one slot: one load, one store
-                gptr ad = reinterpret_cast<gptr>(sg.addr[k] + ((int64_t)c0 << lg));
-                u32x4 v;
-                uint32_t x;
-                load_chunk(ad, v, x);
-                gstore16(dst + (tid + u * GATHER_BLOCK) * 16, realign(v, x, (uint32_t)reinterpret_cast<uintptr_t>(ad) & 3u));
-            } else {
-                // touches a slot boundary, padding or the arena end: per element
-                for (int e = 0; e < tpc; ++e) {
-                    const int32_t tok = c0 + e;
-                    if (tok >= tile_len) break;
-                    while (k + 1 < n_all && sg.start[k + 1] <= tok) ++k;
-                    if (k >= 0 && tok < sg.end[k])
-                        store_elem(lg, dst + ((int64_t)tok << lg),
-                                   load_elem(lg, reinterpret_cast<gptr>(sg.addr[k] + ((int64_t)tok << lg))));
-                }
-            }
-        }
-        __syncthreads();
-        if (!more) break;
-        // rare: more than SEG_BATCH slots start inside this tile - next batch
-        seg_base += SEG_BATCH;
-        pass_begin = pass_end;
-    }
-}
-
-// ---------------------------------------------------------------- sparse tiles: one wave, no LDS
+// ---------------------------------------------------------------- sparse granules: one wave, no LDS
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 #define DC_CONSTANT __attribute__((address_space(4)))
@@ -266,7 +174,7 @@ __device__ __forceinline__ void move_wave_sparse(const FieldDesc& fd, int n_src,
     const int es = 1 << lg;
     const int tpc = 16 >> lg;                              // tokens per 16-byte chunk
     const int tpi = WAVE * tpc;                            // tokens one wave instruction covers
-    const int lane = threadIdx.x & (WAVE - 1);
+    int lane = threadIdx.x & (WAVE - 1);
     gptr_w dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(BACK ? back_dst : fd.dst) + (wave_begin << lg));
 
     SlotS e[REC_SLOTS];
@@ -370,6 +278,167 @@ __device__ __forceinline__ void move_wave_sparse(const FieldDesc& fd, int n_src,
             for (int r = 0; r < EB; ++r)
                 if (ok[r]) store_elem(lg, dst + ((int64_t)(c0 + e0 + r) << lg), val[r]);
         }
+    }
+}
+
+// ---------------------------------------------------------------- dense granules: one wave, LDS words of its own
+// The slots that reach into a granule, relative to its first token, DENSE_SLOTS at a time.  A pass serves the chunks
+// that begin before slot DENSE_OWN of it; the slots behind are the look-ahead such a chunk may reach into (16 tokens at
+// most, one per slot).  Lane k stages slot k; the last entry says "no slot".
+// Bound by latency: the granule's table entries, the slots' descriptors and the payload are each one trip to memory for
+// the whole granule.  The gather kernel takes 6.6 us for 15 550 tokens in 64 sequences, 34 us for 3.3 M tokens in 15 360
+// and 261 us for 31.5 M tokens in 65 536 (5 fields).  With the slots staged per tile by the workgroup, one chunk per lane
+// at a time and an edge chunk's elements one after the other it took 14.7, 70 and 307 us.
+constexpr int DENSE_SLOTS = WAVE - 1;
+constexpr int DENSE_OWN = DENSE_SLOTS - 16;
+constexpr int DENSE_CHUNKS = GATHER_GRAN / 4;                  // chunks of a granule of 4-byte elements, the most there are
+struct WaveSlots {
+    int32_t  start[WAVE];          // first destination token of the slot (REL_FAR: none)
+    int32_t  end[WAVE];            // one past its last token
+    int64_t  addr[WAVE];           // source byte address of the granule's token 0 (may lie before the buffer)
+    uint32_t adv[WAVE];            // (advantage arena) bits of the slot's advantage
+    uint32_t edge[DENSE_CHUNKS];   // chunks that do not lie inside one slot: first token | (slot + 1) << 16
+};
+static_assert(GATHER_GRAN <= (1 << 16), "a token of the granule and a slot share a word");
+
+// Stage slots from `base` on; src0: the only rollout buffer (n_src == 1), else fd.src[] has the slot's.
+__device__ __forceinline__ void stage_wave_slots(const GatherArgs& a, WaveSlots& sg, const FieldDesc& fd, int n_src,
+                                                 const char* src0, int lg, int lane, int base, int last, int64_t wave_begin) {
+    const int j = base + lane;
+    int32_t st = REL_FAR, en = REL_FAR;
+    int64_t ad = 0;
+    if (lane < DENSE_SLOTS && j <= last) {
+        const int64_t d = a.dst_tok_off[j] - wave_begin;
+        st = (int32_t)max((int64_t)-REL_FAR, min((int64_t)REL_FAR, d));
+        en = st + a.slot_len[j];
+        const char* from = src0;
+        if (n_src > 1) from = fd.src[a.slot_shard[j] & (DC_MAX_SRC_SHARDS - 1)];
+        ad = reinterpret_cast<int64_t>(from) + ((a.slot_src_off[j] - d) << lg);
+    }
+    __builtin_amdgcn_wave_barrier();                       // (the wave's reads of the pass before come first)
+    sg.start[lane] = st; sg.end[lane] = en; sg.addr[lane] = ad;
+    __builtin_amdgcn_wave_barrier();
+}
+
+// First token behind the chunks of this pass; *more: the granule has slots left behind them.
+__device__ __forceinline__ int32_t dense_pass_end(const WaveSlots& sg, int base, int last, int32_t limit, bool* more) {
+    const int32_t next = __builtin_amdgcn_readfirstlane(sg.start[DENSE_OWN]);
+    *more = last - base + 1 > DENSE_SLOTS && next < limit;
+    return *more ? next : limit;
+}
+
+// Lanes of the mask below this one.
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// The probe distance a bisection over n slots starts with (2 p - 1 >= n; n <= DENSE_SLOTS).
+__device__ __forceinline__ int dense_first_step(int n) {
+    return 1 << (31 - __builtin_clz((uint32_t)max(n, 1)));
+}
+
+// The wave's granule of one field, slots first .. last reaching into it (same arguments as move_wave_sparse otherwise).
+template <bool BACK>
+__device__ __forceinline__ void move_wave_dense(const GatherArgs& a, WaveSlots& sg, const FieldDesc& fd, int n_src,
+                                                char* back_dst, const char* back_src, int lg, int first, int last,
+                                                int64_t wave_begin, int32_t limit) {
+    const int es = 1 << lg;
+    const int lg_tpc = 4 - lg, tpc = 16 >> lg;             // tokens per 16-byte chunk
+    int lane = threadIdx.x & (WAVE - 1);
+    gptr_w dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(BACK ? back_dst : fd.dst) + (wave_begin << lg));
+    constexpr int MAXU = 4, NARROWU = 2;                   // chunks per lane; of 1- and 2-byte elements
+    int base = first;
+    int32_t pass_begin = 0;
+    for (;;) {
+        asm volatile("" : "+v"(lane), "+s"(base));         // (what depends on them is worked out here, not kept across passes and fields)
+        stage_wave_slots(a, sg, fd, BACK ? 1 : n_src, BACK ? back_src : fd.src[0], lg, lane, base, last, wave_begin);
+        bool more;
+        const int32_t pass_end = dense_pass_end(sg, base, last, limit, &more);
+        // ---- every chunk's slot: the last one that starts at or before it ----
+        int k[MAXU];
+#pragma unroll
+        for (int u = 0; u < MAXU; ++u) k[u] = -1;
+#pragma unroll 1
+        for (int step = dense_first_step(min(last - base + 1, DENSE_SLOTS)); step >= 1; step >>= 1) {   // (uniform)
+#pragma unroll
+            for (int u = 0; u < MAXU; ++u)
+                if (u < es && sg.start[min(k[u] + step, WAVE - 1)] <= (u * WAVE + lane) * tpc) k[u] += step;
+        }
+        // ---- chunks inside one slot; the others are listed ----
+        uint32_t in_mask = 0;                              // bit u: chunk u is inside one slot
+        int n_edge = 0;                                    // (uniform)
+#pragma unroll
+        for (int u = 0; u < MAXU; ++u) {
+            if (u < es) {                                  // uniform
+                const int32_t c0 = (u * WAVE + lane) * tpc;
+                const bool mine = c0 >= pass_begin && c0 < pass_end;
+                const bool in = mine && k[u] >= 0 && c0 + tpc <= min(sg.end[max(k[u], 0)], limit);
+                if (in) in_mask |= 1u << u;
+                const uint64_t edges = __ballot(mine && !in);
+                if (mine && !in) sg.edge[n_edge + lanes_below(edges)] = (uint32_t)c0 | ((uint32_t)(k[u] + 1) << 16);
+                n_edge += __popcll(edges);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        u32x4 v[MAXU];
+        uint32_t x[NARROWU], shift[NARROWU];               // (4-byte sources are 4-byte aligned)
+#pragma unroll
+        for (int u = 0; u < MAXU; ++u)
+            if (in_mask & (1u << u)) {
+                gptr from = reinterpret_cast<gptr>(sg.addr[k[u]] + (u * WAVE + lane) * 16);
+                if (u < NARROWU) {
+                    shift[u] = (uint32_t)reinterpret_cast<uintptr_t>(from) & 3u;
+                    load_chunk(from, v[u], x[u]);
+                } else {
+                    v[u] = gload16_a4(from);
+                }
+            }
+        // ---- the listed chunks, one element per lane: the first EDGE_MAX elements' loads go out with the loads above ----
+        constexpr int EDGE_MAX = 2;
+        const int n_items = n_edge << lg_tpc;              // (uniform)
+        uint32_t val[EDGE_MAX];
+        int32_t tok[EDGE_MAX];                             // the element's token, -1: nothing there
+        auto edge_load = [&](int from_item) {
+#pragma unroll
+            for (int r = 0; r < EDGE_MAX; ++r) {
+                tok[r] = -1;
+                val[r] = 0;
+                const int item = from_item + r * WAVE + lane;
+                if (from_item + r * WAVE < n_items) {      // uniform
+                    const uint32_t e = sg.edge[min(item >> lg_tpc, DENSE_CHUNKS - 1)];
+                    const int32_t t = (int32_t)(e & 0xFFFFu) + (item & (tpc - 1));
+                    int q = (int)(e >> 16) - 1;
+                    if (item < n_items) {
+                        while (q + 1 < WAVE && sg.start[q + 1] <= t) ++q;
+                        if (q >= 0 && t < sg.end[q] && t < limit) {
+                            tok[r] = t;
+                            val[r] = load_elem(lg, reinterpret_cast<gptr>(sg.addr[q] + ((int64_t)t << lg)));
+                        }
+                    }
+                }
+            }
+        };
+        auto edge_store = [&]() {
+#pragma unroll
+            for (int r = 0; r < EDGE_MAX; ++r)
+                if (tok[r] >= 0) store_elem(lg, dst + ((int64_t)tok[r] << lg), val[r]);
+        };
+        if (n_items > 0) edge_load(0);
+        asm volatile("" : "+v"(lane));
+#pragma unroll
+        for (int u = 0; u < MAXU; ++u)
+            if (in_mask & (1u << u)) {
+                gstore16(dst + (u * WAVE + lane) * 16, u < NARROWU ? realign(v[u], x[u], shift[u]) : v[u]);
+            }
+        if (n_items > 0) edge_store();
+#pragma unroll 1
+        for (int item = EDGE_MAX * WAVE; item < n_items; item += EDGE_MAX * WAVE) {
+            edge_load(item);
+            edge_store();
+        }
+        if (!more) break;
+        base += DENSE_OWN;
+        pass_begin = pass_end;
     }
 }
 
@@ -532,110 +601,135 @@ __device__ __forceinline__ void adv_wave_sparse(const FieldDesc& mk, int n_src, 
     }
 }
 
-// The same for a tile with many short sequences: slots staged in LDS (whole workgroup).
-__device__ __forceinline__ void adv_tile_dense(const GatherArgs& a, SegLds& sg, uint32_t* sg_adv, const char* const* src,
-                                               const AdvSynth& s, char* mask_dst, int seg_first, int seg_last,
-                                               int64_t tile_begin, int32_t tile_len) {
-    const int tid = threadIdx.x;
+// The same for a granule with more slots than its record holds: slots and their advantages staged in the wave's LDS words.
+__device__ __forceinline__ void adv_wave_dense(const GatherArgs& a, WaveSlots& sg, const FieldDesc& mk, int n_src,
+                                               const AdvSynth& s, int first, int last, int64_t wave_begin, int32_t limit) {
+    int lane = threadIdx.x & (WAVE - 1);
     const int N = a.n_seq;
-    gptr_w dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(s.dst) + (tile_begin << 2));
-    gptr_w mdst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(mask_dst) + tile_begin);
-    int seg_base = seg_first;
+    gptr_w dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(s.dst) + (wave_begin << 2));
+    gptr_w mdst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(mk.dst) + wave_begin);
+    constexpr int NU = GATHER_GRAN / ADV_TPI;
+    int base = first;
     int32_t pass_begin = 0;
     for (;;) {
-        stage_slots(a, sg, src, 0, seg_base, seg_last, tile_begin);          // addresses in mask bytes
+        asm volatile("" : "+v"(lane), "+s"(base));
+        uint32_t av = 0;
+        if (lane < DENSE_SLOTS && base + lane <= last) {
+            const uint32_t sq = min((uint32_t)s.perm[base + lane], (uint32_t)(N - 1));
+            av = __float_as_uint(s.adv_seq[sq]);
+        }
+        stage_wave_slots(a, sg, mk, n_src, mk.src[0], 0, lane, base, last, wave_begin);            // addresses in mask bytes
+        sg.adv[lane] = av;
+        __builtin_amdgcn_wave_barrier();
+        bool more;
+        const int32_t pass_end = dense_pass_end(sg, base, last, limit, &more);
+        int k[NU];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int k = q * SEG_BATCH + tid;
-            const int j = seg_base + k;
-            if (q == 0 || tid < SEG_AHEAD) {
-                uint32_t v = 0;
-                if (j <= seg_last) {
-                    const uint32_t sq = min((uint32_t)s.perm[j], (uint32_t)(N - 1));
-                    v = __float_as_uint(s.adv_seq[sq]);
-                }
-                sg_adv[k] = v;
-            }
-        }
-        __syncthreads();
-        const int n_left = seg_last - seg_base + 1;
-        const int n_all = min(n_left, NSEG);
-        const bool more = n_left > SEG_BATCH && sg.start[SEG_BATCH] < tile_len;
-        const int32_t pass_end = more ? sg.start[SEG_BATCH] : tile_len;
+        for (int u = 0; u < NU; ++u) k[u] = -1;
 #pragma unroll 1
-        for (int u = 0; u < GATHER_TILE_TOKENS / (GATHER_BLOCK * ADV_TPC); ++u) {
-            const int32_t c0 = (tid + u * GATHER_BLOCK) * ADV_TPC;
-            if (c0 < pass_begin || c0 >= pass_end) continue;
-            int k = find_seg(sg.start, n_all, c0);
-            if (k >= 0 && c0 + ADV_TPC <= sg.end[k] && c0 + ADV_TPC <= tile_len) {
-                gptr ad = reinterpret_cast<gptr>(sg.addr[k] + c0);
-                uint32_t w0, w1;
-                load_mask4(ad, w0, w1);
-                const uint32_t m = mask4_of(w0, w1, ad);
-                gstore16(dst + (tid + u * GATHER_BLOCK) * 16, select_adv4(m, sg_adv[k]));
-                gstore4(mdst + (tid + u * GATHER_BLOCK) * 4, m);
-            } else {
-                for (int r = 0; r < ADV_TPC; ++r) {
-                    const int32_t tok = c0 + r;
-                    if (tok >= tile_len) break;
-                    while (k + 1 < n_all && sg.start[k + 1] <= tok) ++k;
-                    if (k >= 0 && tok < sg.end[k]) {
-                        const uint32_t m = load_elem(0, reinterpret_cast<gptr>(sg.addr[k] + tok));
-                        store_elem(2, dst + ((int64_t)tok << 2), m ? sg_adv[k] : 0u);
-                        store_elem(0, mdst + tok, m);
-                    }
-                }
+        for (int step = dense_first_step(min(last - base + 1, DENSE_SLOTS)); step >= 1; step >>= 1) {   // (uniform)
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+                if (sg.start[min(k[u] + step, WAVE - 1)] <= (u * WAVE + lane) * ADV_TPC) k[u] += step;
+        }
+        uint32_t in_mask = 0;
+        int n_edge = 0;                                    // (uniform)
+        gptr from[NU];
+        uint32_t w0[NU], w1[NU], sel[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int32_t c0 = (u * WAVE + lane) * ADV_TPC;
+            const int at = max(k[u], 0);
+            const bool mine = c0 >= pass_begin && c0 < pass_end;
+            const bool in = mine && k[u] >= 0 && c0 + ADV_TPC <= sg.end[at] && c0 + ADV_TPC <= limit;
+            if (in) in_mask |= 1u << u;
+            from[u] = reinterpret_cast<gptr>(sg.addr[at] + c0);
+            sel[u] = sg.adv[at];
+            const uint64_t edges = __ballot(mine && !in);
+            if (mine && !in) sg.edge[n_edge + lanes_below(edges)] = (uint32_t)c0 | ((uint32_t)(k[u] + 1) << 16);
+            n_edge += __popcll(edges);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            if (in_mask & (1u << u)) load_mask4(from[u], w0[u], w1[u]);
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            if (in_mask & (1u << u)) {
+                const uint32_t m = mask4_of(w0[u], w1[u], from[u]);
+                gstore16(dst + (u * WAVE + lane) * 16, select_adv4(m, sel[u]));
+                gstore4(mdst + (u * WAVE + lane) * 4, m);
+            }
+#pragma unroll 1
+        for (int item = lane; item < n_edge * ADV_TPC; item += WAVE) {        // one token per lane
+            const uint32_t e = sg.edge[item / ADV_TPC];
+            const int32_t t = (int32_t)(e & 0xFFFFu) + (item & (ADV_TPC - 1));
+            int q = (int)(e >> 16) - 1;
+            while (q + 1 < WAVE && sg.start[q + 1] <= t) ++q;
+            if (q >= 0 && t < sg.end[q] && t < limit) {
+                const uint32_t m = load_elem(0, reinterpret_cast<gptr>(sg.addr[q] + t));
+                store_elem(2, dst + ((int64_t)t << 2), m ? sg.adv[q] : 0u);
+                store_elem(0, mdst + t, m);
             }
         }
-        __syncthreads();
         if (!more) break;
-        seg_base += SEG_BATCH;
+        base += DENSE_OWN;
         pass_begin = pass_end;
     }
 }
 
 // ---------------------------------------------------------------- the kernel
+// What wave w of a tile needs of its granule.  F[g] = first slot ending after granule g's first token; slots F[g] ..
+// F[g + 1] are the ones that can reach into granule g.  The tables are padded, so the entries of a whole tile (and one
+// more) exist even for the last, partial tile.
+struct WaveGran {
+    u32x16  rec;
+    int     first, last;           // slots that can reach into the granule
+    int32_t limit;                 // tokens of it that exist in the arena
+};
+__device__ __forceinline__ WaveGran wave_granule(const GatherArgs& a, uint32_t tile, int w) {
+    const int64_t g0 = (int64_t)tile * GRAN_PER_TILE;
+    const u32x8 F = sload8(a.gran_first + g0);
+    WaveGran g;
+    g.rec = sload16(a.gran_rec + g0 + w);
+    g.first = (int)F[0];
+    int next = (int)F[1];
+#pragma unroll
+    for (int i = 1; i < GRAN_PER_TILE; ++i)
+        if (w == i) { g.first = (int)F[i]; next = (int)F[i + 1]; }
+    g.last = min(max(next, g.first), a.n_seq - 1);
+    g.limit = (int32_t)max((int64_t)0, min((int64_t)GATHER_GRAN, a.capacity - (g0 + w) * GATHER_GRAN));
+    return g;
+}
+
 // The tile `tile` of carrier field fc.  BACK = false: the forward direction, fields as the
 // table gives them.  BACK = true: the reverse direction, destination = the field's rollout
 // buffer of segment seg, only source = its training arena.
 template <bool BACK>
-__device__ __forceinline__ void move_tile(const GatherArgs& a, const FieldTable& ft, uint32_t tile, uint32_t fc, int seg) {
-    __shared__ SegLds sg;
-    __shared__ const char* src[DC_MAX_SRC_SHARDS];
+__device__ __forceinline__ void move_tile(const GatherArgs& a, const FieldTable& ft, WaveSlots* slots, uint32_t tile, uint32_t fc,
+                                          int seg) {
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int N = a.n_seq;
-    const int64_t tile_begin = (int64_t)tile * GATHER_TILE_TOKENS;
-    const int64_t g0 = (int64_t)tile * GRAN_PER_TILE;
+    const int64_t wave_begin = (int64_t)tile * GATHER_TILE_TOKENS + w * GATHER_GRAN;
+    const WaveGran g = wave_granule(a, tile, w);
+    if (g.limit <= 0 || g.first < 0 || g.first >= N) return;      // behind the arena's end, or nothing reaches into the granule
 
-    // granule table of the tile: F[g] = first slot ending after granule g's first token; slots
-    // F[g] .. F[g+1] are the ones that can reach into granule g.  The tables are padded, so the
-    // entries of a whole tile (and one more) exist even for the last, partial tile.
-    const u32x8 F = sload8(a.gran_first + g0);
-    const u32x16 rec = sload16(a.gran_rec + g0 + w);
-    const int first = (int)F[0];
-    if (first < 0 || first >= N) return;                   // nothing reaches into this tile
-    bool dense = false;
-#pragma unroll
-    for (int i = 0; i < GRAN_PER_TILE; ++i)
-        dense = dense || ((int)F[i] < N && min((int)F[i + 1], N - 1) - (int)F[i] + 1 > REC_SLOTS);
-    const int32_t limit = (int32_t)min((int64_t)GATHER_TILE_TOKENS, a.capacity - tile_begin);
-    const int32_t wave_limit = min(limit - w * GATHER_GRAN, GATHER_GRAN);
-    const int last = min(max((int)F[GRAN_PER_TILE], first), N - 1);
-
-    for (uint32_t f = fc; f < a.n_carriers + a.n_riders; f = f < a.n_carriers ? a.n_carriers + f : f + a.n_carriers) {
-        // f = fc, then the riders n_carriers + fc, n_carriers + fc + n_carriers, ...
-        const FieldDesc& fd = ft.f[f];
-        const int lg = fd.elem_bytes == 4 ? 2 : (fd.elem_bytes == 2 ? 1 : 0);
-        char* back_dst = BACK ? const_cast<char*>(fd.src[seg]) : nullptr;
-        const char* back_src = BACK ? fd.dst : nullptr;
-        if (!dense) {
-            if (wave_limit > 0)
-                move_wave_sparse<BACK>(fd, ft.n_src, back_dst, back_src, lg, rec, tile_begin + w * GATHER_GRAN, wave_limit);
-        } else {
-            __syncthreads();                               // the previous field's readers of src[] and sg are done
-            if (threadIdx.x < DC_MAX_SRC_SHARDS) src[threadIdx.x] = BACK ? back_src : fd.src[threadIdx.x];
-            __syncthreads();
-            move_tile_dense(a, sg, src, lg, BACK ? back_dst : fd.dst, first, last, tile_begin, limit);
+    // f = fc, then the riders n_carriers + fc, n_carriers + fc + n_carriers, ...  (Two loops rather than a test inside one:
+    // the registers of the one path do not add to the other's.)
+    const uint32_t n = a.n_carriers + a.n_riders;
+    auto next_field = [&](uint32_t f) { return f < a.n_carriers ? a.n_carriers + f : f + a.n_carriers; };
+    auto lg_of = [&](const FieldDesc& fd) { return fd.elem_bytes == 4 ? 2 : (fd.elem_bytes == 2 ? 1 : 0); };
+    if (g.last - g.first < REC_SLOTS) {
+        for (uint32_t f = fc; f < n; f = next_field(f)) {
+            const FieldDesc& fd = ft.f[f];
+            move_wave_sparse<BACK>(fd, ft.n_src, BACK ? const_cast<char*>(fd.src[seg]) : nullptr, BACK ? fd.dst : nullptr, lg_of(fd),
+                                   g.rec, wave_begin, g.limit);
+        }
+    } else {
+        for (uint32_t f = fc; f < n; f = next_field(f)) {
+            const FieldDesc& fd = ft.f[f];
+            move_wave_dense<BACK>(a, slots[w], fd, ft.n_src, BACK ? const_cast<char*>(fd.src[seg]) : nullptr, BACK ? fd.dst : nullptr,
+                                  lg_of(fd), g.first, g.last, wave_begin, g.limit);
         }
     }
 }
@@ -649,46 +743,29 @@ __global__ __launch_bounds__(GATHER_BLOCK) void gather_kernel(GatherArgs a, Fiel
     // carrier r mod n_carriers, right after their own data and from the same granule record.
     // A wave of a narrow field has only 1 or 2 KB in flight; as a workgroup of its own it
     // would hold a wave slot as long as a 4 KB one.
-    move_tile<false>(a, ft, blockIdx.x % a.tiles, blockIdx.x / a.tiles, 0);
+    // (the division runs in the vector unit; the wave's place is the same in every lane)
+    const uint32_t fc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x / a.tiles));
+    __shared__ WaveSlots slots[GRAN_PER_TILE];
+    move_tile<false>(a, ft, slots, blockIdx.x - fc * a.tiles, fc, 0);
 }
 
 // The tile `tile` of the advantage arena and of the mask field.
-__device__ __forceinline__ void adv_tile(const GatherArgs& a, const FieldTable& ft, uint32_t mask_field, uint32_t tile) {
-    __shared__ SegLds sg;
-    __shared__ uint32_t sg_adv[NSEG];
-    __shared__ const char* src[DC_MAX_SRC_SHARDS];
+__device__ __forceinline__ void adv_tile(const GatherArgs& a, const FieldTable& ft, WaveSlots* slots, uint32_t mask_field,
+                                         uint32_t tile) {
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int N = a.n_seq;
-    const int64_t tile_begin = (int64_t)tile * GATHER_TILE_TOKENS;
-    const int64_t g0 = (int64_t)tile * GRAN_PER_TILE;
-    const u32x8 F = sload8(a.gran_first + g0);
-    const u32x16 rec = sload16(a.gran_rec + g0 + w);
-    const int first = (int)F[0];
-    if (first < 0 || first >= N) return;
-    bool dense = false;
-#pragma unroll
-    for (int i = 0; i < GRAN_PER_TILE; ++i)
-        dense = dense || ((int)F[i] < N && min((int)F[i + 1], N - 1) - (int)F[i] + 1 > REC_SLOTS);
-    const int32_t limit = (int32_t)min((int64_t)GATHER_TILE_TOKENS, a.capacity - tile_begin);
-    const int32_t wave_limit = min(limit - w * GATHER_GRAN, GATHER_GRAN);
-    const int last = min(max((int)F[GRAN_PER_TILE], first), N - 1);
-    int wave_first = (int)F[0];
-#pragma unroll
-    for (int i = 1; i < GRAN_PER_TILE; ++i)
-        if (w == i) wave_first = (int)F[i];
+    const int64_t wave_begin = (int64_t)tile * GATHER_TILE_TOKENS + w * GATHER_GRAN;
+    const WaveGran g = wave_granule(a, tile, w);
+    if (g.limit <= 0 || g.first < 0 || g.first >= N) return;
 
     const FieldDesc& mk = ft.f[mask_field];
     const AdvSynth s = adv_synth_of(ft.f[mask_field + 1]);
-    if (!dense) {
-        if (wave_limit > 0) {
-            uint32_t adv[REC_SLOTS];
-            slot_adv_scalar(s, N, wave_first, adv);
-            adv_wave_sparse(mk, ft.n_src, s, adv, rec, tile_begin + w * GATHER_GRAN, wave_limit);
-        }
+    if (g.last - g.first < REC_SLOTS) {
+        uint32_t adv[REC_SLOTS];
+        slot_adv_scalar(s, N, g.first, adv);
+        adv_wave_sparse(mk, ft.n_src, s, adv, g.rec, wave_begin, g.limit);
     } else {
-        if (threadIdx.x < DC_MAX_SRC_SHARDS) src[threadIdx.x] = mk.src[threadIdx.x];
-        __syncthreads();
-        adv_tile_dense(a, sg, sg_adv, src, s, mk.dst, first, last, tile_begin, limit);
+        adv_wave_dense(a, slots[w], mk, ft.n_src, s, g.first, g.last, wave_begin, g.limit);
     }
 }
 
@@ -697,13 +774,14 @@ __global__ __launch_bounds__(GATHER_BLOCK) void gather_adv_kernel(GatherArgs a, 
     // The advantage tiles write four bytes for every byte they read; a run of them at the end of the
     // grid would be a pure write stream, which the memory serves more slowly than a mix.  They are
     // dealt in between the others instead: every (n_carriers + 1)-th workgroup takes one.
+    __shared__ WaveSlots slots[GRAN_PER_TILE];
     const uint32_t per = a.n_carriers + 1;
     const uint32_t round = blockIdx.x / per, r = blockIdx.x % per;
     if (r == a.n_carriers) {
-        adv_tile(a, ft, mask_field, (uint32_t)__builtin_amdgcn_readfirstlane((int)round));
+        adv_tile(a, ft, slots, mask_field, (uint32_t)__builtin_amdgcn_readfirstlane((int)round));
     } else {
         const uint32_t idx = round * a.n_carriers + r;
-        move_tile<false>(a, ft, (uint32_t)__builtin_amdgcn_readfirstlane((int)(idx % a.tiles)),
+        move_tile<false>(a, ft, slots, (uint32_t)__builtin_amdgcn_readfirstlane((int)(idx % a.tiles)),
                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(idx / a.tiles)), 0);
     }
 }
@@ -712,7 +790,8 @@ __global__ __launch_bounds__(GATHER_BLOCK) void gather_adv_kernel(GatherArgs a, 
 // a.dst_tok_off, a.slot_* and the granule tables arrive as the arrays of all segments; the
 // workgroup narrows them to its segment's part.
 __global__ __launch_bounds__(GATHER_BLOCK) void gather_back_kernel(GatherArgs a, FieldTable ft, BackSegs bs) {
-    const uint32_t t = blockIdx.x % a.tiles;
+    const uint32_t fc = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x / a.tiles));
+    const uint32_t t = blockIdx.x - fc * a.tiles;
     int seg = 0;
 #pragma unroll
     for (int q = 0; q + 1 < DC_MAX_SRC_SHARDS; ++q) seg += t >= bs.tile_end[q] ? 1 : 0;   // t < tile_end[last]
@@ -726,7 +805,8 @@ __global__ __launch_bounds__(GATHER_BLOCK) void gather_back_kernel(GatherArgs a,
     a.slot_shard += first_seq;
     a.gran_first += bs.gran_base[seg];
     a.gran_rec += bs.gran_base[seg];
-    move_tile<true>(a, ft, tile, blockIdx.x / a.tiles, seg);
+    __shared__ WaveSlots slots[GRAN_PER_TILE];
+    move_tile<true>(a, ft, slots, tile, fc, seg);
 }
 
 // Field table with the 4-byte fields first (they carry, the others ride) and the grid's shape.
