@@ -77,6 +77,8 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_advantage_kernel(BalanceArg
 static_assert(BAL_BLOCK == PLAN_BLOCK && BAL_ROUNDS == PLAN_IPT, "one lane handles the same slots in both");
 constexpr size_t BAL_PLAN_LDS = sizeof(BalLds) > sizeof(PlanLds) ? sizeof(BalLds) : sizeof(PlanLds);
 
+// MANY: 33 .. 63 or 65 .. 256 workers; else up to 32 or 64 (two kernels: see balance_body_t).
+template <bool MANY>
 __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(BalanceArgs b, PlanArgs p, AdvArgs a, SourceDesc sd) {
     __shared__ __align__(16) unsigned char lds[BAL_PLAN_LDS];
     if (blockIdx.x != 0) {
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(Balan
         return;
     }
     SlotRegs s;
-    balance_body_t<true>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq,
+    balance_body_t<true, !MANY, MANY>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq,
                          b.shard_load, b.status, s);
 #pragma unroll
     for (int q = 0; q < PLAN_IPT; ++q) {                          // the slots' lengths, for the launch that builds the granule tables
@@ -119,14 +121,18 @@ hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_
                                          int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
                                          int64_t* d_shard_load, const PlanArgs& plan, const AdvArgs& adv,
                                          const SourceDesc& src, int32_t n_groups, int32_t* d_status, hipStream_t st) {
-    // (the kernel holds the code of these shapes only)
-    if (!((n_shards >= 1 && n_shards <= 32) || n_shards == 64) || (int64_t)cap_eff * n_shards != n_seq || n_seq <= 0 || n_seq > DC_MAX_SEQ)
+    // (the kernels hold the code of these shapes only)
+    if (n_shards < 1 || n_shards > BAL_PLAN_MAX_SHARDS || (int64_t)cap_eff * n_shards != n_seq || n_seq <= 0 || n_seq > DC_MAX_SEQ)
         return hipErrorInvalidValue;
+    static_assert(BAL_PLAN_MAX_SHARDS == MULTI_MAX, "the packed rounds' limit");
     BalanceArgs b;
     b.N = n_seq; b.P = n_shards; b.C = cap_eff; b.seq_len = d_seq_len; b.perm = d_perm;
     b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = d_shard_of_seq; b.shard_load = d_shard_load; b.status = d_status;
     const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
-    hipLaunchKernelGGL(balance_plan_advantage_kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src);
+    if (n_shards <= 32 || n_shards == WAVE)
+        hipLaunchKernelGGL(balance_plan_advantage_kernel<false>, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src);
+    else
+        hipLaunchKernelGGL(balance_plan_advantage_kernel<true>, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src);
     return hipGetLastError();
 }
 

@@ -559,7 +559,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     // WIDTH 64: P == 64.  WIDTH 8, 16 and 32: any P <= WIDTH; the keys of the lanes without a worker sort behind the
     // workers' and must stay where they are, so what is offered to their ranks is nothing: those lanes read the
     // zero word behind the last item, round after round (a stride of their own, no instruction more per round).
-    constexpr bool SOME = WIDTH != WAVE && !PORTION;
+    constexpr bool SOME = WIDTH != WAVE;
     const bool offers = !SOME || mine_exists;
     const int stride = offers ? P : 0;                            // from a rank's item of one round to its item of the next
     const uint64_t everyone = P == WAVE ? ~0ull : (1ull << P) - 1ull;
@@ -801,6 +801,240 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     return pos;
 }
 
+// ---------------------------------------------------------------- rounds of one wave that keeps up to 256 workers
+// The packed rounds for 33 .. 63 and 65 .. 256 workers: wave 0 keeps K = 1, 2 or 4 of the sorted keys in a lane (rank
+// r * 64 + lane in register r; key = load << 8 | worker, rebased as above), sorts them with wave_sort_multi, and never
+// goes back from ranks to workers: a worker's number of items stands in the LDS (not at all while every worker holds the
+// same number), its load goes out when it is full or at the end.  Two kinds of round:
+//   sure     the bound of lpt_rounds_packed says that the round places one item on every worker: nothing is tested;
+//   general  the longest accepted prefix of the ranks takes its items; full workers have sorted behind the open ones.
+// Bound by the chain of sorts, of which one wave runs a step in about 20 cycles whether it carries one or two chains.
+// Up to 256 workers: 8192 sequences on 128 workers take 66 us with the plan in the same launch, where the rounds that the
+// whole workgroup runs (lpt_rounds_wide32_portion: five barriers and a bisection per 64 workers in each) took 175 and
+// slots and plan 23 more; 25 472 sequences on 128 workers: 95 us for the assignment, a step of 632 us takes 285.  With
+// eight keys to a lane a sort is four times the work and a step of the network is no longer hidden by its neighbours.
+//
+// items, rows, pitch: as for lpt_rounds_packed.  The call returns, before all N items are placed, when a row holds
+// row_cap items.
+constexpr int MULTI_MAX = 4 * WAVE;                      // workers
+constexpr int MULTI_ID_BITS = 8;
+constexpr uint32_t MULTI_ID_MASK = (1u << MULTI_ID_BITS) - 1u;
+constexpr uint32_t MULTI_FULL = ~MULTI_ID_MASK;          // | worker id: full (or absent) worker
+static_assert(MULTI_MAX <= (1 << MULTI_ID_BITS), "worker id fits the key's low bits");
+// (rebased whenever the smallest key has passed 2^30 and looked at every 64 rounds at least: see lpt_rounds)
+static_assert((1ull << 30) + 66ull * ((uint64_t)PACKED_MAX_LEN << MULTI_ID_BITS) < (uint64_t)MULTI_FULL, "keys stay below 2^32");
+
+// What is kept per worker between two calls, in the LDS behind the other tables of BalLds::cnt.
+struct MultiLds {
+    uint32_t key[MULTI_MAX];       // by rank
+    int32_t  cnt[MULTI_MAX];       // by worker: items in its row
+    int32_t  lim[MULTI_MAX];       // by worker: items it could take when the row was empty
+    int64_t  taken;                // load taken off the keys by rebasing
+};
+constexpr int MULTI_AT = 2048;                           // words into BalLds::cnt
+static_assert(MULTI_AT * sizeof(uint32_t) + sizeof(MultiLds) <= sizeof(uint32_t) * 256 * CNT_PITCH && MULTI_AT >= WCOUNT_AT + 2 * WAVE,
+              "the table fits behind the others");
+__device__ __forceinline__ MultiLds& multi_lds(BalLds& L) { return *reinterpret_cast<MultiLds*>(L.cnt + MULTI_AT); }
+// (threads 0 .. MULTI_MAX - 1 at least)
+__device__ __forceinline__ void multi_fresh(MultiLds& m, int P, int C) {
+    const int tid = threadIdx.x;
+    if (tid < MULTI_MAX) {
+        m.key[tid] = tid < P && C > 0 ? (uint32_t)tid : (MULTI_FULL | (uint32_t)tid);
+        m.cnt[tid] = 0;
+        m.lim[tid] = C;
+    }
+    if (tid == 0) m.taken = 0;
+}
+
+template <int K>
+__device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* items, uint32_t* rows, int pitch, int row_cap,
+                                                uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
+    constexpr uint32_t NONE = 0xFFFFFFFFu;
+    const int lane = threadIdx.x;                                 // (wave 0)
+    uint32_t sk[K], e[K];
+    bool offers[K];                                               // while all workers are open: a worker has this rank
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        sk[r] = m.key[r * WAVE + lane];
+        offers[r] = r * WAVE + lane < P;
+        e[r] = items[offers[r] ? r * WAVE + lane : N];            // (zeros behind the last item)
+    }
+    int64_t taken = m.taken;
+    int pos = 0;
+    // level: every row holds c_row items; else the LDS says.  slack: items until the first worker is full (0: one is);
+    // c_hi: items of the fullest row
+    bool level = false, fresh = false;                            // fresh: slack and c_hi are as the LDS says
+    int c_row = 0, slack = 0, c_hi = 0;
+    auto count_rows = [&]() {
+        uint32_t hi = 0, room = NONE, room_hi = 0;
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const int k = min(r * WAVE + lane, P - 1);            // (any worker once more where there is none)
+            const uint32_t c = (uint32_t)m.cnt[k], left = (uint32_t)(m.lim[k] - m.cnt[k]);
+            hi = max(hi, c);
+            room = min(room, left);
+            room_hi = max(room_hi, left);
+        }
+        wave_all_reduce([&](auto j) {
+            constexpr int J = decltype(j)::value;
+            const uint32_t a = lane_xor<J>(hi), b = lane_xor<J>(room), c = lane_xor<J>(room_hi);
+            hi = max(hi, a);
+            room = min(room, b);
+            room_hi = max(room_hi, c);
+        });
+        c_hi = __builtin_amdgcn_readfirstlane((int)hi);
+        slack = __builtin_amdgcn_readfirstlane((int)room);
+        fresh = true;
+        return __builtin_amdgcn_readfirstlane((int)room_hi);
+    };
+    {
+        const int room_hi = count_rows();                         // (the rows are empty: c_hi == 0)
+        level = room_hi == slack && slack > 0;
+    }
+
+    auto sure_round = [&](auto level_c) {
+        constexpr bool LEVEL = decltype(level_c)::value;
+        uint32_t v[K], e1[K];
+        int32_t c[K];
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            v[r] = sk[r] + ((e[r] >> 16) << MULTI_ID_BITS);
+            e1[r] = items[offers[r] ? pos + P + r * WAVE + lane : N];
+            c[r] = LEVEL ? c_row : m.cnt[sk[r] & MULTI_ID_MASK];
+        }
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const uint32_t id = sk[r] & MULTI_ID_MASK;
+            uint32_t* at = rows + ((int)id * pitch + c[r]);
+            *(offers[r] ? at : spare_word) = e[r];                // filed with its worker
+            if constexpr (!LEVEL) m.cnt[id] = c[r] + 1;           // (an absent worker's count is nobody's)
+        }
+        wave_sort_multi<K>(v);
+#pragma unroll
+        for (int r = 0; r < K; ++r) { sk[r] = v[r]; e[r] = e1[r]; }
+        pos += P;
+        c_row += 1;
+        c_hi += 1;
+        slack -= 1;
+    };
+
+    // a worker that holds all it may hold: its load goes out, its key goes behind the open ones
+    auto close_if_full = [&](uint32_t key, int32_t c) -> uint32_t {
+        const uint32_t id = key & MULTI_ID_MASK;
+        if (c != m.lim[id]) return key;
+        shard_load[id] = (int64_t)(key >> MULTI_ID_BITS) + taken;
+        return MULTI_FULL | id;
+    };
+
+    while (pos < N) {
+        const uint32_t min0 = (uint32_t)__builtin_amdgcn_readlane((int)sk[0], 0);
+        if (min0 >= 0x40000000u && min0 < MULTI_FULL) {           // rebase: subtract the minimum load
+            const uint32_t sub = min0 & ~MULTI_ID_MASK;
+#pragma unroll
+            for (int r = 0; r < K; ++r)
+                if (sk[r] < MULTI_FULL) sk[r] -= sub;
+            taken += (int64_t)(sub >> MULTI_ID_BITS);
+        }
+        if (!fresh) count_rows();
+        if (c_hi >= row_cap) break;                               // a row is full: the caller empties them all
+        // how many rounds does the bound cover?  Lane i looks at the last item of the (i + 1)-th round from here.
+        const int may = min(min(slack, row_cap - c_hi), (N - pos) / P);
+        int sure = 0;
+        if (may > 0) {
+            uint32_t top = sk[0];
+#pragma unroll
+            for (int r = 1; r < K; ++r)
+                if (P > r * WAVE) top = sk[r];                    // (uniform)
+            const uint32_t k_hi = (uint32_t)__builtin_amdgcn_readlane((int)top, (P - 1) & (WAVE - 1));
+            const uint32_t k_lo = (uint32_t)__builtin_amdgcn_readlane((int)sk[0], 0);
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)e[0], 0) >> 16;
+            const uint32_t need = max((k_hi - k_lo) >> MULTI_ID_BITS, first >> 1);
+            const uint32_t probe = items[min(pos + (lane + 1) * P - 1, N - 1)] >> 16;
+            const uint64_t good = __ballot(lane < may && probe > need);
+            sure = (~good == 0ull) ? WAVE : (__ffsll((long long)~good) - 1);
+        }
+        if (sure > 0) {
+            if (level) {
+                for (int b = 0; b < sure; ++b) sure_round(std::true_type{});
+            } else {
+                for (int b = 0; b < sure; ++b) sure_round(std::false_type{});
+                if (slack == 0) {                                 // (level: everyone is full together, behind the last item)
+#pragma unroll
+                    for (int r = 0; r < K; ++r)
+                        if (offers[r]) sk[r] = close_if_full(sk[r], m.cnt[sk[r] & MULTI_ID_MASK]);
+                    wave_sort_multi<K>(sk);
+                }
+            }
+            continue;
+        }
+
+        // ---- a general round ----
+        uint32_t newk[K];
+        uint32_t run_min = NONE;                                  // (uniform) smallest updated key of the registers before
+        int took = 0;
+        bool whole = true;                                        // (uniform) every rank so far takes its item
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const bool valid = sk[r] < MULTI_FULL && pos + r * WAVE + lane < N;
+            newk[r] = valid ? sk[r] + ((e[r] >> 16) << MULTI_ID_BITS) : NONE;
+            const uint32_t inc = wave_incl_scan_umin(newk[r]);
+            const uint32_t pm = umin32(dpp_mov<DPP_WAVE_SHR1>(NONE, inc), run_min);
+            const uint64_t acc = __ballot(valid && sk[r] < pm);
+            const int n = (~acc == 0ull) ? WAVE : (__ffsll((long long)~acc) - 1);
+            if (whole) took += n;
+            whole = whole && n == WAVE;
+            run_min = umin32(run_min, (uint32_t)__builtin_amdgcn_readlane((int)inc, WAVE - 1));
+        }
+        if (took == 0) break;                                     // cannot happen: an open worker always takes an item
+        int32_t c[K];
+#pragma unroll
+        for (int r = 0; r < K; ++r) c[r] = level ? c_row : m.cnt[sk[r] & MULTI_ID_MASK];
+        const bool still = level && took == P;                    // (uniform) everyone took one: the rows stay level
+        if (level && !still) {                                    // from here on the LDS counts
+#pragma unroll
+            for (int r = 0; r < K; ++r) m.cnt[sk[r] & MULTI_ID_MASK] = c[r];
+        }
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const bool take = r * WAVE + lane < took;
+            const uint32_t id = sk[r] & MULTI_ID_MASK;
+            if (take) {
+                rows[(int)id * pitch + c[r]] = e[r];
+                if (!still) m.cnt[id] = c[r] + 1;
+                sk[r] = still ? newk[r] : close_if_full(newk[r], c[r] + 1);
+            }
+        }
+        pos += took;
+        level = still;
+        c_row += 1;                                               // (if level)
+        c_hi += 1;
+        slack -= 1;
+        fresh = still;
+#pragma unroll
+        for (int r = 0; r < K; ++r) e[r] = items[offers[r] ? pos + r * WAVE + lane : N];      // (zeros behind the last item)
+        wave_sort_multi<K>(sk);
+    }
+    // the workers that are not full (level: none is marked)
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const uint32_t id = sk[r] & MULTI_ID_MASK;
+        if (sk[r] < MULTI_FULL) shard_load[id] = (int64_t)(sk[r] >> MULTI_ID_BITS) + taken;
+        if (level) m.cnt[id] = c_row;
+        m.key[r * WAVE + lane] = sk[r];
+    }
+    if (lane == 0) m.taken = taken;
+    return pos;
+}
+
+// The rounds that serve P workers with equal partitions and lengths up to PACKED_MAX_LEN.
+__device__ __forceinline__ bool multi_serves(int P) { return (P > 32 && P < WAVE) || (P > WAVE && P <= MULTI_MAX); }
+__device__ __forceinline__ int lpt_rounds_multi_any(int N, int P, const uint32_t* items, uint32_t* rows, int pitch, int row_cap,
+                                                    uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
+    if (P <= WAVE) return lpt_rounds_multi<1>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
+    if (P <= 2 * WAVE) return lpt_rounds_multi<2>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
+    return lpt_rounds_multi<4>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
+}
+
 // The same rounds for 64 < P <= DC_MAX_SHARDS workers, run by the whole workgroup: thread k keeps
 // worker k (64-bit key load << 10 | k, all-ones-ish when full or absent), thread r also plays
 // rank r of the sorted order.  Every thread of the workgroup must call it (barriers inside).
@@ -1032,10 +1266,10 @@ struct SlotRegs {
     int32_t len[BAL_ROUNDS];
 };
 
-// FILL (only with P <= 32 or P == 64, and P * C == N): also fill slots; the code of other shapes is left out (the
-// kernel is executed once from front to back, most of it straight code that the instruction cache has not seen,
-// and its size shows in its time).
-template <bool FILL>
+// FEW: the code for up to 32 or 64 workers; MANY: for the other numbers of them.  FILL (only with P * C == N): also
+// fill slots.  What a launch is never made for is left out of its kernel (it is executed once from front to back, most
+// of it straight code that the instruction cache has not seen, and its size shows in its time).
+template <bool FILL, bool FEW, bool MANY>
 __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, int32_t C,
                                                const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                                int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
@@ -1043,8 +1277,9 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
 
     // every partition ends with exactly C items (Algorithm 1 as printed: C = N / K): rows per worker
-    const int pitch = (P <= WAVE && C > 0 && (int64_t)P * C == N) ? place_pitch(C) : 0;
-    const bool tight = pitch != 0 && (P <= 32 || P == 64);                  // what the packed rounds serve
+    const bool equal = C > 0 && (int64_t)P * C == N;
+    const int pitch = (P <= WAVE && equal) ? place_pitch(C) : 0;
+    const bool tight = equal && P <= MULTI_MAX;                             // what the packed rounds serve
     const bool exact = pitch != 0 && (P == 16 || P == 32 || P == 64);      // a worker in every lane of a 16-, 32- or 64-lane sort
     if (tight) bin_sort_clear(L);                                 // (uniform; the barrier below stands between this and the bins' use)
 
@@ -1080,7 +1315,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     int32_t* part_off = reinterpret_cast<int32_t*>(L.cnt) + PART_OFF_AT;
     int32_t* placed = reinterpret_cast<int32_t*>(L.cnt) + PLACED_AT;
 
-    // ---- the printed algorithm on up to 32 or on 64 workers with lengths below 2^16 (lpt_rounds_packed) ----
+    // ---- the printed algorithm on up to 256 workers with lengths below 2^16 (lpt_rounds_packed, lpt_rounds_multi) ----
     // One word per sequence, length << 16 | index, is all that is kept: the sort moves those words between
     // the two halves of the LDS (a pass takes its digit from the word it moves, not from a table of lengths),
     // the rounds read them in sorted order, and the half the sort ends in leaves the other one to the workers'
@@ -1112,18 +1347,25 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         if (tid < PLACE_PAD) items[N + tid] = 0;                  // the rounds read a little beyond the last item
         __syncthreads();
         const int rpitch = row_pitch(C);
-        if (w == 0) {
-            int32_t* worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;
-            uint32_t* spare = reinterpret_cast<uint32_t*>(L.spare);
-            int n_placed;
-            if (P <= 8) n_placed = lpt_rounds_packed<8>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-            else if (P <= 16) n_placed = lpt_rounds_packed<16>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-            else if (P <= 32) n_placed = lpt_rounds_packed<32>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-            else n_placed = lpt_rounds_packed<64>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-            const int32_t c = worker_count[lane];
-            const int32_t inc = (int32_t)wave_incl_scan_add_u32((uint32_t)c);
-            if (lane < P) shard_seq_off[lane] = inc - c;
-            if (lane == 0) { shard_seq_off[P] = N; *placed = n_placed; }
+        uint32_t* const spare = reinterpret_cast<uint32_t*>(L.spare);
+        if (MANY && multi_serves(P)) {                            // (uniform)
+            if constexpr (MANY) {
+                MultiLds& m = multi_lds(L);
+                multi_fresh(m, P, C);
+                if (tid <= P) shard_seq_off[tid] = tid * C;
+                __syncthreads();
+                if (w == 0) lpt_rounds_multi_any(N, P, items, rows, rpitch, C + 1, spare, m, shard_load);     // (a row takes a whole partition)
+            }
+        } else if (w == 0) {
+            if constexpr (FEW) {
+                int32_t* worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;
+                if (P <= 8) lpt_rounds_packed<8>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                else if (P <= 16) lpt_rounds_packed<16>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                else if (P <= 32) lpt_rounds_packed<32>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                else lpt_rounds_packed<64>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                if (lane < P) shard_seq_off[lane] = lane * C;     // (every partition ends with C items)
+                if (lane == 0) shard_seq_off[P] = N;
+            }
         }
         __syncthreads();
         // ---- P_0, P_1, ... are the rows; the worker of a sequence is the row it stands in ----
@@ -1173,9 +1415,8 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const uint16_t* sorted = src;                                 // I of Algorithm 1
     uint16_t* step_slot = dst;                                    // place of I[t] inside its worker's partition
     // ---- b) assignment rounds: wave 0 for up to 64 workers, else the whole workgroup ----
-    // (FILL: the caller has up to 32 or 64 workers and equal partitions; the other shapes' code stays out of its kernel)
-    if (!FILL && P > WAVE) {
-        if constexpr (!FILL) {
+    if (MANY && P > WAVE) {
+        if constexpr (MANY) {
             const int n_placed = lpt_rounds_wide(L, N, P, C, sorted, step_slot, mx, shard_seq_off, shard_load);
             if (tid == 0) *placed = n_placed;
         }
@@ -1184,12 +1425,16 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         int32_t* spare = L.spare;
         LptCarry fresh = lpt_fresh(P, C);
         int n_placed = 0;
-        if (exact && P == 16) n_placed = lpt_rounds<16, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        else if (exact && P == 32) n_placed = lpt_rounds<32, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        else if (exact) n_placed = lpt_rounds<64, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        else if (P <= 16) n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        else if (P <= 32) n_placed = lpt_rounds<32>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        else if constexpr (!FILL) n_placed = lpt_rounds<64>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+        if constexpr (FEW) {
+            if (exact && P == 16) n_placed = lpt_rounds<16, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (exact && P == 32) n_placed = lpt_rounds<32, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (exact) n_placed = lpt_rounds<64, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (P <= 16) n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (P <= 32) n_placed = lpt_rounds<32>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+        }
+        if constexpr (MANY) {
+            if (P > 32 && !(FEW && exact)) n_placed = lpt_rounds<64>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+        }
         // start of every P_k inside perm
         const int32_t c = worker_count[lane];
         const int32_t inc = (int32_t)wave_incl_scan_add_u32((uint32_t)c);
@@ -1230,6 +1475,22 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         shard_of_seq[u] = k;
         perm[part_off[k] + step_slot[t]] = u;
     }
+    if constexpr (FILL && MANY) {                                 // (more than 64 workers, lengths of 2^16 and more)
+        __threadfence_block();
+        __syncthreads();
+#pragma unroll
+        for (int qq = 0; qq < BAL_ROUNDS; ++qq) {
+            const int q = qq * BAL_BLOCK + tid;
+            slots.seq[qq] = -1;
+            slots.len[qq] = 0;
+            if (q < N) {
+                const int u = min(max(perm[q], 0), N - 1);
+                const int32_t s = seq_len[u];
+                slots.seq[qq] = u;
+                slots.len[qq] = (s <= 0 || s > DC_MAX_SEQ_LEN) ? 1 : s;
+            }
+        }
+    }
 }
 
 __device__ __forceinline__ void balance_body(BalLds& L, int32_t N, int32_t P, int32_t C,
@@ -1237,7 +1498,7 @@ __device__ __forceinline__ void balance_body(BalLds& L, int32_t N, int32_t P, in
                                              int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
                                              int64_t* __restrict__ shard_load, int32_t* status) {
     SlotRegs unused;
-    balance_body_t<false>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
+    balance_body_t<false, true, true>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
 }
 
 }  // namespace dc

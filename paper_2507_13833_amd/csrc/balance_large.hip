@@ -10,8 +10,8 @@ namespace dc {
 //      LDS arrays the rounds read (lpt_rounds / lpt_rounds_wide as they are; the workers' keys, counts and loads are
 //      carried from portion to portion); it leaves one word per sorted item: worker << 16 | place in its partition;
 //   3. layout_large_kernel: perm and shard_of_seq from those words, by many workgroups.
-// The printed algorithm (N == P * C) on 16, 32 or 64 workers with lengths below 2^16 runs lpt_rounds_packed on each
-// portion instead; every partition's place in perm is known beforehand then (P_k starts at k * C), and stage 2 leaves,
+// The printed algorithm (N == P * C) on up to 256 workers with lengths below 2^16 runs lpt_rounds_packed or
+// lpt_rounds_multi on each portion instead; every partition's place in perm is known beforehand then (P_k starts at k * C), and stage 2 leaves,
 // per place in perm, the sorted position of the item that stands there.
 struct BalanceLargeWs {
     const int32_t* sorted;      // [N] I of Algorithm 1
@@ -21,32 +21,58 @@ struct BalanceLargeWs {
 
 // Both kernels take the same decision from the same words.
 __device__ __forceinline__ bool packed_rounds_apply(int32_t N, int32_t P, int32_t C, int32_t longest) {
-    return (P == 16 || P == 32 || P == 64) && (int64_t)P * C == N && (uint32_t)longest <= PACKED_MAX_LEN;
+    return P <= MULTI_MAX && (int64_t)P * C == N && (uint32_t)longest <= PACKED_MAX_LEN;
 }
 
 // Row length of a worker inside the LDS words that idx_a and idx_b span: odd, so that the rows start in different banks.
 __device__ __forceinline__ int portion_pitch(int P) { return (((DC_MAX_SEQ + PLACE_PAD) / P) - 1) | 1; }
 
-template <int WIDTH>
-__device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P, int32_t C, int32_t mx,
-                                                int32_t* __restrict__ shard_seq_off, int64_t* __restrict__ shard_load,
-                                                const BalanceLargeWs& ws) {
+// rounds(n, items, rows, pitch): the assignment of n items by the whole workgroup; fills count_before[P] and
+// count[P] (items per worker before and after) and returns the items placed, in every thread.
+template <typename Rounds>
+__device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P, int32_t C, const int32_t* count_before,
+                                                const int32_t* count, int32_t* __restrict__ shard_seq_off,
+                                                const BalanceLargeWs& ws, Rounds rounds) {
     static_assert(offsetof(BalLds, idx_b) == offsetof(BalLds, idx_a) + sizeof(uint16_t) * (DC_MAX_SEQ + PLACE_PAD) &&
                   offsetof(BalLds, idx_a) % 4 == 0, "the two index arrays are one run of words");
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     uint32_t* const items = reinterpret_cast<uint32_t*>(L.keys);
     uint32_t* const rows = reinterpret_cast<uint32_t*>(L.idx_a);
-    int32_t* const worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;      // [64] after a portion
-    int32_t* const count_before = worker_count + WAVE;                                // [64] before it
-    int32_t* const placed = reinterpret_cast<int32_t*>(L.cnt) + PLACED_AT;
     const int pitch = portion_pitch(P);
-    PackedCarry carry = packed_fresh(P, C);
     int c0 = 0;
     while (c0 < N) {                                              // (uniform)
         const int n = min(DC_MAX_SEQ, N - c0);
         for (int t = tid; t < n + PLACE_PAD; t += BAL_BLOCK)      // length << 16 | index inside the portion; zeros behind
             items[t] = t < n ? ((uint32_t)ws.sorted_len[c0 + t] << 16) | (uint32_t)t : 0u;
         __syncthreads();
+        const int done = rounds(n, items, rows, pitch);
+        // empty the rows: worker k's items number count_before[k] .. count[k] - 1 stand in perm from k * C on
+        for (int k = w; k < P; k += BAL_WAVES) {
+            const int first = count_before[k], got = min(count[k] - first, pitch);
+            for (int j = lane; j < got; j += WAVE) {
+                const int at = k * C + first + j;
+                if (at < N) ws.place[at] = c0 + (int32_t)(rows[k * pitch + j] & 0xFFFFu);
+            }
+        }
+        __syncthreads();
+        if (done <= 0) break;                                     // (cannot happen: an open worker always takes an item)
+        c0 += done;
+    }
+    for (int k = tid; k <= P; k += BAL_BLOCK) shard_seq_off[k] = k * C;
+}
+
+// Up to 32 or 64 workers: wave 0, lane k = worker k.
+template <int WIDTH>
+__device__ __forceinline__ void packed_portions_few(BalLds& L, int32_t N, int32_t P, int32_t C, int32_t mx,
+                                                    int32_t* __restrict__ shard_seq_off, int64_t* __restrict__ shard_load,
+                                                    const BalanceLargeWs& ws) {
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    int32_t* const worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;      // [64] after a portion
+    int32_t* const count_before = worker_count + WAVE;                                // [64] before it
+    int32_t* const placed = reinterpret_cast<int32_t*>(L.cnt) + PLACED_AT;
+    PackedCarry carry = packed_fresh(P, C);
+    packed_portions(L, N, P, C, count_before, worker_count, shard_seq_off, ws,
+                    [&](int n, const uint32_t* items, uint32_t* rows, int pitch) {
         if (w == 0) {
             count_before[lane] = carry.count;
             const int done = lpt_rounds_packed<WIDTH, true>(n, P, C, items, mx, rows, pitch, reinterpret_cast<uint32_t*>(L.spare),
@@ -54,21 +80,41 @@ __device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P,
             if (lane == 0) *placed = done;
         }
         __syncthreads();
-        // empty the rows: worker k's items number count_before[k] .. worker_count[k] - 1 stand in perm from k * C on
-        for (int k = w; k < P; k += BAL_WAVES) {
-            const int first = count_before[k], got = min(worker_count[k] - first, pitch);
-            for (int j = lane; j < got; j += WAVE) {
-                const int at = k * C + first + j;
-                if (at < N) ws.place[at] = c0 + (int32_t)(rows[k * pitch + j] & 0xFFFFu);
-            }
+        return *placed;
+    });
+}
+
+// The other numbers of workers, up to 256: wave 0, the workers' state in the LDS.
+__device__ __forceinline__ void packed_portions_many(BalLds& L, int32_t N, int32_t P, int32_t C,
+                                                     int32_t* __restrict__ shard_seq_off, int64_t* __restrict__ shard_load,
+                                                     const BalanceLargeWs& ws) {
+    const int tid = threadIdx.x, w = tid / WAVE;
+    MultiLds& m = multi_lds(L);
+    int32_t* const count = reinterpret_cast<int32_t*>(&m + 1);                        // [256] after a portion
+    int32_t* const count_before = count + MULTI_MAX;                                  // [256] before it
+    static_assert(MULTI_AT * sizeof(uint32_t) + sizeof(MultiLds) + 2 * MULTI_MAX * sizeof(int32_t) <= sizeof(uint32_t) * 256 * CNT_PITCH,
+                  "the counts fit behind the workers' state");
+    int32_t* const placed = reinterpret_cast<int32_t*>(L.cnt) + PLACED_AT;
+    multi_fresh(m, P, C);
+    if (tid < MULTI_MAX) count[tid] = 0;
+    packed_portions(L, N, P, C, count_before, count, shard_seq_off, ws,
+                    [&](int n, const uint32_t* items, uint32_t* rows, int pitch) {
+        if (tid < MULTI_MAX) {                                    // (a barrier stands between this and the rows' last use)
+            const int32_t had = count[tid];
+            count_before[tid] = had;
+            m.cnt[tid] = 0;
+            m.lim[tid] = C - had;
         }
-        const int done = *placed;
         __syncthreads();
-        if (done <= 0) break;                                     // (cannot happen: an open worker always takes an item)
-        c0 += done;
-    }
-    if (tid < P) shard_seq_off[tid] = tid * C;
-    if (tid == 0) shard_seq_off[P] = N;
+        if (w == 0) {
+            const int done = lpt_rounds_multi_any(n, P, items, rows, pitch, pitch, reinterpret_cast<uint32_t*>(L.spare), m, shard_load);
+            if (tid == 0) *placed = done;
+        }
+        __syncthreads();
+        if (tid < MULTI_MAX) count[tid] = count_before[tid] + m.cnt[tid];
+        __syncthreads();
+        return *placed;
+    });
 }
 
 __global__ __launch_bounds__(BAL_BLOCK) void balance_large_kernel(int32_t N, int32_t P, int32_t C,
@@ -80,9 +126,11 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_large_kernel(int32_t N, int
     const int32_t mx = ws.sorted_len[0];                          // the longest sequence comes first
 
     if (packed_rounds_apply(N, P, C, mx)) {                       // (uniform)
-        if (P == 16) packed_portions<16>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
-        else if (P == 32) packed_portions<32>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
-        else packed_portions<64>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
+        if (multi_serves(P)) packed_portions_many(L, N, P, C, shard_seq_off, shard_load, ws);
+        else if (P <= 8) packed_portions_few<8>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
+        else if (P <= 16) packed_portions_few<16>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
+        else if (P <= 32) packed_portions_few<32>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
+        else packed_portions_few<64>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         return;
     }
 

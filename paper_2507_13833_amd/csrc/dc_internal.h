@@ -136,7 +136,8 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
 hipError_t launch_records_slots(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, hipStream_t st);
 
 // Balance, group advantage and the plan in one launch (workgroup 0: Algorithm 1, then the plan as its tail;
-// the other workgroups: the advantage stage).  Needs n_shards in {16, 32, 64}, cap_eff * n_shards == n_seq.
+// the other workgroups: the advantage stage).  Needs n_shards <= BAL_PLAN_MAX_SHARDS, cap_eff * n_shards == n_seq.
+constexpr int BAL_PLAN_MAX_SHARDS = 256;
 hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
                                          int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
                                          int64_t* d_shard_load, const PlanArgs& plan, const AdvArgs& adv,

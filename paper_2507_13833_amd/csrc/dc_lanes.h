@@ -210,6 +210,44 @@ __device__ __forceinline__ uint32_t wave_sort_steps(uint32_t v, Side&& side) {
 
 __device__ __forceinline__ uint32_t umin32(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
+// Ascending sort of 64 * K keys of one wave, K = 1, 2 or 4 to a lane: key r * 64 + lane of the order in v[r].  The same
+// bitonic network over the index r * 64 + lane: the K registers are K independent chains (they fill the idle cycles
+// between a step's two dependent instructions), and a step whose partner is 64 or more away needs no move between lanes.
+template <int KK, int J, int K>
+__device__ __forceinline__ void multi_step(uint32_t (&v)[K]) {
+    if constexpr (J >= 64) {
+        constexpr int D = J / 64;
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+            if ((r & D) == 0) {
+                const uint32_t a = v[r], b = v[r + D];
+                const bool asc = ((r * 64) & KK) == 0;
+                v[r] = asc ? (a < b ? a : b) : (a < b ? b : a);
+                v[r + D] = asc ? (a < b ? b : a) : (a < b ? a : b);
+            }
+    } else {
+        const uint32_t lane = threadIdx.x & 63u;
+        XchgPair x[K];
+#pragma unroll
+        for (int r = 0; r < K; ++r) x[r] = xchg_fetch<J>(v[r]);
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const bool asc = KK < 64 ? (lane & KK) == 0 : ((r * 64) & KK) == 0;
+            v[r] = umed3(x[r].a, x[r].b, ((lane & J) == 0) == asc ? 0u : 0xFFFFFFFFu);
+        }
+    }
+}
+template <int KK, int J, int K>
+__device__ __forceinline__ void multi_merge(uint32_t (&v)[K]) {
+    multi_step<KK, J, K>(v);
+    if constexpr (J > 1) multi_merge<KK, J / 2, K>(v);
+}
+template <int K, int KK = 2>
+__device__ __forceinline__ void wave_sort_multi(uint32_t (&v)[K]) {
+    multi_merge<KK, KK / 2, K>(v);
+    if constexpr (KK < 64 * K) wave_sort_multi<K, KK * 2>(v);
+}
+
 // Inclusive min-scan over the 64 lanes (lane i: min of lanes 0..i).
 __device__ __forceinline__ uint32_t wave_incl_scan_umin(uint32_t v) {
     const uint32_t ID = 0xFFFFFFFFu;

@@ -3,7 +3,7 @@
 import numpy as np
 import pytest
 
-from test_gpu_parity import _custom, check_gather_advantage, check_scatter, check_step
+from test_gpu_parity import _check_balance_ws, _custom, check_gather_advantage, check_scatter, check_step
 
 pytestmark = pytest.mark.gpu
 
@@ -20,3 +20,40 @@ def test_slots_of_a_granule(length):
         check_step(w, align=align, label=f"length {length}", two_calls=True)
         check_gather_advantage(w, align=align, label=f"length {length}")
     check_scatter(_custom(lens, 4, 4, 4096, n_src=2, seed=length), label=f"length {length}")
+
+
+def _lengths(kind, n, rng):
+    if kind == "geometric":
+        return np.minimum(rng.geometric(0.004, n), 6000)
+    if kind == "tail":                                   # a few workers far above the others: rounds that few workers join
+        x = np.minimum(64 * (1.0 - rng.random(n)) ** (-1 / 1.1), 30000).astype(np.int64) + rng.integers(1, 60, n)
+        x[: max(1, n // 50)] = rng.integers(1, 4, max(1, n // 50))
+        return x
+    if kind == "equal":
+        return np.full(n, 77)
+    assert kind == "long"                                # one sequence of 2^16 tokens or more: the general rounds
+    x = rng.integers(1, 300, n)
+    x[n // 2] = 70000
+    return x
+
+
+@pytest.mark.parametrize("kind", ["geometric", "tail", "equal", "long"])
+@pytest.mark.parametrize("shards", [33, 48, 63, 65, 96, 127, 128, 129, 200, 255, 256, 257])
+def test_one_wave_with_up_to_256_workers(shards, kind):
+    """One, two and four keys to a lane, with and without lanes that keep no worker, plan in the same launch up to 256."""
+    rng = np.random.default_rng(shards)
+    for per in (1, 2, 21) if kind != "tail" else (3, 16384 // shards):
+        lens = _lengths(kind, shards * per, rng).astype(np.int32)
+        if per > 100:
+            lens = np.minimum(lens, 2000)
+        w = _custom(lens, 1, shards, 1 << 17, fields=())
+        check_step(w, align=7, label=f"{shards} shards of {per}, {kind}", two_calls=True)
+
+
+@pytest.mark.parametrize("shards", [1, 3, 8, 12, 24, 40, 63, 65, 96, 128, 200, 256])
+def test_portions_of_a_long_list(shards):
+    """More sequences than the LDS holds on every width of the packed rounds: rows fill up and are emptied in between."""
+    rng = np.random.default_rng(shards)
+    for kind, n in (("tail", 16385), ("geometric", 40000)):
+        per = -(-n // shards)
+        _check_balance_ws(_lengths(kind, per * shards, rng).astype(np.int32), shards, label=f"{shards} shards of {per}, {kind}")
