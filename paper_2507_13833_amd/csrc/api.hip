@@ -21,12 +21,12 @@ Workspace carve_workspace(void* base, int32_t n_seq, int64_t dst_capacity_tokens
     w.plan_ok = reinterpret_cast<int32_t*>(p + off);      off += 256;     // plan_ok, then own_shard_off, in one block
     w.own_shard_off = w.plan_ok + 16;
     static_assert((16 + DC_MAX_SRC_SHARDS + 1) * sizeof(int32_t) <= 256, "both fit the block");
-    w.gpre = nullptr; w.word_starts = nullptr; w.word_last = nullptr;
+    w.gpre = nullptr; w.start_bits = nullptr; w.tile_tokens = nullptr;
     if (n_seq > DC_MAX_SEQ) {
         const size_t words = n / 32 + 2;
         w.gpre = reinterpret_cast<int64_t*>(p + off);        off += round_up((n + 1) * sizeof(int64_t), 256);
-        w.word_starts = reinterpret_cast<int32_t*>(p + off); off += round_up(words * sizeof(int32_t), 256);
-        w.word_last = reinterpret_cast<int32_t*>(p + off);   off += round_up(words * sizeof(int32_t), 256);
+        w.start_bits = reinterpret_cast<int32_t*>(p + off);  off += round_up(words * sizeof(int32_t), 256);
+        w.tile_tokens = reinterpret_cast<int64_t*>(p + off); off += round_up(words * sizeof(int32_t), 256);
     }
     w.bytes = off + 256;
     return w;

@@ -45,9 +45,9 @@ struct Workspace {
     GranRec* gran_rec;       // [n_gran]
     int32_t* plan_ok;        // [1] 0 if the plan kernel found the shard table unusable and planned nothing
     int32_t* own_shard_off;  // [DC_MAX_SRC_SHARDS + 1] the rollout shards' sequence offsets, for a plan that keeps them
-    int64_t* gpre;           // [N + 1]  } only above DC_MAX_SEQ slots (else null): what plan_kernel keeps in LDS
-    int32_t* word_starts;    // [N / 32 + 2]
-    int32_t* word_last;      // [N / 32 + 2]
+    int64_t* gpre;           // [N + 1]  } only above DC_MAX_SEQ slots (else null): dense prefix of the slot lengths,
+    int32_t* start_bits;     // [N / 32 + 2] slots that open a micro-batch, one bit each,
+    int64_t* tile_tokens;    // [N / 64 + 1] tokens of every tile of slots
     int64_t  n_gran;         // ceil(capacity / GATHER_GRAN) + GRAN_TABLE_PAD; entries past the arena hold N / no slot
     size_t   bytes;
 };
@@ -118,11 +118,10 @@ struct PlanArgs {
     int32_t* slot_shard;
     int32_t* plan_ok;
     int32_t* status;
-    // more than DC_MAX_SEQ slots only (workspace): dense prefix of the slot lengths, and per word of 32 slots
-    // the micro-batch starts before it / the last start before it
+    // more than DC_MAX_SEQ slots only (workspace, see Workspace)
     int64_t* gpre;
-    int32_t* word_starts;
-    int32_t* word_last;
+    int32_t* start_bits;
+    int64_t* tile_tokens;
 };
 
 PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, const int32_t* d_seq_len,
@@ -143,9 +142,9 @@ hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_
                                          int64_t* d_shard_load, const PlanArgs& plan, const AdvArgs& adv,
                                          const SourceDesc& src, int32_t n_groups, int32_t* d_status, hipStream_t st);
 
-// plan_kernel's work for DC_MAX_SEQ < n_seq <= DC_MAX_SEQ_LARGE: one workgroup, the prefix and the per-word
-// tables in the workspace instead of the LDS.
-hipError_t launch_plan_large(const PlanArgs& a, hipStream_t st);
+// The work of slots_kernel and plan_kernel for DC_MAX_SEQ < n_seq <= DC_MAX_SEQ_LARGE: many workgroups, the prefix and
+// the per-word tables in the workspace instead of the LDS.
+hipError_t launch_plan_large(const PlanArgs& a, const SourceDesc& src, hipStream_t st);
 
 hipError_t launch_plan(const dc_params& prm, const SourceDesc& src, const int64_t* d_src_tok_off,
                        const int32_t* d_seq_len, const int32_t* d_perm, const int32_t* d_shard_seq_off,

@@ -29,39 +29,6 @@ namespace dc {
 // gathers over seq_len / src_tok_off, which one workgroup alone could not keep in flight.
 constexpr int SLOTS_BLOCK = 256;
 
-// The sequence behind slot j with its place in the rollout layout, validated (what the gather may rely
-// on): ln = tokens to move (0 if a check fails), so = element offset in rollout shard sh.  ln_in < 0: the
-// length is taken from a.seq_len; else it is the slot's length as the caller has it already.  Sets the
-// device status on a failed check (and on a sequence above the token budget, which is still laid out).
-__device__ __forceinline__ void slot_source(const PlanArgs& a, const SourceDesc& sd, int j, int32_t ln_in,
-                                            int32_t* ln_out, int64_t* so_out, int32_t* sh_out) {
-    const int N = a.n_seq;
-    const int32_t i = a.perm ? a.perm[j] : j;                                     // no permutation: slot j holds sequence j
-    const bool placed = i >= 0 && i < N;
-    int32_t ln = placed ? (ln_in < 0 ? a.seq_len[i] : ln_in) : 0;
-    const int64_t so = placed ? a.src_tok_off[i] : 0;
-    int32_t sh = 0;                                      // rollout shard (seq_off[s] = N from s = n_src on)
-    if (sd.n_src > 1 && placed) {
-#pragma unroll
-        for (int s = 1; s < DC_MAX_SRC_SHARDS; ++s) sh += i >= sd.seq_off[s] ? 1 : 0;
-    }
-    int64_t tokens = sd.tokens[0];
-#pragma unroll
-    for (int s = 1; s < DC_MAX_SRC_SHARDS; ++s) tokens = sh == s ? sd.tokens[s] : tokens;
-    const bool bad_len = placed && (ln <= 0 || ln > DC_MAX_SEQ_LEN);
-    const bool bad_off = placed && !bad_len && (so < 0 || so + ln > tokens);
-    const bool over = placed && !bad_len && !bad_off && ln > a.budget;   // still laid out, alone in its micro-batch
-    const int32_t e = !placed ? DC_ERR_BAD_LAYOUT
-                      : bad_len ? DC_ERR_ZERO_LENGTH_SEQ
-                      : bad_off ? DC_ERR_BAD_LAYOUT
-                      : over ? DC_ERR_SEQ_EXCEEDS_BUDGET : 0;
-    if (e != 0) set_status(a.status, e);
-    if (!placed || bad_len || bad_off) ln = 0;
-    *ln_out = ln;
-    *so_out = placed ? so : 0;
-    *sh_out = sh;
-}
-
 __global__ __launch_bounds__(SLOTS_BLOCK) void slots_kernel(PlanArgs a, SourceDesc sd) {
     const int j = blockIdx.x * SLOTS_BLOCK + threadIdx.x;
     const int N = a.n_seq;
@@ -281,17 +248,17 @@ hipError_t launch_plan(const dc_params& prm, const SourceDesc& src, const int64_
     PlanArgs a = make_plan_args(prm, d_src_tok_off, d_seq_len, d_perm, d_shard_seq_off, dst_capacity, d_dst_tok_off,
                                 d_shard_tok_off, d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb, ws, d_status);
     if (!d_shard_seq_off) { a.own_shard_off = ws.own_shard_off; a.shard_seq_off = ws.own_shard_off; }
-    if (prm.n_seq > 0 || a.own_shard_off) {
-        hipLaunchKernelGGL(slots_kernel, dim3((unsigned)max(1, (prm.n_seq + SLOTS_BLOCK - 1) / SLOTS_BLOCK)),
-                           dim3(SLOTS_BLOCK), 0, st, a, src);
-        hipError_t e0 = hipGetLastError();
-        if (e0 != hipSuccess) return e0;
-    }
     hipError_t e;
     if (prm.n_seq > DC_MAX_SEQ) {
         if (!ws.gpre) return hipErrorInvalidValue;
-        e = launch_plan_large(a, st);
+        e = launch_plan_large(a, src, st);
     } else {
+        if (prm.n_seq > 0 || a.own_shard_off) {
+            hipLaunchKernelGGL(slots_kernel, dim3((unsigned)max(1, (prm.n_seq + SLOTS_BLOCK - 1) / SLOTS_BLOCK)),
+                               dim3(SLOTS_BLOCK), 0, st, a, src);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(PLAN_BLOCK), 0, st, a);
         e = hipGetLastError();
     }
@@ -332,7 +299,7 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
     a.mb_seq_off = d_mb_seq_off; a.cu_seqlens = d_cu_seqlens; a.n_mb = d_n_mb;
     a.slot_src_off = ws.slot_src_off; a.slot_len = ws.slot_len; a.slot_shard = ws.slot_shard;
     a.plan_ok = ws.plan_ok; a.status = d_status;
-    a.gpre = ws.gpre; a.word_starts = ws.word_starts; a.word_last = ws.word_last;
+    a.gpre = ws.gpre; a.start_bits = ws.start_bits; a.tile_tokens = ws.tile_tokens;
     a.own_shard_off = nullptr;
     return a;
 }

@@ -13,6 +13,38 @@ constexpr int PLAN_WAVES = PLAN_BLOCK / WAVE;
 constexpr int PLAN_IPT = DC_MAX_SEQ / PLAN_BLOCK;        // slots per lane at the size limit
 constexpr int PLAN_WORDS = DC_MAX_SEQ / 32;
 
+// The sequence behind slot j with its place in the rollout layout, validated (what the gather may rely
+// on): ln = tokens to move (0 if a check fails), so = element offset in rollout shard sh.  ln_in < 0: the
+// length is taken from a.seq_len; else it is the slot's length as the caller has it already.  Sets the
+// device status on a failed check (and on a sequence above the token budget, which is still laid out).
+__device__ __forceinline__ void slot_source(const PlanArgs& a, const SourceDesc& sd, int j, int32_t ln_in,
+                                            int32_t* ln_out, int64_t* so_out, int32_t* sh_out) {
+    const int N = a.n_seq;
+    const int32_t i = a.perm ? a.perm[j] : j;                                     // no permutation: slot j holds sequence j
+    const bool placed = i >= 0 && i < N;
+    int32_t ln = placed ? (ln_in < 0 ? a.seq_len[i] : ln_in) : 0;
+    const int64_t so = placed ? a.src_tok_off[i] : 0;
+    int32_t sh = 0;                                      // rollout shard (seq_off[s] = N from s = n_src on)
+    if (sd.n_src > 1 && placed) {
+#pragma unroll
+        for (int s = 1; s < DC_MAX_SRC_SHARDS; ++s) sh += i >= sd.seq_off[s] ? 1 : 0;
+    }
+    int64_t tokens = sd.tokens[0];
+#pragma unroll
+    for (int s = 1; s < DC_MAX_SRC_SHARDS; ++s) tokens = sh == s ? sd.tokens[s] : tokens;
+    const bool bad_len = placed && (ln <= 0 || ln > DC_MAX_SEQ_LEN);
+    const bool bad_off = placed && !bad_len && (so < 0 || so + ln > tokens);
+    const bool over = placed && !bad_len && !bad_off && ln > a.budget;   // still laid out, alone in its micro-batch
+    const int32_t e = !placed ? DC_ERR_BAD_LAYOUT
+                      : bad_len ? DC_ERR_ZERO_LENGTH_SEQ
+                      : bad_off ? DC_ERR_BAD_LAYOUT
+                      : over ? DC_ERR_SEQ_EXCEEDS_BUDGET : 0;
+    if (e != 0) set_status(a.status, e);
+    if (!placed || bad_len || bad_off) ln = 0;
+    *ln_out = ln;
+    *so_out = placed ? so : 0;
+    *sh_out = sh;
+}
 
 struct PlanLds {
     int64_t  gpre[DC_MAX_SEQ + 1];          // dense exclusive prefix of slot lengths

@@ -1,203 +1,243 @@
 // The plan of the packed training layout for more slots than one workgroup's LDS holds
-// (DC_MAX_SEQ < N <= DC_MAX_SEQ_LARGE): plan_kernel's four steps by one workgroup, with the dense prefix
-// of the slot lengths and the per-word tables in the workspace and the loops over N in steps of
-// 1024 slots with a carry.  Only the bitmaps (first "sequence seen", then "slot opens a micro-batch") and
-// the shard tables stay in the LDS.  A slow path: every probe of the prefix is a global access.
-#include "dc_device.h"
-#include "dc_internal.h"
-#include "dc_lanes.h"
+// (DC_MAX_SEQ < N <= DC_MAX_SEQ_LARGE): the steps of slots_kernel and plan_kernel over MANY workgroups, each step a
+// launch (no workgroup waits for another inside one), the dense prefix of the slot lengths in the workspace:
+//   slots    every slot's source, validated; the tokens of every tile of PL_TILE slots; every sequence notes a slot that
+//            claims it;
+//   prefix   a tile's first token is the sum of the tiles before it (summed by every workgroup for itself); dense prefix;
+//            a slot whose sequence has noted another slot means that perm is no permutation;
+//   walk     workgroup p: the aligned start of shard p (likewise summed), and its next-fit micro-batches, by one wave that
+//            probes 64 slots of the prefix at once, the shard's part of it staged in the LDS;
+//   outputs  tiles of slots: the micro-batches that open before a tile are counted in the bitmap by every workgroup for
+//            itself.
+// Bound by launches and by the walk of the longest shard.  65 536 slots on 64 shards: 5.0 + 4.7 + 7.6 + 4.9 us; one
+// workgroup doing all of it behind slots_kernel, every probe a read of global memory, took 4.7 + 208 us.
+#include "plan_device.h"
 
 namespace dc {
 
-constexpr int PLANL_BLOCK = 1024;
-constexpr int PLANL_WAVES = PLANL_BLOCK / WAVE;
+constexpr int PL_TILE = 256;                              // slots of one workgroup (slots, prefix)
+constexpr int PL_WALK = 256;                              // threads that stage a shard
+constexpr int PL_STAGE = 32768;                           // slots of a shard that fit the LDS
+constexpr int PL_OUT = 1024;                              // slots of one workgroup (outputs)
+constexpr int PL_OUT_WORDS = PL_OUT / 32;
+static_assert(PL_TILE % 32 == 0 && DC_MAX_SEQ_LARGE % PL_TILE == 0, "a tile owns whole words of the bitmap");
+static_assert(sizeof(int64_t) * 64 <= sizeof(int32_t) * PL_TILE, "a word of the table per 32 slots holds the tiles' tokens");
 
-struct PlanLargeLds {
-    uint32_t bits[DC_MAX_SEQ_LARGE / 32];   // one bit per sequence / per slot
-    int64_t  shard_base[DC_MAX_SHARDS + 1]; // aligned token offset of each shard
-    int32_t  shard_off[DC_MAX_SHARDS + 1];  // copy of shard_seq_off
-    int64_t  tmp64[16];
-    int32_t  tmp32[16];
-    int32_t  ok;
-};
-
-// Exclusive max-scan over the workgroup (identity -1) and the maximum of all values.
-__device__ __forceinline__ int32_t block_excl_scan_max_total(int32_t v, int32_t* tmp, int32_t* total) {
-    const int lane = lane_id(), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
-    const int32_t inc = wave_incl_scan_max(v);
-    if (lane == WAVE - 1) tmp[w] = inc;
-    __syncthreads();
-    const int32_t upto = wave_incl_scan_max(lane < nw ? tmp[lane] : -1);      // (lane i: the waves up to wave i)
-    const int32_t base = wave_read_lane(wave_shift_up1(upto, -1), w);
-    const int32_t up = wave_shift_up1(inc, -1);
-    __syncthreads();
-    *total = wave_read_lane(upto, WAVE - 1);
-    return max(base, up);
-}
-
-__global__ __launch_bounds__(PLANL_BLOCK) void plan_large_kernel(PlanArgs a) {
-    __shared__ PlanLargeLds L;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-    const int N = a.n_seq, P = a.n_shards;
-    const int n_words = (N + 31) / 32;
-
-    for (int i = tid; i < n_words; i += PLANL_BLOCK) L.bits[i] = 0;
-    if (tid == 0) L.ok = 1;
-    __syncthreads();
-    for (int p = tid; p <= P; p += PLANL_BLOCK) {
-        const int32_t v = a.shard_seq_off[p];
-        L.shard_off[p] = v;
-        bool bad = v < 0 || v > N || (p == 0 && v != 0) || (p == P && v != N);
-        if (p < P && a.shard_seq_off[p + 1] < v) bad = true;
-        if (bad) L.ok = 0;
-    }
-    __syncthreads();
-    if (tid == 0) *a.plan_ok = L.ok;                     // read by records_kernel
-    if (!L.ok) {                                         // unusable shard table: plan nothing
-        if (tid == 0) { set_status(a.status, DC_ERR_BAD_LAYOUT); *a.n_mb = 0; }
-        return;
-    }
-
-    // ---- 1. permutation check (a repeat moves nothing), dense prefix of the slot lengths ----
-    bool dup = false;
-    for (int j = tid; j < N; j += PLANL_BLOCK) {
-        const int32_t i = a.perm ? a.perm[j] : j;        // out-of-range entries were emptied by slots_kernel
-        if (i >= 0 && i < N && ((atomicOr(&L.bits[i >> 5], 1u << (i & 31)) >> (i & 31)) & 1u)) {
-            dup = true;
-            a.slot_len[j] = 0;
+// `note`: one word per sequence (cu_seqlens serves: the last launch writes all N of them), null without a permutation.
+__global__ __launch_bounds__(PL_TILE) void plan_large_slots_kernel(PlanArgs a, SourceDesc sd, int32_t* note) {
+    __shared__ int64_t tmp[PL_TILE / WAVE];
+    const int j = blockIdx.x * PL_TILE + threadIdx.x;
+    const int N = a.n_seq;
+    if (a.own_shard_off && j <= sd.n_src) a.own_shard_off[j] = sd.seq_off[j];     // the plan keeps the rollout shards
+    int32_t ln = 0;
+    if (j < N) {
+        int32_t sh;
+        int64_t so;
+        slot_source(a, sd, j, -1, &ln, &so, &sh);
+        a.slot_src_off[j] = so;
+        a.slot_len[j] = ln;
+        a.slot_shard[j] = sh;
+        if (note) {
+            const int32_t i = a.perm[j];
+            if (i >= 0 && i < N) note[i] = j;
         }
     }
-    if (dup) set_status(a.status, DC_ERR_BAD_LAYOUT);
-    __threadfence_block();
-    __syncthreads();
-    int64_t carry = 0;
-    for (int base = 0; base < N; base += PLANL_BLOCK) {  // uniform
-        const int j = base + tid;
-        const int64_t len = j < N ? a.slot_len[j] : 0;
-        int64_t total;
-        const int64_t ex = block_excl_scan_add<int64_t>(len, L.tmp64, &total);
-        if (j < N) a.gpre[j] = carry + ex;
-        carry += total;
-    }
-    if (tid == 0) a.gpre[N] = carry;
-    for (int i = tid; i < n_words; i += PLANL_BLOCK) L.bits[i] = 0;     // from here on: slot opens a micro-batch
-    __threadfence_block();
-    __syncthreads();
+    int64_t total;
+    block_excl_scan_add<int64_t>(ln, tmp, &total);
+    if (threadIdx.x == 0) a.tile_tokens[blockIdx.x] = total;
+}
 
-    // ---- 2. shard bases: exclusive scan of the loads rounded up to the alignment ----
-    {
-        const int64_t first = tid < P ? a.gpre[L.shard_off[tid]] : 0;
-        const int64_t load = tid < P ? a.gpre[L.shard_off[tid + 1]] - first : 0;
-        const int64_t padded = (load + a.align - 1) / a.align * a.align;
-        int64_t end;
-        const int64_t base = block_excl_scan_add<int64_t>(padded, L.tmp64, &end);
-        if (tid < P) { L.shard_base[tid] = base; a.shard_tok_off[tid] = base; }
+// Sum of one value per thread over the workgroup, in every thread.
+__device__ __forceinline__ int64_t block_sum(int64_t v, int64_t* tmp) {
+    int64_t total;
+    block_excl_scan_add<int64_t>(v, tmp, &total);
+    return total;
+}
+
+__global__ __launch_bounds__(PL_TILE) void plan_large_prefix_kernel(PlanArgs a, const int32_t* note) {
+    __shared__ int64_t tmp[PL_TILE / WAVE];
+    const int tid = threadIdx.x, t = blockIdx.x;
+    const int j = t * PL_TILE + tid;
+    const int N = a.n_seq, P = a.n_shards;
+    if (t == 0) {                                         // the shard table
+        bool bad = false;
+        for (int p = tid; p <= P; p += PL_TILE) {
+            const int32_t v = a.shard_seq_off[p];
+            bad |= v < 0 || v > N || (p == 0 && v != 0) || (p == P && v != N);
+            if (p < P && a.shard_seq_off[p + 1] < v) bad = true;
+        }
+        const int any = __syncthreads_or(bad ? 1 : 0);
         if (tid == 0) {
-            L.shard_base[P] = end;
+            *a.plan_ok = any ? 0 : 1;                     // read by the launches behind this one
+            if (any) { set_status(a.status, DC_ERR_BAD_LAYOUT); *a.n_mb = 0; }
+        }
+    }
+    int64_t mine = 0;
+    for (int i = tid; i < t; i += PL_TILE) mine += a.tile_tokens[i];
+    const int64_t base = block_sum(mine, tmp);
+    __syncthreads();
+    const int64_t len = j < N ? a.slot_len[j] : 0;
+    int64_t total;
+    const int64_t ex = block_excl_scan_add<int64_t>(len, tmp, &total);
+    if (j < N) a.gpre[j] = base + ex;
+    if (j == N - 1) a.gpre[N] = base + ex + len;
+    if (j < N && note) {
+        const int32_t i = a.perm[j];
+        if (i >= 0 && i < N && note[i] != j) set_status(a.status, DC_ERR_BAD_LAYOUT);
+    }
+    if (tid < PL_TILE / 32 && t * (PL_TILE / 32) + tid < (N + 31) / 32) a.start_bits[t * (PL_TILE / 32) + tid] = 0;
+}
+
+// The micro-batches of n slots by next-fit, one wave; at(c): tokens of the shard before its slot c, 0 <= c <= n.
+// Each hop probes the 64 ends round the one that a micro-batch as long as the one before would have, then, where the end
+// lies outside, 64 places spread over what is left.
+template <typename At>
+__device__ __forceinline__ void walk_shard(const PlanArgs& a, int first_slot, int n, At at) {
+    const int lane = threadIdx.x;
+    int j = 0, sz = 0;
+    while (j < n) {                                       // (uniform)
+        if (lane == 0) atomicOr(&a.start_bits[(first_slot + j) >> 5], (int32_t)(1u << ((first_slot + j) & 31)));
+        const int64_t limit = at(j) + a.budget;
+        const int first = max(j + 1, j + sz + 1 - WAVE / 4);
+        int lo, hi = n, e = j + 1;                        // the last e in (j, n] with at(e) <= limit, or j + 1
+        {
+            const int c = first + lane;
+            const int cnt = __popcll(__ballot(c <= n && at(min(c, n)) <= limit));
+            if (cnt == 0) { lo = j + 1; hi = first - 1; }
+            else { e = first + cnt - 1; lo = (cnt == WAVE && first + WAVE <= n) ? first + WAVE : n + 1; }
+        }
+        while (lo <= hi) {
+            const int S = (hi - lo + WAVE) / WAVE;        // ceil(candidates / 64) >= 1
+            const int cnt = __popcll(__ballot(at(min(lo + (lane + 1) * S - 1, hi)) <= limit));
+            if (cnt > 0) e = min(lo + cnt * S - 1, hi);
+            if (cnt == WAVE) break;
+            hi = min(lo + (cnt + 1) * S - 1, hi) - 1;
+            lo += cnt * S;
+        }
+        sz = e - j;
+        j = e;
+    }
+}
+
+__global__ __launch_bounds__(PL_WALK) void plan_large_walk_kernel(PlanArgs a) {
+    __shared__ uint32_t part[PL_STAGE];
+    __shared__ int64_t tmp[PL_WALK / WAVE];
+    const int tid = threadIdx.x, p = blockIdx.x;
+    const int N = a.n_seq, P = a.n_shards;
+    if (*a.plan_ok == 0) return;                          // (uniform)
+    int64_t mine = 0;                                     // aligned tokens of the shards before mine
+    for (int q = tid; q < p; q += PL_WALK) {
+        const int64_t load = a.gpre[a.shard_seq_off[q + 1]] - a.gpre[a.shard_seq_off[q]];
+        mine += a.align == 1 ? load : (load + a.align - 1) / a.align * a.align;
+    }
+    const int64_t base = block_sum(mine, tmp);
+    const int s0 = a.shard_seq_off[p], n = a.shard_seq_off[p + 1] - s0;
+    const int64_t g0 = a.gpre[s0], load = a.gpre[s0 + n] - g0;
+    if (tid == 0) {
+        a.shard_tok_off[p] = base;
+        if (p == P - 1) {
+            const int64_t end = base + (load + a.align - 1) / a.align * a.align;
             a.shard_tok_off[P] = end;
             a.dst_tok_off[N] = end;
             if (end > a.capacity) set_status(a.status, DC_ERR_OVERFLOW);
         }
     }
-
-    // ---- 3. micro-batch starts: a group of lanes (few shards) or a lane (many) walks a shard ----
-    if (P <= PLANL_WAVES * 4) {
-        const int spw = P <= PLANL_WAVES ? 1 : (P <= 2 * PLANL_WAVES ? 2 : 4);     // shards per wave
-        const int G = WAVE / spw, g = lane / G, gl = lane - g * G;
-        const uint64_t group_mask = (G == WAVE ? ~0ull : (1ull << G) - 1ull);
-        const int p = w * spw + g;
-        if (p < P) {
-            const int b = L.shard_off[p + 1];
-            int j = L.shard_off[p];
-            while (j < b) {                                  // uniform over the group
-                if (gl == 0) atomicOr(&L.bits[j >> 5], 1u << (j & 31));
-                const int64_t limit = a.gpre[j] + a.budget;
-                int lo = j + 1, e = j + 1;                   // an over-budget slot still advances by one
-                for (int win = 0;; ++win) {
-                    const int c = lo + gl;
-                    const bool fits = c <= b && a.gpre[min(c, b)] <= limit;
-                    const int cnt = __popcll((__ballot(fits) >> (g * G)) & group_mask);
-                    if (cnt > 0) e = lo + cnt - 1;
-                    if (cnt < G || lo + G > b) break;
-                    lo += G;
-                    if (win == 1) {                          // every lane of the group reads the same words
-                        int l = e, h = b;
-                        while (l < h) {
-                            const int mid = (l + h + 1) >> 1;
-                            if (a.gpre[mid] <= limit) l = mid; else h = mid - 1;
-                        }
-                        e = l;
-                        break;
-                    }
-                }
-                j = e;
-            }
-        }
-    } else if (tid < P) {
-        const int b = L.shard_off[tid + 1];
-        int j = L.shard_off[tid];
-        while (j < b) {
-            atomicOr(&L.bits[j >> 5], 1u << (j & 31));
-            const int64_t limit = a.gpre[j] + a.budget;
-            int lo = j + 1, hi = b;                          // largest e in [lo, hi] with gpre[e] <= limit, else lo
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (a.gpre[mid] <= limit) lo = mid; else hi = mid - 1;
-            }
-            j = lo;
-        }
-    }
+    const bool staged = n < PL_STAGE && load <= 0xFFFFFFFFLL;        // (uniform)
+    if (staged)
+        for (int c = tid; c <= n; c += PL_WALK) part[c] = (uint32_t)(a.gpre[s0 + c] - g0);
     __syncthreads();
-
-    // ---- 4. per word of 32 slots: starts before it and the last start before it; then the outputs ----
-    int32_t M = 0, last_before = -1;
-    for (int wb = 0; wb < n_words; wb += PLANL_BLOCK) {      // uniform
-        const int wi = wb + tid;
-        const uint32_t bits = wi < n_words ? L.bits[wi] : 0u;
-        int32_t n_here, max_here;
-        const int32_t before = block_excl_scan_add<int32_t>((int32_t)__popc(bits), L.tmp32, &n_here);
-        const int32_t last = block_excl_scan_max_total(bits ? wi * 32 + 31 - __clz(bits) : -1, L.tmp32, &max_here);
-        if (wi < n_words) { a.word_starts[wi] = M + before; a.word_last[wi] = max(last_before, last); }
-        M += n_here;
-        last_before = max(last_before, max_here);
-    }
-    if (tid == 0) a.word_starts[n_words] = M;
-    __threadfence_block();
-    __syncthreads();
-    for (int j = tid; j < N; j += PLANL_BLOCK) {
-        const uint32_t bits = L.bits[j >> 5];
-        const uint32_t upto = bits & (0xFFFFFFFFu >> (31 - (j & 31)));           // starts at slots <= j of the word
-        const int32_t m = a.word_starts[j >> 5] + (int32_t)__popc(upto) - 1;     // my micro-batch
-        const int32_t cur_start = upto ? (j & ~31) + 31 - __clz(upto) : a.word_last[j >> 5];
-        if ((bits >> (j & 31)) & 1u) a.mb_seq_off[m] = j;
-        const int64_t g = a.gpre[j];
-        int64_t d = g;
-        if (a.align != 1) {                                  // uniform: shard of the slot, then its aligned base
-            int lo = 0, hi = P - 1;                          // largest p with shard_off[p] <= j
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (L.shard_off[mid] <= j) lo = mid; else hi = mid - 1;
-            }
-            d = g + (L.shard_base[lo] - a.gpre[L.shard_off[lo]]);
-        }
-        a.dst_tok_off[j] = d;
-        const int64_t gs = a.gpre[cur_start >= 0 ? cur_start : 0];
-        a.cu_seqlens[j + m] = (int32_t)(g - gs);
-        const bool closes = (j + 1 == N) || ((L.bits[(j + 1) >> 5] >> ((j + 1) & 31)) & 1u);
-        if (closes) a.cu_seqlens[j + m + 1] = (int32_t)(a.gpre[j + 1] - gs);
-    }
-    for (int p = tid; p <= P; p += PLANL_BLOCK) {            // micro-batches before each shard's first slot
-        const int js = L.shard_off[p];
-        int32_t c = M;
-        if (js < N) c = a.word_starts[js >> 5] + (int32_t)__popc(L.bits[js >> 5] & ((1u << (js & 31)) - 1u));
-        a.shard_mb_off[p] = c;
-    }
-    if (tid == 0) { *a.n_mb = M; a.mb_seq_off[M] = N; }
+    if (tid >= WAVE) return;
+    if (staged) walk_shard(a, s0, n, [&](int c) { return (int64_t)part[c]; });
+    else walk_shard(a, s0, n, [&](int c) { return a.gpre[s0 + c] - g0; });
 }
 
-hipError_t launch_plan_large(const PlanArgs& a, hipStream_t st) {
-    if (a.n_seq > DC_MAX_SEQ_LARGE || !a.gpre || !a.word_starts || !a.word_last) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(plan_large_kernel, dim3(1), dim3(PLANL_BLOCK), 0, st, a);
+__global__ __launch_bounds__(PL_OUT) void plan_large_out_kernel(PlanArgs a) {
+    __shared__ uint32_t bits_of[PL_OUT_WORDS + 1];        // the tile's words and the one behind them
+    __shared__ int32_t starts_before[PL_OUT_WORDS + 1], last_before[PL_OUT_WORDS];
+    __shared__ int32_t shard_off[DC_MAX_SHARDS + 1];
+    __shared__ int64_t shard_shift[DC_MAX_SHARDS];
+    __shared__ int64_t tmp64[PL_OUT / WAVE];
+    __shared__ int32_t tmp32[PL_OUT / WAVE];
+    const int tid = threadIdx.x, t = blockIdx.x;
+    const int N = a.n_seq, P = a.n_shards;
+    const int n_words = (N + 31) / 32, w0 = t * PL_OUT_WORDS;
+    if (*a.plan_ok == 0) return;                          // (uniform)
+    for (int p = tid; p <= P; p += PL_OUT) {
+        shard_off[p] = a.shard_seq_off[p];
+        if (p < P) shard_shift[p] = a.align == 1 ? 0 : a.shard_tok_off[p] - a.gpre[a.shard_seq_off[p]];
+    }
+    if (tid <= PL_OUT_WORDS) bits_of[tid] = w0 + tid < n_words ? (uint32_t)a.start_bits[w0 + tid] : 0u;
+    // starts in the words before the tile, and the last of them
+    int64_t n_mine = 0;
+    int32_t last_mine = -1;
+    for (int i = tid; i < w0; i += PL_OUT) {
+        const uint32_t b = (uint32_t)a.start_bits[i];
+        n_mine += __popc(b);
+        if (b) last_mine = i * 32 + 31 - __clz(b);        // (i grows)
+    }
+    const int32_t m0 = (int32_t)block_sum(n_mine, tmp64);
+    last_mine = wave_incl_scan_max(last_mine);
+    if ((tid & (WAVE - 1)) == WAVE - 1) tmp32[tid / WAVE] = last_mine;
+    __syncthreads();
+    if (tid < WAVE) {                                     // one wave: the tile's 32 words
+        int32_t l0 = -1;
+        for (int i = 0; i < PL_OUT / WAVE; ++i) l0 = max(l0, tmp32[i]);
+        const uint32_t b = tid < PL_OUT_WORDS ? bits_of[tid] : 0u;
+        const int32_t c = (int32_t)__popc(b);
+        const int32_t inc = wave_incl_scan_add<int32_t>(c);
+        const int32_t l = wave_incl_scan_max(b ? (w0 + tid) * 32 + 31 - __clz(b) : -1);
+        if (tid < PL_OUT_WORDS) {
+            starts_before[tid] = m0 + inc - c;
+            last_before[tid] = max(l0, wave_shift_up1(l, -1));
+        }
+        if (tid == PL_OUT_WORDS - 1) starts_before[PL_OUT_WORDS] = m0 + inc;
+    }
+    __syncthreads();
+    const int j = t * PL_OUT + tid;
+    const int wl = tid >> 5;
+    if (j < N) {
+        const uint32_t bits = bits_of[wl];
+        const uint32_t upto = bits & (0xFFFFFFFFu >> (31 - (j & 31)));           // starts at slots <= j of the word
+        const int32_t m = starts_before[wl] + (int32_t)__popc(upto) - 1;         // my micro-batch
+        const int32_t first = upto ? (j & ~31) + 31 - __clz(upto) : max(last_before[wl], 0);
+        if ((bits >> (j & 31)) & 1u) a.mb_seq_off[m] = j;
+        const int64_t g = a.gpre[j], gs = a.gpre[first];
+        int64_t d = g;
+        if (a.align != 1) {                               // uniform: shard of the slot, then its aligned base
+            int lo = 0, hi = P - 1;                       // largest p with shard_off[p] <= j
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (shard_off[mid] <= j) lo = mid; else hi = mid - 1;
+            }
+            d = g + shard_shift[lo];
+        }
+        a.dst_tok_off[j] = d;
+        a.cu_seqlens[j + m] = (int32_t)(g - gs);
+        const bool closes = (j + 1 == N) || ((bits_of[(tid + 1) >> 5] >> ((j + 1) & 31)) & 1u);
+        if (closes) a.cu_seqlens[j + m + 1] = (int32_t)(a.gpre[j + 1] - gs);
+    }
+    const bool last_tile = (t + 1) * PL_OUT >= N;
+    for (int p = tid; p <= P; p += PL_OUT) {              // micro-batches before each shard's first slot
+        const int js = shard_off[p];
+        if (js < N ? js / PL_OUT != t : !last_tile) continue;
+        const int w = (js - t * PL_OUT) >> 5;
+        a.shard_mb_off[p] = js < N ? starts_before[w] + (int32_t)__popc(bits_of[w] & ((1u << (js & 31)) - 1u)) : starts_before[PL_OUT_WORDS];
+    }
+    if (last_tile && tid == 0) {
+        const int32_t M = starts_before[PL_OUT_WORDS];
+        *a.n_mb = M;
+        a.mb_seq_off[M] = N;
+    }
+}
+
+hipError_t launch_plan_large(const PlanArgs& a, const SourceDesc& src, hipStream_t st) {
+    if (a.n_seq > DC_MAX_SEQ_LARGE || a.n_seq <= 0 || !a.gpre || !a.start_bits || !a.tile_tokens) return hipErrorInvalidValue;
+    const unsigned tiles = (unsigned)((a.n_seq + PL_TILE - 1) / PL_TILE);
+    int32_t* note = a.perm ? a.cu_seqlens : nullptr;
+    hipLaunchKernelGGL(plan_large_slots_kernel, dim3(tiles), dim3(PL_TILE), 0, st, a, src, note);
+    hipLaunchKernelGGL(plan_large_prefix_kernel, dim3(tiles), dim3(PL_TILE), 0, st, a, note);
+    hipLaunchKernelGGL(plan_large_walk_kernel, dim3((unsigned)a.n_shards), dim3(PL_WALK), 0, st, a);
+    hipLaunchKernelGGL(plan_large_out_kernel, dim3((unsigned)((a.n_seq + PL_OUT - 1) / PL_OUT)), dim3(PL_OUT), 0, st, a);
     return hipGetLastError();
 }
 

@@ -57,3 +57,19 @@ def test_portions_of_a_long_list(shards):
     for kind, n in (("tail", 16385), ("geometric", 40000)):
         per = -(-n // shards)
         _check_balance_ws(_lengths(kind, per * shards, rng).astype(np.int32), shards, label=f"{shards} shards of {per}, {kind}")
+
+
+@pytest.mark.parametrize("n,shards,budget,align,cap", [
+    (16385, 1, 64, 1, 0),               # one slot more than the LDS holds, a shard of one wave's whole walk
+    (16640, 65, 8, 3, 0),               # most micro-batches hold one or two slots
+    (33000, 1, 1 << 20, 1, 0),          # a shard that is probed in global memory; few micro-batches
+    (32768, 1, 300, 64, 0),             # the first that is
+    (32767, 1, 300, 64, 0),             # the last that is staged
+    (20000, 1000, 4096, 16, 0),
+    (20480, 16, 40, 1, 20480),          # partitions of unequal size, tiles that end with the last slot
+])
+def test_plan_of_many_slots(n, shards, budget, align, cap):
+    """dc_plan above DC_MAX_SEQ sequences: tiles, staged and unstaged shards, budgets from one slot to a whole shard."""
+    lens = np.random.default_rng(n).integers(1, 40, n).astype(np.int32)
+    w = _custom(lens, 1, shards, max(budget, 40), n_src=1, fields=())
+    check_step(w, align=align, cap=cap, label=f"{n} slots on {shards} shards, budget {budget}")
