@@ -555,18 +555,20 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     const int check_every = (int)min(64u, fit - 2u);
     int until_check = 1;
     const uint32_t full = KEY_FULL | lane;
-    const bool mine_exists = (int)lane < P;                       // lane k keeps worker k, and plays rank k of the sorted order
+    const bool mine_exists = (int)lane < P;                       // lane k keeps worker k ...
+    const uint32_t rank = net_lane(lane);                         // ... and plays this rank of the sorted order (in the general
+                                                                  // rounds: rank k)
     // WIDTH 64: P == 64.  WIDTH 8, 16 and 32: any P <= WIDTH; the keys of the lanes without a worker sort behind the
     // workers' and must stay where they are, so what is offered to their ranks is nothing: those lanes read the
     // zero word behind the last item, round after round (a stride of their own, no instruction more per round).
     constexpr bool SOME = WIDTH != WAVE;
-    const bool offers = !SOME || mine_exists;
+    const bool offers = !SOME || (int)rank < P;
     const int stride = offers ? P : 0;                            // from a rank's item of one round to its item of the next
     const uint64_t everyone = P == WAVE ? ~0ull : (1ull << P) - 1ull;
     constexpr bool EVERY_LANE = WIDTH == WAVE;
     constexpr int NS = net_steps(WIDTH);
-    constexpr int LAST = 2 * NS - 1;                              // the last gap of the sort (what an 8-lane sort has no later gap for goes there)
-    static_assert(LAST >= 11, "the rounds' side work is laid out over twelve gaps at least");
+    constexpr int LAST = NS - 1;                                  // the last gap of the sort (what an 8-lane sort has no later gap for goes there)
+    static_assert(LAST >= 5, "the rounds' side work is laid out over six gaps at least");
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     uint32_t key = (mine_exists && C > 0) ? lane : full;
     int32_t count = 0;
@@ -574,13 +576,13 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     if constexpr (PORTION) { key = carry->key; count = carry->count; load = carry->load; }
     const int32_t row_base = count;                               // PORTION: my row's first entry is my item number row_base
     int pos = 0;
-    uint32_t e = items[offers ? (int)lane : N];                   // the item offered to rank `lane` (the array is padded with zeros)
+    uint32_t e = items[mine_exists ? (int)lane : N];              // the item offered to rank `lane` (the array is padded with zeros)
     bool all_take = C > 0;
     if constexpr (PORTION) all_take = __ballot(mine_exists && key >= KEY_FULL) == 0ull;
     const uint32_t pitch4 = (uint32_t)pitch * 4u;
     int no_look = 0, look_wait = 0;                               // tested rounds before the bound is looked at again
     char* const rows_b = reinterpret_cast<char*>(rows);
-    char* const spare_b = reinterpret_cast<char*>(spare_word);
+    const uint32_t spare_at = (uint32_t)(reinterpret_cast<char*>(spare_word) - rows_b);      // (both lie in the LDS)
 
     while (pos < N) {
         if constexpr (PORTION) {                                  // a full row ends the portion
@@ -605,33 +607,37 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
             const int64_t off = load - (int64_t)(key >> 6);       // what the key does not hold of my worker's load
             int64_t taken = 0;                                    // load taken off the keys by rebasing in here
             int rounds = 0;
-            uint32_t sk = wave_sort_asc<WIDTH>(key);
+            uint32_t sk = net_swap_order(wave_sort_asc<WIDTH>(key));
+            e = net_swap_order(e);                                // from here on by `rank`
+            uint32_t len = e >> 16;
             // >= 1: until a worker (PORTION: or a row) is full or the items run out
             const int n_rounds = PORTION ? min(min(C - __builtin_amdgcn_readfirstlane((int)gmax), row_cap - c_hi), (N - pos) / P)
                                          : min(C - c_hi, (N - pos) / P);
-            const uint32_t* next_item = offers ? items + pos + P + (int)lane : items + N;      // the item of the next round for this rank
+            const uint32_t* next_item = offers ? items + pos + P + (int)rank : items + N;      // the item of the next round for this rank
             int32_t count4 = in_row * 4;                          // lane k: 4 x (worker k's place in its row at round 0 of the phase)
             uint64_t refused_acc = 0;                             // ranks a refused round would have accepted
 
             // One round that is known to stand; r = rounds done before it in this phase.  LEVEL: all counts are c_lo.
+            // (Two instructions of side work per gap are free, see wave_sort_steps.)
             auto sure_round = [&](int r, auto level_c) {
                 constexpr bool LEVEL = decltype(level_c)::value;
-                uint32_t v = sk + ((e >> 16) << 6);               // the keys after this round
-                const uint32_t id = sk & 63u;                     // the worker rank `lane` belongs to
-                uint32_t e1 = 0;
-                int32_t before4 = 0;
+                uint32_t v = sk + (len << 6);                     // the keys after this round
                 const uint32_t row_at = 4u * (uint32_t)(LEVEL ? c_lo + r : r);
+                uint32_t id = 0, e1 = 0, at = 0;                  // id: the worker this rank belongs to
+                int32_t before4 = 0;
                 v = wave_sort_steps<WIDTH, 0, NS>(v, [&](auto slot) {
                     constexpr int S = decltype(slot)::value;
-                    if constexpr (S == 0) e1 = *next_item;
-                    if constexpr (S == 1 && !LEVEL) before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4);
-                    if constexpr (S == 3) next_item += stride;
-                    if constexpr (S == 8) {
-                        char* at = rows_b + (__umul24(id, pitch4) + (uint32_t)before4 + row_at);
-                        if constexpr (!EVERY_LANE) at = mine_exists ? at : spare_b;
-                        *reinterpret_cast<uint32_t*>(at) = e;      // filed with its worker
+                    constexpr int STORE = LEVEL ? 3 : (LAST < 9 ? LAST : 9);      // (!LEVEL: the cross-lane read has come back)
+                    if constexpr (S == 0) { e1 = *next_item; id = sk & 63u; }
+                    if constexpr (S == 1) { at = __umul24(id, pitch4); next_item += stride; }
+                    if constexpr (S == 2 && !LEVEL) before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4);
+                    if constexpr (S == (LEVEL ? 2 : STORE)) {
+                        at += row_at;
+                        if constexpr (!LEVEL) at += (uint32_t)before4;
+                        if constexpr (!EVERY_LANE) at = offers ? at : spare_at;
                     }
-                    if constexpr (S == (LAST < 12 ? LAST : 12)) e = e1;
+                    if constexpr (S == STORE) *reinterpret_cast<uint32_t*>(rows_b + at) = e;      // filed with its worker
+                    if constexpr (S == LAST) { e = e1; len = e1 >> 16; }
                 });
                 sk = v;
             };
@@ -639,32 +645,31 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
             // it); false, and nothing changed but refused_acc, if it does not stand.  The row entry is written before
             // the outcome is known: a worker that does not take the item files its next one in the same place.
             auto tested_round = [&](int r) -> bool {
-                const uint32_t sk_in = sk, e_in = e;
-                uint32_t v = sk + ((e >> 16) << 6);
-                uint32_t m = v;                                   // becomes the running minimum of the updated keys
-                const uint32_t id = sk & 63u;
-                uint32_t e1 = 0;
+                const uint32_t sk_in = sk, e_in = e, len_in = len;
+                uint32_t v = sk + (len << 6);
+                uint32_t m = v;                                   // becomes the running minimum of the updated keys, by rank
+                uint32_t id = 0, e1 = 0, at = 0, sk_by_rank = 0;
                 int32_t before4 = 0;
                 v = wave_sort_steps<WIDTH, 0, NS>(v, [&](auto slot) {
                     constexpr int S = decltype(slot)::value;
-                    if constexpr (S == 0) e1 = *next_item;
-                    if constexpr (S == 1) before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4);
-                    if constexpr (S == 3) m = umin32(m, dpp_mov<DPP_ROW_SHR1>(NONE, m));
-                    if constexpr (S == 5) m = umin32(m, dpp_mov<DPP_ROW_SHR2>(NONE, m));
-                    if constexpr (S == 6) m = umin32(m, dpp_mov<DPP_ROW_SHR4>(NONE, m));
-                    if constexpr (S == 7) m = umin32(m, dpp_mov<DPP_ROW_SHR8>(NONE, m));
-                    if constexpr (S == 8) m = umin32(m, dpp_mov<DPP_ROW_BCAST15, 0xA>(NONE, m));
-                    if constexpr (S == 9) m = umin32(m, dpp_mov<DPP_ROW_BCAST31, 0xC>(NONE, m));
-                    if constexpr (S == 10) {
-                        char* at = rows_b + (__umul24(id, pitch4) + (uint32_t)before4 + 4u * (uint32_t)r);
-                        if constexpr (!EVERY_LANE) at = mine_exists ? at : spare_b;
-                        *reinterpret_cast<uint32_t*>(at) = e;
+                    constexpr int STORE = LAST < 9 ? LAST : 9;
+                    if constexpr (S == 0) { e1 = *next_item; m = net_swap_order(m); }
+                    if constexpr (S == 1) { id = sk & 63u; m = umin32(m, dpp_mov<DPP_ROW_SHR1>(NONE, m)); }
+                    if constexpr (S == 2) { before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4); m = umin32(m, dpp_mov<DPP_ROW_SHR2>(NONE, m)); }
+                    if constexpr (S == 3) { at = __umul24(id, pitch4); m = umin32(m, dpp_mov<DPP_ROW_SHR4>(NONE, m)); }
+                    if constexpr (S == 4 && WIDTH > 8) m = umin32(m, dpp_mov<DPP_ROW_SHR8>(NONE, m));
+                    if constexpr (S == 5 && WIDTH > 16) m = umin32(m, dpp_mov<DPP_ROW_BCAST15, 0xA>(NONE, m));
+                    if constexpr (S == 6 && WIDTH > 32) m = umin32(m, dpp_mov<DPP_ROW_BCAST31, 0xC>(NONE, m));
+                    if constexpr (S == (LAST < 7 ? LAST : 7)) { m = dpp_mov<DPP_WAVE_SHR1>(NONE, m); sk_by_rank = net_swap_order(sk_in); }
+                    if constexpr (S == STORE) {
+                        at += (uint32_t)before4 + 4u * (uint32_t)r;
+                        if constexpr (!EVERY_LANE) at = offers ? at : spare_at;
+                        *reinterpret_cast<uint32_t*>(rows_b + at) = e;
                     }
-                    if constexpr (S == 11) m = dpp_mov<DPP_WAVE_SHR1>(NONE, m);
-                    if constexpr (S == (LAST < 13 ? LAST : 13)) e = e1;
+                    if constexpr (S == LAST) { e = e1; len = e1 >> 16; }
                 });
-                const uint64_t acc = __ballot(sk_in < m) & everyone;
-                if (__builtin_expect(acc != everyone, 0)) { e = e_in; refused_acc = acc; return false; }
+                const uint64_t acc = __ballot(sk_by_rank < m) & everyone;
+                if (__builtin_expect(acc != everyone, 0)) { e = e_in; len = len_in; refused_acc = acc; return false; }
                 next_item += stride;
                 sk = v;
                 return true;
@@ -675,17 +680,17 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
             // sits out (count4, told to the worker's lane), and the next round's items start behind the ones taken.
             auto short_round = [&]() {
                 const int took = __ffsll((long long)~refused_acc) - 1;     // >= 1: the lowest rank always takes
-                const bool take = (int)lane < took;
-                uint32_t v = take ? sk + ((e >> 16) << 6) : sk;
-                const uint32_t to = mine_exists ? (sk & 63u) : lane;        // lanes without a worker talk to themselves
-                const uint32_t* const at = offers ? items + pos + took + (int)lane : items + N;      // (the array is padded)
+                const bool take = (int)rank < took;
+                uint32_t v = take ? sk + (len << 6) : sk;
+                const uint32_t to = offers ? (sk & 63u) : rank;             // ranks without a worker talk to lanes without one
+                const uint32_t* const at = offers ? items + pos + took + (int)rank : items + N;      // (the array is padded)
                 uint32_t e1 = 0;
                 int32_t behind4 = 0;
                 v = wave_sort_steps<WIDTH, 0, NS>(v, [&](auto slot) {
                     constexpr int S = decltype(slot)::value;
                     if constexpr (S == 0) e1 = *at;
                     if constexpr (S == 1) behind4 = __builtin_amdgcn_ds_permute((int)(to << 2), take ? 0 : 4);
-                    if constexpr (S == (LAST < 12 ? LAST : 12)) { count4 -= behind4; e = e1; }
+                    if constexpr (S == LAST) { count4 -= behind4; e = e1; len = e1 >> 16; }
                 });
                 sk = v;
                 next_item = at + stride;
@@ -708,7 +713,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                 const int may = min(n_rounds - rounds, until_check) / FAST_BATCH;      // batches before the phase ends / the next check
                 if (may > 0 && --no_look < 0) {
                     const uint32_t k_lo = (uint32_t)__builtin_amdgcn_readlane((int)sk, 0);
-                    const uint32_t k_hi = (uint32_t)__builtin_amdgcn_readlane((int)sk, P - 1);        // (the workers' largest)
+                    const uint32_t k_hi = (uint32_t)__builtin_amdgcn_readlane((int)sk, (int)net_lane((uint32_t)P - 1u));        // (the workers' largest)
                     const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)e, 0) >> 16;
                     const uint32_t need = max((k_hi - k_lo) >> 6, first >> 1);
                     const uint32_t probe = items[min(pos + ((int)lane + 1) * (FAST_BATCH * P) - 1, N - 1)] >> 16;
@@ -748,8 +753,9 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                     no_look -= want - burst;
                 }
             }
-            // back to worker lanes: rank r sends its key to lane (sk & 63); lanes without a worker send theirs to themselves
-            if (!mine_exists) sk = full;                          // (whatever the rounds left in their lanes)
+            // back to worker lanes: a rank sends its key to lane (sk & 63), ranks without a worker to the lanes without one
+            if ((int)rank >= P) sk = KEY_FULL | rank;             // (whatever the rounds left in their lanes)
+            e = net_swap_order(e);                                // by lane again
             key = (uint32_t)__builtin_amdgcn_ds_permute((int)((sk & 63u) << 2), (int)sk);
             if (mine_exists) {
                 count = (count4 >> 2) + rounds + (PORTION ? row_base : 0);      // one item per round but the ones sat out
@@ -792,7 +798,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
             key = (count == C) ? full : nk;
         }
         pos += m;
-        e = offers ? next_e : 0u;
+        e = !SOME || mine_exists ? next_e : 0u;
         all_take = __ballot(mine_exists && key >= KEY_FULL) == 0ull;      // every worker is open: the next round is tried above
     }
     if (mine_exists) shard_load[lane] = load;
@@ -803,7 +809,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
 
 // ---------------------------------------------------------------- rounds of one wave that keeps up to 256 workers
 // The packed rounds for 33 .. 63 and 65 .. 256 workers: wave 0 keeps K = 1, 2 or 4 of the sorted keys in a lane (rank
-// r * 64 + lane in register r; key = load << 8 | worker, rebased as above), sorts them with wave_sort_multi, and never
+// r * 64 + net_lane(lane) in register r; key = load << 8 | worker, rebased as above), sorts them with wave_sort_multi, and never
 // goes back from ranks to workers: a worker's number of items stands in the LDS (not at all while every worker holds the
 // same number), its load goes out when it is full or at the end.  Two kinds of round:
 //   sure     the bound of lpt_rounds_packed says that the round places one item on every worker: nothing is tested;
@@ -851,13 +857,14 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
                                                 uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     const int lane = threadIdx.x;                                 // (wave 0)
+    const int rl = (int)net_lane(lane);                           // register r of this lane holds rank r * 64 + rl
     uint32_t sk[K], e[K];
     bool offers[K];                                               // while all workers are open: a worker has this rank
 #pragma unroll
     for (int r = 0; r < K; ++r) {
-        sk[r] = m.key[r * WAVE + lane];
-        offers[r] = r * WAVE + lane < P;
-        e[r] = items[offers[r] ? r * WAVE + lane : N];            // (zeros behind the last item)
+        sk[r] = m.key[r * WAVE + rl];
+        offers[r] = r * WAVE + rl < P;
+        e[r] = items[offers[r] ? r * WAVE + rl : N];              // (zeros behind the last item)
     }
     int64_t taken = m.taken;
     int pos = 0;
@@ -899,7 +906,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             v[r] = sk[r] + ((e[r] >> 16) << MULTI_ID_BITS);
-            e1[r] = items[offers[r] ? pos + P + r * WAVE + lane : N];
+            e1[r] = items[offers[r] ? pos + P + r * WAVE + rl : N];
             c[r] = LEVEL ? c_row : m.cnt[sk[r] & MULTI_ID_MASK];
         }
 #pragma unroll
@@ -945,7 +952,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
 #pragma unroll
             for (int r = 1; r < K; ++r)
                 if (P > r * WAVE) top = sk[r];                    // (uniform)
-            const uint32_t k_hi = (uint32_t)__builtin_amdgcn_readlane((int)top, (P - 1) & (WAVE - 1));
+            const uint32_t k_hi = (uint32_t)__builtin_amdgcn_readlane((int)top, (int)net_lane((P - 1) & (WAVE - 1)));
             const uint32_t k_lo = (uint32_t)__builtin_amdgcn_readlane((int)sk[0], 0);
             const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)e[0], 0) >> 16;
             const uint32_t need = max((k_hi - k_lo) >> MULTI_ID_BITS, first >> 1);
@@ -975,11 +982,12 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         bool whole = true;                                        // (uniform) every rank so far takes its item
 #pragma unroll
         for (int r = 0; r < K; ++r) {
-            const bool valid = sk[r] < MULTI_FULL && pos + r * WAVE + lane < N;
+            const bool valid = sk[r] < MULTI_FULL && pos + r * WAVE + rl < N;
             newk[r] = valid ? sk[r] + ((e[r] >> 16) << MULTI_ID_BITS) : NONE;
-            const uint32_t inc = wave_incl_scan_umin(newk[r]);
+            // (the scan and the ballot go by rank)
+            const uint32_t inc = wave_incl_scan_umin(net_swap_order(newk[r]));
             const uint32_t pm = umin32(dpp_mov<DPP_WAVE_SHR1>(NONE, inc), run_min);
-            const uint64_t acc = __ballot(valid && sk[r] < pm);
+            const uint64_t acc = __ballot(net_swap_order(valid ? sk[r] : NONE) < pm);
             const int n = (~acc == 0ull) ? WAVE : (__ffsll((long long)~acc) - 1);
             if (whole) took += n;
             whole = whole && n == WAVE;
@@ -996,7 +1004,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         }
 #pragma unroll
         for (int r = 0; r < K; ++r) {
-            const bool take = r * WAVE + lane < took;
+            const bool take = r * WAVE + rl < took;
             const uint32_t id = sk[r] & MULTI_ID_MASK;
             if (take) {
                 rows[(int)id * pitch + c[r]] = e[r];
@@ -1011,7 +1019,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         slack -= 1;
         fresh = still;
 #pragma unroll
-        for (int r = 0; r < K; ++r) e[r] = items[offers[r] ? pos + r * WAVE + lane : N];      // (zeros behind the last item)
+        for (int r = 0; r < K; ++r) e[r] = items[offers[r] ? pos + r * WAVE + rl : N];        // (zeros behind the last item)
         wave_sort_multi<K>(sk);
     }
     // the workers that are not full (level: none is marked)
@@ -1020,7 +1028,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         const uint32_t id = sk[r] & MULTI_ID_MASK;
         if (sk[r] < MULTI_FULL) shard_load[id] = (int64_t)(sk[r] >> MULTI_ID_BITS) + taken;
         if (level) m.cnt[id] = c_row;
-        m.key[r * WAVE + lane] = sk[r];
+        m.key[r * WAVE + rl] = sk[r];
     }
     if (lane == 0) m.taken = taken;
     return pos;

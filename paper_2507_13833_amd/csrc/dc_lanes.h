@@ -18,6 +18,8 @@ constexpr int DPP_ROW_SHR4 = 0x114;
 constexpr int DPP_ROW_SHR8 = 0x118;
 constexpr int DPP_ROW_ROR8 = 0x128;         // lane ^ 8
 constexpr int DPP_WAVE_SHR1 = 0x138;        // lane i <- lane i-1 across the whole wave
+constexpr int DPP_QUAD_PERM_0123R = 0x1B;   // lane ^ 3
+constexpr int DPP_ROW_HALF_MIRROR = 0x141;  // lane ^ 7
 constexpr int DPP_ROW_BCAST15 = 0x142;      // lane 15 of each row -> every lane of the next row
 constexpr int DPP_ROW_BCAST31 = 0x143;      // lane 31 -> every lane of rows 2 and 3
 
@@ -144,8 +146,15 @@ __device__ __forceinline__ uint32_t wave_sort_back(uint32_t v, uint32_t after) {
     return bitonic_merge<WIDTH, WIDTH / 4>(v);
 }
 
-// The same network one compare-exchange at a time, so that a caller can place other work between the
-// steps.  Step i of the sort of WIDTH lanes is (net_k(i), net_j(i)): merge size and partner distance.
+// The same network one compare-exchange at a time, so that a caller can place other work between the steps, over lanes
+// in another order: position r of the order stands in lane net_lane(r), which is r with the lanes of every second quad
+// reversed.  Partners at distance 4 are then lanes at distance 7, which one DPP move reaches (row_half_mirror) where
+// lane ^ 4 takes two with the idle cycles of a second one between them; distances 1, 2, 8, 16, 32 are lanes at the same.
+// Step i of the sort of WIDTH lanes is (net_k(i), net_j(i)): merge size and partner distance.
+__device__ __forceinline__ uint32_t net_lane(uint32_t r) { return r ^ ((r & 4u) ? 3u : 0u); }       // its own inverse
+// The value of position `lane` of the order from one in position order, and the other way round.
+__device__ __forceinline__ uint32_t net_swap_order(uint32_t v) { return dpp_mov<DPP_QUAD_PERM_0123R, 0xF, 0xA>(v, v); }
+
 constexpr int net_steps(int width) {
     int n = 0;
     for (int k = 2; k <= width; k <<= 1)
@@ -163,46 +172,55 @@ constexpr int net_j(int i) {
             if (i-- == 0) return j;
 }
 struct XchgPair { uint32_t a, b; };       // a lane's key and its partner's, in either order
-// First half of a step: fetch the partner's key (the cross-lane move).
+// First half of a step: fetch the partner's key (the cross-lane move).  v2: a second register with v's value where the
+// move swaps rows of two registers (distance 16 and 32).
 template <int J>
-__device__ __forceinline__ XchgPair xchg_fetch(uint32_t v) {
+__device__ __forceinline__ XchgPair xchg_fetch(uint32_t v, uint32_t v2) {
     XchgPair x;
     if constexpr (J == 16) {
-        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        auto r = __builtin_amdgcn_permlane16_swap(v, v2, false, false);
         x.a = r[0]; x.b = r[1];
     } else if constexpr (J == 32) {
-        auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        auto r = __builtin_amdgcn_permlane32_swap(v, v2, false, false);
         x.a = r[0]; x.b = r[1];
     } else {
-        x.a = v; x.b = lane_xor<J>(v);
+        x.a = v;
+        if constexpr (J == 4) x.b = dpp_perm<DPP_ROW_HALF_MIRROR>(v);
+        else x.b = lane_xor<J>(v);
     }
     return x;
 }
 // Second half: keep the smaller or the larger of the two (see bitonic_step).
 template <int K, int J>
-__device__ __forceinline__ uint32_t xchg_keep(XchgPair x) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t pick = ((lane & J) == 0) == ((lane & K) == 0) ? 0u : 0xFFFFFFFFu;
-    return umed3(x.a, x.b, pick);
+__device__ __forceinline__ uint32_t xchg_pick() {
+    const uint32_t r = net_lane(threadIdx.x & 63u);
+    return ((r & J) == 0) == ((r & K) == 0) ? 0u : 0xFFFFFFFFu;
+}
+// The same median once more, in a register of its own (behind the first one it costs one issue; a copy of the first
+// one's result would wait for it).
+__device__ __forceinline__ uint32_t umed3_again(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm volatile("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
-// Steps [FROM, TO) of the sort of WIDTH lanes.  side(slot) is called twice per step, with the compile-time
-// slot numbers 2 i (between the fetch and the keep of step i) and 2 i + 1 (behind the keep); what it does
-// there is issued in the idle cycles between the step's two dependent instructions and must not depend
-// on the sort.  The scheduler is told to leave that order alone.
+// Steps [FROM, TO) of the sort of WIDTH lanes.  side(slot) is called behind every step, slot = the step's number: what
+// it does there is issued between the step's last instruction and the next step's cross-lane move, which has to wait two
+// issue slots for it: two instructions there are free, and must not depend on the sort.  (An instruction of this
+// wave issues every four cycles whether it depends on the one before or not, but for those two slots; a step is the
+// move, the median and the wait, 16 cycles.)  The scheduler is told to leave that order alone.
 template <int WIDTH, int FROM, int TO, typename Side>
-__device__ __forceinline__ uint32_t wave_sort_steps(uint32_t v, Side&& side) {
+__device__ __forceinline__ uint32_t wave_sort_steps(uint32_t v, Side&& side, uint32_t v2 = 0) {
     if constexpr (FROM < TO) {
         constexpr int K = net_k(FROM), J = net_j(FROM);
-        const XchgPair x = xchg_fetch<J>(v);
+        const XchgPair x = xchg_fetch<J>(v, v2);
+        const uint32_t pick = xchg_pick<K, J>();
+        v = umed3(x.a, x.b, pick);
+        if constexpr (FROM + 1 < TO && net_j(FROM + 1) >= 16) v2 = umed3_again(x.a, x.b, pick);
         __builtin_amdgcn_sched_barrier(0);
-        side(std::integral_constant<int, 2 * FROM>{});
+        side(std::integral_constant<int, FROM>{});
         __builtin_amdgcn_sched_barrier(0);
-        v = xchg_keep<K, J>(x);
-        __builtin_amdgcn_sched_barrier(0);
-        side(std::integral_constant<int, 2 * FROM + 1>{});
-        __builtin_amdgcn_sched_barrier(0);
-        return wave_sort_steps<WIDTH, FROM + 1, TO>(v, side);
+        return wave_sort_steps<WIDTH, FROM + 1, TO>(v, side, v2);
     } else {
         return v;
     }
@@ -210,8 +228,8 @@ __device__ __forceinline__ uint32_t wave_sort_steps(uint32_t v, Side&& side) {
 
 __device__ __forceinline__ uint32_t umin32(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
-// Ascending sort of 64 * K keys of one wave, K = 1, 2 or 4 to a lane: key r * 64 + lane of the order in v[r].  The same
-// bitonic network over the index r * 64 + lane: the K registers are K independent chains (they fill the idle cycles
+// Ascending sort of 64 * K keys of one wave, K = 1, 2 or 4 to a lane: position r * 64 + net_lane(lane) of the order in
+// v[r].  The same bitonic network over that position: the K registers are K independent chains (they fill the idle cycles
 // between a step's two dependent instructions), and a step whose partner is 64 or more away needs no move between lanes.
 template <int KK, int J, int K>
 __device__ __forceinline__ void multi_step(uint32_t (&v)[K]) {
@@ -226,10 +244,10 @@ __device__ __forceinline__ void multi_step(uint32_t (&v)[K]) {
                 v[r + D] = asc ? (a < b ? b : a) : (a < b ? a : b);
             }
     } else {
-        const uint32_t lane = threadIdx.x & 63u;
+        const uint32_t lane = net_lane(threadIdx.x & 63u);    // (the position this lane holds)
         XchgPair x[K];
 #pragma unroll
-        for (int r = 0; r < K; ++r) x[r] = xchg_fetch<J>(v[r]);
+        for (int r = 0; r < K; ++r) x[r] = xchg_fetch<J>(v[r], v[r]);
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             const bool asc = KK < 64 ? (lane & KK) == 0 : ((r * 64) & KK) == 0;
