@@ -93,7 +93,7 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(Balan
         const int j = q * PLAN_BLOCK + (int)threadIdx.x;
         if (j < b.N) p.slot_len[j] = s.len[q];
     }
-    __syncthreads();                                              // Algorithm 1's tables have been read for the last time
+    lds_barrier();                                                // Algorithm 1's tables have been read for the last time
     plan_body(*reinterpret_cast<PlanLds*>(lds), p, s.seq, s.len, false, b.C);
 }
 

@@ -53,7 +53,7 @@ __device__ __forceinline__ void counting_pass(BalLds& L, int N, int rounds, Digi
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     const int wave_base = w * rounds * WAVE;
     for (int i = tid; i < 256 * CNT_PITCH; i += BAL_BLOCK) L.cnt[i] = 0;
-    __syncthreads();
+    lds_barrier();
     uint32_t packed[BAL_ROUNDS];                                  // digit << 16 | rank before me in my wave
 #pragma unroll
     for (int r = 0; r < BAL_ROUNDS; ++r) {
@@ -88,7 +88,7 @@ __device__ __forceinline__ void counting_pass(BalLds& L, int N, int rounds, Digi
             packed[r] = (d << 16) | (old + (uint32_t)before);
         }
     }
-    __syncthreads();
+    lds_barrier();
     {   // exclusive scan of the 4096 counters in (digit, wave) order: thread t takes digit t / 4, waves 4 (t % 4) ...
         static_assert(BAL_BLOCK * 4 == 256 * BAL_WAVES, "four counters per thread");
         uint32_t* mine = &L.cnt[(tid >> 2) * CNT_PITCH + (tid & 3) * 4];
@@ -100,7 +100,7 @@ __device__ __forceinline__ void counting_pass(BalLds& L, int N, int rounds, Digi
 #pragma unroll
         for (int q = 0; q < 4; ++q) { mine[q] = run; run += c4[q]; }
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int r = 0; r < BAL_ROUNDS; ++r) {
         if (r < rounds) {
@@ -111,7 +111,7 @@ __device__ __forceinline__ void counting_pass(BalLds& L, int N, int rounds, Digi
             }
         }
     }
-    __syncthreads();
+    lds_barrier();
 }
 
 // The packed items (length << 16 | index, one per sequence) in the order of Algorithm 1's sorted list, longest
@@ -211,7 +211,7 @@ __device__ __forceinline__ bool bin_sort_packed(BalLds& L, int N, uint32_t longe
             }
         }
     }
-    __syncthreads();
+    lds_barrier();
     // counts -> starts: a thread takes `per` consecutive 16-byte pieces (an odd number of them where that fits, for the banks)
     uint4* quads = reinterpret_cast<uint4*>(L.keys);
     const int nq = (nw + 3) >> 2;
@@ -253,7 +253,7 @@ __device__ __forceinline__ bool bin_sort_packed(BalLds& L, int N, uint32_t longe
         }
         *((k < per && lo + k < nq) ? quads + lo + k : nowhere) = make_uint4(y[0], y[1], y[2], y[3]);
     }
-    __syncthreads();
+    lds_barrier();
     auto run_of = [&](uint32_t b) {                               // start of the run of bin b | its size << 16
         const uint32_t wa = bins[b >> 1], wb = bins[(b >> 1) + 1];
         const uint32_t start = (b & 1u) ? wa >> 16 : wa & 0xFFFFu;
@@ -278,7 +278,7 @@ __device__ __forceinline__ bool bin_sort_packed(BalLds& L, int N, uint32_t longe
         }
     }
     out[N + (tid & 127)] = 0;
-    __syncthreads();
+    lds_barrier();
     // Is every run in index order?  (A thread looks at places q * BAL_BLOCK + tid here, not at its sequences; a
     // place beyond the last one repeats the last one's work.)
     {
@@ -296,7 +296,7 @@ __device__ __forceinline__ bool bin_sort_packed(BalLds& L, int N, uint32_t longe
         }
         const bool here = __ballot(wrong) != 0ull;
         if (lane == 0) L.red[tid / WAVE] = here ? 1 : 0;
-        __syncthreads();
+        lds_barrier();
         int any = 0;
 #pragma unroll
         for (int i = 0; i < BAL_WAVES; ++i) any |= L.red[i];
@@ -1082,14 +1082,14 @@ __device__ __forceinline__ int lpt_rounds_wide_portion(BalLds& L, int N, int P, 
     int pos = 0;
     while (pos < N) {                                                 // pos is the same in every thread
         kbuf[tid] = key;
-        __syncthreads();
+        lds_barrier();
         // my rank = keys below mine (keys are distinct: the worker id sits in the low bits)
         if (tid < P) {
             int rank = 0;
             for (int j = 0; j < P; ++j) rank += kbuf[j] < key ? 1 : 0;
             sbuf[rank] = key;
         }
-        __syncthreads();
+        lds_barrier();
         // ---- rank view: thread r offers item I[pos + r] to the worker with the r-th smallest key ----
         const uint64_t sk = tid < P ? sbuf[tid] : ~0ull;
         const int t = pos + tid;
@@ -1106,19 +1106,19 @@ __device__ __forceinline__ int lpt_rounds_wide_portion(BalLds& L, int N, int P, 
         uint64_t pm = __shfl_up(inc, 1, WAVE);
         if (lane == 0) pm = ~0ull;
         if (lane == WAVE - 1) L.tmp64[w] = inc;
-        __syncthreads();
+        lds_barrier();
         for (int q = 0; q < w; ++q) pm = umin64(pm, L.tmp64[q]);
         // accepted prefix: ranks below the first one whose worker is no longer the minimum
         const uint64_t fail = __ballot(!(valid && sk < pm));
         if (lane == 0) L.red[w] = fail ? w * WAVE + (__ffsll((long long)fail) - 1) : BAL_BLOCK;
-        __syncthreads();
+        lds_barrier();
         int m = BAL_BLOCK;
         for (int q = 0; q < BAL_WAVES; ++q) m = min(m, L.red[q]);
         if (m == 0) break;                                            // cannot happen: cap * P >= N (uniform)
         // back to the workers: rank r sends its updated key, its own rank in place of the worker id
         if (tid < m) kbuf[sk & WIDE_ID_MASK] = (newk & ~WIDE_ID_MASK) | (uint64_t)tid;
         const uint64_t thr = sbuf[m - 1];
-        __syncthreads();
+        lds_barrier();
         if (tid < P && key <= thr) {                                  // my worker is among the m smallest
             const uint64_t recv = kbuf[tid];
             const uint64_t nk = (recv & ~WIDE_ID_MASK) | (uint64_t)tid;
@@ -1186,7 +1186,7 @@ __device__ __forceinline__ int lpt_rounds_wide32_portion(BalLds& L, int N, int P
             mine = wave_sort_asc<WAVE>(key);
             run[tid] = mine;
         }
-        __syncthreads();
+        lds_barrier();
         if (w < nw) {
             int rank = lane;
             for (int q0 = 0; q0 < nw; q0 += 4) {                      // (uniform)
@@ -1201,7 +1201,7 @@ __device__ __forceinline__ int lpt_rounds_wide32_portion(BalLds& L, int N, int P
             }
             sbuf[min(rank, DC_MAX_SHARDS - 1)] = mine;                // (keys are distinct: every rank is taken once)
         }
-        __syncthreads();
+        lds_barrier();
         // ---- rank view: thread r offers item I[pos + r] to the worker with the r-th smallest key ----
         const uint32_t sk = tid < P ? sbuf[tid] : 0xFFFFFFFFu;
         low = sbuf[0];
@@ -1213,19 +1213,19 @@ __device__ __forceinline__ int lpt_rounds_wide32_portion(BalLds& L, int N, int P
         const uint32_t inc = wave_incl_scan_umin(newk);
         uint32_t pm = dpp_mov<DPP_WAVE_SHR1>(0xFFFFFFFFu, inc);
         if (lane == WAVE - 1) L.tmp32[w] = inc;
-        __syncthreads();
+        lds_barrier();
         for (int q = 0; q < w; ++q) pm = umin32(pm, L.tmp32[q]);
         // accepted prefix: ranks below the first one whose worker is no longer the minimum
         const uint64_t fail = __ballot(!(valid && sk < pm));
         if (lane == 0) L.red[w] = fail ? w * WAVE + (__ffsll((long long)fail) - 1) : BAL_BLOCK;
-        __syncthreads();
+        lds_barrier();
         int m = BAL_BLOCK;
         for (int q = 0; q < BAL_WAVES; ++q) m = min(m, L.red[q]);
         if (m == 0) break;                                            // cannot happen: cap * P >= N (uniform)
         // back to the workers: rank r sends its updated key, its own rank in place of the worker id
         if (tid < m) kbuf[sk & W32_ID_MASK] = (newk & ~W32_ID_MASK) | (uint32_t)tid;
         const uint32_t thr = sbuf[m - 1];
-        __syncthreads();
+        lds_barrier();
         if (tid < P && key <= thr) {                                  // my worker is among the m smallest
             const uint32_t recv = kbuf[tid];
             const uint32_t nk = (recv & ~W32_ID_MASK) | (uint32_t)tid;
@@ -1248,7 +1248,7 @@ __device__ __forceinline__ int lpt_rounds_wide32_portion(BalLds& L, int N, int P
 __device__ __forceinline__ void lpt_wide_finish(BalLds& L, int N, int P, const WideCarry& carry,
                                                 int32_t* __restrict__ shard_seq_off, int64_t* __restrict__ shard_load) {
     const int tid = threadIdx.x;
-    __syncthreads();                                                  // kbuf / sbuf are done with: the tables take their place
+    lds_barrier();                                                  // kbuf / sbuf are done with: the tables take their place
     int32_t total;
     const int32_t off = block_excl_scan_add<int32_t>(carry.count, reinterpret_cast<int32_t*>(L.tmp32), &total);
     int32_t* part_off = reinterpret_cast<int32_t*>(L.cnt) + PART_OFF_AT;
@@ -1295,12 +1295,21 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const int rounds = (N + BAL_BLOCK - 1) / BAL_BLOCK;           // <= BAL_ROUNDS
     int32_t mx = 0, mn = INT32_MAX;
     int32_t mine_len[BAL_ROUNDS];
+    // (every load of the lane is issued before the first is looked at: a test between them would make each wait for its own)
+#pragma unroll
+    for (int g = 0; g < BAL_ROUNDS; g += BIN_GROUP) {
+#pragma unroll
+        for (int q = g; q < g + BIN_GROUP; ++q) mine_len[q] = 1;
+        if (g < rounds) {                                         // (uniform)
+#pragma unroll
+            for (int q = g; q < g + BIN_GROUP; ++q) mine_len[q] = seq_len[min(bal_item(q, rounds), N - 1)];
+        }
+    }
 #pragma unroll
     for (int q = 0; q < BAL_ROUNDS; ++q) {
-        const int i = bal_item(q, rounds);
+        int32_t s = mine_len[q];
         mine_len[q] = 1;
-        if (q < rounds && i < N) {
-            int32_t s = seq_len[i];
+        if (q < rounds && bal_item(q, rounds) < N) {
             if (s <= 0 || s > DC_MAX_SEQ_LEN) { set_status(status, DC_ERR_ZERO_LENGTH_SEQ); s = 1; }
             mine_len[q] = s;
             mx = max(mx, s);
@@ -1314,7 +1323,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         mn = min(mn, (int32_t)lo);
     });
     if (lane == 0) { L.red[w] = mx; L.red[BAL_WAVES + w] = mn; }
-    __syncthreads();
+    lds_barrier();
     mx = 0; mn = INT32_MAX;
     for (int i = 0; i < BAL_WAVES; ++i) { mx = max(mx, L.red[i]); mn = min(mn, L.red[BAL_WAVES + i]); }
     const uint32_t range = N > 0 ? (uint32_t)(mx - mn) : 0u;
@@ -1341,7 +1350,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                 const int i = bal_item(q, rounds);
                 if (q < rounds && i < N) src[i] = ((uint32_t)mine_len[q] << 16) | (uint32_t)i;
             }
-            __syncthreads();
+            lds_barrier();
             for (int pass = 0; pass < passes; ++pass) {
                 const int shift = pass * 8;
                 counting_pass(L, N, rounds,
@@ -1353,7 +1362,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         uint32_t* const items = src;                              // I of Algorithm 1, each entry with its length
         uint32_t* const rows = dst;
         if (tid < PLACE_PAD) items[N + tid] = 0;                  // the rounds read a little beyond the last item
-        __syncthreads();
+        lds_barrier();
         const int rpitch = row_pitch(C);
         uint32_t* const spare = reinterpret_cast<uint32_t*>(L.spare);
         if (MANY && multi_serves(P)) {                            // (uniform)
@@ -1361,7 +1370,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                 MultiLds& m = multi_lds(L);
                 multi_fresh(m, P, C);
                 if (tid <= P) shard_seq_off[tid] = tid * C;
-                __syncthreads();
+                lds_barrier();
                 if (w == 0) lpt_rounds_multi_any(N, P, items, rows, rpitch, C + 1, spare, m, shard_load);     // (a row takes a whole partition)
             }
         } else if (w == 0) {
@@ -1375,7 +1384,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                 if (lane == 0) shard_seq_off[P] = N;
             }
         }
-        __syncthreads();
+        lds_barrier();
         // ---- P_0, P_1, ... are the rows; the worker of a sequence is the row it stands in ----
         // (gathered by sequence in the LDS, where the sorted items were, so that both outputs leave in index
         // order: 16 384 scattered 4-byte stores take longer to drain than the rounds save)
@@ -1398,7 +1407,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             r += step_r;
             if (r >= C) { r -= C; k += 1; }
         }
-        __syncthreads();
+        lds_barrier();
         for (int i = tid; i < N; i += BAL_BLOCK) shard_of_seq[i] = (int32_t)worker_of[i];
         return;
     }
@@ -1412,7 +1421,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     for (int i = tid; i < N; i += BAL_BLOCK) L.idx_a[i] = (uint16_t)i;
     uint16_t* src = L.idx_a;
     uint16_t* dst = L.idx_b;
-    __syncthreads();
+    lds_barrier();
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = pass * 8;
         counting_pass(L, N, rounds,
@@ -1450,7 +1459,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         if (lane < P) shard_seq_off[lane] = inc - c;
         if (lane == 0) { shard_seq_off[P] = N; *placed = n_placed; }
     }
-    __syncthreads();
+    lds_barrier();
 
     // ---- c) lay out P_0, P_1, ... each in insertion order ----
     const int n_placed = *placed;

@@ -75,9 +75,18 @@ __device__ __forceinline__ T wave_read_lane(T v, int from) {
     }
 }
 
+// Workgroup barrier for data that the threads exchange through the LDS only.  __syncthreads() also waits until every
+// global store the wave has issued is acknowledged (a microsecond or two behind a pass of output stores); here they
+// drain while the workgroup goes on.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Block-wide exclusive add-scan of one value per thread.  `tmp` holds one T per
 // wave (at most 64).  Returns the exclusive prefix; *total gets the block sum.
-// Contains __syncthreads(): every thread of the block must call it.
+// Contains barriers (for the LDS only): every thread of the block must call it.
 // (The waves' sums are scanned by every wave for itself, lane i taking wave i's: one LDS read and a register
 // scan, where a loop over the waves would wait for the LDS once per wave.)
 template <typename T>
@@ -85,10 +94,10 @@ __device__ __forceinline__ T block_excl_scan_add(T v, T* tmp, T* total) {
     const int lane = lane_id(), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     T inc = wave_incl_scan_add(v);
     if (lane == WAVE - 1) tmp[w] = inc;
-    __syncthreads();
+    lds_barrier();
     const T mine = lane < nw ? tmp[lane] : T(0);
     const T upto = wave_incl_scan_add(mine);
-    __syncthreads();
+    lds_barrier();
     *total = wave_read_lane(upto, WAVE - 1);
     return wave_read_lane((T)(upto - mine), w) + inc - v;
 }
@@ -98,11 +107,11 @@ __device__ __forceinline__ int32_t block_excl_scan_max(int32_t v, int32_t* tmp) 
     const int lane = lane_id(), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     int32_t inc = wave_incl_scan_max(v);
     if (lane == WAVE - 1) tmp[w] = inc;
-    __syncthreads();
+    lds_barrier();
     const int32_t upto = wave_incl_scan_max(lane < nw ? tmp[lane] : -1);
     const int32_t base = wave_read_lane(wave_shift_up1(upto, -1), w);
     const int32_t up = wave_shift_up1(inc, -1);
-    __syncthreads();
+    lds_barrier();
     return max(base, up);
 }
 

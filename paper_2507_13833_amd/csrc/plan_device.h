@@ -12,6 +12,7 @@ constexpr int PLAN_BLOCK = 1024;
 constexpr int PLAN_WAVES = PLAN_BLOCK / WAVE;
 constexpr int PLAN_IPT = DC_MAX_SEQ / PLAN_BLOCK;        // slots per lane at the size limit
 constexpr int PLAN_WORDS = DC_MAX_SEQ / 32;
+constexpr int PLAN_NEXT_MAX = DC_MAX_SEQ / 2;            // slots up to which the unused end of the prefix holds a word per slot
 
 // The sequence behind slot j with its place in the rollout layout, validated (what the gather may rely
 // on): ln = tokens to move (0 if a check fails), so = element offset in rollout shard sh.  ln_in < 0: the
@@ -53,7 +54,7 @@ struct PlanLds {
     int32_t  word_starts[PLAN_WORDS + 1];   // starts in the words before this one
     int32_t  word_last[PLAN_WORDS];         // last start in the words before this one, or -1
     int64_t  wave_pref[PLAN_IPT * PLAN_WAVES];  // tokens before the 64 slots a wave handles in one step
-    int64_t  shard_base[DC_MAX_SHARDS + 1]; // aligned token offset of each shard
+    int64_t  shard_shift[DC_MAX_SHARDS];    // aligned token offset of each shard minus its dense one
     int32_t  shard_off[DC_MAX_SHARDS + 1];  // copy of shard_seq_off
     int64_t  tmp64[16];
     int32_t  tmp32[16];
@@ -73,7 +74,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
 
     for (int i = tid; i < PLAN_WORDS; i += PLAN_BLOCK) { L.start_bits[i] = 0; L.seen_bits[i] = 0; }
     if (tid == 0) L.ok = 1;
-    __syncthreads();
+    lds_barrier();
     for (int p = tid; p <= P; p += PLAN_BLOCK) {         // P + 1 entries, P up to the block size
         if (fixed_c > 0) { L.shard_off[p] = p * fixed_c; continue; }        // (uniform) N == P * fixed_c: nothing to check
         const int32_t v = a.shard_seq_off[p];
@@ -82,7 +83,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         if (p < P && a.shard_seq_off[p + 1] < v) bad = true;
         if (bad) L.ok = 0;
     }
-    __syncthreads();
+    lds_barrier();
     if (tid == 0) *a.plan_ok = L.ok;                     // read by records_kernel
     if (!L.ok) {                                         // unusable shard table: plan nothing
         if (tid == 0) { set_status(a.status, DC_ERR_BAD_LAYOUT); *a.n_mb = 0; }
@@ -108,19 +109,22 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     int32_t inc[PLAN_IPT];
 #pragma unroll
     for (int q = 0; q < PLAN_IPT; ++q) {
-        inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
-        if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
+        inc[q] = 0;
+        if (q < nb) {                                    // (uniform)
+            inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
+            if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
+        }
     }
-    __syncthreads();
+    lds_barrier();
     // ... an exclusive scan of the 256 step totals in slot order (step q, wave w) ...
     {
-        const int64_t v = tid < PLAN_IPT * PLAN_WAVES ? L.wave_pref[tid] : 0;
+        const int64_t v = tid < nb * PLAN_WAVES ? L.wave_pref[tid] : 0;
         int64_t total;
         const int64_t ex = block_excl_scan_add<int64_t>(v, L.tmp64, &total);
         if (tid < PLAN_IPT * PLAN_WAVES) L.wave_pref[tid] = ex;
         if (tid == 0) L.gpre[N] = total;
     }
-    __syncthreads();
+    lds_barrier();
     // ... and their sum
     const int whole_steps = N / PLAN_BLOCK;              // (uniform) steps in which every lane has a slot
 #pragma unroll
@@ -128,7 +132,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         const int j = q * PLAN_BLOCK + tid;
         if (q < whole_steps || j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
     }
-    __syncthreads();
+    lds_barrier();
 
     // ---- 2. shard bases: lane p takes shard p; exclusive scan of the loads rounded up to the alignment ----
     if (P <= WAVE) {                                     // (uniform) one wave holds every shard: no barrier, the others go on
@@ -139,9 +143,8 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
             const int64_t inc = wave_incl_scan_add<int64_t>(padded);
             const int64_t end = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)inc >> 32), WAVE - 1) << 32) |
                                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)inc, WAVE - 1));
-            if (lane < P) { L.shard_base[lane] = inc - padded; a.shard_tok_off[lane] = inc - padded; }
+            if (lane < P) { L.shard_shift[lane] = inc - padded - first; a.shard_tok_off[lane] = inc - padded; }
             if (lane == 0) {
-                L.shard_base[P] = end;
                 a.shard_tok_off[P] = end;
                 a.dst_tok_off[N] = end;
                 if (end > a.capacity) set_status(a.status, DC_ERR_OVERFLOW);
@@ -153,9 +156,8 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         const int64_t padded = (load + a.align - 1) / a.align * a.align;
         int64_t end;
         const int64_t base = block_excl_scan_add<int64_t>(padded, L.tmp64, &end);
-        if (tid < P) { L.shard_base[tid] = base; a.shard_tok_off[tid] = base; }
+        if (tid < P) { L.shard_shift[tid] = base - first; a.shard_tok_off[tid] = base; }
         if (tid == 0) {
-            L.shard_base[P] = end;
             a.shard_tok_off[P] = end;
             a.dst_tok_off[N] = end;
             if (end > a.capacity) set_status(a.status, DC_ERR_OVERFLOW);
@@ -163,6 +165,53 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     }
 
     // ---- 3. micro-batch starts ----
+    const uint64_t all_tokens = (uint64_t)L.gpre[N];
+    if (N <= PLAN_NEXT_MAX && all_tokens <= 0xFFFFFFFFull &&
+        all_tokens > (uint64_t)(4 + 4 * nb) * (uint64_t)P * (uint64_t)a.budget) {         // (uniform)
+        // Few slots and long chains: every slot finds the end of the micro-batch that would start with it (a bisection of
+        // the prefix's low words, a lane's slots side by side), and lane p follows shard p's chain, one LDS read a hop.
+        // A walk's hop (below) reads the start, probes a window and counts: 620 cycles against 250, but the search takes
+        // 1.3 K for every 1024 slots, so it pays from about 4 + 4 hops per 1024 slots on.  2048 slots on 8 shards, 25 hops
+        // each: 16.2 K -> 8.7 K cycles; 8192 on 32 shards with 23 hops, which the line leaves to the walk: 15.6 K -> 16.9 K.
+        uint16_t* const next = reinterpret_cast<uint16_t*>(&L.gpre[PLAN_NEXT_MAX + 1]);
+        const int span = fixed_c > 0 ? fixed_c : N;          // slots of a shard, at most
+        const int first_step = 1 << (31 - __clz(max(span, 1)));
+        auto low = [&](int at) { return reinterpret_cast<const uint32_t*>(&L.gpre[at])[0]; };
+        constexpr int SIDE = 4;
+        for (int q0 = 0; q0 < nb; q0 += SIDE) {              // (uniform)
+            int lo[SIDE], hi[SIDE];
+            uint32_t limit[SIDE];
+#pragma unroll
+            for (int i = 0; i < SIDE; ++i) {
+                const int j = min((q0 + i) * PLAN_BLOCK + tid, N - 1);
+                lo[i] = j + 1;
+                hi[i] = min(N, j + span);
+                limit[i] = (uint32_t)min((uint64_t)low(j) + (uint64_t)a.budget, (uint64_t)0xFFFFFFFFull);
+            }
+            for (int step = first_step; step >= 1; step >>= 1) {     // (uniform) the last e in (j, hi] that fits, or j + 1
+#pragma unroll
+                for (int i = 0; i < SIDE; ++i) {
+                    const int c = lo[i] + step;
+                    const uint32_t g = low(min(c, N));
+                    if (c <= hi[i] && g <= limit[i]) lo[i] = c;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < SIDE; ++i) {
+                const int j = (q0 + i) * PLAN_BLOCK + tid;
+                if (j < N) next[j] = (uint16_t)lo[i];
+            }
+        }
+        lds_barrier();
+        if (tid < P) {
+            const int b = L.shard_off[tid + 1];
+            for (int j = L.shard_off[tid]; j < b;) {
+                const int e = min((int)next[j], b);
+                atomicOr(&L.start_bits[j >> 5], 1u << (j & 31));
+                j = e;
+            }
+        }
+    } else
     // Many shards: lane p walks shard p.
     // Each hop looks for the last slot that still fits under the budget.  Slots of a shard come in
     // descending length, so a micro-batch holds about as many slots as the one before it: the
@@ -251,7 +300,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
             j = lo;
         }
     }
-    __syncthreads();
+    lds_barrier();
 
     // ---- 4. micro-batch index per slot, outputs ----
     // per word of 32 slots: starts in the words before it, and the last start before it
@@ -262,7 +311,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         const int32_t inc_n = wave_incl_scan_add<int32_t>(n_here), inc_l = wave_incl_scan_max(last_here);
         int32_t* tmp_l = reinterpret_cast<int32_t*>(L.tmp64);
         if (lane == WAVE - 1) { L.tmp32[w] = inc_n; tmp_l[w] = inc_l; }
-        __syncthreads();
+        lds_barrier();
         int32_t before = inc_n - n_here, last = wave_shift_up1(inc_l, -1);
         M = 0;
         for (int i = 0; i < PLAN_WAVES; ++i) {
@@ -273,7 +322,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         if (tid < PLAN_WORDS) { L.word_starts[tid] = before; L.word_last[tid] = last; }
         if (tid == 0) L.word_starts[PLAN_WORDS] = M;
     }
-    __syncthreads();
+    lds_barrier();
     // One slot per lane and step.  Nothing here depends on a lane's own condition except the stores of a last,
     // partial step: every slot of a micro-batch stores the micro-batch's first slot (the same word with the same
     // value), and every slot stores the cu_seqlens entry behind its own, which is either the entry that the next
@@ -281,6 +330,10 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     // so they are taken between the low words.
     const bool shift_bases = a.align != 1;               // (uniform)
     auto low_word = [&](int at) { return reinterpret_cast<const uint32_t*>(&L.gpre[at])[0]; };
+    // (equal shards: slot j stands in shard j / fixed_c; one division per lane, then steps of PLAN_BLOCK slots)
+    const bool by_c = shift_bases && fixed_c > 0;        // (uniform)
+    const int step_k = by_c ? PLAN_BLOCK / fixed_c : 0, step_r = by_c ? PLAN_BLOCK - step_k * fixed_c : 0;
+    int shard = by_c ? tid / fixed_c : 0, in_shard = by_c ? tid - shard * fixed_c : 0;
     auto slot_out = [&](int q, bool whole) {             // whole (uniform): every lane has a slot in this step
         const int jr = q * PLAN_BLOCK + tid, j = whole ? jr : min(jr, N - 1);
         const uint32_t bits = L.start_bits[j >> 5];
@@ -290,13 +343,18 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         const int64_t g = L.gpre[j];
         const uint32_t g_next = low_word(j + 1), g_first = low_word(max(first, 0));
         int64_t d = g;
-        if (shift_bases) {                               // shard of the slot, then its aligned base
+        if (by_c) {
+            d = g + L.shard_shift[min(shard, P - 1)];
+            shard += step_k;
+            in_shard += step_r;
+            if (in_shard >= fixed_c) { in_shard -= fixed_c; shard += 1; }
+        } else if (shift_bases) {                        // shard of the slot, then its aligned base
             int lo = 0, hi = P - 1;                      // largest p with shard_off[p] <= j
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
                 if (L.shard_off[mid] <= j) lo = mid; else hi = mid - 1;
             }
-            d = g + (L.shard_base[lo] - L.gpre[L.shard_off[lo]]);
+            d = g + L.shard_shift[lo];
         }
         if (whole || jr < N) {
             a.dst_tok_off[(uint32_t)j] = d;

@@ -73,3 +73,13 @@ def test_plan_of_many_slots(n, shards, budget, align, cap):
     lens = np.random.default_rng(n).integers(1, 40, n).astype(np.int32)
     w = _custom(lens, 1, shards, max(budget, 40), n_src=1, fields=())
     check_step(w, align=align, cap=cap, label=f"{n} slots on {shards} shards, budget {budget}")
+
+
+@pytest.mark.parametrize("n,shards,budget", [(64, 1, 41), (1024, 2, 64), (1025, 2, 64), (2040, 8, 41), (2048, 1, 4096),
+                                             (8192, 1, 100), (8193, 3, 100), (300, 150, 41)])
+def test_plan_of_few_slots_and_long_chains(n, shards, budget):
+    """Dozens of micro-batches per shard: every slot's own end, then the chain; 8192 slots are the most that takes."""
+    lens = np.random.default_rng(n).integers(1, 41, n).astype(np.int32)
+    for align in (1, 6):
+        check_step(_custom(lens, 1, shards, budget, fields=()), align=align, two_calls=n % shards == 0,
+                   cap=0 if n % shards == 0 else n, label=f"{n} slots on {shards} shards, budget {budget}")
