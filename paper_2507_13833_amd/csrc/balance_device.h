@@ -39,6 +39,8 @@ struct BalLds {
 static_assert(sizeof(uint32_t) * 256 * BAL_WAVES >= 2 * sizeof(uint64_t) * DC_MAX_SHARDS, "two key tables fit the counters");
 static_assert(DC_MAX_SHARDS <= BAL_BLOCK, "one thread per worker");
 
+constexpr uint32_t PACKED_MAX_LEN = 0xFFFFu;           // lengths up to this take the packed path
+
 // Where the tables of the assignment live inside BalLds::cnt once the sort is done.
 constexpr int PART_OFF_AT = 0;                         // int32 [P + 1]: start of every P_k inside perm
 constexpr int PLACED_AT = DC_MAX_SHARDS + 8;           // int32: items placed
@@ -307,6 +309,65 @@ __device__ __forceinline__ bool bin_sort_packed(BalLds& L, int N, uint32_t longe
     return false;
 }
 
+// The same list for up to SMALL_SORT_MAX sequences, K to a lane: a bitonic sort over the workgroup's registers of distinct
+// words (longest - by - length, then index), so that no order between equal lengths is left to chance.  A wave sorts its
+// 64 * K words alone (wave_sort_multi), then the waves' runs are merged, exchanging words through the LDS where the partner
+// stands in another wave (one barrier each: two buffers) and in registers where not.  Every lane of the workgroup must
+// call it; len[q] = length of sequence bal_item(q, K); out[0, N) gets the words.
+// Bound by latency: 6 exchanges of ~250 cycles for 512 sequences, 10 for 1024 and more.  The bins, whose scans, waiting
+// turns and check cost the same for 64 sequences as for 1024, take 16 to 17.5 K cycles; this takes 2.5 K for 64
+// sequences, 6.4 K for 512 and 12.6 K for 2048 (with four to a lane, the next size, there is nothing left to gain).
+constexpr int SMALL_SORT_MAX = 2 * BAL_BLOCK;
+template <int K>
+__device__ __forceinline__ void small_sort_packed(BalLds& L, int N, const int32_t (&len)[BAL_ROUNDS], uint32_t* out) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    constexpr int RUN = WAVE * K;
+    const int runs = (N + RUN - 1) / RUN;                         // waves that hold sequences
+    uint32_t* const buf = reinterpret_cast<uint32_t*>(L.keys);    // two buffers of BAL_BLOCK * K words
+    static_assert(2 * SMALL_SORT_MAX <= DC_MAX_SEQ, "both fit the keys");
+    uint32_t v[K];
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const int i = bal_item(r, K);
+        v[r] = i < N ? ((PACKED_MAX_LEN - (uint32_t)len[r]) << 16) | (uint32_t)i : 0xFFFFFFFFu;     // (lengths are positive)
+    }
+    // (a wave that has to sort downwards sorts the complements upwards)
+    auto flip = [&](bool down) {
+        const uint32_t x = down ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int r = 0; r < K; ++r) v[r] ^= x;
+    };
+    flip((w & 1) != 0);
+    wave_sort_multi<K>(v);
+    flip((w & 1) != 0);
+    int side = 0;
+    for (int m = 2; m < 2 * runs; m <<= 1) {                      // (uniform) runs of m waves
+        const bool down = (w & m) != 0;
+        for (int d = m >> 1; d >= 1; d >>= 1) {
+            uint32_t* const mine = buf + side * (BAL_BLOCK * K);
+            side ^= 1;
+#pragma unroll
+            for (int r = 0; r < K; ++r) mine[w * RUN + r * WAVE + lane] = v[r];
+            lds_barrier();
+            const bool keep_min = ((w & d) == 0) != down;
+#pragma unroll
+            for (int r = 0; r < K; ++r) {
+                const uint32_t o = mine[(w ^ d) * RUN + r * WAVE + lane];
+                v[r] = keep_min ? umin32(v[r], o) : max(v[r], o);
+            }
+        }
+        flip(down);
+        multi_merge<RUN, RUN / 2, K>(v);
+        flip(down);
+    }
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const int at = w * RUN + r * WAVE + (int)net_lane((uint32_t)lane);
+        if (at < N) out[at] = v[r] ^ (PACKED_MAX_LEN << 16);      // back to length << 16 | index
+    }
+}
+
 // The assignment rounds (wave 0 only).  WIDTH = 16, 32 or 64 >= P lanes take part in the sort.
 // pitch == 0: step_slot[t] = place of item I[t] inside its worker's partition; pitch > 0 (every
 // partition will hold exactly C items): step_slot[k * pitch + c] = the c-th item of worker k.
@@ -525,7 +586,6 @@ __device__ __forceinline__ int lpt_rounds(int N, int P, int C, int32_t* keys, co
 // the rows start empty with every call and hold row_cap items each, and the call returns, before all N items are
 // placed, as soon as one row is full (the caller empties the rows and offers the rest again).
 constexpr int FAST_BATCH = 4;
-constexpr uint32_t PACKED_MAX_LEN = 0xFFFFu;             // lengths up to this take the packed path
 
 __device__ __forceinline__ int row_pitch(int C) { return C | 1; }      // odd: the workers' rows start in different banks
 
@@ -1289,7 +1349,8 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const int pitch = (P <= WAVE && equal) ? place_pitch(C) : 0;
     const bool tight = equal && P <= MULTI_MAX;                             // what the packed rounds serve
     const bool exact = pitch != 0 && (P == 16 || P == 32 || P == 64);      // a worker in every lane of a 16-, 32- or 64-lane sort
-    if (tight) bin_sort_clear(L);                                 // (uniform; the barrier below stands between this and the bins' use)
+    const bool small = N <= SMALL_SORT_MAX;                       // (uniform)
+    if (tight && !small) bin_sort_clear(L);                       // (the barrier below stands between this and the bins' use)
 
     // ---- load lengths, range (register q of a thread: sequence bal_item(q, rounds)) ----
     const int rounds = (N + BAL_BLOCK - 1) / BAL_BLOCK;           // <= BAL_ROUNDS
@@ -1342,7 +1403,11 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                       offsetof(BalLds, idx_a) % 4 == 0, "the two index arrays are one run of words");
         uint32_t* src = reinterpret_cast<uint32_t*>(L.keys);      // DC_MAX_SEQ + PLACE_PAD words each
         uint32_t* dst = reinterpret_cast<uint32_t*>(L.idx_a);
-        if (range != 0u && range <= BIN_RANGE_MAX && bin_sort_packed(L, N, (uint32_t)mx, range, mine_len, dst)) {     // (uniform)
+        if (small) {                                              // (uniform)
+            if (rounds <= 1) small_sort_packed<1>(L, N, mine_len, dst);
+            else small_sort_packed<2>(L, N, mine_len, dst);
+            uint32_t* t = src; src = dst; dst = t;
+        } else if (range != 0u && range <= BIN_RANGE_MAX && bin_sort_packed(L, N, (uint32_t)mx, range, mine_len, dst)) {     // (uniform)
             uint32_t* t = src; src = dst; dst = t;
         } else {
 #pragma unroll

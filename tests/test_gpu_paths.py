@@ -83,3 +83,13 @@ def test_plan_of_few_slots_and_long_chains(n, shards, budget):
     for align in (1, 6):
         check_step(_custom(lens, 1, shards, budget, fields=()), align=align, two_calls=n % shards == 0,
                    cap=0 if n % shards == 0 else n, label=f"{n} slots on {shards} shards, budget {budget}")
+
+
+@pytest.mark.parametrize("kind", ["geometric", "equal", "tail"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 500, 1023, 1024, 1025, 1990, 2047, 2048, 2049])
+def test_sort_of_few_sequences(n, kind):
+    """Up to 2048 sequences: one wave, several, all sixteen, one and two words to a lane, and the first size of the bins."""
+    lens = _lengths(kind, n, np.random.default_rng(n)).astype(np.int32)
+    if kind == "tail":
+        lens = np.sort(lens)[:: 1 if n % 2 else -1].copy()       # ascending and descending input
+    check_step(_custom(lens, 1, 1, 1 << 17, fields=()), label=f"{n} sequences, {kind}", two_calls=True)
