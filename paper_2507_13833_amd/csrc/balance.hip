@@ -88,11 +88,11 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(Balan
     SlotRegs s;
     balance_body_t<true, !MANY, MANY>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq,
                          b.shard_load, b.status, s);
-#pragma unroll
-    for (int q = 0; q < PLAN_IPT; ++q) {                          // the slots' lengths, for the launch that builds the granule tables
+    unrolled_steps<PLAN_IPT>((b.N + PLAN_BLOCK - 1) / PLAN_BLOCK, [&](auto qc) {      // the slots' lengths, for the launch that
+        constexpr int q = decltype(qc)::value;                                        // builds the granule tables
         const int j = q * PLAN_BLOCK + (int)threadIdx.x;
         if (j < b.N) p.slot_len[j] = s.len[q];
-    }
+    });
     lds_barrier();                                                // Algorithm 1's tables have been read for the last time
     plan_body(*reinterpret_cast<PlanLds*>(lds), p, s.seq, s.len, false, b.C);
 }

@@ -1358,25 +1358,25 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     int32_t mine_len[BAL_ROUNDS];
     // (every load of the lane is issued before the first is looked at: a test between them would make each wait for its own)
 #pragma unroll
-    for (int g = 0; g < BAL_ROUNDS; g += BIN_GROUP) {
+    for (int q = 0; q < BAL_ROUNDS; ++q) mine_len[q] = 1;
+    unrolled_steps<BAL_ROUNDS / BIN_GROUP>((rounds + BIN_GROUP - 1) / BIN_GROUP, [&](auto gc) {
+        constexpr int g = decltype(gc)::value * BIN_GROUP;
 #pragma unroll
-        for (int q = g; q < g + BIN_GROUP; ++q) mine_len[q] = 1;
-        if (g < rounds) {                                         // (uniform)
-#pragma unroll
-            for (int q = g; q < g + BIN_GROUP; ++q) mine_len[q] = seq_len[min(bal_item(q, rounds), N - 1)];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < BAL_ROUNDS; ++q) {
+        for (int q = g; q < g + BIN_GROUP; ++q) mine_len[q] = seq_len[min(bal_item(q, rounds), N - 1)];
+    });
+    unrolled_steps<BAL_ROUNDS>(rounds, [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
         int32_t s = mine_len[q];
-        mine_len[q] = 1;
-        if (q < rounds && bal_item(q, rounds) < N) {
-            if (s <= 0 || s > DC_MAX_SEQ_LEN) { set_status(status, DC_ERR_ZERO_LENGTH_SEQ); s = 1; }
-            mine_len[q] = s;
-            mx = max(mx, s);
-            mn = min(mn, s);
-        }
-    }
+        const bool mine = bal_item(q, rounds) < N, fine = s > 0 && s <= DC_MAX_SEQ_LEN;
+        if (mine && !fine) set_status(status, DC_ERR_ZERO_LENGTH_SEQ);
+        s = mine && fine ? s : 1;
+        mine_len[q] = s;
+        mx = max(mx, mine ? s : 0);
+        mn = min(mn, mine ? s : INT32_MAX);
+    });
+#pragma unroll
+    for (int q = BIN_GROUP - 1; q < BAL_ROUNDS; ++q)              // (the last group's loads beyond the last register)
+        if (q >= rounds) mine_len[q] = 1;
     wave_all_reduce([&](auto j) {                                 // (lengths are positive: unsigned order is theirs)
         constexpr int J = decltype(j)::value;
         const uint32_t hi = lane_xor<J>((uint32_t)mx), lo = lane_xor<J>((uint32_t)mn);
@@ -1457,10 +1457,13 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         // (slot q = worker q / C, place q mod C: one division per lane, then steps of BAL_BLOCK slots)
         const int step_k = BAL_BLOCK / C, step_r = BAL_BLOCK - step_k * C;
         int k = tid / C, r = tid - k * C;
+        if constexpr (FILL) {
 #pragma unroll
-        for (int qq = 0; qq < BAL_ROUNDS; ++qq) {
+            for (int qq = 0; qq < BAL_ROUNDS; ++qq) { slots.seq[qq] = -1; slots.len[qq] = 0; }
+        }
+        unrolled_steps<BAL_ROUNDS>(rounds, [&](auto qc) {
+            constexpr int qq = decltype(qc)::value;
             const int q = qq * BAL_BLOCK + tid;
-            if constexpr (FILL) { slots.seq[qq] = -1; slots.len[qq] = 0; }
             if (q < N) {
                 const uint32_t e = rows[k * rpitch + r];
                 const uint32_t u = min(e & 0xFFFFu, (uint32_t)(N - 1));      // (no index leaves the arrays whatever a word holds)
@@ -1471,7 +1474,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             k += step_k;
             r += step_r;
             if (r >= C) { r -= C; k += 1; }
-        }
+        });
         lds_barrier();
         for (int i = tid; i < N; i += BAL_BLOCK) shard_of_seq[i] = (int32_t)worker_of[i];
         return;

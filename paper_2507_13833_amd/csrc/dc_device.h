@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "dc_internal.h"
 
 namespace dc {
@@ -72,6 +73,18 @@ __device__ __forceinline__ T wave_read_lane(T v, int from) {
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, at);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), at);
         return (T)(((uint64_t)hi << 32) | lo);
+    }
+}
+
+// body(integral_constant q) for q = 0 .. min(n, END) - 1, unrolled, left at the first q >= n (n uniform).  A small batch
+// that steps over a test per copy of the body instead fetches every copy from memory just to leave it.
+template <int END, int Q = 0, typename Body>
+__device__ __forceinline__ void unrolled_steps(int n, Body&& body) {
+    if constexpr (Q < END) {
+        if (Q < n) {
+            body(std::integral_constant<int, Q>{});
+            unrolled_steps<END, Q + 1>(n, body);
+        }
     }
 }
 

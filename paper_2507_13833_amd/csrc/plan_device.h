@@ -107,14 +107,11 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     }
     // dense prefix: inclusive scan inside each wave step (a wave's 64 slots hold < 2^31 tokens) ...
     int32_t inc[PLAN_IPT];
-#pragma unroll
-    for (int q = 0; q < PLAN_IPT; ++q) {
-        inc[q] = 0;
-        if (q < nb) {                                    // (uniform)
-            inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
-            if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
-        }
-    }
+    unrolled_steps<PLAN_IPT>(nb, [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
+        if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
+    });
     lds_barrier();
     // ... an exclusive scan of the 256 step totals in slot order (step q, wave w) ...
     {
@@ -127,11 +124,11 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     lds_barrier();
     // ... and their sum
     const int whole_steps = N / PLAN_BLOCK;              // (uniform) steps in which every lane has a slot
-#pragma unroll
-    for (int q = 0; q < PLAN_IPT; ++q) {
+    unrolled_steps<PLAN_IPT>(nb, [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
         const int j = q * PLAN_BLOCK + tid;
         if (q < whole_steps || j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
-    }
+    });
     lds_barrier();
 
     // ---- 2. shard bases: lane p takes shard p; exclusive scan of the loads rounded up to the alignment ----
