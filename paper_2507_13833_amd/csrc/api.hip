@@ -250,9 +250,12 @@ dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source*
     }
     const AdvArgs adv = make_adv_args(prm->n_seq, sd, src->d_src_tok_off, d_seq_len, d_reward, d_group_off, n_groups,
                                       prm->eps, prm->ddof, mask_src_base, d_adv_seq, adv_tok_src_base, d_status);
-    const PlanArgs plan = make_plan_args(*prm, src->d_src_tok_off, d_seq_len, d_perm, d_shard_seq_off, dst_capacity_tokens,
-                                         d_dst_tok_off, d_shard_tok_off, d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb,
-                                         ws, d_status);
+    PlanArgs plan = make_plan_args(*prm, src->d_src_tok_off, d_seq_len, d_perm, d_shard_seq_off, dst_capacity_tokens,
+                                   d_dst_tok_off, d_shard_tok_off, d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb,
+                                   ws, d_status);
+    if (prm->n_seq <= SMALL_REC_SLOTS && ws.n_gran <= SMALL_REC_GRANS) {
+        plan.gran_first = ws.gran_first; plan.gran_rec = ws.gran_rec; plan.n_gran = ws.n_gran;
+    }
     hipError_t e = launch_balance_plan_advantage(prm->n_seq, prm->n_shards, cap_eff, d_seq_len, d_perm, d_shard_seq_off,
                                                  d_shard_of_seq, d_shard_load, plan, adv, sd, n_groups, d_status, st);
     if (e != hipSuccess) return DC_ERR_HIP;

@@ -77,24 +77,37 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_advantage_kernel(BalanceArg
 static_assert(BAL_BLOCK == PLAN_BLOCK && BAL_ROUNDS == PLAN_IPT, "one lane handles the same slots in both");
 constexpr size_t BAL_PLAN_LDS = sizeof(BalLds) > sizeof(PlanLds) ? sizeof(BalLds) : sizeof(PlanLds);
 
-// MANY: 33 .. 63 or 65 .. 256 workers; else up to 32 or 64 (two kernels: see balance_body_t).
-template <bool MANY>
+// MANY: 33 .. 63 or 65 .. 256 workers; else up to 32 or 64.  IPT: see balance_body_t.  (Four kernels, each with the code of
+// its shapes alone.)
+template <bool MANY, int IPT>
 __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(BalanceArgs b, PlanArgs p, AdvArgs a, SourceDesc sd) {
     __shared__ __align__(16) unsigned char lds[BAL_PLAN_LDS];
     if (blockIdx.x != 0) {
         advantage_wave(a, sd, (int64_t)(blockIdx.x - 1) * BAL_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
         return;
     }
-    SlotRegs s;
-    balance_body_t<true, !MANY, MANY>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq,
+    SlotRegs<IPT> s;
+    balance_body_t<true, !MANY, MANY, IPT>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq,
                          b.shard_load, b.status, s);
-    unrolled_steps<PLAN_IPT>((b.N + PLAN_BLOCK - 1) / PLAN_BLOCK, [&](auto qc) {      // the slots' lengths, for the launch that
+    unrolled_steps<IPT>((b.N + PLAN_BLOCK - 1) / PLAN_BLOCK, [&](auto qc) {      // the slots' lengths, for the launch that
         constexpr int q = decltype(qc)::value;                                        // builds the granule tables
         const int j = q * PLAN_BLOCK + (int)threadIdx.x;
         if (j < b.N) p.slot_len[j] = s.len[q];
     });
+    int64_t src_off[SMALL_REC_IPT];                               // (asked for here: they come while the plan runs)
+    if constexpr (IPT == SMALL_IPT) {
+        static_assert(SMALL_IPT == SMALL_REC_IPT, "the lane's slots");
+#pragma unroll
+        for (int q = 0; q < SMALL_REC_IPT; ++q) {
+            src_off[q] = 0;
+            if (p.gran_rec) src_off[q] = p.src_tok_off[min(max(s.seq[q], 0), b.N - 1)];      // (uniform)
+        }
+    }
     lds_barrier();                                                // Algorithm 1's tables have been read for the last time
     plan_body(*reinterpret_cast<PlanLds*>(lds), p, s.seq, s.len, false, b.C);
+    if constexpr (IPT == SMALL_IPT) {
+        if (p.gran_rec) small_records(*reinterpret_cast<PlanLds*>(lds), p, sd, s.seq, s.len, src_off, b.C);      // (uniform)
+    }
 }
 
 hipError_t launch_balance(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
@@ -125,14 +138,15 @@ hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_
     if (n_shards < 1 || n_shards > BAL_PLAN_MAX_SHARDS || (int64_t)cap_eff * n_shards != n_seq || n_seq <= 0 || n_seq > DC_MAX_SEQ)
         return hipErrorInvalidValue;
     static_assert(BAL_PLAN_MAX_SHARDS == MULTI_MAX, "the packed rounds' limit");
+    static_assert(SMALL_REC_SLOTS == SMALL_SORT_MAX, "the small kernels make the tables");
     BalanceArgs b;
     b.N = n_seq; b.P = n_shards; b.C = cap_eff; b.seq_len = d_seq_len; b.perm = d_perm;
     b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = d_shard_of_seq; b.shard_load = d_shard_load; b.status = d_status;
     const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
-    if (n_shards <= 32 || n_shards == WAVE)
-        hipLaunchKernelGGL(balance_plan_advantage_kernel<false>, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src);
-    else
-        hipLaunchKernelGGL(balance_plan_advantage_kernel<true>, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src); };
+    const bool many = n_shards > 32 && n_shards != WAVE;
+    if (n_seq <= SMALL_SORT_MAX) launch(many ? balance_plan_advantage_kernel<true, SMALL_IPT> : balance_plan_advantage_kernel<false, SMALL_IPT>);
+    else launch(many ? balance_plan_advantage_kernel<true, BAL_ROUNDS> : balance_plan_advantage_kernel<false, BAL_ROUNDS>);
     return hipGetLastError();
 }
 

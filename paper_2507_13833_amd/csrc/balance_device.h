@@ -318,8 +318,8 @@ __device__ __forceinline__ bool bin_sort_packed(BalLds& L, int N, uint32_t longe
 // turns and check cost the same for 64 sequences as for 1024, take 16 to 17.5 K cycles; this takes 2.5 K for 64
 // sequences, 6.4 K for 512 and 12.6 K for 2048 (with four to a lane, the next size, there is nothing left to gain).
 constexpr int SMALL_SORT_MAX = 2 * BAL_BLOCK;
-template <int K>
-__device__ __forceinline__ void small_sort_packed(BalLds& L, int N, const int32_t (&len)[BAL_ROUNDS], uint32_t* out) {
+template <int K, int IPT>
+__device__ __forceinline__ void small_sort_packed(BalLds& L, int N, const int32_t (&len)[IPT], uint32_t* out) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid / WAVE);
     constexpr int RUN = WAVE * K;
@@ -1329,19 +1329,23 @@ __device__ __forceinline__ int lpt_rounds_wide(BalLds& L, int N, int P, int C, c
 // The whole of Algorithm 1, by one workgroup of BAL_BLOCK threads.
 // What a lane hands to the plan when that runs as the tail of this workgroup: the sequence and the length of
 // output slots tid, tid + BAL_BLOCK, ... (seq = -1, len = 0 beyond N).
+template <int IPT>
 struct SlotRegs {
-    int32_t seq[BAL_ROUNDS];
-    int32_t len[BAL_ROUNDS];
+    int32_t seq[IPT];
+    int32_t len[IPT];
 };
+constexpr int SMALL_IPT = SMALL_SORT_MAX / BAL_BLOCK;
 
 // FEW: the code for up to 32 or 64 workers; MANY: for the other numbers of them.  FILL (only with P * C == N): also
 // fill slots.  What a launch is never made for is left out of its kernel (it is executed once from front to back, most
 // of it straight code that the instruction cache has not seen, and its size shows in its time).
-template <bool FILL, bool FEW, bool MANY>
+// IPT: sequences per lane at most, BAL_ROUNDS, or SMALL_IPT for a launch of up to SMALL_SORT_MAX sequences (FILL with
+// BAL_ROUNDS: for more than that).
+template <bool FILL, bool FEW, bool MANY, int IPT>
 __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, int32_t C,
                                                const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                                int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
-                                               int64_t* __restrict__ shard_load, int32_t* status, SlotRegs& slots) {
+                                               int64_t* __restrict__ shard_load, int32_t* status, SlotRegs<IPT>& slots) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
 
     // every partition ends with exactly C items (Algorithm 1 as printed: C = N / K): rows per worker
@@ -1349,22 +1353,23 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const int pitch = (P <= WAVE && equal) ? place_pitch(C) : 0;
     const bool tight = equal && P <= MULTI_MAX;                             // what the packed rounds serve
     const bool exact = pitch != 0 && (P == 16 || P == 32 || P == 64);      // a worker in every lane of a 16-, 32- or 64-lane sort
-    const bool small = N <= SMALL_SORT_MAX;                       // (uniform)
+    const bool small = IPT == SMALL_IPT || (!FILL && N <= SMALL_SORT_MAX);      // (uniform)
     if (tight && !small) bin_sort_clear(L);                       // (the barrier below stands between this and the bins' use)
 
     // ---- load lengths, range (register q of a thread: sequence bal_item(q, rounds)) ----
-    const int rounds = (N + BAL_BLOCK - 1) / BAL_BLOCK;           // <= BAL_ROUNDS
+    constexpr int GROUP = IPT < BIN_GROUP ? IPT : BIN_GROUP;
+    const int rounds = (N + BAL_BLOCK - 1) / BAL_BLOCK;           // <= IPT
     int32_t mx = 0, mn = INT32_MAX;
-    int32_t mine_len[BAL_ROUNDS];
+    int32_t mine_len[IPT];
     // (every load of the lane is issued before the first is looked at: a test between them would make each wait for its own)
 #pragma unroll
-    for (int q = 0; q < BAL_ROUNDS; ++q) mine_len[q] = 1;
-    unrolled_steps<BAL_ROUNDS / BIN_GROUP>((rounds + BIN_GROUP - 1) / BIN_GROUP, [&](auto gc) {
-        constexpr int g = decltype(gc)::value * BIN_GROUP;
+    for (int q = 0; q < IPT; ++q) mine_len[q] = 1;
+    unrolled_steps<(IPT + GROUP - 1) / GROUP>((rounds + GROUP - 1) / GROUP, [&](auto gc) {
+        constexpr int g = decltype(gc)::value * GROUP;
 #pragma unroll
-        for (int q = g; q < g + BIN_GROUP; ++q) mine_len[q] = seq_len[min(bal_item(q, rounds), N - 1)];
+        for (int q = g; q < g + GROUP; ++q) mine_len[q] = seq_len[min(bal_item(q, rounds), N - 1)];
     });
-    unrolled_steps<BAL_ROUNDS>(rounds, [&](auto qc) {
+    unrolled_steps<IPT>(rounds, [&](auto qc) {
         constexpr int q = decltype(qc)::value;
         int32_t s = mine_len[q];
         const bool mine = bal_item(q, rounds) < N, fine = s > 0 && s <= DC_MAX_SEQ_LEN;
@@ -1375,7 +1380,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         mn = min(mn, mine ? s : INT32_MAX);
     });
 #pragma unroll
-    for (int q = BIN_GROUP - 1; q < BAL_ROUNDS; ++q)              // (the last group's loads beyond the last register)
+    for (int q = GROUP - 1; q < IPT; ++q)              // (the last group's loads beyond the last register)
         if (q >= rounds) mine_len[q] = 1;
     wave_all_reduce([&](auto j) {                                 // (lengths are positive: unsigned order is theirs)
         constexpr int J = decltype(j)::value;
@@ -1403,15 +1408,19 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                       offsetof(BalLds, idx_a) % 4 == 0, "the two index arrays are one run of words");
         uint32_t* src = reinterpret_cast<uint32_t*>(L.keys);      // DC_MAX_SEQ + PLACE_PAD words each
         uint32_t* dst = reinterpret_cast<uint32_t*>(L.idx_a);
+        bool sorted_to_dst = false;
         if (small) {                                              // (uniform)
             if (rounds <= 1) small_sort_packed<1>(L, N, mine_len, dst);
             else small_sort_packed<2>(L, N, mine_len, dst);
+            sorted_to_dst = true;
+        } else if constexpr (IPT == BAL_ROUNDS) {
+            sorted_to_dst = range != 0u && range <= BIN_RANGE_MAX && bin_sort_packed(L, N, (uint32_t)mx, range, mine_len, dst);     // (uniform)
+        }
+        if (sorted_to_dst) {
             uint32_t* t = src; src = dst; dst = t;
-        } else if (range != 0u && range <= BIN_RANGE_MAX && bin_sort_packed(L, N, (uint32_t)mx, range, mine_len, dst)) {     // (uniform)
-            uint32_t* t = src; src = dst; dst = t;
-        } else {
+        } else if constexpr (IPT == BAL_ROUNDS) {
 #pragma unroll
-            for (int q = 0; q < BAL_ROUNDS; ++q) {
+            for (int q = 0; q < IPT; ++q) {
                 const int i = bal_item(q, rounds);
                 if (q < rounds && i < N) src[i] = ((uint32_t)mine_len[q] << 16) | (uint32_t)i;
             }
@@ -1459,9 +1468,9 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         int k = tid / C, r = tid - k * C;
         if constexpr (FILL) {
 #pragma unroll
-            for (int qq = 0; qq < BAL_ROUNDS; ++qq) { slots.seq[qq] = -1; slots.len[qq] = 0; }
+            for (int qq = 0; qq < IPT; ++qq) { slots.seq[qq] = -1; slots.len[qq] = 0; }
         }
-        unrolled_steps<BAL_ROUNDS>(rounds, [&](auto qc) {
+        unrolled_steps<IPT>(rounds, [&](auto qc) {
             constexpr int qq = decltype(qc)::value;
             const int q = qq * BAL_BLOCK + tid;
             if (q < N) {
@@ -1481,7 +1490,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     }
 
 #pragma unroll
-    for (int q = 0; q < BAL_ROUNDS; ++q) {
+    for (int q = 0; q < IPT; ++q) {
         const int i = bal_item(q, rounds);
         if (q < rounds && i < N) L.keys[i] = mine_len[q];
     }
@@ -1535,7 +1544,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         const int step_k = BAL_BLOCK / C, step_r = BAL_BLOCK - step_k * C;
         int k = tid / C, r = tid - k * C;                         // slot q = worker q / C, place q mod C
 #pragma unroll
-        for (int qq = 0; qq < BAL_ROUNDS; ++qq) {
+        for (int qq = 0; qq < IPT; ++qq) {
             const int q = qq * BAL_BLOCK + tid;
             if constexpr (FILL) { slots.seq[qq] = -1; slots.len[qq] = 0; }
             if (q < N) {
@@ -1564,7 +1573,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         __threadfence_block();
         __syncthreads();
 #pragma unroll
-        for (int qq = 0; qq < BAL_ROUNDS; ++qq) {
+        for (int qq = 0; qq < IPT; ++qq) {
             const int q = qq * BAL_BLOCK + tid;
             slots.seq[qq] = -1;
             slots.len[qq] = 0;
@@ -1582,8 +1591,8 @@ __device__ __forceinline__ void balance_body(BalLds& L, int32_t N, int32_t P, in
                                              const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                              int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
                                              int64_t* __restrict__ shard_load, int32_t* status) {
-    SlotRegs unused;
-    balance_body_t<false, true, true>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
+    SlotRegs<BAL_ROUNDS> unused;
+    balance_body_t<false, true, true, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
 }
 
 }  // namespace dc

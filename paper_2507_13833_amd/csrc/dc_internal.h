@@ -122,7 +122,13 @@ struct PlanArgs {
     int64_t* gpre;
     int32_t* start_bits;
     int64_t* tile_tokens;
+    // not null: the launch that balances and plans also builds the granule tables (small batches)
+    int32_t* gran_first;
+    GranRec* gran_rec;
+    int64_t  n_gran;
 };
+constexpr int SMALL_REC_SLOTS = 2048;
+constexpr int64_t SMALL_REC_GRANS = 2048;
 
 PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, const int32_t* d_seq_len,
                         const int32_t* d_perm, const int32_t* d_shard_seq_off, int64_t dst_capacity,

@@ -120,56 +120,6 @@ __device__ __forceinline__ int first_slot_after(RecLds& L, int N, const int64_t*
     return lo;
 }
 
-// Tables of granule g of a token axis holding N slots (starts[N+1], the last entry its end);
-// usable = false leaves the granule empty.  desc(j, &ln, &so, &sh): the validated source of slot j.
-// found >= 0: the first slot whose successor starts after the granule's first token (else it is looked for here).
-template <typename Desc>
-__device__ __forceinline__ void build_record(int N, bool usable, const int64_t* starts, Desc desc, int64_t g,
-                                             int32_t* first_out, GranRec* rec_out, int found = -1) {
-    const int64_t begin = g * GATHER_GRAN;
-    int first = N;
-    if (usable && N > 0) {
-        // first j whose successor starts after `begin` ...
-        int lo = 0, hi = N;
-        if (found >= 0) lo = hi = found;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (starts[mid + 1] > begin) hi = mid; else lo = mid + 1;
-        }
-        // ... and if `begin` lies in the padding behind that slot (or the slot is empty), the next one
-        while (lo < N) {
-            int32_t ln, sh;
-            int64_t so;
-            desc(lo, &ln, &so, &sh);
-            if (starts[lo] + ln > begin) break;
-            ++lo;
-        }
-        first = lo;
-    }
-    GranRec rec;
-#pragma unroll
-    for (int r = 0; r < REC_SLOTS; ++r) {
-        rec.e[r].start = REL_FAR; rec.e[r].lensh = 0; rec.e[r].src_off = 0;
-        const int j = first + r;
-        if (j < N) {
-            const int64_t d = starts[j] - begin;
-            if (d < GATHER_GRAN) {
-                int32_t ln, sh;
-                int64_t so;
-                desc(j, &ln, &so, &sh);
-                rec.e[r].start = (int32_t)max(d, (int64_t)-REL_FAR);
-                rec.e[r].lensh = ln | (sh << LENSH_SHIFT);
-                rec.e[r].src_off = so;
-            }
-        }
-    }
-    *first_out = first;
-    u32x4* out = reinterpret_cast<u32x4*>(rec_out);
-    const u32x4* in = reinterpret_cast<const u32x4*>(&rec);
-#pragma unroll
-    for (int r = 0; r < REC_SLOTS; ++r) out[r] = in[r];
-}
-
 // The descriptors as slots_kernel left them in the workspace.
 struct StoredDesc {
     const int64_t* slot_src_off;
@@ -280,6 +230,7 @@ hipError_t launch_records_slots(const PlanArgs& p, const SourceDesc& src, const 
     r.n_seq = p.n_seq; r.n_gran = ws.n_gran; r.dst_tok_off = p.dst_tok_off;
     r.slot_src_off = ws.slot_src_off; r.slot_len = ws.slot_len; r.slot_shard = ws.slot_shard;
     r.plan_ok = ws.plan_ok; r.gran_first = ws.gran_first; r.gran_rec = ws.gran_rec;
+    if (p.gran_rec) return hipSuccess;                           // (built by the launch before, see small_records)
     const unsigned rec_blocks = (unsigned)((ws.n_gran + REC_BLOCK - 1) / REC_BLOCK);
     const unsigned slot_blocks = (unsigned)((p.n_seq + REC_BLOCK - 1) / REC_BLOCK);
     hipLaunchKernelGGL(records_slots_kernel, dim3(rec_blocks + slot_blocks), dim3(REC_BLOCK), 0, st, r, p, src, rec_blocks);
@@ -301,6 +252,7 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
     a.plan_ok = ws.plan_ok; a.status = d_status;
     a.gpre = ws.gpre; a.start_bits = ws.start_bits; a.tile_tokens = ws.tile_tokens;
     a.own_shard_off = nullptr;
+    a.gran_first = nullptr; a.gran_rec = nullptr; a.n_gran = 0;
     return a;
 }
 

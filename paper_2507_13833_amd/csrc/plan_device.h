@@ -14,17 +14,10 @@ constexpr int PLAN_IPT = DC_MAX_SEQ / PLAN_BLOCK;        // slots per lane at th
 constexpr int PLAN_WORDS = DC_MAX_SEQ / 32;
 constexpr int PLAN_NEXT_MAX = DC_MAX_SEQ / 2;            // slots up to which the unused end of the prefix holds a word per slot
 
-// The sequence behind slot j with its place in the rollout layout, validated (what the gather may rely
-// on): ln = tokens to move (0 if a check fails), so = element offset in rollout shard sh.  ln_in < 0: the
-// length is taken from a.seq_len; else it is the slot's length as the caller has it already.  Sets the
-// device status on a failed check (and on a sequence above the token budget, which is still laid out).
-__device__ __forceinline__ void slot_source(const PlanArgs& a, const SourceDesc& sd, int j, int32_t ln_in,
-                                            int32_t* ln_out, int64_t* so_out, int32_t* sh_out) {
-    const int N = a.n_seq;
-    const int32_t i = a.perm ? a.perm[j] : j;                                     // no permutation: slot j holds sequence j
-    const bool placed = i >= 0 && i < N;
-    int32_t ln = placed ? (ln_in < 0 ? a.seq_len[i] : ln_in) : 0;
-    const int64_t so = placed ? a.src_tok_off[i] : 0;
+// The place of sequence i in the rollout layout, validated, from its length and its element offset as they were read
+// (placed: i is a sequence at all); see slot_source.
+__device__ __forceinline__ void slot_source_of(const PlanArgs& a, const SourceDesc& sd, int32_t i, bool placed, int32_t ln, int64_t so,
+                                               int32_t* ln_out, int64_t* so_out, int32_t* sh_out) {
     int32_t sh = 0;                                      // rollout shard (seq_off[s] = N from s = n_src on)
     if (sd.n_src > 1 && placed) {
 #pragma unroll
@@ -47,6 +40,19 @@ __device__ __forceinline__ void slot_source(const PlanArgs& a, const SourceDesc&
     *sh_out = sh;
 }
 
+// The sequence behind slot j with its place in the rollout layout, validated (what the gather may rely
+// on): ln = tokens to move (0 if a check fails), so = element offset in rollout shard sh.  ln_in < 0: the
+// length is taken from a.seq_len; else it is the slot's length as the caller has it already.  Sets the
+// device status on a failed check (and on a sequence above the token budget, which is still laid out).
+__device__ __forceinline__ void slot_source(const PlanArgs& a, const SourceDesc& sd, int j, int32_t ln_in,
+                                            int32_t* ln_out, int64_t* so_out, int32_t* sh_out) {
+    const int32_t i = a.perm ? a.perm[j] : j;                                     // no permutation: slot j holds sequence j
+    const bool placed = i >= 0 && i < a.n_seq;
+    const int32_t ln = placed ? (ln_in < 0 ? a.seq_len[i] : ln_in) : 0;
+    const int64_t so = placed ? a.src_tok_off[i] : 0;
+    slot_source_of(a, sd, i, placed, ln, so, ln_out, so_out, sh_out);
+}
+
 struct PlanLds {
     int64_t  gpre[DC_MAX_SEQ + 1];          // dense exclusive prefix of slot lengths
     uint32_t start_bits[PLAN_WORDS];        // slot opens a micro-batch
@@ -59,6 +65,7 @@ struct PlanLds {
     int64_t  tmp64[16];
     int32_t  tmp32[16];
     int32_t  ok;
+    int64_t  end;                           // d_shard_tok_off[P]
 };
 
 
@@ -66,11 +73,12 @@ struct PlanLds {
 // (seq = -1, len = 0 beyond N).  check_perm: seq comes from a caller's permutation and must be checked;
 // fixed_c > 0: shard p owns slots [p * fixed_c, (p + 1) * fixed_c) and a.shard_seq_off is not read.
 // Every lane of the workgroup must call it (barriers inside).
-__device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t (&seq)[PLAN_IPT], int32_t (&len)[PLAN_IPT],
+template <int IPT>
+__device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t (&seq)[IPT], int32_t (&len)[IPT],
                                           bool check_perm, int fixed_c) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     const int N = a.n_seq, P = a.n_shards;
-    const int nb = (N + PLAN_BLOCK - 1) / PLAN_BLOCK;    // steps of 1024 slots, <= PLAN_IPT
+    const int nb = (N + PLAN_BLOCK - 1) / PLAN_BLOCK;    // steps of 1024 slots, <= IPT
 
     for (int i = tid; i < PLAN_WORDS; i += PLAN_BLOCK) { L.start_bits[i] = 0; L.seen_bits[i] = 0; }
     if (tid == 0) L.ok = 1;
@@ -94,7 +102,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     uint32_t dup = 0;                                    // bit q: perm repeats an earlier entry at my slot of step q
     if (check_perm) {                                    // (uniform)
 #pragma unroll
-        for (int q = 0; q < PLAN_IPT; ++q) {
+        for (int q = 0; q < IPT; ++q) {
             const int32_t i = seq[q];                    // -1 beyond N; out-of-range entries were emptied by slots_kernel
             if (i >= 0 && i < N) dup |= ((atomicOr(&L.seen_bits[i >> 5], 1u << (i & 31)) >> (i & 31)) & 1u) << q;
         }
@@ -102,12 +110,12 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     if (__ballot(dup != 0) != 0ull) {                    // uniform, rare: perm is not a permutation; a repeat moves nothing
         if (dup != 0) set_status(a.status, DC_ERR_BAD_LAYOUT);
 #pragma unroll
-        for (int q = 0; q < PLAN_IPT; ++q)
+        for (int q = 0; q < IPT; ++q)
             if ((dup >> q) & 1u) { len[q] = 0; a.slot_len[q * PLAN_BLOCK + tid] = 0; }
     }
     // dense prefix: inclusive scan inside each wave step (a wave's 64 slots hold < 2^31 tokens) ...
-    int32_t inc[PLAN_IPT];
-    unrolled_steps<PLAN_IPT>(nb, [&](auto qc) {
+    int32_t inc[IPT];
+    unrolled_steps<IPT>(nb, [&](auto qc) {
         constexpr int q = decltype(qc)::value;
         inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
         if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
@@ -124,7 +132,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     lds_barrier();
     // ... and their sum
     const int whole_steps = N / PLAN_BLOCK;              // (uniform) steps in which every lane has a slot
-    unrolled_steps<PLAN_IPT>(nb, [&](auto qc) {
+    unrolled_steps<IPT>(nb, [&](auto qc) {
         constexpr int q = decltype(qc)::value;
         const int j = q * PLAN_BLOCK + tid;
         if (q < whole_steps || j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
@@ -142,6 +150,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
                                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)inc, WAVE - 1));
             if (lane < P) { L.shard_shift[lane] = inc - padded - first; a.shard_tok_off[lane] = inc - padded; }
             if (lane == 0) {
+                L.end = end;
                 a.shard_tok_off[P] = end;
                 a.dst_tok_off[N] = end;
                 if (end > a.capacity) set_status(a.status, DC_ERR_OVERFLOW);
@@ -155,6 +164,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         const int64_t base = block_excl_scan_add<int64_t>(padded, L.tmp64, &end);
         if (tid < P) { L.shard_shift[tid] = base - first; a.shard_tok_off[tid] = base; }
         if (tid == 0) {
+            L.end = end;
             a.shard_tok_off[P] = end;
             a.dst_tok_off[N] = end;
             if (end > a.capacity) set_status(a.status, DC_ERR_OVERFLOW);
@@ -370,6 +380,101 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
         a.shard_mb_off[p] = c;
     }
     if (tid == 0) { *a.n_mb = M; a.mb_seq_off[M] = N; }
+}
+
+// Tables of granule g of a token axis holding N slots (starts[N+1], the last entry its end);
+// usable = false leaves the granule empty.  desc(j, &ln, &so, &sh): the validated source of slot j.
+// found >= 0: the first slot whose successor starts after the granule's first token (else it is looked for here).
+template <typename Desc>
+__device__ __forceinline__ void build_record(int N, bool usable, const int64_t* starts, Desc desc, int64_t g,
+                                             int32_t* first_out, GranRec* rec_out, int found = -1) {
+    const int64_t begin = g * GATHER_GRAN;
+    int first = N;
+    if (usable && N > 0) {
+        // first j whose successor starts after `begin` ...
+        int lo = 0, hi = N;
+        if (found >= 0) lo = hi = found;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (starts[mid + 1] > begin) hi = mid; else lo = mid + 1;
+        }
+        // ... and if `begin` lies in the padding behind that slot (or the slot is empty), the next one
+        while (lo < N) {
+            int32_t ln, sh;
+            int64_t so;
+            desc(lo, &ln, &so, &sh);
+            if (starts[lo] + ln > begin) break;
+            ++lo;
+        }
+        first = lo;
+    }
+    GranRec rec;
+#pragma unroll
+    for (int r = 0; r < REC_SLOTS; ++r) {
+        rec.e[r].start = REL_FAR; rec.e[r].lensh = 0; rec.e[r].src_off = 0;
+        const int j = first + r;
+        if (j < N) {
+            const int64_t d = starts[j] - begin;
+            if (d < GATHER_GRAN) {
+                int32_t ln, sh;
+                int64_t so;
+                desc(j, &ln, &so, &sh);
+                rec.e[r].start = (int32_t)max(d, (int64_t)-REL_FAR);
+                rec.e[r].lensh = ln | (sh << LENSH_SHIFT);
+                rec.e[r].src_off = so;
+            }
+        }
+    }
+    *first_out = first;
+    u32x4* out = reinterpret_cast<u32x4*>(rec_out);
+    const u32x4* in = reinterpret_cast<const u32x4*>(&rec);
+#pragma unroll
+    for (int r = 0; r < REC_SLOTS; ++r) out[r] = in[r];
+}
+
+// The granule tables and the per-slot source descriptors as the tail of the launch that balances and plans (fixed_c > 0,
+// behind plan_body), for a batch small enough that one workgroup is quicker with them than a launch of its own is started:
+// up to SMALL_REC_SLOTS slots and SMALL_REC_GRANS granules, the slots' starts and sources in the LDS behind the prefix.
+// src_off[q]: d_src_tok_off of the slots' sequences, asked for before the plan.
+// A launch of its own takes 5 to 7.5 us: steps of 64 and 512 sequences 26.8 -> 21.4 and 34.6 -> 29.7 us.  With 3200 granules
+// (2048 sequences of 1600 tokens) the two are level.
+struct SmallRecLds {
+    int64_t start[SMALL_REC_SLOTS + 1];     // d_dst_tok_off
+    int64_t src_off[SMALL_REC_SLOTS];
+    int32_t lensh[SMALL_REC_SLOTS];         // length | rollout shard << LENSH_SHIFT
+};
+constexpr int SMALL_REC_IPT = SMALL_REC_SLOTS / PLAN_BLOCK;
+static_assert(sizeof(SmallRecLds) <= sizeof(int64_t) * (DC_MAX_SEQ - SMALL_REC_SLOTS), "it fits behind the prefix of as many slots");
+__device__ __forceinline__ void small_records(PlanLds& L, const PlanArgs& a, const SourceDesc& sd, const int32_t (&seq)[SMALL_REC_IPT],
+                                              const int32_t (&len)[SMALL_REC_IPT], const int64_t (&src_off)[SMALL_REC_IPT], int fixed_c) {
+    SmallRecLds& R = *reinterpret_cast<SmallRecLds*>(&L.gpre[SMALL_REC_SLOTS + 1]);
+    const int tid = threadIdx.x;
+    const int N = a.n_seq;
+    lds_barrier();                                       // (the words behind the prefix are not the plan's any more)
+#pragma unroll
+    for (int q = 0; q < SMALL_REC_IPT; ++q) {
+        const int j = q * PLAN_BLOCK + tid;
+        if (j < N) {
+            int32_t ln, sh;
+            int64_t so;
+            slot_source_of(a, sd, seq[q], seq[q] >= 0 && seq[q] < N, len[q], src_off[q], &ln, &so, &sh);
+            R.start[j] = L.gpre[j] + (a.align != 1 ? L.shard_shift[j / fixed_c] : 0);
+            R.src_off[j] = so;
+            R.lensh[j] = ln | (sh << LENSH_SHIFT);
+            a.slot_src_off[j] = so;
+            a.slot_len[j] = ln;
+            a.slot_shard[j] = sh;
+        }
+    }
+    if (tid == 0) R.start[N] = L.end;
+    lds_barrier();
+    for (int64_t g = tid; g < a.n_gran; g += PLAN_BLOCK)
+        build_record(N, true, R.start,
+                     [&](int j, int32_t* ln, int64_t* so, int32_t* sh) {
+                         const int32_t ls = R.lensh[j];
+                         *ln = ls & ((1 << LENSH_SHIFT) - 1); *sh = ls >> LENSH_SHIFT; *so = R.src_off[j];
+                     },
+                     g, a.gran_first + g, a.gran_rec + g);
 }
 
 }  // namespace dc

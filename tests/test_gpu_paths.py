@@ -93,3 +93,17 @@ def test_sort_of_few_sequences(n, kind):
     if kind == "tail":
         lens = np.sort(lens)[:: 1 if n % 2 else -1].copy()       # ascending and descending input
     check_step(_custom(lens, 1, 1, 1 << 17, fields=()), label=f"{n} sequences, {kind}", two_calls=True)
+
+
+@pytest.mark.parametrize("tokens", [1024, 2032 * 1024, 2032 * 1024 + 1])
+@pytest.mark.parametrize("align", [1, 48])
+def test_granule_tables_of_a_small_batch(tokens, align):
+    """Up to 2048 table entries the balance workgroup makes them itself, behind that a launch does."""
+    n, shards = 256, 4
+    room = tokens - shards * (align - 1)
+    lens = np.random.default_rng(tokens).integers(1, 2 * room // n, n)
+    lens = np.maximum(1, lens * (room // n) // max(1, int(lens.mean())))
+    lens[0] += max(0, room - int(lens.sum()))
+    lens = lens.astype(np.int32)
+    check_step(_custom(lens, 4, shards, 1 << 22, n_src=2, fields=()), align=align, label=f"{tokens} tokens of capacity", two_calls=True)
+    check_gather_advantage(_custom(lens, 4, shards, 1 << 22, n_src=2, fields=()), align=align, label=f"{tokens} tokens")
