@@ -6,10 +6,10 @@
 // With t_1 < ... < t_m the loss-bearing tokens of a sequence:
 //   delta_k = r_k + gamma V[t_{k+1}] - V[t_k]   (V[t_{m+1}] = 0; r_k = KL penalty, plus the score on t_m)
 //   A_k     = delta_k + gamma lambda A_{k+1},   ret_k = A_k + V[t_k]
-// a first-order linear recurrence running backwards in time.  A workgroup of GAE_WAVES
-// wavefronts shares one sequence and walks it from the end; per iteration a wave takes 512
-// tokens, a lane 8 consecutive ones (two aligned 16-byte groups of the value array), lane 0 of
-// wave 0 the latest.  Inside an iteration
+// a first-order linear recurrence running backwards in time.  A workgroup of NW wavefronts shares
+// one sequence and walks it from the end; per iteration a wave takes 64 * T tokens, a lane T = 8
+// consecutive ones (two aligned 16-byte groups of the value array; short sequences: 4, one
+// group), lane 0 of wave 0 the latest.  Inside an iteration
 //   * "gamma V of the next loss-bearing token" is a copy from the nearest earlier lane (or wave)
 //     that holds one, not arithmetic;
 //   * each lane folds its tokens into one affine map A_after = P A_in + B, the lanes' maps are
@@ -19,11 +19,12 @@
 //     again; a wave without any loss-bearing token (a prompt) only writes zeros;
 //   * the outputs leave through a transpose in LDS, so that a store instruction writes 64
 //     consecutive 16-byte chunks (a lane's own 8 tokens are 32 bytes: two instructions that
-//     each write every other 16 bytes, which streaming stores handle at a third of the rate).
+//     each write every other 16 bytes, which streaming stores handle at a third of the rate; with 4
+//     tokens a lane writes one chunk as it is).
 // All arithmetic is float64 (the kernel is bound by HBM, not by the vector unit: 13 B per token,
 // 21 with the KL penalty); outputs are rounded once to float32.
 // Measured rationale: one wave per sequence left the longest sequence (36 K tokens, 141 dependent
-// blocks) running alone for 160 us; with two waves it is still 36 dependent iterations, which
+// blocks) running alone for 160 us; with two or four waves it is still 36 or 18 dependent iterations, which
 // run on alone when the sequence's workgroup starts late, so the first workgroups of the grid
 // look for long sequences and start those; anything derived from a loaded mask word at load time makes
 // the wave wait for the loads it has just issued (the prefetch ring keeps the raw words);
@@ -35,8 +36,6 @@
 #include "dc_lanes.h"
 
 namespace dc {
-
-constexpr int GAE_WAVES = 2;                 // waves that share one sequence
 
 struct GaeArgs {
     int32_t        n_seq, use_kl;
@@ -56,14 +55,12 @@ struct GaeArgs {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int GAE_TPL = 8;                   // tokens per lane: two aligned 16-byte groups of the value array
-
-// One lane's 8 consecutive tokens: elements x0 .. x0+7 of the shard's buffers (x0 a multiple of 8).
-template <bool KL>
+// One lane's T consecutive tokens, T = 8 or 4: elements x0 .. x0 + T - 1 of the shard's buffers (x0 a multiple of T).
+template <bool KL, int T>
 struct GaeLane {
-    float    v[GAE_TPL];                       // values (0 outside the sequence)
-    float    lp[KL ? GAE_TPL : 1], rf[KL ? GAE_TPL : 1];   // log-probabilities, policy and reference (KL penalty only)
-    uint32_t m[2];                             // the 8 mask bytes as loaded (0 outside the sequence); nothing is
+    float    v[T];                             // values (0 outside the sequence)
+    float    lp[KL ? T : 1], rf[KL ? T : 1];   // log-probabilities, policy and reference (KL penalty only)
+    uint32_t m[T / 4];                         // the mask bytes as loaded (0 outside the sequence); nothing is
                                                // derived from them before the lane's turn comes: a use here would make
                                                // the wave wait for the loads it has only just issued
     uint32_t inside;                           // bit t: token t belongs to the sequence
@@ -74,34 +71,39 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t m) {
            ((m & 0x00FF0000u) ? 4u : 0u) | ((m & 0xFF000000u) ? 8u : 0u);
 }
 
-template <bool KL>
+template <bool KL, int T>
 __device__ __forceinline__ void load_lane(const float* __restrict__ V, const uint8_t* __restrict__ M,
                                           const float* __restrict__ LP, const float* __restrict__ RF,
-                                          int64_t x0, bool live, int64_t so, int64_t end, GaeLane<KL>& g) {
-    if (live && x0 >= so && x0 + GAE_TPL <= end) {        // all 8 tokens inside the sequence: vector loads
-        const f32x4 va = *reinterpret_cast<const f32x4*>(V + x0), vb = *reinterpret_cast<const f32x4*>(V + x0 + 4);
-        g.m[0] = *reinterpret_cast<const uint32_t*>(M + x0);
-        g.m[1] = *reinterpret_cast<const uint32_t*>(M + x0 + 4);
-        g.v[0] = va.x; g.v[1] = va.y; g.v[2] = va.z; g.v[3] = va.w;
-        g.v[4] = vb.x; g.v[5] = vb.y; g.v[6] = vb.z; g.v[7] = vb.w;
-        g.inside = 0xFFu;
+                                          int64_t x0, bool live, int64_t so, int64_t end, GaeLane<KL, T>& g) {
+    if (live && x0 >= so && x0 + T <= end) {              // all tokens inside the sequence: vector loads
+        f32x4 v[T / 4], p[T / 4], r[T / 4];
+#pragma unroll
+        for (int h = 0; h < T / 4; ++h) v[h] = *reinterpret_cast<const f32x4*>(V + x0 + 4 * h);
+#pragma unroll
+        for (int h = 0; h < T / 4; ++h) g.m[h] = *reinterpret_cast<const uint32_t*>(M + x0 + 4 * h);
         if constexpr (KL) {
-            const f32x4 pa = *reinterpret_cast<const f32x4*>(LP + x0), pb = *reinterpret_cast<const f32x4*>(LP + x0 + 4);
-            const f32x4 ra = *reinterpret_cast<const f32x4*>(RF + x0), rb = *reinterpret_cast<const f32x4*>(RF + x0 + 4);
-            g.lp[0] = pa.x; g.lp[1] = pa.y; g.lp[2] = pa.z; g.lp[3] = pa.w;
-            g.lp[4] = pb.x; g.lp[5] = pb.y; g.lp[6] = pb.z; g.lp[7] = pb.w;
-            g.rf[0] = ra.x; g.rf[1] = ra.y; g.rf[2] = ra.z; g.rf[3] = ra.w;
-            g.rf[4] = rb.x; g.rf[5] = rb.y; g.rf[6] = rb.z; g.rf[7] = rb.w;
+#pragma unroll
+            for (int h = 0; h < T / 4; ++h) p[h] = *reinterpret_cast<const f32x4*>(LP + x0 + 4 * h);
+#pragma unroll
+            for (int h = 0; h < T / 4; ++h) r[h] = *reinterpret_cast<const f32x4*>(RF + x0 + 4 * h);
+        }
+        g.inside = (1u << T) - 1u;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            g.v[t] = v[t >> 2][t & 3];
+            if constexpr (KL) { g.lp[t] = p[t >> 2][t & 3]; g.rf[t] = r[t >> 2][t & 3]; }
         }
     } else {                                              // the sequence starts or ends inside, or lies elsewhere
-        g.m[0] = 0; g.m[1] = 0; g.inside = 0;
+        g.inside = 0;
 #pragma unroll
-        for (int t = 0; t < GAE_TPL; ++t) g.v[t] = 0.0f;
+        for (int h = 0; h < T / 4; ++h) g.m[h] = 0;
 #pragma unroll
-        for (int t = 0; t < (KL ? GAE_TPL : 1); ++t) { g.lp[t] = 0.0f; g.rf[t] = 0.0f; }
+        for (int t = 0; t < T; ++t) g.v[t] = 0.0f;
+#pragma unroll
+        for (int t = 0; t < (KL ? T : 1); ++t) { g.lp[t] = 0.0f; g.rf[t] = 0.0f; }
         if (live) {
 #pragma unroll
-            for (int t = 0; t < GAE_TPL; ++t) {
+            for (int t = 0; t < T; ++t) {
                 const int64_t x = x0 + t;
                 if (x >= so && x < end) {
                     g.inside |= 1u << t;
@@ -155,23 +157,19 @@ __device__ __forceinline__ int gae_longest_of_set(const GaeArgs& a, int set, int
     return key < 0 ? -1 : set + (GAE_SET - 1 - (int)(key & 0xFF)) * a.n_early;
 }
 
-// Iterations whose loads are in flight ahead of the one worked on.
-template <bool KL> constexpr int GAE_AHEAD = 2;
-
-// One workgroup of NW waves per sequence.  An iteration covers NW * 512 tokens, wave 0 the
-// latest 512 of them, lane 0 of a wave its latest 8.  The waves exchange two things through LDS:
+// One workgroup of NW waves per sequence, T tokens to a lane, the loads of AHEAD iterations in flight ahead of the one
+// worked on.  An iteration covers NW * 64 * T tokens, wave 0 the latest 64 * T of them, lane 0 of a wave its latest T.
+// The waves exchange two things through LDS (one wave: nothing):
 // gamma * V of each wave's earliest loss-bearing token (a later wave's first loss-bearing token
 // needs it), and each wave's composed map, from which every wave derives the state entering its
 // tokens and the state carried to the next iteration.  Two barriers per iteration; every wave
 // of the workgroup runs the same number of iterations (a wave whose lanes all lie before the
 // sequence's start just takes part in the barriers).
-template <int NW, bool KL>
+template <int NW, bool KL, int T, int AHEAD>
 __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd) {
-    constexpr int AHEAD = GAE_AHEAD<KL>;
-    constexpr int T = GAE_TPL;
     __shared__ double s_u[NW], s_P[NW], s_B[NW];
     __shared__ int32_t s_has[NW];
-    __shared__ __attribute__((aligned(16))) float s_stage[NW][2 * WAVE * GAE_TPL];   // a wave's outputs on their way out
+    __shared__ __attribute__((aligned(16))) float s_stage[NW][T == 8 ? 2 * WAVE * T : 4];   // a wave's outputs on their way out
     const int lane = threadIdx.x & (WAVE - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     // One workgroup per sequence, in index order, behind n_early workgroups that each start the longest
@@ -179,21 +177,34 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
     // a 36 K-token sequence is 36 dependent iterations, and started late it runs on alone after the rest.
     int i = (int)blockIdx.x - a.n_early;
     const bool early = i < 0;
-    if (early || gae_is_long(a.seq_len[i], a.long_len)) {          // uniform over the workgroup
+    // (all the sequence's words are asked for at once: one trip to memory)
+    int32_t ln = 0;
+    int64_t so = 0, next = 0;
+    float score = 0.0f;
+    auto fetch = [&]() {
+        ln = a.seq_len[i];
+        so = a.src_tok_off[i];
+        next = a.src_tok_off[min(i + 1, a.n_seq - 1)];
+        score = a.reward[i];
+    };
+    if (!early) fetch();
+    if (early || gae_is_long(ln, a.long_len)) {                    // uniform over the workgroup
         const int set = early ? (int)blockIdx.x : i % a.n_early;
         const int longest = gae_longest_of_set(a, set, lane);
         if (early ? longest < 0 : longest == i) return;            // nothing to start early / started early
-        if (early) i = __builtin_amdgcn_readfirstlane(longest);
+        if (early) {
+            i = __builtin_amdgcn_readfirstlane(longest);
+            fetch();
+        }
     }
-    int s = 0;
-    while (s + 1 < sd.n_src && i >= sd.seq_off[s + 1]) ++s;
-    const int64_t so = a.src_tok_off[i];
-    const int32_t ln = a.seq_len[i];
+    int s = 0;                                                     // (seq_off[k] = N from k = n_src on)
+#pragma unroll
+    for (int k = 1; k < DC_MAX_SRC_SHARDS; ++k) s += i >= sd.seq_off[k] ? 1 : 0;
     if (ln <= 0 || ln > DC_MAX_SEQ_LEN) {                          // uniform over the workgroup
         if (threadIdx.x == 0) set_status(a.status, DC_ERR_ZERO_LENGTH_SEQ);
         return;
     }
-    if (so < 0 || so + ln > sd.tokens[s] || (i + 1 < sd.seq_off[s + 1] && a.src_tok_off[i + 1] < so + ln)) {
+    if (so < 0 || so + ln > sd.tokens[s] || (i + 1 < sd.seq_off[s + 1] && next < so + ln)) {
         if (threadIdx.x == 0) set_status(a.status, DC_ERR_BAD_LAYOUT);   // outside its buffer or overlapping the next
         return;
     }
@@ -204,41 +215,44 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
     float* __restrict__ ADV = a.adv[s];
     float* __restrict__ RET = a.ret[s];
     const int64_t end = so + ln;
-    const int64_t q_lo = so >> 3, q_hi = (end - 1) >> 3;          // aligned 8-token lane groups the sequence touches
+    constexpr int LG_T = T == 8 ? 3 : 2;
+    static_assert(T == 1 << LG_T, "8 or 4 tokens to a lane");
+    const int64_t q_lo = so >> LG_T, q_hi = (end - 1) >> LG_T;    // aligned T-token lane groups the sequence touches
     const double gamma = a.gamma, decay = a.decay, klc = a.kl_coef;
     constexpr int STEP = NW * WAVE;                                // lane groups per iteration
-    double decay_pow_T = 1.0;                                      // decay^8: a lane's multiplier when all its tokens bear loss
+    double decay_pow_T = 1.0;                                      // decay^T: a lane's multiplier when all its tokens bear loss
 #pragma unroll
     for (int t = 0; t < T; ++t) decay_pow_T *= decay;
 
     // carried from iteration to iteration (uniform): A of the next loss-bearing token, and gamma * its
     // value, which starts out as the sequence's score (so the score lands on the last such token)
-    double A_carry = 0.0, U_carry = (double)a.reward[i];
+    double A_carry = 0.0, U_carry = (double)score;
 
-    GaeLane<KL> ring[AHEAD > 0 ? AHEAD : 1];
+    GaeLane<KL, T> ring[AHEAD > 0 ? AHEAD : 1];
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) {
         const int64_t q = q_hi - (int64_t)k * STEP - w * WAVE - lane;
-        load_lane<KL>(V, M, LP, RF, q * T, q >= q_lo, so, end, ring[k]);
+        load_lane<KL, T>(V, M, LP, RF, q * T, q >= q_lo, so, end, ring[k]);
     }
     for (int64_t top = q_hi; top >= q_lo; top -= STEP) {
         const int64_t q = top - w * WAVE - lane;                   // my lane group; lane 0 of wave 0 holds the latest one
-        GaeLane<KL> cur;
+        GaeLane<KL, T> cur;
         if constexpr (AHEAD > 0) {
             cur = ring[0];
 #pragma unroll
             for (int k = 0; k + 1 < AHEAD; ++k) ring[k] = ring[k + 1];
             const int64_t qn = q - (int64_t)AHEAD * STEP;
-            load_lane<KL>(V, M, LP, RF, qn * T, qn >= q_lo, so, end, ring[AHEAD - 1]);
+            load_lane<KL, T>(V, M, LP, RF, qn * T, qn >= q_lo, so, end, ring[AHEAD - 1]);
         } else {
-            load_lane<KL>(V, M, LP, RF, q * T, q >= q_lo, so, end, cur);
+            load_lane<KL, T>(V, M, LP, RF, q * T, q >= q_lo, so, end, cur);
         }
-        const uint32_t loss = nonzero_bytes(cur.m[0]) | (nonzero_bytes(cur.m[1]) << 4);   // bit t: token t bears loss
+        uint32_t loss = nonzero_bytes(cur.m[0]);                   // bit t: token t bears loss
+        if constexpr (T == 8) loss |= nonzero_bytes(cur.m[1]) << 4;
         const uint64_t holders = __ballot(loss != 0);              // lanes of my wave with a loss-bearing token
         const bool any = holders != 0ull;                          // uniform over the wave
-        // uniform: every lane that holds tokens of the sequence at all holds 8 loss-bearing ones (the
+        // uniform: every lane that holds tokens of the sequence at all holds T loss-bearing ones (the
         // inside of a response); then no mask is looked at again
-        const bool solid = any && __ballot(loss != 0xFFu && cur.inside != 0u) == 0ull;
+        const bool solid = any && __ballot(loss != (1u << T) - 1u && cur.inside != 0u) == 0ull;
 
         // ---- gamma * V of my earliest loss-bearing token; the wave's earliest goes to the other waves ----
         double U_last;
@@ -252,15 +266,19 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
             U_last = gamma * (double)first;
         }
         const double U_wave = readlane_f64(U_last, any ? 63 - __builtin_clzll(holders) : 0);
-        if (lane == 0) { s_has[w] = any ? 1 : 0; s_u[w] = U_wave; }
-        __syncthreads();
         double U_w = U_carry, U_next = U_carry;                    // entering my wave / carried to the next iteration
+        if constexpr (NW == 1) {
+            if (any) U_next = U_wave;
+        } else {
+            if (lane == 0) { s_has[w] = any ? 1 : 0; s_u[w] = U_wave; }
+            lds_barrier();
 #pragma unroll
-        for (int k = 0; k < NW; ++k) {
-            const bool h = s_has[k] != 0;
-            const double u = s_u[k];
-            if (h && k < w) U_w = u;
-            if (h) U_next = u;
+            for (int k = 0; k < NW; ++k) {
+                const bool h = s_has[k] != 0;
+                const double u = s_u[k];
+                if (h && k < w) U_w = u;
+                if (h) U_next = u;
+            }
         }
 
         // ---- my tokens, latest first: r[t] = what token t adds to decay * A (its TD residual), and the lane's map
@@ -304,14 +322,18 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
             affine_scan_step<DPP_ROW_BCAST15, 0xA>(Pi, Bi);
             affine_scan_step<DPP_ROW_BCAST31, 0xC>(Pi, Bi);
         }
-        if (lane == WAVE - 1) { s_P[w] = Pi; s_B[w] = Bi; }       // the wave's whole map (identity without loss)
-        __syncthreads();
         double A_w = A_carry, A_next = A_carry;                    // entering my wave / carried to the next iteration
+        if constexpr (NW == 1) {
+            A_next = __builtin_fma(readlane_f64(Pi, WAVE - 1), A_next, readlane_f64(Bi, WAVE - 1));
+        } else {
+            if (lane == WAVE - 1) { s_P[w] = Pi; s_B[w] = Bi; }   // the wave's whole map (identity without loss)
+            lds_barrier();
 #pragma unroll
-        for (int k = 0; k < NW; ++k) {
-            const double Pk = s_P[k], Bk = s_B[k];
-            if (k == w) A_w = A_next;
-            A_next = __builtin_fma(Pk, A_next, Bk);
+            for (int k = 0; k < NW; ++k) {
+                const double Pk = s_P[k], Bk = s_B[k];
+                if (k == w) A_w = A_next;
+                A_next = __builtin_fma(Pk, A_next, Bk);
+            }
         }
 
         // ---- outputs: replay my tokens from the state entering my lane ----
@@ -344,25 +366,7 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
         // a third of the rate of 64 consecutive 16-byte chunks (2.3 against 6.3 TB/s, write-only probe).
         // Memory order runs against lane order; the wave's window starts at lane 63's first token.
         if (__ballot(cur.inside != 0u) != 0ull) {                  // uniform: some token of the window lies inside
-            float* st_a = s_stage[w];
-            float* st_r = st_a + WAVE * T;
-            const int mine = (WAVE - 1 - lane) * T;
-            f32x4 o;
-            o.x = oa[0]; o.y = oa[1]; o.z = oa[2]; o.w = oa[3];
-            *reinterpret_cast<f32x4*>(st_a + mine) = o;
-            o.x = oa[4]; o.y = oa[5]; o.z = oa[6]; o.w = oa[7];
-            *reinterpret_cast<f32x4*>(st_a + mine + 4) = o;
-            o.x = orr[0]; o.y = orr[1]; o.z = orr[2]; o.w = orr[3];
-            *reinterpret_cast<f32x4*>(st_r + mine) = o;
-            o.x = orr[4]; o.y = orr[5]; o.z = orr[6]; o.w = orr[7];
-            *reinterpret_cast<f32x4*>(st_r + mine + 4) = o;
-            const int64_t base = (top - (int64_t)w * WAVE - (WAVE - 1)) * T;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int c = (u * WAVE + lane) * 4;               // my chunk of 4 tokens in this instruction
-                const int64_t t0 = base + c;
-                const f32x4 va = *reinterpret_cast<const f32x4*>(st_a + c);
-                const f32x4 vr = *reinterpret_cast<const f32x4*>(st_r + c);
+            auto store4 = [&](int64_t t0, f32x4 va, f32x4 vr) {
                 if (t0 >= so && t0 + 4 <= end) {
                     __builtin_nontemporal_store(va, reinterpret_cast<f32x4*>(ADV + t0));
                     __builtin_nontemporal_store(vr, reinterpret_cast<f32x4*>(RET + t0));
@@ -370,6 +374,31 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (t0 + e >= so && t0 + e < end) { ADV[t0 + e] = va[e]; RET[t0 + e] = vr[e]; }
+                }
+            };
+            if constexpr (T == 4) {
+                f32x4 va, vr;
+                va.x = oa[0]; va.y = oa[1]; va.z = oa[2]; va.w = oa[3];
+                vr.x = orr[0]; vr.y = orr[1]; vr.z = orr[2]; vr.w = orr[3];
+                store4(q * T, va, vr);
+            } else {
+                float* st_a = s_stage[w];
+                float* st_r = st_a + WAVE * T;
+                const int mine = (WAVE - 1 - lane) * T;
+                f32x4 o;
+                o.x = oa[0]; o.y = oa[1]; o.z = oa[2]; o.w = oa[3];
+                *reinterpret_cast<f32x4*>(st_a + mine) = o;
+                o.x = oa[T - 4]; o.y = oa[T - 3]; o.z = oa[T - 2]; o.w = oa[T - 1];
+                *reinterpret_cast<f32x4*>(st_a + mine + 4) = o;
+                o.x = orr[0]; o.y = orr[1]; o.z = orr[2]; o.w = orr[3];
+                *reinterpret_cast<f32x4*>(st_r + mine) = o;
+                o.x = orr[T - 4]; o.y = orr[T - 3]; o.z = orr[T - 2]; o.w = orr[T - 1];
+                *reinterpret_cast<f32x4*>(st_r + mine + 4) = o;
+                const int64_t base = (top - (int64_t)w * WAVE - (WAVE - 1)) * T;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int c = (u * WAVE + lane) * 4;           // my chunk of 4 tokens in this instruction
+                    store4(base + c, *reinterpret_cast<const f32x4*>(st_a + c), *reinterpret_cast<const f32x4*>(st_r + c));
                 }
             }
         }
@@ -388,13 +417,10 @@ hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src
     a.n_seq = n_seq; a.use_kl = kl_coef != 0.0 ? 1 : 0;
     a.gamma = gamma; a.decay = gamma * lambda; a.kl_coef = kl_coef;
     a.src_tok_off = d_src_tok_off; a.seq_len = d_seq_len; a.reward = d_reward; a.status = d_status;
-    // long: at least twice the mean (the buffers' sizes bound the lengths' sum) and at least 4 iterations
     int64_t tokens = 0;
     for (int s = 0; s < src.n_src; ++s) tokens += src.tokens[s];
-    const int64_t twice_mean = 2 * (tokens / n_seq);
-    a.long_len = (int32_t)std::min<int64_t>(std::max<int64_t>(twice_mean, 4 * GAE_WAVES * WAVE * GAE_TPL), INT32_MAX);
+    const int64_t mean = tokens / n_seq;                           // (the buffers' sizes bound the lengths' sum)
     a.n_early = (n_seq + GAE_SET - 1) / GAE_SET;
-    const unsigned grid = (unsigned)(n_seq + a.n_early);
     for (int s = 0; s < DC_MAX_SRC_SHARDS; ++s) {
         const bool on = s < src.n_src;
         a.value[s] = on ? value_base[s] : nullptr;
@@ -404,10 +430,31 @@ hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src
         a.adv[s] = on ? adv_base[s] : nullptr;
         a.ret[s] = on ? ret_base[s] : nullptr;
     }
-    if (a.use_kl)
-        hipLaunchKernelGGL((gae_kernel<GAE_WAVES, true>), dim3(grid), dim3(GAE_WAVES * WAVE), 0, st, a, src);
-    else
-        hipLaunchKernelGGL((gae_kernel<GAE_WAVES, false>), dim3(grid), dim3(GAE_WAVES * WAVE), 0, st, a, src);
+    auto launch = [&](auto nw, auto t, auto ahead) {
+        constexpr int NW = decltype(nw)::value, T = decltype(t)::value, AHEAD = decltype(ahead)::value;
+        // long: at least twice the mean and at least 4 iterations
+        a.long_len = (int32_t)std::min<int64_t>(std::max<int64_t>(2 * mean, 4 * NW * WAVE * T), INT32_MAX);
+        const dim3 grid((unsigned)(n_seq + a.n_early)), block(NW * WAVE);
+        if (a.use_kl) hipLaunchKernelGGL((gae_kernel<NW, true, T, AHEAD>), grid, block, 0, st, a, src);
+        else hipLaunchKernelGGL((gae_kernel<NW, false, T, AHEAD>), grid, block, 0, st, a, src);
+    };
+    // Waves per sequence and tokens per lane, by what the chip holds at once and how long a sequence is (us before, with
+    // two waves of 8 tokens and two iterations ahead for every batch, and now; no KL penalty where not said):
+    //   up to 1024 sequences, and up to 4096 long ones: four waves of 8 tokens; the longest sequence's iterations are the
+    //   time (1024 of 1512 tokens 15.4 -> 12.5, of 4033 with KL 35.0 -> 28.1; 2048 of 4021 41.2 -> 33.0);
+    //   up to 2048: two waves of 8, or four of 4 above 1024 tokens (2048 of 1597 16.9 -> 16.5), all resident at once;
+    //   more: a wave that holds few tokens for its registers and its trips to memory is the time, so one wave of 4 tokens
+    //   to a lane up to 384 tokens (16 384 of 249 39.6 -> 19.5; four waves per SIMD become eight), two up to 1280 (16 384
+    //   of 697 48.4 -> 33.6, of 996 55.1 -> 43.7), four beyond (16 384 of 2594 with KL 171.2 -> 168; two of 8 are level).
+    using std::integral_constant;
+    constexpr integral_constant<int, 0> c0; constexpr integral_constant<int, 1> c1; constexpr integral_constant<int, 2> c2;
+    constexpr integral_constant<int, 4> c4; constexpr integral_constant<int, 8> c8;
+    if (n_seq <= 1024 || (n_seq <= 4096 && mean > 2048)) launch(c4, c8, c1);
+    else if (n_seq <= 2048 && mean <= 1024) launch(c2, c8, c2);
+    else if (n_seq <= 2048) launch(c4, c4, c0);
+    else if (mean <= 384) launch(c1, c4, c0);
+    else if (mean <= 1280) launch(c2, c4, c0);
+    else launch(c4, c4, c1);
     return hipGetLastError();
 }
 

@@ -3,7 +3,7 @@
 import numpy as np
 import pytest
 
-from test_gpu_parity import _check_balance_ws, _custom, check_gather_advantage, check_scatter, check_step
+from test_gpu_parity import _check_balance_ws, _custom, _with_ppo_fields, check_gae, check_gather_advantage, check_scatter, check_step
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +107,17 @@ def test_granule_tables_of_a_small_batch(tokens, align):
     lens = lens.astype(np.int32)
     check_step(_custom(lens, 4, shards, 1 << 22, n_src=2, fields=()), align=align, label=f"{tokens} tokens of capacity", two_calls=True)
     check_gather_advantage(_custom(lens, 4, shards, 1 << 22, n_src=2, fields=()), align=align, label=f"{tokens} tokens")
+
+
+@pytest.mark.parametrize("kl", [0.0, 0.05])
+@pytest.mark.parametrize("n,mean", [(1024, 300), (1025, 40), (1025, 1100), (2048, 1030), (2049, 30), (2049, 380), (2049, 400), (2500, 1270),
+                                    (2500, 1300), (1100, 2100)])
+def test_gae_waves_and_tokens_per_lane(n, mean, kl):
+    """Each way of sharing a sequence among waves and lanes, on both sides of the lines between them, with sequences that
+    start and end anywhere in a lane's tokens, single tokens, and a few of many iterations."""
+    rng = np.random.default_rng(n + mean)
+    lens = rng.integers(1, 2 * mean - 1, n)
+    lens[:: n // 3] = 4 * mean + rng.integers(0, 9)
+    lens[1:: n // 3] = 1
+    w = _with_ppo_fields(_custom(lens.astype(np.int32), 1, 1, 1 << 20, fields=()), seed=n)
+    check_gae(w, 0.99, 0.95, kl, label=f"{n} sequences of {mean}")
