@@ -131,9 +131,7 @@ def strerror(code: int) -> str:
 
 def _ptr(x) -> Optional[int]:
     """Device address of a torch tensor (or pass an int / None through)."""
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
     if not x.is_cuda:
         raise TypeError("expected a device tensor")
@@ -142,10 +140,18 @@ def _ptr(x) -> Optional[int]:
     return x.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        # the current stream's handle without the Stream object that torch.cuda.current_stream() builds round it
+        # (1.5 us of a call that takes 8)
+        global _raw_stream
+        if _raw_stream is None:
+            import torch
+            _raw_stream = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+        return _raw_stream[0](_raw_stream[1]()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
@@ -169,8 +175,15 @@ class Source:
         self.n_src_shards = n
 
 
-def _ptr_array(items: Sequence) -> C.Array:
-    return (C.c_void_p * len(items))(*[_ptr(t) for t in items])
+_ARRAYS = tuple(C.c_void_p * n for n in range(DC_MAX_SRC_SHARDS + 1))       # array types by length
+
+
+def _ptr_array(items: Optional[Sequence]) -> Optional[C.Array]:
+    """Host array of device addresses; None (a null pointer) stays None."""
+    if items is None:
+        return None
+    n = len(items)
+    return (_ARRAYS[n] if n <= DC_MAX_SRC_SHARDS else C.c_void_p * n)(*[_ptr(t) for t in items])
 
 
 class Fields:
@@ -218,13 +231,9 @@ def dc_balance_ws(prm: dc_params, d_seq_len, d_perm, d_shard_seq_off, d_shard_of
 def dc_group_advantage(prm: dc_params, src: Source, d_seq_len, d_reward, d_group_off, n_groups: int,
                        mask_src: Optional[Sequence], d_adv_seq, adv_tok_src: Optional[Sequence],
                        d_status, stream=None) -> None:
-    m = _ptr_array(mask_src) if mask_src is not None else None
-    a = _ptr_array(adv_tok_src) if adv_tok_src is not None else None
     _check(load().dc_group_advantage(C.byref(prm), C.byref(src.struct), _ptr(d_seq_len), _ptr(d_reward),
                                      _ptr(d_group_off), int(n_groups),
-                                     C.cast(m, C.POINTER(C.c_void_p)) if m is not None else None,
-                                     _ptr(d_adv_seq),
-                                     C.cast(a, C.POINTER(C.c_void_p)) if a is not None else None,
+                                     _ptr_array(mask_src), _ptr(d_adv_seq), _ptr_array(adv_tok_src),
                                      _ptr(d_status), _stream(stream)),
            "dc_group_advantage")
 
@@ -315,25 +324,20 @@ def dc_scatter(prm: dc_params, src: Source, d_seq_len, d_perm, fields: Fields, d
 def dc_gae(prm: dc_params, src: Source, d_seq_len, d_reward, value_src: Sequence, mask_src: Sequence,
            logp_src: Optional[Sequence], ref_src: Optional[Sequence], gamma: float, lam: float, kl_coef: float,
            adv_tok_src: Sequence, ret_tok_src: Sequence, d_status, stream=None) -> None:
-    def arr(x):
-        return C.cast(_ptr_array(x), C.POINTER(C.c_void_p)) if x is not None else None
-    keep = [arr(value_src), arr(mask_src), arr(logp_src), arr(ref_src), arr(adv_tok_src), arr(ret_tok_src)]
-    _check(load().dc_gae(C.byref(prm), C.byref(src.struct), _ptr(d_seq_len), _ptr(d_reward), keep[0], keep[1],
-                         keep[2], keep[3], float(gamma), float(lam), float(kl_coef), keep[4], keep[5],
-                         _ptr(d_status), _stream(stream)),
+    _check(load().dc_gae(C.byref(prm), C.byref(src.struct), _ptr(d_seq_len), _ptr(d_reward), _ptr_array(value_src),
+                         _ptr_array(mask_src), _ptr_array(logp_src), _ptr_array(ref_src), float(gamma), float(lam),
+                         float(kl_coef), _ptr_array(adv_tok_src), _ptr_array(ret_tok_src), _ptr(d_status),
+                         _stream(stream)),
            "dc_gae")
 
 
 def dc_balance_group_advantage(prm: dc_params, src: Source, d_seq_len, d_perm, d_shard_seq_off, d_shard_of_seq,
                                d_shard_load, d_reward, d_group_off, n_groups: int, mask_src: Optional[Sequence],
                                d_adv_seq, adv_tok_src: Optional[Sequence], d_status, stream=None) -> None:
-    m = _ptr_array(mask_src) if mask_src is not None else None
-    a = _ptr_array(adv_tok_src) if adv_tok_src is not None else None
     _check(load().dc_balance_group_advantage(
         C.byref(prm), C.byref(src.struct), _ptr(d_seq_len), _ptr(d_perm), _ptr(d_shard_seq_off), _ptr(d_shard_of_seq),
         _ptr(d_shard_load), _ptr(d_reward), _ptr(d_group_off), int(n_groups),
-        C.cast(m, C.POINTER(C.c_void_p)) if m is not None else None, _ptr(d_adv_seq),
-        C.cast(a, C.POINTER(C.c_void_p)) if a is not None else None, _ptr(d_status), _stream(stream)),
+        _ptr_array(mask_src), _ptr(d_adv_seq), _ptr_array(adv_tok_src), _ptr(d_status), _stream(stream)),
         "dc_balance_group_advantage")
 
 
@@ -342,13 +346,10 @@ def dc_balance_plan_group_advantage(prm: dc_params, src: Source, d_seq_len, d_pe
                                     d_adv_seq, adv_tok_src: Optional[Sequence], dst_capacity_tokens: int, d_dst_tok_off,
                                     d_shard_tok_off, d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb, d_ws,
                                     ws_bytes: int, d_status, stream=None) -> None:
-    m = _ptr_array(mask_src) if mask_src is not None else None
-    a = _ptr_array(adv_tok_src) if adv_tok_src is not None else None
     _check(load().dc_balance_plan_group_advantage(
         C.byref(prm), C.byref(src.struct), _ptr(d_seq_len), _ptr(d_perm), _ptr(d_shard_seq_off), _ptr(d_shard_of_seq),
         _ptr(d_shard_load), _ptr(d_reward), _ptr(d_group_off), int(n_groups),
-        C.cast(m, C.POINTER(C.c_void_p)) if m is not None else None, _ptr(d_adv_seq),
-        C.cast(a, C.POINTER(C.c_void_p)) if a is not None else None, int(dst_capacity_tokens), _ptr(d_dst_tok_off),
+        _ptr_array(mask_src), _ptr(d_adv_seq), _ptr_array(adv_tok_src), int(dst_capacity_tokens), _ptr(d_dst_tok_off),
         _ptr(d_shard_tok_off), _ptr(d_shard_mb_off), _ptr(d_mb_seq_off), _ptr(d_cu_seqlens), _ptr(d_n_mb),
         _ptr(d_ws), int(ws_bytes), _ptr(d_status), _stream(stream)),
         "dc_balance_plan_group_advantage")
