@@ -175,14 +175,13 @@ hipError_t launch_gather_advantage(int32_t n_seq, const FieldTable& ft, int mask
 hipError_t launch_records(int32_t n_seq, const int64_t* d_dst_tok_off, const Workspace& ws, hipStream_t st);
 
 // Workspace of the reverse path: the rollout layout seen as a destination.  Sequence i of
-// rollout shard s is "slot" i of that shard; r_dst_off has one more entry per shard (its end).
+// rollout shard s is "slot" i of that shard and starts at its rollout offset.
 // The granule tables of the rollout buffers lie one behind the other, each padded like the
 // forward path's.
 struct ScatterWorkspace {
-    int64_t* r_dst_off;      // [N + n_src] slot start in the rollout buffer, shard s at index seq_off[s] + s
     int64_t* r_src_off;      // [N] element offset of the sequence in the training arena
     int32_t* r_len;          // [N] tokens to move (0 if a check failed or perm does not place the sequence)
-    int32_t* r_shard;        // [N] zeros: the arena is the only "source shard"
+    int32_t* note;           // [N] a slot that claims the sequence
     int32_t* gran_first;     // [n_gran_all]
     GranRec* gran_rec;       // [n_gran_all]
     int64_t  n_gran_all;
@@ -202,8 +201,9 @@ struct BackSegs {
 };
 BackSegs make_back_segs(const SourceDesc& src);
 
-hipError_t launch_records_back(const BackSegs& bs, const ScatterWorkspace& ws, hipStream_t st);
-hipError_t launch_gather_back(const BackSegs& bs, const FieldTable& ft, const ScatterWorkspace& ws, hipStream_t st);
+// d_src_tok_off: the sequences' starts in their rollout buffers.
+hipError_t launch_gather_back(const BackSegs& bs, const FieldTable& ft, const int64_t* d_src_tok_off, const ScatterWorkspace& ws,
+                              hipStream_t st);
 
 hipError_t launch_scatter(int32_t n_seq, const SourceDesc& src, const int64_t* d_src_tok_off,
                           const int32_t* d_seq_len, const int32_t* d_perm, const FieldTable& ft,

@@ -799,10 +799,9 @@ __global__ __launch_bounds__(GATHER_BLOCK) void gather_back_kernel(GatherArgs a,
     const int first_seq = bs.first_seq[seg];
     a.n_seq = bs.n_seq[seg];
     a.capacity = bs.tokens[seg];
-    a.dst_tok_off += first_seq + seg;
+    a.dst_tok_off += first_seq;
     a.slot_src_off += first_seq;
     a.slot_len += first_seq;
-    a.slot_shard += first_seq;
     a.gran_first += bs.gran_base[seg];
     a.gran_rec += bs.gran_base[seg];
     __shared__ WaveSlots slots[GRAN_PER_TILE];
@@ -886,7 +885,8 @@ hipError_t launch_gather_advantage(int32_t n_seq, const FieldTable& ft, int mask
     return hipGetLastError();
 }
 
-hipError_t launch_gather_back(const BackSegs& bs, const FieldTable& ft, const ScatterWorkspace& ws, hipStream_t st) {
+hipError_t launch_gather_back(const BackSegs& bs, const FieldTable& ft, const int64_t* d_src_tok_off, const ScatterWorkspace& ws,
+                              hipStream_t st) {
     const int64_t tiles = bs.tile_end[DC_MAX_SRC_SHARDS - 1];
     if (ft.n_fields == 0 || tiles == 0) return hipSuccess;
     if (tiles * ft.n_fields > 0x7FFFFFFFLL) return hipErrorInvalidValue;
@@ -899,10 +899,10 @@ hipError_t launch_gather_back(const BackSegs& bs, const FieldTable& ft, const Sc
     GatherArgs a;
     a.n_seq = 0;
     a.capacity = 0;
-    a.dst_tok_off = ws.r_dst_off;
+    a.dst_tok_off = d_src_tok_off;
     a.slot_src_off = ws.r_src_off;
     a.slot_len = ws.r_len;
-    a.slot_shard = ws.r_shard;
+    a.slot_shard = nullptr;                                // (the arena is the only source)
     a.gran_first = ws.gran_first;
     a.gran_rec = ws.gran_rec;
     FieldTable sorted;

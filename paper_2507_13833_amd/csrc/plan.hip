@@ -62,8 +62,6 @@ __global__ __launch_bounds__(PLAN_BLOCK) void plan_kernel(PlanArgs a) {
 // plan_kernel on the same stream): F[g] = first slot that ends after the granule's first
 // token, found by bisection over the slot starts, and the record of the first REC_SLOTS
 // slots from F[g] on that start before the granule's end.
-constexpr int REC_BLOCK = 256;
-
 struct RecArgs {
     int32_t        n_seq;
     int64_t        n_gran;
@@ -75,50 +73,6 @@ struct RecArgs {
     int32_t*       gran_first;
     GranRec*       gran_rec;
 };
-
-// The first slot j of a token axis (starts[N + 1], the last entry its end) whose successor starts after `begin`, or N:
-// what build_record's bisection finds, for the REC_BLOCK consecutive granules of a workgroup together (every thread of
-// the workgroup must call it; begin must not decrease with the thread index).  A bisection of its own is 14 dependent
-// reads of global memory per lane at 16 384 slots.  Here the workgroup reads REC_BLOCK evenly spaced starts at once,
-// every lane finds its stretch between two of them in the LDS, the workgroup reads the stretches of all its lanes
-// (one run of starts: the granules are neighbours) and every lane bisects its own stretch in the LDS: two reads of
-// global memory in a row.  A run longer than REC_STAGE entries is bisected where it lies.
-constexpr int REC_STAGE = 1024;
-struct RecLds {
-    int64_t sample[REC_BLOCK];
-    int64_t stage[REC_STAGE];
-    int32_t run_lo, run_hi;
-};
-__device__ __forceinline__ int first_slot_after(RecLds& L, int N, const int64_t* starts, int64_t begin) {
-    const int tid = threadIdx.x;
-    const int stride = (N + REC_BLOCK - 1) / REC_BLOCK;              // >= 1 (N > 0)
-    L.sample[tid] = starts[min(tid * stride, N)];
-    __syncthreads();
-    // the last sample that does not lie after `begin` (sample 0 is starts[0] = 0 <= begin)
-    int i = 0;
-#pragma unroll
-    for (int step = REC_BLOCK / 2; step >= 1; step >>= 1)
-        if (L.sample[i + step] <= begin) i += step;
-    // the answer lies in [lo, hi]: everything before sample i starts at or before `begin`; the slot before sample i + 1
-    // has a successor behind `begin` (no sample i + 1: hi = N stands for "none")
-    int lo = min(i * stride, N);
-    int hi = i + 1 < REC_BLOCK ? min((i + 1) * stride, N) - 1 : N;
-    hi = max(hi, lo);
-    if (tid == 0) L.run_lo = lo;
-    if (tid == REC_BLOCK - 1) L.run_hi = hi;
-    __syncthreads();
-    const int run_lo = L.run_lo, run_hi = L.run_hi;                   // the bisections read starts[run_lo + 1 .. run_hi]
-    const bool staged = run_hi - run_lo + 1 <= REC_STAGE;             // (uniform)
-    if (staged)
-        for (int k = tid; k <= run_hi - run_lo; k += REC_BLOCK) L.stage[k] = starts[min(run_lo + k, N)];
-    __syncthreads();
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const int64_t next = staged ? L.stage[mid + 1 - run_lo] : starts[mid + 1];
-        if (next > begin) hi = mid; else lo = mid + 1;
-    }
-    return lo;
-}
 
 // The descriptors as slots_kernel left them in the workspace.
 struct StoredDesc {
@@ -136,9 +90,9 @@ __global__ __launch_bounds__(REC_BLOCK) void records_kernel(RecArgs a) {
     const bool usable = *a.plan_ok != 0;
     int found = -1;
     if (usable && a.n_seq > 0)                                   // (uniform) lanes behind the last granule look for its slot
-        found = first_slot_after(L, a.n_seq, a.dst_tok_off, min(g, a.n_gran - 1) * GATHER_GRAN);
+        found = first_slot_after(L, a.n_seq, [&](int j) { return a.dst_tok_off[j]; }, min(g, a.n_gran - 1) * GATHER_GRAN);
     if (g >= a.n_gran) return;
-    build_record(a.n_seq, usable, a.dst_tok_off, StoredDesc{a.slot_src_off, a.slot_len, a.slot_shard}, g,
+    build_record(a.n_seq, usable, [&](int j) { return a.dst_tok_off[j]; }, StoredDesc{a.slot_src_off, a.slot_len, a.slot_shard}, g,
                  a.gran_first + g, a.gran_rec + g, found);
 }
 
@@ -154,9 +108,9 @@ __global__ __launch_bounds__(REC_BLOCK) void records_slots_kernel(RecArgs a, Pla
         const bool usable = *a.plan_ok != 0;
         int found = -1;
         if (usable && a.n_seq > 0)
-            found = first_slot_after(L, a.n_seq, a.dst_tok_off, min(g, a.n_gran - 1) * GATHER_GRAN);
+            found = first_slot_after(L, a.n_seq, [&](int j) { return a.dst_tok_off[j]; }, min(g, a.n_gran - 1) * GATHER_GRAN);
         if (g >= a.n_gran) return;
-        build_record(a.n_seq, usable, a.dst_tok_off,
+        build_record(a.n_seq, usable, [&](int j) { return a.dst_tok_off[j]; },
                      [&](int j, int32_t* ln, int64_t* so, int32_t* sh) { slot_source(p, sd, j, max(p.slot_len[j], 0), ln, so, sh); },
                      g, a.gran_first + g, a.gran_rec + g, found);
         return;
@@ -170,24 +124,6 @@ __global__ __launch_bounds__(REC_BLOCK) void records_slots_kernel(RecArgs a, Pla
     p.slot_src_off[j] = so;
     p.slot_shard[j] = sh;
     if (ln != had) p.slot_len[j] = ln;
-}
-
-// The same for the reverse path: the granule tables of every rollout buffer, one behind the
-// other; a.dst_tok_off holds the slot starts of segment s from index first_seq[s] + s on.
-__global__ __launch_bounds__(REC_BLOCK) void records_back_kernel(RecArgs a, BackSegs bs) {
-    const int64_t g = (int64_t)blockIdx.x * REC_BLOCK + threadIdx.x;
-    if (g >= a.n_gran) return;
-    int s = 0;
-#pragma unroll
-    for (int q = 1; q < DC_MAX_SRC_SHARDS; ++q) s += (q < bs.n_seg && g >= bs.gran_base[q]) ? 1 : 0;
-    int32_t first_seq = bs.first_seq[0], n = bs.n_seq[0];
-    int64_t gb = bs.gran_base[0];
-#pragma unroll
-    for (int q = 1; q < DC_MAX_SRC_SHARDS; ++q)
-        if (s == q) { first_seq = bs.first_seq[q]; n = bs.n_seq[q]; gb = bs.gran_base[q]; }
-    build_record(n, true, a.dst_tok_off + first_seq + s,
-                 StoredDesc{a.slot_src_off + first_seq, a.slot_len + first_seq, a.slot_shard + first_seq},
-                 g - gb, a.gran_first + g, a.gran_rec + g);
 }
 
 hipError_t launch_plan(const dc_params& prm, const SourceDesc& src, const int64_t* d_src_tok_off,
@@ -254,17 +190,6 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
     a.own_shard_off = nullptr;
     a.gran_first = nullptr; a.gran_rec = nullptr; a.n_gran = 0;
     return a;
-}
-
-hipError_t launch_records_back(const BackSegs& bs, const ScatterWorkspace& ws, hipStream_t st) {
-    RecArgs r;
-    r.n_seq = 0; r.n_gran = ws.n_gran_all; r.dst_tok_off = ws.r_dst_off;
-    r.slot_src_off = ws.r_src_off; r.slot_len = ws.r_len; r.slot_shard = ws.r_shard;
-    r.plan_ok = nullptr; r.gran_first = ws.gran_first; r.gran_rec = ws.gran_rec;
-    if (ws.n_gran_all <= 0) return hipSuccess;
-    hipLaunchKernelGGL(records_back_kernel, dim3((unsigned)((ws.n_gran_all + REC_BLOCK - 1) / REC_BLOCK)), dim3(REC_BLOCK),
-                       0, st, r, bs);
-    return hipGetLastError();
 }
 
 }  // namespace dc

@@ -382,11 +382,58 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     if (tid == 0) { *a.n_mb = M; a.mb_seq_off[M] = N; }
 }
 
-// Tables of granule g of a token axis holding N slots (starts[N+1], the last entry its end);
+constexpr int REC_BLOCK = 256;                            // granules of one workgroup
+
+// The first slot j of a token axis (starts(j) as for build_record) whose successor starts after `begin`, or N:
+// what build_record's bisection finds, for the REC_BLOCK consecutive granules of a workgroup together (every thread of
+// the workgroup must call it; begin must not decrease with the thread index).  A bisection of its own is 14 dependent
+// reads of global memory per lane at 16 384 slots.  Here the workgroup reads REC_BLOCK evenly spaced starts at once,
+// every lane finds its stretch between two of them in the LDS, the workgroup reads the stretches of all its lanes
+// (one run of starts: the granules are neighbours) and every lane bisects its own stretch in the LDS: two reads of
+// global memory in a row.  A run longer than REC_STAGE entries is bisected where it lies.
+constexpr int REC_STAGE = 1024;
+struct RecLds {
+    int64_t sample[REC_BLOCK];
+    int64_t stage[REC_STAGE];
+    int32_t run_lo, run_hi;
+};
+template <typename Starts>
+__device__ __forceinline__ int first_slot_after(RecLds& L, int N, Starts starts, int64_t begin) {
+    const int tid = threadIdx.x;
+    const int stride = (N + REC_BLOCK - 1) / REC_BLOCK;              // >= 1 (N > 0)
+    L.sample[tid] = starts(min(tid * stride, N));
+    __syncthreads();
+    // the last sample that does not lie after `begin` (the first one if all do)
+    int i = 0;
+#pragma unroll
+    for (int step = REC_BLOCK / 2; step >= 1; step >>= 1)
+        if (L.sample[i + step] <= begin) i += step;
+    // the answer lies in [lo, hi]: everything before sample i starts at or before `begin`; the slot before sample i + 1
+    // has a successor behind `begin` (no sample i + 1: hi = N stands for "none")
+    int lo = min(i * stride, N);
+    int hi = i + 1 < REC_BLOCK ? min((i + 1) * stride, N) - 1 : N;
+    hi = max(hi, lo);
+    if (tid == 0) L.run_lo = lo;
+    if (tid == REC_BLOCK - 1) L.run_hi = hi;
+    __syncthreads();
+    const int run_lo = L.run_lo, run_hi = L.run_hi;                   // the bisections read starts[run_lo + 1 .. run_hi]
+    const bool staged = run_hi - run_lo + 1 <= REC_STAGE;             // (uniform)
+    if (staged)
+        for (int k = tid; k <= run_hi - run_lo; k += REC_BLOCK) L.stage[k] = starts(min(run_lo + k, N));
+    __syncthreads();
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const int64_t next = staged ? L.stage[mid + 1 - run_lo] : starts(mid + 1);
+        if (next > begin) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
+// Tables of granule g of a token axis holding N slots (starts(j), 0 <= j <= N; starts(N): its end);
 // usable = false leaves the granule empty.  desc(j, &ln, &so, &sh): the validated source of slot j.
 // found >= 0: the first slot whose successor starts after the granule's first token (else it is looked for here).
-template <typename Desc>
-__device__ __forceinline__ void build_record(int N, bool usable, const int64_t* starts, Desc desc, int64_t g,
+template <typename Starts, typename Desc>
+__device__ __forceinline__ void build_record(int N, bool usable, Starts starts, Desc desc, int64_t g,
                                              int32_t* first_out, GranRec* rec_out, int found = -1) {
     const int64_t begin = g * GATHER_GRAN;
     int first = N;
@@ -396,14 +443,14 @@ __device__ __forceinline__ void build_record(int N, bool usable, const int64_t* 
         if (found >= 0) lo = hi = found;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (starts[mid + 1] > begin) hi = mid; else lo = mid + 1;
+            if (starts(mid + 1) > begin) hi = mid; else lo = mid + 1;
         }
         // ... and if `begin` lies in the padding behind that slot (or the slot is empty), the next one
         while (lo < N) {
             int32_t ln, sh;
             int64_t so;
             desc(lo, &ln, &so, &sh);
-            if (starts[lo] + ln > begin) break;
+            if (starts(lo) + ln > begin) break;
             ++lo;
         }
         first = lo;
@@ -414,7 +461,7 @@ __device__ __forceinline__ void build_record(int N, bool usable, const int64_t* 
         rec.e[r].start = REL_FAR; rec.e[r].lensh = 0; rec.e[r].src_off = 0;
         const int j = first + r;
         if (j < N) {
-            const int64_t d = starts[j] - begin;
+            const int64_t d = starts(j) - begin;
             if (d < GATHER_GRAN) {
                 int32_t ln, sh;
                 int64_t so;
@@ -469,7 +516,7 @@ __device__ __forceinline__ void small_records(PlanLds& L, const PlanArgs& a, con
     if (tid == 0) R.start[N] = L.end;
     lds_barrier();
     for (int64_t g = tid; g < a.n_gran; g += PLAN_BLOCK)
-        build_record(N, true, R.start,
+        build_record(N, true, [&](int j) { return R.start[j]; },
                      [&](int j, int32_t* ln, int64_t* so, int32_t* sh) {
                          const int32_t ls = R.lensh[j];
                          *ln = ls & ((1 << LENSH_SHIFT) - 1); *sh = ls >> LENSH_SHIFT; *so = R.src_off[j];
