@@ -121,3 +121,27 @@ def test_gae_waves_and_tokens_per_lane(n, mean, kl):
     lens[1:: n // 3] = 1
     w = _with_ppo_fields(_custom(lens.astype(np.int32), 1, 1, 1 << 20, fields=()), seed=n)
     check_gae(w, 0.99, 0.95, kl, label=f"{n} sequences of {mean}")
+
+
+@pytest.mark.parametrize("n,group,n_src", [(16384, 8, 1), (16385, 1, 1), (16386, 2, 2), (20000, 5, 4), (16384, 64, 8), (16400, 82, 1)])
+@pytest.mark.parametrize("kind", ["geometric", "ones", "mixed"])
+def test_advantages_of_many_short_sequences(n, group, n_src, kind):
+    """Eight sequences to a wave: the last wave's remainder, sequences of one token and of more than its four steps, groups
+    larger than a wave's share, rollout shards that end inside a wave."""
+    rng = np.random.default_rng(n + group)
+    lens = np.minimum(rng.geometric(0.01, n), 900) if kind == "geometric" else np.ones(n, np.int64)
+    if kind == "mixed":
+        lens = rng.integers(1, 12, n)
+        lens[:: n // 40] = rng.integers(1000, 5000, len(lens[:: n // 40]))
+    w = _custom(lens.astype(np.int32), group, 1, 1 << 17, n_src=n_src, seed=n, fields=())
+    check_step(w, label=f"{n} sequences, groups of {group}, {kind}")
+
+
+def test_advantages_of_many_short_sequences_in_uneven_groups():
+    rng = np.random.default_rng(3)
+    n = 16384
+    w = _custom(np.minimum(rng.geometric(0.02, n), 500).astype(np.int32), 1, 1, 1 << 17, fields=())
+    cuts = np.unique(np.concatenate([[0, n], rng.integers(0, n, 700)])).astype(np.int32)
+    w.group_off = cuts
+    w.reward[cuts[5]:cuts[6]] = 0.25                     # rewards all alike: exactly +0
+    check_step(w, label="uneven groups")
