@@ -27,8 +27,8 @@ __device__ __forceinline__ bool packed_rounds_apply(int32_t N, int32_t P, int32_
 // Row length of a worker inside the LDS words that idx_a and idx_b span: odd, so that the rows start in different banks.
 __device__ __forceinline__ int portion_pitch(int P) { return (((DC_MAX_SEQ + PLACE_PAD) / P) - 1) | 1; }
 
-// rounds(n, items, rows, pitch): the assignment of n items by the whole workgroup; fills count_before[P] and
-// count[P] (items per worker before and after) and returns the items placed, in every thread.
+// rounds(n, items, rows, pitch, meanwhile): the assignment of n items by wave 0, while the other waves call meanwhile();
+// fills count_before[P] and count[P] (items per worker before and after) and returns the items placed, in every thread.
 template <typename Rounds>
 __device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P, int32_t C, const int32_t* count_before,
                                                 const int32_t* count, int32_t* __restrict__ shard_seq_off,
@@ -39,13 +39,31 @@ __device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P,
     uint32_t* const items = reinterpret_cast<uint32_t*>(L.keys);
     uint32_t* const rows = reinterpret_cast<uint32_t*>(L.idx_a);
     const int pitch = portion_pitch(P);
+    // (The threads that do not run the rounds fetch the next portion's lengths meanwhile; a portion that ends early, with a
+    // full row, is followed by another run of items and fetches them then.  The rows' stores drain behind LDS barriers.)
+    constexpr int FETCH = (DC_MAX_SEQ + BAL_BLOCK - WAVE - 1) / (BAL_BLOCK - WAVE);
+    int32_t fetched[FETCH];
+    auto fetch = [&](int from) {                                  // lane of the fetching threads: item from + q * (BAL_BLOCK - WAVE) + it
+#pragma unroll
+        for (int q = 0; q < FETCH; ++q) fetched[q] = ws.sorted_len[min(from + q * (BAL_BLOCK - WAVE) + tid - WAVE, N - 1)];
+    };
+    int have = -1;                                                // where the fetched items begin
     int c0 = 0;
     while (c0 < N) {                                              // (uniform)
         const int n = min(DC_MAX_SEQ, N - c0);
-        for (int t = tid; t < n + PLACE_PAD; t += BAL_BLOCK)      // length << 16 | index inside the portion; zeros behind
-            items[t] = t < n ? ((uint32_t)ws.sorted_len[c0 + t] << 16) | (uint32_t)t : 0u;
-        __syncthreads();
-        const int done = rounds(n, items, rows, pitch);
+        if (w != 0) {
+            if (have != c0) fetch(c0);                            // (uniform)
+#pragma unroll
+            for (int q = 0; q < FETCH; ++q) {                     // length << 16 | index inside the portion
+                const int t = q * (BAL_BLOCK - WAVE) + tid - WAVE;
+                if (t < n) items[t] = ((uint32_t)fetched[q] << 16) | (uint32_t)t;
+            }
+        } else {
+            for (int t = lane; t < PLACE_PAD; t += WAVE) items[n + t] = 0u;       // zeros behind
+        }
+        lds_barrier();
+        have = c0 + n;
+        const int done = rounds(n, items, rows, pitch, [&]() { if (have < N) fetch(have); });
         // empty the rows: worker k's items number count_before[k] .. count[k] - 1 stand in perm from k * C on
         for (int k = w; k < P; k += BAL_WAVES) {
             const int first = count_before[k], got = min(count[k] - first, pitch);
@@ -54,7 +72,7 @@ __device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P,
                 if (at < N) ws.place[at] = c0 + (int32_t)(rows[k * pitch + j] & 0xFFFFu);
             }
         }
-        __syncthreads();
+        lds_barrier();
         if (done <= 0) break;                                     // (cannot happen: an open worker always takes an item)
         c0 += done;
     }
@@ -72,14 +90,16 @@ __device__ __forceinline__ void packed_portions_few(BalLds& L, int32_t N, int32_
     int32_t* const placed = reinterpret_cast<int32_t*>(L.cnt) + PLACED_AT;
     PackedCarry carry = packed_fresh(P, C);
     packed_portions(L, N, P, C, count_before, worker_count, shard_seq_off, ws,
-                    [&](int n, const uint32_t* items, uint32_t* rows, int pitch) {
+                    [&](int n, const uint32_t* items, uint32_t* rows, int pitch, auto meanwhile) {
         if (w == 0) {
             count_before[lane] = carry.count;
             const int done = lpt_rounds_packed<WIDTH, true>(n, P, C, items, mx, rows, pitch, reinterpret_cast<uint32_t*>(L.spare),
                                                             worker_count, shard_load, &carry, pitch);
             if (lane == 0) *placed = done;
+        } else {
+            meanwhile();
         }
-        __syncthreads();
+        lds_barrier();
         return *placed;
     });
 }
@@ -98,21 +118,23 @@ __device__ __forceinline__ void packed_portions_many(BalLds& L, int32_t N, int32
     multi_fresh(m, P, C);
     if (tid < MULTI_MAX) count[tid] = 0;
     packed_portions(L, N, P, C, count_before, count, shard_seq_off, ws,
-                    [&](int n, const uint32_t* items, uint32_t* rows, int pitch) {
+                    [&](int n, const uint32_t* items, uint32_t* rows, int pitch, auto meanwhile) {
         if (tid < MULTI_MAX) {                                    // (a barrier stands between this and the rows' last use)
             const int32_t had = count[tid];
             count_before[tid] = had;
             m.cnt[tid] = 0;
             m.lim[tid] = C - had;
         }
-        __syncthreads();
+        lds_barrier();
         if (w == 0) {
             const int done = lpt_rounds_multi_any(n, P, items, rows, pitch, pitch, reinterpret_cast<uint32_t*>(L.spare), m, shard_load);
             if (tid == 0) *placed = done;
+        } else {
+            meanwhile();
         }
-        __syncthreads();
+        lds_barrier();
         if (tid < MULTI_MAX) count[tid] = count_before[tid] + m.cnt[tid];
-        __syncthreads();
+        lds_barrier();
         return *placed;
     });
 }
