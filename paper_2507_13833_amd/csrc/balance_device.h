@@ -604,7 +604,10 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
     return c;
 }
 
-template <int WIDTH, bool PORTION = false>
+// SKIP: rounds of one length are not sorted (mixed_rounds).  Not in the kernels where such rounds are rare and the code's
+// mere presence costs 0.4 to 3.7 us: up to 2048 sequences, and 64 workers up to DC_MAX_SEQ (a length would have to occur more
+// than 64 times among 16 384); nor where the sort is six steps (8 workers).
+template <int WIDTH, bool PORTION = false, bool SKIP = PORTION>
 __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint32_t* items, int32_t max_len,
                                                  uint32_t* rows, int pitch, uint32_t* spare_word,
                                                  int32_t* worker_count, int64_t* __restrict__ shard_load,
@@ -701,6 +704,33 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                 });
                 sk = v;
             };
+            // Sure rounds, all rows level, many of them of one length: such a round adds the same to every key, so there is
+            // nothing to sort.  The round's other work comes in front of the sort here instead of into its waits (a sorted
+            // round takes ~300 cycles on 32 lanes instead of 270), one that needs no sort ~100.  15 360 short answers on 24
+            // shards (51 % of the rounds), whole step: 164.5 -> 145 us; 65 536 sequences on 64 shards (33 %): 569 -> 530.
+            // With the side work in the sort's waits, the other rounds in a branch of their own and a loop over single
+            // rounds: 159 and 556.
+            auto mixed_rounds = [&](int n) {
+                for (int done = 0; done < n; done += WAVE) {
+                    const int m = min(n - done, WAVE);            // (a multiple of FAST_BATCH)
+                    const int at = min(pos + (done + (int)lane) * P, N - P);      // (lane i: the i-th round of these)
+                    uint64_t one_length = __ballot((items[at] ^ items[at + P - 1]) < 0x10000u);
+                    for (int r = rounds + done; r < rounds + done + m; r += FAST_BATCH, one_length >>= FAST_BATCH) {
+#pragma unroll
+                        for (int u = 0; u < FAST_BATCH; ++u) {
+                            const uint32_t e1 = *next_item;
+                            next_item += stride;
+                            uint32_t at_row = __umul24(sk & 63u, pitch4) + 4u * (uint32_t)(c_lo + r + u);
+                            if constexpr (!EVERY_LANE) at_row = offers ? at_row : spare_at;
+                            *reinterpret_cast<uint32_t*>(rows_b + at_row) = e;
+                            sk += len << 6;
+                            if (((uint32_t)one_length & (1u << u)) == 0u) sk = wave_sort_steps<WIDTH, 0, NS>(sk, [](auto) {});      // (uniform)
+                            e = e1;
+                            len = e1 >> 16;
+                        }
+                    }
+                }
+            };
             // One round with the exact test (every rank's key below the smallest updated key of the ranks before
             // it); false, and nothing changed but refused_acc, if it does not stand.  The row entry is written before
             // the outcome is known: a worker that does not take the item files its next one in the same place.
@@ -770,6 +800,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                 // How many batches does the bound cover?  It asks for L > max(D / 64, F / 2) (D in key units); lane i
                 // looks at the last item of the (i + 1)-th batch from here, and the items only get shorter.
                 int sure = 0;
+                bool mixed = false;
                 const int may = min(n_rounds - rounds, until_check) / FAST_BATCH;      // batches before the phase ends / the next check
                 if (may > 0 && --no_look < 0) {
                     const uint32_t k_lo = (uint32_t)__builtin_amdgcn_readlane((int)sk, 0);
@@ -783,9 +814,16 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                     // others, as after a very long sequence) the next look waits, longer every time
                     look_wait = sure > 0 ? 0 : min(2 * look_wait + 2, 32);
                     no_look = look_wait;
+                    // (a length that ends spoils one round, so fewer lengths than rounds leave rounds of one length)
+                    if constexpr (SKIP)
+                        mixed = level && sure > 1 &&
+                                first - (uint32_t)__builtin_amdgcn_readlane((int)probe, sure - 1) < (uint32_t)(sure * FAST_BATCH);
                 }
                 if (sure > 0) {
-                    if (level) {
+                    if (SKIP && __builtin_expect(mixed, 0)) {
+                        mixed_rounds(sure * FAST_BATCH);
+                        rounds += sure * FAST_BATCH;
+                    } else if (level) {
                         for (int b = 0; b < sure; ++b) {
 #pragma unroll
                             for (int u = 0; u < FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
@@ -1451,8 +1489,8 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             if constexpr (FEW) {
                 int32_t* worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;
                 if (P <= 8) lpt_rounds_packed<8>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-                else if (P <= 16) lpt_rounds_packed<16>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-                else if (P <= 32) lpt_rounds_packed<32>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                else if (P <= 16) lpt_rounds_packed<16, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                else if (P <= 32) lpt_rounds_packed<32, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else lpt_rounds_packed<64>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 if (lane < P) shard_seq_off[lane] = lane * C;     // (every partition ends with C items)
                 if (lane == 0) shard_seq_off[P] = N;

@@ -3,7 +3,8 @@
 import numpy as np
 import pytest
 
-from test_gpu_parity import _check_balance_ws, _custom, _with_ppo_fields, check_gae, check_gather_advantage, check_scatter, check_step
+import oracle
+from test_gpu_parity import _check_balance_ws, _custom, _gpu, _with_ppo_fields, check_gae, check_gather_advantage, check_scatter, check_step
 
 pytestmark = pytest.mark.gpu
 
@@ -145,3 +146,39 @@ def test_advantages_of_many_short_sequences_in_uneven_groups():
     w.group_off = cuts
     w.reward[cuts[5]:cuts[6]] = 0.25                     # rewards all alike: exactly +0
     check_step(w, label="uneven groups")
+
+
+def test_plan_of_many_slots_without_permutation_and_shard_table():
+    """dc_plan above DC_MAX_SEQ sequences that keeps the rollout shards: no notes to check, the shard
+    table made on the device."""
+    torch, binding, runner = _gpu()
+    lens = np.random.default_rng(5).integers(1, 60, 20000).astype(np.int32)
+    w = _custom(lens, 1, 4, 512, n_src=4, fields=())
+    d = runner.DeviceBatch(w, poison=True)
+    binding.dc_plan(d.prm, d.source, d.seq_len, None, None, d.capacity, d.dst_tok_off, d.shard_tok_off, d.shard_mb_off,
+                    d.mb_seq_off, d.cu_seqlens, d.n_mb, d.ws, d.ws_bytes, d.status)
+    torch.cuda.synchronize()
+    assert d.read_status() == 0
+    pl = oracle.plan(w.seq_len, np.arange(w.n_seq, dtype=np.int32), w.src_shard_seq_off, w.token_budget)
+    M = int(d.n_mb.item())
+    assert M == pl.n_mb
+    for got, want in ((d.dst_tok_off, pl.dst_tok_off), (d.shard_tok_off, pl.shard_tok_off), (d.shard_mb_off, pl.shard_mb_off),
+                      (d.mb_seq_off[:M + 1], pl.mb_seq_off), (d.cu_seqlens[:w.n_seq + M], pl.cu_seqlens)):
+        assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("shards", [3, 8, 9, 16, 17, 24, 31, 32, 64])
+@pytest.mark.parametrize("copies", [0.7, 1.5, 4.0, 70.0])
+def test_rounds_of_one_length(shards, copies):
+    """Lengths that occur `copies` times the number of shards each: rounds that need no sort, single ones and long runs of
+    them, up to the list's end; in one launch and in portions."""
+    rng = np.random.default_rng(int(10 * copies) + shards)
+    for n in (2049, 6000, 16384, 33000):
+        per = -(-n // shards) if n != 16384 else n // shards
+        n = per * shards
+        values = max(1, int(n / (copies * shards)))
+        lens = (40 + rng.integers(0, values, n)).astype(np.int32)
+        if n <= 16384:
+            check_step(_custom(lens, 1, shards, 8192, fields=()), two_calls=True, label=f"{n} on {shards} shards, {values} lengths")
+        else:
+            _check_balance_ws(lens, shards, label=f"{n} on {shards} shards, {values} lengths")
