@@ -27,7 +27,7 @@
  *   dc_gae              the advantage stage of PPO (Sec. 7.1 evaluates PPO with a critic).
  *   dc_balance_group_advantage, dc_balance_plan_group_advantage
  *                       the calls above that depend on nothing but the lengths and the rewards, issued
- *                       as one and as two launches (same results).
+ *                       as one and as one or two launches (same results).
  *   dc_repack_noalloc, dc_gather_timed
  *                       dc_repack without a workspace argument, for callers that cannot allocate;
  *                       dc_gather whose dispatch carries the caller's timing events.
@@ -209,7 +209,8 @@ dc_status dc_balance_group_advantage(const dc_params* prm, const dc_source* src,
  * With Algorithm 1 as printed (cap = 0 or cap * P = N) on up to 256 shards and up to DC_MAX_SEQ
  * sequences, the plan runs as the tail of the workgroup that balances: that workgroup holds every output
  * slot's sequence and length when it is done, which is all the plan reads.  Two launches instead of
- * five; dc_gather (or dc_gather_advantage) follows as after dc_plan.  Other shapes: the two calls one after
+ * five, and one for a batch of up to 2048 sequences and 2048 granules; dc_gather (or dc_gather_advantage)
+ * follows as after dc_plan.  Other shapes: the two calls one after
  * the other.
  */
 dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,

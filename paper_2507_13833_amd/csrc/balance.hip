@@ -1,10 +1,11 @@
 // Algorithm 1, Constrained LPT Load Balancing (Sec. 6 "Load Balancing").
 //
 // One workgroup, everything in LDS (N <= DC_MAX_SEQ, P <= DC_MAX_SHARDS):
-//   a) stable LSD radix sort of the sequence indices by descending length
-//      (8-bit digits of max_len - len, only as many passes as the length range
-//      needs; ranks inside a wave by ballot matching, across waves by a scan of
-//      per-wave digit counters);
+//   a) the sequence indices by descending length, equal lengths in index order: up to 2048
+//      sequences a bitonic network over the workgroup's registers, above that a counting pass over
+//      a bin per length or a stable LSD radix sort (8-bit digits of max_len - len, only as many
+//      passes as the length range needs; ranks inside a wave by ballot matching, across waves by a
+//      scan of per-wave digit counters);
 //   b) the assignment on wave 0, lane k = worker k, in ROUNDS instead of one item
 //      per step.  A lane holds its worker's item count and a 32-bit key
 //      (load - base) << 6 | k (all-ones-ish when the worker is full).  A round
@@ -19,10 +20,11 @@
 //      rebasing the keys when the minimum grows keeps them in 32 bits for any
 //      total load (the minimum grows by at most one longest sequence per round, so
 //      the check runs every so many rounds, not in each);
-//      With more than 64 workers the same rounds run on the whole workgroup, thread k = worker
-//      k, 64-bit keys load << 10 | k: every thread ranks its key by counting the smaller ones,
-//      the accepted prefix comes from a workgroup-wide min-scan, and keys travel between rank
-//      order and worker order through LDS;
+//      Up to 256 workers with N = P * C and lengths below 2^16 the wave keeps length and index of an
+//      item in one word and one, two or four keys to a lane (lpt_rounds_packed, lpt_rounds_multi);
+//      otherwise, with more than 64 workers, the same rounds run on the whole workgroup, thread k =
+//      worker k: the accepted prefix comes from a workgroup-wide min-scan, and keys travel between
+//      rank order and worker order through LDS;
 //   c) a worker that takes an item notes the item's place inside P_k (its item count before) and
 //      its own id (in LDS, where the item's length was); when all items are placed, a scan of the
 //      workers' counts gives the start of every P_k and one pass writes perm (P_0, P_1, ... each in

@@ -13,8 +13,10 @@
 //      totals -> dense prefix gpre[0..N] (int64, LDS);
 //   2. shard bases: exclusive scan of the shard loads, each rounded up to the alignment (a base is
 //      always a multiple of it, so rounding the running sum equals summing the rounded loads);
-//   3. micro-batch starts: one lane per shard hops from start to start, each hop a
-//      bisection for the last slot that still fits under the budget -> start bits;
+//   3. micro-batch starts -> start bits: a group of lanes per shard hops from start to start, probing a
+//      window of slots at once for the last one that still fits under the budget (above 64 shards one
+//      lane per shard, each hop a bisection); where the micro-batches are short, every slot's hop is
+//      found first, all slots side by side, and the walk only follows them;
 //   4. per 32 slots: starts before the word and the last start before it (two scans over
 //      512 words); then every slot reads its micro-batch index and start from those and
 //      writes its outputs.

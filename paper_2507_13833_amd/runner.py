@@ -162,8 +162,8 @@ class DeviceBatch:
                                           self.n_mb, self.ws, self.ws_bytes, self.status)
 
     def step_two_calls(self, gather_events=None, per_token: bool = True, dispatch_events=None) -> None:
-        """The whole pass as two calls: dc_balance_plan_group_advantage (balance, advantage stage and plan: two
-        launches where the shape allows it), then the gather.  gather_events: optional (start, end) torch events
+        """The whole pass as two calls: dc_balance_plan_group_advantage (balance, advantage stage and plan: one or
+        two launches where the shape allows it), then the gather.  gather_events: optional (start, end) torch events
         recorded around the gather launch; dispatch_events: optional (begins, ends) events carried by the gather
         kernel's dispatch itself (see gather)."""
         self.balance_plan_group_advantage(per_token)
