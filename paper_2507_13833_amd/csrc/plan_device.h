@@ -5,6 +5,7 @@
 #include "dc_device.h"
 #include "dc_internal.h"
 #include "dc_lanes.h"
+#include "plan_walk.h"
 
 namespace dc {
 
@@ -244,30 +245,11 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
             while (j < b) {                                  // uniform over the group
                 if (gl == 0) atomicOr(&L.start_bits[j >> 5], 1u << (j & 31));
                 const int64_t limit = L.gpre[j] + a.budget;
-                // the last e in (j, b] with gpre[e] <= limit (j + 1 if there is none: an over-budget slot still
-                // advances by one).  The first window probes G slots one by one, placed around the end that a micro-batch
-                // as long as the one before would have (slots of a shard come in descending length, so it holds a few
-                // more; the first one of a shard: the G slots behind the start).  Most micro-batches end inside it; if
-                // not, the group's lanes spread evenly over what is left on the side where the end lies, then over the
-                // stretch between the last probe that fits and the first that does not.
-                const int first = max(j + 1, j + sz + 1 - (G >> 2));
-                int lo, hi = b, e = j + 1;                   // candidates [lo, hi]; everything below lo fits
-                {
-                    const int c = first + gl;
-                    const bool fits = c <= b && L.gpre[min(c, b)] <= limit;
-                    const int cnt = __popcll((__ballot(fits) >> (g * G)) & group_mask);
-                    if (cnt == 0) { lo = j + 1; hi = first - 1; }            // it ends before the window (or with its first slot)
-                    else { e = first + cnt - 1; lo = (cnt == G && first + G <= b) ? first + G : b + 1; }     // b + 1: found
-                }
-                while (lo <= hi) {
-                    const int S = (hi - lo + G) >> lg_G;     // ceil(candidates / G) >= 1
-                    const bool fits = L.gpre[min(lo + (gl + 1) * S - 1, hi)] <= limit;
-                    const int cnt = __popcll((__ballot(fits) >> (g * G)) & group_mask);
-                    if (cnt > 0) e = min(lo + cnt * S - 1, hi);
-                    if (cnt == G) break;                     // the last lane's probe is hi itself
-                    hi = min(lo + (cnt + 1) * S - 1, hi) - 1;
-                    lo += cnt * S;
-                }
+                const int e = next_fit_end(G, lg_G, j, sz, b, [&](int c, int step, int last, bool inside) {
+                    c += gl * step;
+                    const bool fits = (!inside || c <= last) && L.gpre[min(c, last)] <= limit;
+                    return __popcll((__ballot(fits) >> (g * G)) & group_mask);
+                });
                 sz = e - j;
                 j = e;
             }

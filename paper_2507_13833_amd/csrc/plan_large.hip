@@ -89,8 +89,6 @@ __global__ __launch_bounds__(PL_TILE) void plan_large_prefix_kernel(PlanArgs a, 
 }
 
 // The micro-batches of n slots by next-fit, one wave; at(c): tokens of the shard before its slot c, 0 <= c <= n.
-// Each hop probes the 64 ends round the one that a micro-batch as long as the one before would have, then, where the end
-// lies outside, 64 places spread over what is left.
 template <typename At>
 __device__ __forceinline__ void walk_shard(const PlanArgs& a, int first_slot, int n, At at) {
     const int lane = threadIdx.x;
@@ -98,22 +96,10 @@ __device__ __forceinline__ void walk_shard(const PlanArgs& a, int first_slot, in
     while (j < n) {                                       // (uniform)
         if (lane == 0) atomicOr(&a.start_bits[(first_slot + j) >> 5], (int32_t)(1u << ((first_slot + j) & 31)));
         const int64_t limit = at(j) + a.budget;
-        const int first = max(j + 1, j + sz + 1 - WAVE / 4);
-        int lo, hi = n, e = j + 1;                        // the last e in (j, n] with at(e) <= limit, or j + 1
-        {
-            const int c = first + lane;
-            const int cnt = __popcll(__ballot(c <= n && at(min(c, n)) <= limit));
-            if (cnt == 0) { lo = j + 1; hi = first - 1; }
-            else { e = first + cnt - 1; lo = (cnt == WAVE && first + WAVE <= n) ? first + WAVE : n + 1; }
-        }
-        while (lo <= hi) {
-            const int S = (hi - lo + WAVE) / WAVE;        // ceil(candidates / 64) >= 1
-            const int cnt = __popcll(__ballot(at(min(lo + (lane + 1) * S - 1, hi)) <= limit));
-            if (cnt > 0) e = min(lo + cnt * S - 1, hi);
-            if (cnt == WAVE) break;
-            hi = min(lo + (cnt + 1) * S - 1, hi) - 1;
-            lo += cnt * S;
-        }
+        const int e = next_fit_end(WAVE, 6, j, sz, n, [&](int c, int step, int last, bool inside) {
+            c += lane * step;
+            return (int)__popcll(__ballot((!inside || c <= last) && at(min(c, last)) <= limit));
+        });
         sz = e - j;
         j = e;
     }

@@ -182,3 +182,42 @@ def test_rounds_of_one_length(shards, copies):
             check_step(_custom(lens, 1, shards, 8192, fields=()), two_calls=True, label=f"{n} on {shards} shards, {values} lengths")
         else:
             _check_balance_ws(lens, shards, label=f"{n} on {shards} shards, {values} lengths")
+
+
+def _plan_alone(lens, shards, budget, align=1, perm=None, n_src=1):
+    """dc_plan as a call of its own, d_perm null unless given, every output against the oracle; shards: number of slots of each."""
+    torch, binding, runner = _gpu()
+    w = _custom(np.asarray(lens, np.int32), 1, len(shards), budget, n_src=n_src, fields=())
+    d = runner.DeviceBatch(w, align_tokens=align, cap=w.n_seq, poison=True)
+    off = np.concatenate([[0], np.cumsum(shards)]).astype(np.int32)
+    assert off[-1] == w.n_seq
+    d.shard_seq_off = torch.from_numpy(off).to(d.dev)
+    d_perm = None if perm is None else torch.from_numpy(perm.astype(np.int32)).to(d.dev)
+    binding.dc_plan(d.prm, d.source, d.seq_len, d_perm, d.shard_seq_off, d.capacity, d.dst_tok_off, d.shard_tok_off, d.shard_mb_off,
+                    d.mb_seq_off, d.cu_seqlens, d.n_mb, d.ws, d.ws_bytes, d.status)
+    torch.cuda.synchronize()
+    assert d.read_status() == 0
+    pl = oracle.plan(w.seq_len, np.arange(w.n_seq, dtype=np.int32) if perm is None else perm.astype(np.int32), off, budget, align)
+    M = int(d.n_mb.item())
+    assert M == pl.n_mb
+    for got, want in ((d.dst_tok_off, pl.dst_tok_off), (d.shard_tok_off, pl.shard_tok_off), (d.shard_mb_off, pl.shard_mb_off),
+                      (d.mb_seq_off[:M + 1], pl.mb_seq_off), (d.cu_seqlens[:w.n_seq + M], pl.cu_seqlens)):
+        assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("slots,n_shards", [(150, 1), (300, 4), (150, 17), (150, 64), (9000, 1), (1000, 16), (256, 64), (150, 70), (16384, 1),
+                                            (20000, 1), (16000, 2), (600, 64), (27000, 3), (33000, 1), (40000, 2), (300, 200)])
+def test_micro_batches_where_long_sequences_come_last(slots, n_shards):
+    """Slots in ascending length (a caller's order; the balance leaves them descending): behind a micro-batch of many short
+    ones fewer slots are left than it held, and they do not fit.  Few shards and many, one that is walked in the LDS and one
+    (32 768 slots and more) in global memory, the last one of a batch among them, without a permutation and with one."""
+    longer = min(slots // 3, 200)
+    budget = slots - longer                              # all the short ones in one micro-batch, then two at a time
+    shard = np.concatenate([np.full(budget, 1), np.full(longer, budget // 2)])
+    lens = np.tile(shard, n_shards)
+    _plan_alone(lens, [slots] * n_shards, budget)
+    _plan_alone(lens, [slots] * n_shards, budget, align=24)
+    perm = np.random.default_rng(slots).permutation(len(lens))
+    back = np.empty_like(lens)
+    back[perm] = lens                                    # the same lengths in slot order
+    _plan_alone(back, [slots] * n_shards, budget, perm=perm)
