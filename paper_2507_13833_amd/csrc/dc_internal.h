@@ -45,7 +45,7 @@ struct Workspace {
     GranRec* gran_rec;       // [n_gran]
     int32_t* plan_ok;        // [1] 0 if the plan kernel found the shard table unusable and planned nothing
     int32_t* own_shard_off;  // [DC_MAX_SRC_SHARDS + 1] the rollout shards' sequence offsets, for a plan that keeps them
-    int64_t* gpre;           // [N + 1]  } only above DC_MAX_SEQ slots (else null): dense prefix of the slot lengths,
+    int64_t* gpre;           // [N + 1]  } only above DC_MAX_SEQ slots (else null): prefix of the slot lengths inside every tile of slots,
     int32_t* start_bits;     // [N / 32 + 2] slots that open a micro-batch, one bit each,
     int64_t* tile_tokens;    // [N / 64 + 1] tokens of every tile of slots
     int64_t  n_gran;         // ceil(capacity / GATHER_GRAN) + GRAN_TABLE_PAD; entries past the arena hold N / no slot

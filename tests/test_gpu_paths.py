@@ -221,3 +221,70 @@ def test_micro_batches_where_long_sequences_come_last(slots, n_shards):
     back = np.empty_like(lens)
     back[perm] = lens                                    # the same lengths in slot order
     _plan_alone(back, [slots] * n_shards, budget, perm=perm)
+
+
+def _plan_of(lens, shards, budget, align):
+    """The plan of slots of these lengths (0: an empty slot), straight from the header's text."""
+    tok, stok, smb, mb, cu, base = [], [], [], [], [], 0
+    j = 0
+    for n in shards:
+        stok.append(base); smb.append(len(mb))
+        at = base
+        used = None
+        for ln in lens[j:j + n]:
+            if used is None or used + ln > budget:
+                if used is not None:
+                    cu.append(used)
+                mb.append(len(tok)); used = 0
+            cu.append(used); tok.append(at)
+            at += ln; used += ln
+        if used is not None:
+            cu.append(used)
+        base += -(-(at - base) // align) * align
+        j += n
+    return dict(tok=tok + [base], stok=stok + [base], smb=smb + [len(mb)], mb=mb + [len(tok)], cu=cu)
+
+
+@pytest.mark.parametrize("n,shards,align", [(1000, 8, 1), (1000, 8, 16), (16384, 16, 1), (16640, 16, 1), (20480, 16, 16), (66048, 129, 1)])
+def test_a_repeat_in_perm_moves_nothing(n, shards, align):
+    """Of the slots that name one sequence all but one (any) are empty: they take no room in the layout and move nothing, up
+    to DC_MAX_SEQ slots and above.  The second call finds the first one's words in its buffers."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    w = _custom(rng.integers(20, 200, n).astype(np.int32), 4, shards, 1024, n_src=2, fields=("i32",))
+    d = runner.DeviceBatch(w, align_tokens=align, poison=True)
+    d.balance(); torch.cuda.synchronize()
+    perm = d.perm.cpu().numpy().copy()
+    a, b, c = n - 2, n // 2 + 1, 5
+    perm[a] = perm[b]                                    # one sequence twice, far apart; one three times, side by side
+    perm[c + 1] = perm[c + 2] = perm[c]
+    d.perm.copy_(torch.from_numpy(perm))
+    off = np.concatenate([[0], np.cumsum(w.src_shard_tokens)])
+    side = np.searchsorted(w.src_shard_seq_off, np.arange(n), side="right") - 1
+    source = np.concatenate(w.fields[0].shards)
+    for call in range(2):
+        d.plan(); d.gather(); torch.cuda.synchronize()
+        assert d.read_status() == binding.DC_ERR_BAD_LAYOUT
+        d.status.zero_()
+        M = int(d.n_mb.item())
+        got = dict(tok=d.dst_tok_off, stok=d.shard_tok_off, smb=d.shard_mb_off, mb=d.mb_seq_off[:M + 1], cu=d.cu_seqlens[:n + M])
+        got = {k: v.cpu().numpy() for k, v in got.items()}
+        lens = w.seq_len[perm].astype(np.int64)
+        fits = []
+        for keep2 in (a, b):
+            for keep3 in (c, c + 1, c + 2):
+                x = lens.copy()
+                x[[k for k in (a, b, c, c + 1, c + 2) if k not in (keep2, keep3)]] = 0
+                want = _plan_of(x.tolist(), [n // shards] * shards, 1024, align)
+                if all(np.array_equal(got[k], want[k]) for k in want):
+                    fits.append(x)
+        assert len(fits) == 1, (n, call)
+        x = fits[0]
+        arena = np.full(d.capacity, 0x5A5A5A5A, np.int32)
+        for j in range(n):
+            i = perm[j]
+            at = off[side[i]] + w.src_tok_off[i]
+            arena[got["tok"][j]:got["tok"][j] + x[j]] = source[at:at + x[j]]
+        name = w.fields[0].name
+        assert np.array_equal(d.dst_fields[name].cpu().numpy(), arena), (n, call)
+        d.dst_fields[name].fill_(0x5A5A5A5A)
