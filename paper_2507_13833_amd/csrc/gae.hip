@@ -6,16 +6,16 @@
 // With t_1 < ... < t_m the loss-bearing tokens of a sequence:
 //   delta_k = r_k + gamma V[t_{k+1}] - V[t_k]   (V[t_{m+1}] = 0; r_k = KL penalty, plus the score on t_m)
 //   A_k     = delta_k + gamma lambda A_{k+1},   ret_k = A_k + V[t_k]
-// a first-order linear recurrence running backwards in time.  A workgroup of NW wavefronts shares
-// one sequence and walks it from the end; per iteration a wave takes 64 * T tokens, a lane T = 8
-// consecutive ones (two aligned 16-byte groups of the value array; short sequences: 4, one
-// group), lane 0 of wave 0 the latest.  Inside an iteration
+// a first-order linear recurrence running backwards in time.  NW wavefronts share
+// one sequence and walk it from the end; per iteration a wave takes 64 * T tokens, a lane T = 8
+// or 4 consecutive ones (two aligned 16-byte groups of the value array or one; NW and T by the
+// batch, see launch_gae), lane 0 of wave 0 the latest.  Inside an iteration
 //   * "gamma V of the next loss-bearing token" is a copy from the nearest earlier lane (or wave)
 //     that holds one, not arithmetic;
 //   * each lane folds its tokens into one affine map A_after = P A_in + B, the lanes' maps are
 //     composed by a 6-step DPP scan, the waves' maps through LDS, and each lane then replays its
 //     tokens from the state entering it;
-//   * a wave whose 512 tokens all bear loss (the inside of a response) never looks at a mask
+//   * a wave whose tokens all bear loss (the inside of a response) never looks at a mask
 //     again; a wave without any loss-bearing token (a prompt) only writes zeros;
 //   * the outputs leave through a transpose in LDS, so that a store instruction writes 64
 //     consecutive 16-byte chunks (a lane's own 8 tokens are 32 bytes: two instructions that
@@ -26,7 +26,8 @@
 // Measured rationale: one wave per sequence left the longest sequence (36 K tokens, 141 dependent
 // blocks) running alone for 160 us; with two or four waves it is still 36 or 18 dependent iterations, which
 // run on alone when the sequence's workgroup starts late, so the first workgroups of the grid
-// look for long sequences and start those; anything derived from a loaded mask word at load time makes
+// look for long sequences and start those (with all their waves, where the batch's other sequences get
+// a wave each); anything derived from a loaded mask word at load time makes
 // the wave wait for the loads it has just issued (the prefetch ring keeps the raw words);
 // plain loads with streaming stores beat both all-plain and all-streaming accesses (every line
 // of the value array is touched by two load instructions, 32 bytes apart per lane).
@@ -40,7 +41,7 @@ namespace dc {
 struct GaeArgs {
     int32_t        n_seq, use_kl;
     double         gamma, decay, kl_coef;            // decay = gamma * lambda
-    int32_t        n_early, long_len;                // workgroups that start long sequences early; what counts as long
+    int32_t        n_sets, long_len;                 // sets among which long sequences are looked for; what counts as long
     const int64_t* src_tok_off;
     const int32_t* seq_len;
     const float*   reward;
@@ -139,73 +140,75 @@ __device__ __forceinline__ double readlane_f64(double v, int src) {
     return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
 }
 
-constexpr int GAE_SET = 32;                  // sequences among which one may be started early
+constexpr int GAE_SET = 32, GAE_MANY_SET = 64;        // sequences of a set, at most
 __device__ __forceinline__ bool gae_is_long(int32_t ln, int32_t long_len) { return ln >= long_len && ln <= DC_MAX_SEQ_LEN; }
-// The longest long sequence among set, set + n_early, set + 2 n_early, ... (GAE_SET of them; ties: the lowest
-// index), or -1; every wave that asks gets the same answer.
-__device__ __forceinline__ int gae_longest_of_set(const GaeArgs& a, int set, int lane) {
-    const int k = lane & (GAE_SET - 1);
-    const int64_t idx = (int64_t)set + (int64_t)k * a.n_early;
+// The longest long sequence of a set whose key lies below `below` (its own key goes there), or -1; every wave that asks gets
+// the same answer.  Set s of a.n_sets: sequences s, s + n_sets, s + 2 n_sets, ... (up to SET of them, neighbours in different
+// sets).  Key: the length, then the lower index.
+template <int SET>
+__device__ __forceinline__ int gae_longest_of_set(const GaeArgs& a, int set, int lane, int32_t& below) {
+    const int k = lane & (SET - 1);
+    const int64_t idx = (int64_t)set + (int64_t)k * a.n_sets;
     int32_t ln = 0;
     if (idx < a.n_seq) ln = a.seq_len[idx];
-    long long key = gae_is_long(ln, a.long_len) ? (((long long)ln << 8) | (long long)(GAE_SET - 1 - k)) : -1ll;
+    static_assert((int64_t)DC_MAX_SEQ_LEN * SET + SET <= INT32_MAX && SET <= WAVE, "the key fits 32 bits");
+    int32_t key = gae_is_long(ln, a.long_len) ? ln * SET + (SET - 1 - k) : -1;
+    if (key >= below) key = -1;
 #pragma unroll
-    for (int d = GAE_SET / 2; d >= 1; d >>= 1) {
-        const long long o = __shfl_xor(key, d, WAVE);
-        key = o > key ? o : key;
-    }
-    return key < 0 ? -1 : set + (GAE_SET - 1 - (int)(key & 0xFF)) * a.n_early;
+    for (int d = SET / 2; d >= 1; d >>= 1) key = max(key, __shfl_xor(key, d, WAVE));
+    below = __builtin_amdgcn_readfirstlane(key);
+    return below < 0 ? -1 : set + (SET - 1 - (below & (SET - 1))) * a.n_sets;
 }
 
-// One workgroup of NW waves per sequence, T tokens to a lane, the loads of AHEAD iterations in flight ahead of the one
-// worked on.  An iteration covers NW * 64 * T tokens, wave 0 the latest 64 * T of them, lane 0 of a wave its latest T.
-// The waves exchange two things through LDS (one wave: nothing):
+// What the NW waves of a sequence exchange through LDS (one wave: nothing):
 // gamma * V of each wave's earliest loss-bearing token (a later wave's first loss-bearing token
 // needs it), and each wave's composed map, from which every wave derives the state entering its
 // tokens and the state carried to the next iteration.  Two barriers per iteration; every wave
-// of the workgroup runs the same number of iterations (a wave whose lanes all lie before the
+// of a sequence runs the same number of iterations (a wave whose lanes all lie before the
 // sequence's start just takes part in the barriers).
+template <int NW>
+struct GaeLds {
+    double  u[NW], P[NW], B[NW];
+    int32_t has[NW];
+};
+// A wave's outputs on their way out (8 tokens to a lane).
+template <int T>
+struct alignas(16) GaeStage { float x[T == 8 ? 2 * WAVE * T : 4]; };
+
+// What a sequence is, asked for at once: one trip to memory.
+struct GaeSeq {
+    int32_t ln;
+    int64_t so, next;
+    float   score;
+};
+__device__ __forceinline__ GaeSeq gae_fetch(const GaeArgs& a, int i) {
+    GaeSeq q;
+    q.ln = a.seq_len[i];
+    q.so = a.src_tok_off[i];
+    q.next = a.src_tok_off[min(i + 1, a.n_seq - 1)];
+    q.score = a.reward[i];
+    return q;
+}
+
+// Sequence i by NW waves, the workgroup's only ones if there is more than one, of which this is number w (uniform): T tokens
+// to a lane, the loads of AHEAD iterations in flight ahead of the one worked on.  An iteration covers NW * 64 * T tokens,
+// wave 0 the latest 64 * T of them, lane 0 of a wave its latest T.
 template <int NW, bool KL, int T, int AHEAD>
-__global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd) {
-    __shared__ double s_u[NW], s_P[NW], s_B[NW];
-    __shared__ int32_t s_has[NW];
-    __shared__ __attribute__((aligned(16))) float s_stage[NW][T == 8 ? 2 * WAVE * T : 4];   // a wave's outputs on their way out
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-    // One workgroup per sequence, in index order, behind n_early workgroups that each start the longest
-    // sequence of a set of GAE_SET (every n_early-th sequence from their own index on) if it is a long one:
-    // a 36 K-token sequence is 36 dependent iterations, and started late it runs on alone after the rest.
-    int i = (int)blockIdx.x - a.n_early;
-    const bool early = i < 0;
-    // (all the sequence's words are asked for at once: one trip to memory)
-    int32_t ln = 0;
-    int64_t so = 0, next = 0;
-    float score = 0.0f;
-    auto fetch = [&]() {
-        ln = a.seq_len[i];
-        so = a.src_tok_off[i];
-        next = a.src_tok_off[min(i + 1, a.n_seq - 1)];
-        score = a.reward[i];
-    };
-    if (!early) fetch();
-    if (early || gae_is_long(ln, a.long_len)) {                    // uniform over the workgroup
-        const int set = early ? (int)blockIdx.x : i % a.n_early;
-        const int longest = gae_longest_of_set(a, set, lane);
-        if (early ? longest < 0 : longest == i) return;            // nothing to start early / started early
-        if (early) {
-            i = __builtin_amdgcn_readfirstlane(longest);
-            fetch();
-        }
-    }
+__device__ __forceinline__ void gae_sequence(const GaeArgs& a, const SourceDesc& sd, GaeLds<NW>* x, GaeStage<T>& stage, int i,
+                                             const GaeSeq& me, int w, int lane) {
+    constexpr int UNR = NW > 4 ? 1 : NW;                           // (unrolled over 8 waves it would cost 25 registers)
+    const int32_t ln = me.ln;
+    const int64_t so = me.so, next = me.next;
+    const float score = me.score;
     int s = 0;                                                     // (seq_off[k] = N from k = n_src on)
 #pragma unroll
     for (int k = 1; k < DC_MAX_SRC_SHARDS; ++k) s += i >= sd.seq_off[k] ? 1 : 0;
-    if (ln <= 0 || ln > DC_MAX_SEQ_LEN) {                          // uniform over the workgroup
-        if (threadIdx.x == 0) set_status(a.status, DC_ERR_ZERO_LENGTH_SEQ);
+    if (ln <= 0 || ln > DC_MAX_SEQ_LEN) {                          // uniform over the waves
+        if (w == 0 && lane == 0) set_status(a.status, DC_ERR_ZERO_LENGTH_SEQ);
         return;
     }
     if (so < 0 || so + ln > sd.tokens[s] || (i + 1 < sd.seq_off[s + 1] && next < so + ln)) {
-        if (threadIdx.x == 0) set_status(a.status, DC_ERR_BAD_LAYOUT);   // outside its buffer or overlapping the next
+        if (w == 0 && lane == 0) set_status(a.status, DC_ERR_BAD_LAYOUT);   // outside its buffer or overlapping the next
         return;
     }
     const float* __restrict__ V = a.value[s];
@@ -270,12 +273,12 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
         if constexpr (NW == 1) {
             if (any) U_next = U_wave;
         } else {
-            if (lane == 0) { s_has[w] = any ? 1 : 0; s_u[w] = U_wave; }
+            if (lane == 0) { x->has[w] = any ? 1 : 0; x->u[w] = U_wave; }
             lds_barrier();
-#pragma unroll
+#pragma unroll UNR
             for (int k = 0; k < NW; ++k) {
-                const bool h = s_has[k] != 0;
-                const double u = s_u[k];
+                const bool h = x->has[k] != 0;
+                const double u = x->u[k];
                 if (h && k < w) U_w = u;
                 if (h) U_next = u;
             }
@@ -326,11 +329,11 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
         if constexpr (NW == 1) {
             A_next = __builtin_fma(readlane_f64(Pi, WAVE - 1), A_next, readlane_f64(Bi, WAVE - 1));
         } else {
-            if (lane == WAVE - 1) { s_P[w] = Pi; s_B[w] = Bi; }   // the wave's whole map (identity without loss)
+            if (lane == WAVE - 1) { x->P[w] = Pi; x->B[w] = Bi; }   // the wave's whole map (identity without loss)
             lds_barrier();
-#pragma unroll
+#pragma unroll UNR
             for (int k = 0; k < NW; ++k) {
-                const double Pk = s_P[k], Bk = s_B[k];
+                const double Pk = x->P[k], Bk = x->B[k];
                 if (k == w) A_w = A_next;
                 A_next = __builtin_fma(Pk, A_next, Bk);
             }
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
                 vr.x = orr[0]; vr.y = orr[1]; vr.z = orr[2]; vr.w = orr[3];
                 store4(q * T, va, vr);
             } else {
-                float* st_a = s_stage[w];
+                float* st_a = stage.x;
                 float* st_r = st_a + WAVE * T;
                 const int mine = (WAVE - 1 - lane) * T;
                 f32x4 o;
@@ -407,6 +410,59 @@ __global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd
     }
 }
 
+// One workgroup of NW waves per sequence, in index order, behind n_sets workgroups that each start the longest sequence of
+// a set if it is a long one: a 36 K-token sequence is 36 dependent iterations, and started late it runs on alone after
+// the rest.
+template <int NW, bool KL, int T, int AHEAD>
+__global__ __launch_bounds__(NW * WAVE) void gae_kernel(GaeArgs a, SourceDesc sd) {
+    __shared__ GaeLds<NW> x;
+    __shared__ GaeStage<T> stage[NW];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    int i = (int)blockIdx.x - a.n_sets;
+    const bool early = i < 0;
+    GaeSeq me = {0, 0, 0, 0.0f};
+    if (!early) me = gae_fetch(a, i);
+    if (early || gae_is_long(me.ln, a.long_len)) {                 // uniform over the workgroup
+        int32_t below = INT32_MAX;
+        const int longest = gae_longest_of_set<GAE_SET>(a, early ? (int)blockIdx.x : i % a.n_sets, lane, below);
+        if (early ? longest < 0 : longest == i) return;            // nothing to start early / started early
+        if (early) {
+            i = longest;
+            me = gae_fetch(a, i);
+        }
+    }
+    gae_sequence<NW, KL, T, AHEAD>(a, sd, &x, stage[w], i, me, w, lane);
+}
+
+// One WAVE per sequence, W of them to a workgroup, behind GAE_SHARE * n_sets workgroups that take the long sequences with all
+// W waves (alone a wave would be at a 32 K-token sequence for 128 iterations, each waiting for its loads): the r-th
+// workgroup of a set takes its r-th longest, (r + GAE_SHARE)-th, ...  The sets' first workgroups come first.
+constexpr int GAE_SHARE = 4;
+template <int W, bool KL, int T, int AHEAD>
+__global__ __launch_bounds__(W * WAVE, T == 4 ? 8 : 4) void gae_many_kernel(GaeArgs a, SourceDesc sd) {
+    __shared__ GaeLds<W> x;
+    __shared__ GaeStage<T> stage[W];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int n_early = a.n_sets * GAE_SHARE;
+    if ((int)blockIdx.x < n_early) {                               // (uniform)
+        const int r = (int)blockIdx.x / a.n_sets, set = (int)blockIdx.x - r * a.n_sets;
+        int32_t below = INT32_MAX;
+        for (int skip = r;; skip = GAE_SHARE - 1) {
+            int i = gae_longest_of_set<GAE_MANY_SET>(a, set, lane, below);
+            for (int q = 0; q < skip && i >= 0; ++q) i = gae_longest_of_set<GAE_MANY_SET>(a, set, lane, below);
+            if (i < 0) return;
+            gae_sequence<W, KL, T, AHEAD>(a, sd, &x, stage[w], i, gae_fetch(a, i), w, lane);
+        }
+    }
+    const int i = ((int)blockIdx.x - n_early) * W + w;
+    if (i >= a.n_seq) return;
+    const GaeSeq me = gae_fetch(a, i);
+    if (gae_is_long(me.ln, a.long_len)) return;                    // its set's workgroups do it
+    gae_sequence<1, KL, T, 0>(a, sd, nullptr, stage[w], i, me, 0, lane);
+}
+
 hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src_tok_off, const int32_t* d_seq_len,
                       const float* d_reward, const float* const* value_base, const uint8_t* const* mask_base,
                       const float* const* logp_base, const float* const* ref_base, double gamma, double lambda,
@@ -420,7 +476,6 @@ hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src
     int64_t tokens = 0;
     for (int s = 0; s < src.n_src; ++s) tokens += src.tokens[s];
     const int64_t mean = tokens / n_seq;                           // (the buffers' sizes bound the lengths' sum)
-    a.n_early = (n_seq + GAE_SET - 1) / GAE_SET;
     for (int s = 0; s < DC_MAX_SRC_SHARDS; ++s) {
         const bool on = s < src.n_src;
         a.value[s] = on ? value_base[s] : nullptr;
@@ -430,31 +485,58 @@ hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src
         a.adv[s] = on ? adv_base[s] : nullptr;
         a.ret[s] = on ? ret_base[s] : nullptr;
     }
-    auto launch = [&](auto nw, auto t, auto ahead) {
-        constexpr int NW = decltype(nw)::value, T = decltype(t)::value, AHEAD = decltype(ahead)::value;
-        // long: at least twice the mean and at least 4 iterations
-        a.long_len = (int32_t)std::min<int64_t>(std::max<int64_t>(2 * mean, 4 * NW * WAVE * T), INT32_MAX);
-        const dim3 grid((unsigned)(n_seq + a.n_early)), block(NW * WAVE);
-        if (a.use_kl) hipLaunchKernelGGL((gae_kernel<NW, true, T, AHEAD>), grid, block, 0, st, a, src);
-        else hipLaunchKernelGGL((gae_kernel<NW, false, T, AHEAD>), grid, block, 0, st, a, src);
-    };
-    // Waves per sequence and tokens per lane, by what the chip holds at once and how long a sequence is (us before, with
-    // two waves of 8 tokens and two iterations ahead for every batch, and now; no KL penalty where not said):
-    //   up to 1024 sequences, and up to 4096 long ones: four waves of 8 tokens; the longest sequence's iterations are the
-    //   time (1024 of 1512 tokens 15.4 -> 12.5, of 4033 with KL 35.0 -> 28.1; 2048 of 4021 41.2 -> 33.0);
-    //   up to 2048: two waves of 8, or four of 4 above 1024 tokens (2048 of 1597 16.9 -> 16.5), all resident at once;
-    //   more: a wave that holds few tokens for its registers and its trips to memory is the time, so one wave of 4 tokens
-    //   to a lane up to 384 tokens (16 384 of 249 39.6 -> 19.5; four waves per SIMD become eight), two up to 1280 (16 384
-    //   of 697 48.4 -> 33.6, of 996 55.1 -> 43.7), four beyond (16 384 of 2594 with KL 171.2 -> 168; two of 8 are level).
     using std::integral_constant;
+    // (many: gae_many_kernel with that many waves to a workgroup)
+    auto launch = [&](auto kl, auto many, auto nw, auto t, auto ahead) {
+        constexpr bool KL = decltype(kl)::value, MANY = decltype(many)::value;
+        constexpr int NW = decltype(nw)::value, T = decltype(t)::value, AHEAD = decltype(ahead)::value;
+        // long: at least twice the mean and 4 iterations; where a wave has a sequence to itself, four times and 8 iterations
+        const int64_t long_len = MANY ? std::max<int64_t>(4 * mean, 8 * WAVE * T) : std::max<int64_t>(2 * mean, 4 * NW * WAVE * T);
+        a.long_len = (int32_t)std::min<int64_t>(long_len, INT32_MAX);
+        if constexpr (MANY) {
+            a.n_sets = (n_seq + GAE_MANY_SET - 1) / GAE_MANY_SET;
+            const dim3 grid((unsigned)(GAE_SHARE * a.n_sets + (n_seq + NW - 1) / NW)), block(NW * WAVE);
+            hipLaunchKernelGGL((gae_many_kernel<NW, KL, T, AHEAD>), grid, block, 0, st, a, src);
+        } else {
+            a.n_sets = (n_seq + GAE_SET - 1) / GAE_SET;
+            const dim3 grid((unsigned)(n_seq + a.n_sets)), block(NW * WAVE);
+            hipLaunchKernelGGL((gae_kernel<NW, KL, T, AHEAD>), grid, block, 0, st, a, src);
+        }
+    };
+    // Waves per sequence and tokens per lane, by what the chip holds at once and how long a sequence is (us with two waves of
+    // 8 tokens and two iterations ahead for every batch, and so; "+ 1": with one of 32 K tokens among them; KL: with the
+    // penalty, whose loads and registers make a wave of its own per sequence pay up to a smaller mean):
+    //   up to 1024 sequences, and up to 4096 long ones: four waves of 8, one ahead: the longest sequence's iterations are the
+    //   time (1000 of 1499 18.6 -> 13.3, + 1 54 -> 32; 3000 of 2599 KL 39.0 -> 36.4, + 1 61 -> 42);
+    //   up to 2048: two waves of 8, two ahead, or four of 4 above 1024 tokens (2000 of 1499 18.7 -> 16.7);
+    //   more: a wave that holds few tokens for its registers and its trips to memory is the time.
+    //     Short sequences, one wave of 4 each, eight to a workgroup (4096 of 299 14.1 -> 12.2, + 1 54 -> 41; 16 384 of 299
+    //     39.7 -> 23.9, + 1 55 -> 44; of 699 52.8 -> 38.7; KL 67.7 -> 50.5; 32 768 of 849 102 -> 78).  Where the lines lie, in
+    //     us against four waves of 4: 4096 of 299 11.5 / 13.3, of 499 13.1 / 14.2, of 699 17.5 / 16.1; 8192 of 699 25.0 / 27.4,
+    //     of 999 33.2 / 31.4; 16 384 of 849 44 / 50, KL of 599 44.6 / 48.4, of 849 60.3 / 56.0.
+    //     Then four waves of 4 (8192 of 1249 39.3 -> 37.3; 16 384 of 1249 KL 95 -> 79, + 1 95 -> 79; of 3499 167 -> 161; from
+    //     2048 tokens on with KL one ahead, 16 384 of 2599 188 -> 184, of 3499 245 / 241 without and with it), or, without
+    //     KL above 8192 sequences, two waves of 8 without a ring (16 384 of 1599 73 -> 66, four of 4 70; of 2599
+    //     108 -> 96, four of 4 107; of 3499 163, four of 4 161).
     constexpr integral_constant<int, 0> c0; constexpr integral_constant<int, 1> c1; constexpr integral_constant<int, 2> c2;
     constexpr integral_constant<int, 4> c4; constexpr integral_constant<int, 8> c8;
-    if (n_seq <= 1024 || (n_seq <= 4096 && mean > 2048)) launch(c4, c8, c1);
-    else if (n_seq <= 2048 && mean <= 1024) launch(c2, c8, c2);
-    else if (n_seq <= 2048) launch(c4, c4, c0);
-    else if (mean <= 384) launch(c1, c4, c0);
-    else if (mean <= 1280) launch(c2, c4, c0);
-    else launch(c4, c4, c1);
+    constexpr std::true_type many; constexpr std::false_type one;
+    auto pick = [&](auto kl) {
+        constexpr bool KL = decltype(kl)::value;
+        if (n_seq <= 1024 || (n_seq <= 4096 && mean > 2048)) launch(kl, one, c4, c8, c1);
+        else if (n_seq <= 2048 && mean <= 1024) launch(kl, one, c2, c8, c2);
+        else if (n_seq <= 2048) launch(kl, one, c4, c4, c0);
+        else if (mean <= (n_seq <= 4096 ? 384 : KL ? 704 : n_seq <= 8192 ? 768 : 960)) launch(kl, many, c8, c4, c0);
+        else if constexpr (KL) {
+            if (mean <= 2048) launch(kl, one, c4, c4, c0);
+            else launch(kl, one, c4, c4, c1);
+        } else {
+            if (n_seq <= 8192 || mean > 2816) launch(kl, one, c4, c4, c0);
+            else launch(kl, one, c2, c8, c0);
+        }
+    };
+    if (a.use_kl) pick(std::true_type{});
+    else pick(std::false_type{});
     return hipGetLastError();
 }
 

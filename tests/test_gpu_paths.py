@@ -288,3 +288,60 @@ def test_a_repeat_in_perm_moves_nothing(n, shards, align):
         name = w.fields[0].name
         assert np.array_equal(d.dst_fields[name].cpu().numpy(), arena), (n, call)
         d.dst_fields[name].fill_(0x5A5A5A5A)
+
+
+@pytest.mark.parametrize("kl", [0.0, 0.05])
+@pytest.mark.parametrize("n,mean", [(2049, 200), (2049, 384), (2049, 386), (4097, 690), (4097, 715), (8192, 765), (8193, 955), (8193, 965),
+                                    (4097, 2040), (4097, 2060), (8200, 2830)])
+def test_gae_long_sequences_among_short_ones(n, mean, kl):
+    """Each side of the lines between the ways of sharing, with sequences of up to 32 K tokens among them: alone in their
+    set, more in one set than workgroups share it, and lengths round what counts as long."""
+    rng = np.random.default_rng(n + mean)
+    long_len = max(4 * mean, 2048)
+    sets = -(-n // 64)
+    at = np.concatenate([np.arange(7) * sets + 3, np.arange(2) * sets + sets - 1, [n - 1, n // 2, 11, 12, 13]])
+    longs = np.concatenate([[long_len + 5, 9000, 9000, long_len, 12001, long_len + 1, 4096], [7000, 8192], [20000, 32768],
+                            [long_len - 1, long_len, long_len + 1]])
+    lens = rng.integers(max(1, mean // 4), max(2, 2 * mean - mean // 4), n)
+    lens = np.maximum(1, (lens * (mean - longs.sum() / n) / lens.mean()).astype(np.int64))
+    lens[at] = longs
+    short = np.setdiff1d(np.arange(n), at)
+    more, rest = divmod(mean * n - int(lens.sum()), len(short))
+    lens[short] += more                                  # (exactly `mean` on average)
+    lens[short[:rest]] += 1
+    assert lens.min() > 0 and lens.sum() == mean * n
+    w = _with_ppo_fields(_custom(lens.astype(np.int32), 1, 1, 1 << 20, fields=()), seed=n)
+    check_gae(w, 0.99, 0.95, kl, label=f"{n} sequences of {mean}, long ones among them")
+
+
+def _time(torch, call):
+    for _ in range(3):
+        call()
+    best = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        a.record()
+        for _ in range(20):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best.append(a.elapsed_time(b) / 20)
+    return min(best)
+
+
+@pytest.mark.parametrize("kl", [0.0, 0.05])
+@pytest.mark.parametrize("n,mean", [(4096, 300), (16384, 300), (4096, 1200), (16384, 1000)])
+def test_gae_is_not_held_up_by_one_long_sequence(n, mean, kl):
+    """A 32 K-token sequence among short ones starts early and has the waves of a batch of its own: the call takes no longer
+    than the batch without it and twice the sequence alone together (half to two thirds of that are measured; left to a
+    single wave's or two waves' iterations it took 0.8 to 1.5 times that)."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    lens = np.maximum(1, rng.integers(mean // 2, mean * 3 // 2, n))
+    times = []
+    for x in (lens, np.concatenate([[32768], lens[1:]]), np.array([32768])):
+        d = runner.DeviceBatch(_with_ppo_fields(_custom(x.astype(np.int32), 1, 1, 1 << 20, fields=()), seed=n))
+        d.prepare_gae()
+        times.append(_time(torch, lambda: d.gae(1.0, 0.95, kl)))
+    assert times[1] < times[0] + 2.0 * times[2], times
