@@ -8,6 +8,7 @@
 // streams the sequence's own token range: 4 mask bytes in, 16 bytes of float32 out per
 // lane and step (5 B/token, HBM-bound).  A sequence is one contiguous run in its
 // rollout shard, so no lane ever has to search for the sequence a token belongs to.
+#include <algorithm>
 #include "advantage_device.h"
 
 namespace dc {
@@ -23,20 +24,51 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_kernel(AdvArgs a, SourceD
 // advantage by itself (the same sums in the same order), and the wave then streams their tokens, four sequences' mask
 // words in flight at a time, the first four's asked for ahead of the statistics.
 // With a wave per sequence every lane of it works out the same statistics, ~350 vector instructions in float64 for a
-// sequence whose tokens take ten, and 65 536 of those are the stage's time: 73.6 us for 31.5 M tokens in 65 536 sequences,
-// 46.9 with eight to a wave (51.8 with four, 50.1 with sixteen).  Below 16 384 sequences there are not enough waves left
-// (2048 of 1597 tokens 8.4 -> 31), and longer ones want their tokens spread over more waves (16 384 of 2594 53 -> 129).
+// sequence whose tokens take ten, and 65 536 of those are the stage's time: 69.0 us for 28 M tokens in 65 536 sequences,
+// 43.3 with eight to a wave (four and sixteen: 7 to 10 % more).  Below 16 384 sequences there are not enough waves left (8192
+// of 57 tokens 10.4 -> 11.4), and longer ones want their tokens spread over more waves; the line is the mean above which
+// the stage with a quarter of its sequences past the four steps is slower so (16 384 of 326 18.3 / 18.4, of 469 20.6 / 22.9;
+// 24 576 of 416 27.1 / 27.8, of 678 32.2 / 34.8; 32 768 of 792 44.0 / 41.3; 49 152 of 998 69.3 / 68.5).
+// Long sequences are not a single wave's: the first ADV_SETS workgroups look for them, each in a set of its own (of
+// neighbours, as the answers to one prompt are, every one in another set), and take them with all their waves and
+// ADV_UNROLL steps in flight.  16 384 sequences of 190 tokens, 64 of 32 K among them: 28.9 us with a wave per sequence, 17.9
+// here (64 at a stretch: 22.4 and 17.2), where the wave that met them took 98 and 450.
 constexpr int ADV_SEQS = 8;                            // sequences of a wave
 constexpr int ADV_GROUP = 4;                           // sequences in flight
 constexpr int ADV_STEPS = 4;                           // 4-token chunks per lane of one of them in flight
+constexpr int ADV_REST = 8;                            // the same of a longer one's rest
+constexpr int ADV_LONG = 4096;                         // tokens from which a sequence is a long one
+constexpr int ADV_SETS = 509;                          // (half as many: a Pareto tail of 65 536 of 786 tokens 102 us instead of
+                                                       // 83; a prime, so that one long answer to every prompt is in every set)
 constexpr int ADV_BRIEF_MIN_SEQ = 16384;               // a wave per sequence fills the chip's wave slots twice
-constexpr int ADV_BRIEF_MAX_MEAN = ADV_STEPS * WAVE * 4;       // longer sequences leave the four steps
+constexpr int ADV_BRIEF_MAX_MEAN = ADV_STEPS * WAVE * 4;       // (what the four steps take)
+constexpr int ADV_BRIEF_SEQ_PER_TOKEN = 48;            // sequences per token of the mean length, at least
 static_assert(ADV_SEQS % ADV_GROUP == 0 && ADV_SEQS <= WAVE, "a lane per sequence");
 
-__global__ __launch_bounds__(ADV_BLOCK) void advantage_brief_kernel(AdvArgs a, SourceDesc sd) {
+__device__ __forceinline__ bool adv_long(int32_t ln) { return ln >= ADV_LONG && ln <= DC_MAX_SEQ_LEN; }
+
+// (bounded to eight waves to a SIMD: the long ones' code alone would take the scalar registers of one of them)
+__global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a, SourceDesc sd) {
     const int lane = threadIdx.x & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int N = a.n_seq;
-    const int64_t first = ((int64_t)blockIdx.x * ADV_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))) * ADV_SEQS;
+    if (blockIdx.x < ADV_SETS) {                                     // (uniform) long ones, by the workgroup's waves together
+        __shared__ uint64_t found[ADV_WAVES];
+        for (int64_t base = blockIdx.x; base < N; base += (int64_t)ADV_BLOCK * ADV_SETS) {
+            const int64_t at = base + (int64_t)threadIdx.x * ADV_SETS;
+            const uint64_t mine = __ballot(adv_long(at < N ? a.seq_len[at] : 0));
+            if (lane == 0) found[w] = mine;
+            lds_barrier();
+#pragma unroll 1
+            for (int q = 0; q < ADV_WAVES; ++q) {
+                for (uint64_t left = wave_read_lane(found[q], 0); left != 0ull; left &= left - 1ull)      // (uniform)
+                    advantage_sequence<ADV_WAVES>(a, sd, (int)base + (q * WAVE + __ffsll((long long)left) - 1) * ADV_SETS, w);
+            }
+            lds_barrier();
+        }
+        return;
+    }
+    const int64_t first = ((int64_t)(blockIdx.x - ADV_SETS) * ADV_WAVES + w) * ADV_SEQS;
     if (lane < ADV_SEQS && first + lane <= a.n_groups) {             // group table: [0] = 0, non-decreasing, last = N
         const int g = (int)first + lane;
         const int32_t v = a.group_off[g];
@@ -48,9 +80,9 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_brief_kernel(AdvArgs a, S
     // ---- lane k: sequence first + k (lanes beyond the last one repeat it and store nothing) ----
     const int n = (int)min((int64_t)ADV_SEQS, N - first);            // (uniform)
     const int i = (int)first + min(lane, n - 1);
-    const bool mine = lane < n;
     const int64_t so = a.src_tok_off[i], so_next = a.src_tok_off[min(i + 1, N - 1)];
     const int32_t ln = a.seq_len[i];
+    const bool lng = adv_long(ln), mine = lane < n && !lng;          // (a long one is done above)
     const double ri = (double)a.reward[i];
     int g = min((int)(((int64_t)i * a.n_groups) / N), max(a.n_groups - 1, 0));     // where it is if all groups have the same size
     int g0 = a.group_off[g], g1 = a.group_off[min(g + 1, a.n_groups)];
@@ -73,8 +105,8 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_brief_kernel(AdvArgs a, S
     const bool bad_off = !bad_len && (so < 0 || so + ln > buf_tokens || (i + 1 < buf_end && so_next < so + ln));
     if (mine && bad_len) set_status(a.status, DC_ERR_ZERO_LENGTH_SEQ);
     if (mine && bad_off) set_status(a.status, DC_ERR_BAD_LAYOUT);
-    const int64_t end = so + (bad_len || bad_off ? 0 : ln);          // an empty sequence where a check failed
-    const int64_t begin = bad_len || bad_off ? end : so;
+    const bool none = bad_len || bad_off || lng;                     // nothing to write here
+    const int64_t begin = so, end = none ? so : so + ln;
 
     // ---- the wave's view of sequence k ----
     struct Seq {
@@ -150,8 +182,19 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_brief_kernel(AdvArgs a, S
                 const int64_t c = q.a4 + (u * WAVE + lane) * 4;
                 if (c < q.e4) store16(q.out + c, select_by_mask(mk[k][u], av));
             }
-            for (int64_t c = q.a4 + (ADV_STEPS * WAVE + lane) * 4; c < q.e4; c += WAVE * 4)       // a longer one's rest
-                store16(q.out + c, select_by_mask(load4(q.mask + c), av));
+            for (int64_t c0 = q.a4 + ADV_STEPS * WAVE * 4; c0 < q.e4; c0 += ADV_REST * WAVE * 4) {       // (uniform) a longer one's rest
+                uint32_t more[ADV_REST];
+#pragma unroll
+                for (int u = 0; u < ADV_REST; ++u) {
+                    const int64_t c = c0 + (u * WAVE + lane) * 4;
+                    more[u] = c < q.e4 ? load4(q.mask + c) : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < ADV_REST; ++u) {
+                    const int64_t c = c0 + (u * WAVE + lane) * 4;
+                    if (c < q.e4) store16(q.out + c, select_by_mask(more[u], av));
+                }
+            }
         }
     }
 }
@@ -180,9 +223,9 @@ hipError_t launch_advantage(int32_t n_seq, const SourceDesc& src, const int64_t*
                                     mask_base, d_adv_seq, adv_tok_base, d_status);
     int64_t tokens = 0;
     for (int s = 0; s < src.n_src; ++s) tokens += src.tokens[s];
-    if (a.per_token && n_seq >= ADV_BRIEF_MIN_SEQ && tokens / n_seq <= ADV_BRIEF_MAX_MEAN) {
+    if (a.per_token && n_seq >= ADV_BRIEF_MIN_SEQ && tokens / n_seq <= std::min(ADV_BRIEF_MAX_MEAN, n_seq / ADV_BRIEF_SEQ_PER_TOKEN)) {
         const int64_t blocks = (adv_waves(n_seq, n_groups) + ADV_WAVES * ADV_SEQS - 1) / (ADV_WAVES * ADV_SEQS);
-        hipLaunchKernelGGL(advantage_brief_kernel, dim3((unsigned)blocks), dim3(ADV_BLOCK), 0, st, a, src);
+        hipLaunchKernelGGL(advantage_brief_kernel, dim3((unsigned)blocks + ADV_SETS), dim3(ADV_BLOCK), 0, st, a, src);
         return hipGetLastError();
     }
     const int64_t grid = (adv_waves(n_seq, n_groups) + ADV_WAVES - 1) / ADV_WAVES;

@@ -80,23 +80,13 @@ __device__ __forceinline__ u32x4 select_by_mask(uint32_t mk, uint32_t av) {
     return o;
 }
 
-// The work of wave number wv: sequence wv (its advantage, then its tokens), and one entry of the
-// group table to check.  All 64 lanes of the wave must call it.
-__device__ __forceinline__ void advantage_wave(const AdvArgs& a, const SourceDesc& sd, int64_t wv) {
-    const int N = a.n_seq;
+// Sequence i: its advantage, then its tokens.  PARTS waves share it, this is number `part` (uniform).  All 64 lanes of the
+// wave must call it.
+template <int PARTS>
+__device__ __forceinline__ void advantage_sequence(const AdvArgs& a, const SourceDesc& sd, int i, int part) {
     const int lane = threadIdx.x & (WAVE - 1);
-
-    if (wv <= a.n_groups && lane == 0) {                 // group table: [0] = 0, non-decreasing, last = N
-        const int g = (int)wv;
-        const int32_t v = a.group_off[g];
-        bool bad = v < 0 || v > N || (g == 0 && v != 0) || (g == a.n_groups && v != N);
-        if (g < a.n_groups && a.group_off[g + 1] < v) bad = true;
-        if (bad) set_status(a.status, DC_ERR_BAD_LAYOUT);
-    }
-    if (wv >= N) return;
-    const int i = (int)wv;
     const float adv = seq_advantage(a, i);
-    if (lane == 0) a.adv_seq[i] = adv;
+    if (lane == 0 && part == 0) a.adv_seq[i] = adv;
 
     int s = 0;
     while (s + 1 < sd.n_src && i >= sd.seq_off[s + 1]) ++s;
@@ -118,12 +108,12 @@ __device__ __forceinline__ void advantage_wave(const AdvArgs& a, const SourceDes
     const int64_t end = so + ln;
     const int64_t a4 = min(end, (so + 3) & ~int64_t(3));         // first 4-aligned token
     const int64_t e4 = max(a4, end & ~int64_t(3));               // end of the 4-aligned body
-    // ragged head and tail: at most 3 tokens each
+    // ragged head and tail: at most 3 tokens each (of several parts any may write them)
     if (lane < 3 && so + lane < a4) out[so + lane] = mask[so + lane] ? adv : 0.0f;
     if (lane >= 32 && lane < 35 && e4 + (lane - 32) < end) out[e4 + lane - 32] = mask[e4 + lane - 32] ? adv : 0.0f;
     // body: 4 tokens per lane and step, ADV_UNROLL steps in flight
     const int64_t c_end = e4 >> 2;
-    for (int64_t c = (a4 >> 2) + lane; c < c_end; c += WAVE * ADV_UNROLL) {
+    for (int64_t c = (a4 >> 2) + part * (WAVE * ADV_UNROLL) + lane; c < c_end; c += PARTS * WAVE * ADV_UNROLL) {
         uint32_t mk[ADV_UNROLL];
 #pragma unroll
         for (int u = 0; u < ADV_UNROLL; ++u) {
@@ -136,6 +126,19 @@ __device__ __forceinline__ void advantage_wave(const AdvArgs& a, const SourceDes
             if (cu < c_end) store16(out + cu * 4, select_by_mask(mk[u], av));
         }
     }
+}
+
+// The work of wave number wv: sequence wv, and one entry of the group table to check.  All 64 lanes of the wave must call it.
+__device__ __forceinline__ void advantage_wave(const AdvArgs& a, const SourceDesc& sd, int64_t wv) {
+    const int N = a.n_seq;
+    if (wv <= a.n_groups && (threadIdx.x & (WAVE - 1)) == 0) {      // group table: [0] = 0, non-decreasing, last = N
+        const int g = (int)wv;
+        const int32_t v = a.group_off[g];
+        bool bad = v < 0 || v > N || (g == 0 && v != 0) || (g == a.n_groups && v != N);
+        if (g < a.n_groups && a.group_off[g + 1] < v) bad = true;
+        if (bad) set_status(a.status, DC_ERR_BAD_LAYOUT);
+    }
+    if (wv < N) advantage_sequence<1>(a, sd, (int)wv, 0);
 }
 
 // What the host side fills in for either launch.

@@ -345,3 +345,35 @@ def test_gae_is_not_held_up_by_one_long_sequence(n, mean, kl):
         d.prepare_gae()
         times.append(_time(torch, lambda: d.gae(1.0, 0.95, kl)))
     assert times[1] < times[0] + 2.0 * times[2], times
+
+
+@pytest.mark.parametrize("n,shards,n_src", [(24576, 2, 1), (24577, 1, 1), (49152, 3, 8), (140000, 4, 4)])
+def test_advantages_of_long_sequences_among_short_ones(n, shards, n_src):
+    """Eight short sequences to a wave and long ones (4096 tokens and more) to whole workgroups: neighbours, one set's, the
+    first and the last sequence, lengths round the line, ends anywhere in a 16-byte chunk; sets that take more than one look."""
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 40, n)
+    at = np.unique(np.concatenate([[0, n - 1], np.arange(9) + n // 3, np.arange(4) * 509 + 77]))
+    lens[at] = rng.integers(4080, 4120, len(at))
+    lens[at[::3]] = 4096 + np.arange(len(at[::3])) - 2
+    lens[at[1]] = 40001
+    lens[n // 2:n // 2 + 12] = rng.integers(1020, 4096, 12)      # longer than a wave's four steps, not long
+    w = _custom(lens.astype(np.int32), 1 if n % 2 else 4, shards, 1 << 17, n_src=n_src, seed=n, fields=())
+    check_step(w, label=f"{n} sequences, long ones among them")
+
+
+@pytest.mark.parametrize("together", [True, False])
+@pytest.mark.parametrize("n,mean", [(16384, 200), (65536, 100)])
+def test_advantages_are_not_held_up_by_long_sequences(n, mean, together):
+    """64 sequences of 32 K tokens among short ones, side by side or all over the batch: no more than the batch without them
+    and twice the 64 alone together (half of that is measured; one wave after the other through them took 2 to 9 times it)."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    lens = rng.integers(mean // 2, mean * 3 // 2, n)
+    mixed = lens.copy()
+    mixed[np.arange(64) + n // 3 if together else np.arange(64) * (n // 64) + 5] = 32768
+    times = []
+    for x in (lens, mixed, np.full(64, 32768)):
+        d = runner.DeviceBatch(_custom(x.astype(np.int32), 8, 1, 1 << 20, fields=()))
+        times.append(_time(torch, d.group_advantage))
+    assert times[1] < times[0] + 2.0 * times[2], times
