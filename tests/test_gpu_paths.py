@@ -331,19 +331,24 @@ def _time(torch, call):
 
 
 @pytest.mark.parametrize("kl", [0.0, 0.05])
-@pytest.mark.parametrize("n,mean", [(4096, 300), (16384, 300), (4096, 1200), (16384, 1000)])
-def test_gae_is_not_held_up_by_one_long_sequence(n, mean, kl):
-    """A 32 K-token sequence among short ones starts early and has the waves of a batch of its own: the call takes no longer
-    than the batch without it and twice the sequence alone together (half to two thirds of that are measured; left to a
-    single wave's or two waves' iterations it took 0.8 to 1.5 times that)."""
+@pytest.mark.parametrize("n,mean,longs", [(4096, 300, 1), (16384, 300, 1), (4096, 1200, 1), (16384, 1000, 1), (4096, 150, 64), (16384, 150, 64),
+                                          (16384, 150, 128)])
+def test_gae_is_not_held_up_by_long_sequences(n, mean, longs, kl):
+    """A 32 K-token sequence among short ones, or one of 8192 at the same place in every group of a power of two, starts early
+    and has the waves of a batch of its own: the call takes no longer than the batch without them and twice them alone
+    together (a third to two thirds of that are measured; left to one or two waves' iterations it took 0.8 to 1.5 times
+    that, left to a few workgroups one after the other up to 7)."""
     torch, binding, runner = _gpu()
     rng = np.random.default_rng(n)
     lens = np.maximum(1, rng.integers(mean // 2, mean * 3 // 2, n))
+    mixed = lens.copy()
+    mixed[:: n // longs] = 32768 if longs == 1 else 8192
     times = []
-    for x in (lens, np.concatenate([[32768], lens[1:]]), np.array([32768])):
+    for x in (lens, mixed, mixed[:: n // longs]):
         d = runner.DeviceBatch(_with_ppo_fields(_custom(x.astype(np.int32), 1, 1, 1 << 20, fields=()), seed=n))
         d.prepare_gae()
         times.append(_time(torch, lambda: d.gae(1.0, 0.95, kl)))
+    print([round(1e3 * t, 1) for t in times], round(times[1] / (times[0] + 2.0 * times[2]), 2))
     assert times[1] < times[0] + 2.0 * times[2], times
 
 
