@@ -282,15 +282,14 @@ __device__ __forceinline__ void move_wave_sparse(const FieldDesc& fd, int n_src,
 }
 
 // ---------------------------------------------------------------- dense granules: one wave, LDS words of its own
-// The slots that reach into a granule, relative to its first token, DENSE_SLOTS at a time.  A pass serves the chunks
-// that begin before slot DENSE_OWN of it; the slots behind are the look-ahead such a chunk may reach into (16 tokens at
-// most, one per slot).  Lane k stages slot k; the last entry says "no slot".
+// The slots that reach into a granule, relative to its first token, DENSE_SLOTS at a time.  A pass serves the tokens
+// before the slot behind its last one, whose start the last entry holds ("no slot" if there is none); a chunk that this
+// start falls into is served by both passes, each its own tokens.  Lane k stages slot k.
 // Bound by latency: the granule's table entries, the slots' descriptors and the payload are each one trip to memory for
 // the whole granule.  The gather kernel takes 6.6 us for 15 550 tokens in 64 sequences, 34 us for 3.3 M tokens in 15 360
 // and 261 us for 31.5 M tokens in 65 536 (5 fields).  With the slots staged per tile by the workgroup, one chunk per lane
 // at a time and an edge chunk's elements one after the other it took 14.7, 70 and 307 us.
 constexpr int DENSE_SLOTS = WAVE - 1;
-constexpr int DENSE_OWN = DENSE_SLOTS - 16;
 constexpr int DENSE_CHUNKS = GATHER_GRAN / 4;                  // chunks of a granule of 4-byte elements, the most there are
 struct WaveSlots {
     int32_t  start[WAVE];          // first destination token of the slot (REL_FAR: none)
@@ -307,7 +306,7 @@ __device__ __forceinline__ void stage_wave_slots(const GatherArgs& a, WaveSlots&
     const int j = base + lane;
     int32_t st = REL_FAR, en = REL_FAR;
     int64_t ad = 0;
-    if (lane < DENSE_SLOTS && j <= last) {
+    if (j <= last) {
         const int64_t d = a.dst_tok_off[j] - wave_begin;
         st = (int32_t)max((int64_t)-REL_FAR, min((int64_t)REL_FAR, d));
         en = st + a.slot_len[j];
@@ -320,10 +319,10 @@ __device__ __forceinline__ void stage_wave_slots(const GatherArgs& a, WaveSlots&
     __builtin_amdgcn_wave_barrier();
 }
 
-// First token behind the chunks of this pass; *more: the granule has slots left behind them.
-__device__ __forceinline__ int32_t dense_pass_end(const WaveSlots& sg, int base, int last, int32_t limit, bool* more) {
-    const int32_t next = __builtin_amdgcn_readfirstlane(sg.start[DENSE_OWN]);
-    *more = last - base + 1 > DENSE_SLOTS && next < limit;
+// First token behind this pass; *more: the granule has slots left behind it.
+__device__ __forceinline__ int32_t dense_pass_end(const WaveSlots& sg, int32_t limit, bool* more) {
+    const int32_t next = __builtin_amdgcn_readfirstlane(sg.start[DENSE_SLOTS]);
+    *more = next < limit;
     return *more ? next : limit;
 }
 
@@ -353,7 +352,7 @@ __device__ __forceinline__ void move_wave_dense(const GatherArgs& a, WaveSlots& 
         asm volatile("" : "+v"(lane), "+s"(base));         // (what depends on them is worked out here, not kept across passes and fields)
         stage_wave_slots(a, sg, fd, BACK ? 1 : n_src, BACK ? back_src : fd.src[0], lg, lane, base, last, wave_begin);
         bool more;
-        const int32_t pass_end = dense_pass_end(sg, base, last, limit, &more);
+        const int32_t pass_end = dense_pass_end(sg, limit, &more);
         // ---- every chunk's slot: the last one that starts at or before it ----
         int k[MAXU];
 #pragma unroll
@@ -371,8 +370,8 @@ __device__ __forceinline__ void move_wave_dense(const GatherArgs& a, WaveSlots& 
         for (int u = 0; u < MAXU; ++u) {
             if (u < es) {                                  // uniform
                 const int32_t c0 = (u * WAVE + lane) * tpc;
-                const bool mine = c0 >= pass_begin && c0 < pass_end;
-                const bool in = mine && k[u] >= 0 && c0 + tpc <= min(sg.end[max(k[u], 0)], limit);
+                const bool mine = c0 + tpc > pass_begin && c0 < pass_end;
+                const bool in = c0 >= pass_begin && k[u] >= 0 && c0 + tpc <= min(sg.end[max(k[u], 0)], pass_end);
                 if (in) in_mask |= 1u << u;
                 const uint64_t edges = __ballot(mine && !in);
                 if (mine && !in) sg.edge[n_edge + lanes_below(edges)] = (uint32_t)c0 | ((uint32_t)(k[u] + 1) << 16);
@@ -410,7 +409,7 @@ __device__ __forceinline__ void move_wave_dense(const GatherArgs& a, WaveSlots& 
                     int q = (int)(e >> 16) - 1;
                     if (item < n_items) {
                         while (q + 1 < WAVE && sg.start[q + 1] <= t) ++q;
-                        if (q >= 0 && t < sg.end[q] && t < limit) {
+                        if (q >= 0 && t >= pass_begin && t < min(sg.end[q], pass_end)) {
                             tok[r] = t;
                             val[r] = load_elem(lg, reinterpret_cast<gptr>(sg.addr[q] + ((int64_t)t << lg)));
                         }
@@ -437,7 +436,7 @@ __device__ __forceinline__ void move_wave_dense(const GatherArgs& a, WaveSlots& 
             edge_store();
         }
         if (!more) break;
-        base += DENSE_OWN;
+        base += DENSE_SLOTS;
         pass_begin = pass_end;
     }
 }
@@ -622,7 +621,7 @@ __device__ __forceinline__ void adv_wave_dense(const GatherArgs& a, WaveSlots& s
         sg.adv[lane] = av;
         __builtin_amdgcn_wave_barrier();
         bool more;
-        const int32_t pass_end = dense_pass_end(sg, base, last, limit, &more);
+        const int32_t pass_end = dense_pass_end(sg, limit, &more);
         int k[NU];
 #pragma unroll
         for (int u = 0; u < NU; ++u) k[u] = -1;
@@ -640,8 +639,8 @@ __device__ __forceinline__ void adv_wave_dense(const GatherArgs& a, WaveSlots& s
         for (int u = 0; u < NU; ++u) {
             const int32_t c0 = (u * WAVE + lane) * ADV_TPC;
             const int at = max(k[u], 0);
-            const bool mine = c0 >= pass_begin && c0 < pass_end;
-            const bool in = mine && k[u] >= 0 && c0 + ADV_TPC <= sg.end[at] && c0 + ADV_TPC <= limit;
+            const bool mine = c0 + ADV_TPC > pass_begin && c0 < pass_end;
+            const bool in = c0 >= pass_begin && k[u] >= 0 && c0 + ADV_TPC <= min(sg.end[at], pass_end);
             if (in) in_mask |= 1u << u;
             from[u] = reinterpret_cast<gptr>(sg.addr[at] + c0);
             sel[u] = sg.adv[at];
@@ -666,14 +665,14 @@ __device__ __forceinline__ void adv_wave_dense(const GatherArgs& a, WaveSlots& s
             const int32_t t = (int32_t)(e & 0xFFFFu) + (item & (ADV_TPC - 1));
             int q = (int)(e >> 16) - 1;
             while (q + 1 < WAVE && sg.start[q + 1] <= t) ++q;
-            if (q >= 0 && t < sg.end[q] && t < limit) {
+            if (q >= 0 && t >= pass_begin && t < min(sg.end[q], pass_end)) {
                 const uint32_t m = load_elem(0, reinterpret_cast<gptr>(sg.addr[q] + t));
                 store_elem(2, dst + ((int64_t)t << 2), m ? sg.adv[q] : 0u);
                 store_elem(0, mdst + t, m);
             }
         }
         if (!more) break;
-        base += DENSE_OWN;
+        base += DENSE_SLOTS;
         pass_begin = pass_end;
     }
 }

@@ -382,3 +382,46 @@ def test_advantages_are_not_held_up_by_long_sequences(n, mean, together):
         d = runner.DeviceBatch(_custom(x.astype(np.int32), 8, 1, 1 << 20, fields=()))
         times.append(_time(torch, d.group_advantage))
     assert times[1] < times[0] + 2.0 * times[2], times
+
+
+@pytest.mark.parametrize("empties", [3, 15, 17, 40, 130])
+def test_empty_slots_in_a_crowded_granule(empties):
+    """Slots that fail a check take no tokens; however many stand in a row, the sequences on both sides of them are moved whole
+    (every field width, and the advantages made on the way)."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(empties)
+    n = 6000
+    lens = rng.integers(1, 30, n).astype(np.int32)
+    w = _custom(lens, 1, 3, 4096, n_src=3, seed=empties, fields=("i32", "bf16"))
+    none = np.zeros(n, bool)
+    at = 5
+    while at + empties < n:
+        none[at:at + empties] = True
+        at += empties + int(rng.integers(1, 70))
+    d = runner.DeviceBatch(w, poison=True)
+    d.seq_len[torch.from_numpy(np.flatnonzero(none)).to(d.dev)] = 0
+    off = torch.from_numpy(w.src_shard_seq_off).to(d.dev)
+    d.perm.copy_(torch.arange(n))
+    d.adv_seq.copy_(torch.from_numpy(rng.standard_normal(n).astype(np.float32)))
+    binding.dc_plan(d.prm, d.source, d.seq_len, d.perm, off, d.capacity, d.dst_tok_off, d.shard_tok_off, d.shard_mb_off, d.mb_seq_off,
+                    d.cu_seqlens, d.n_mb, d.ws, d.ws_bytes, d.status)
+    torch.cuda.synchronize()
+    assert d.read_status() == binding.DC_ERR_ZERO_LENGTH_SEQ
+    left = np.where(none, 0, lens).astype(np.int64)
+    tok = np.cumsum(left) - left
+    assert np.array_equal(d.dst_tok_off.cpu().numpy()[:n], tok)
+    base = np.repeat(np.concatenate([[0], np.cumsum(w.src_shard_tokens)[:-1]]), n // 3)
+    source = np.concatenate([np.arange(ln) + b + o for ln, b, o in zip(left, base, w.src_tok_off)])
+    total = int(left.sum())
+    d.gather(); torch.cuda.synchronize()
+    for f in w.fields:
+        got = d.dst_fields[f.name].cpu().numpy()
+        want = np.concatenate([np.frombuffer(s.tobytes(), got.dtype) for s in f.shards])[source]
+        assert np.array_equal(got[:total], want), f.name
+        assert np.all(got[total:] == np.frombuffer(b"\x5a" * f.elem_bytes, got.dtype)[0]), f.name
+        d.dst_fields[f.name].fill_(0)
+    d.gather_advantage(); torch.cuda.synchronize()
+    mask = np.concatenate(w.field_by_name("mask").shards)[source]
+    want = np.where(mask != 0, np.repeat(d.adv_seq.cpu().numpy(), left), np.float32(0))
+    assert np.array_equal(d.dst_fields["mask"].cpu().numpy()[:total], mask)
+    assert np.array_equal(d.dst_fields["adv_tok"].view(torch.float32).cpu().numpy()[:total].view(np.uint32), want.view(np.uint32))
