@@ -398,7 +398,9 @@ __device__ __forceinline__ int first_slot_after(RecLds& L, int N, Starts starts,
     if (tid == 0) L.run_lo = lo;
     if (tid == REC_BLOCK - 1) L.run_hi = hi;
     __syncthreads();
-    const int run_lo = L.run_lo, run_hi = L.run_hi;                   // the bisections read starts[run_lo + 1 .. run_hi]
+    const int run_lo = L.run_lo, run_hi = max(L.run_hi, L.run_lo);    // the bisections read starts[run_lo + 1 .. run_hi]
+    lo = min(max(lo, run_lo), run_hi);                                // (starts that do not rise with j, a caller's mistake, give
+    hi = min(hi, run_hi);                                             // a slot that means nothing, but no place outside the run)
     const bool staged = run_hi - run_lo + 1 <= REC_STAGE;             // (uniform)
     if (staged)
         for (int k = tid; k <= run_hi - run_lo; k += REC_BLOCK) L.stage[k] = starts(min(run_lo + k, N));

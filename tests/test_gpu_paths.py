@@ -425,3 +425,31 @@ def test_empty_slots_in_a_crowded_granule(empties):
     want = np.where(mask != 0, np.repeat(d.adv_seq.cpu().numpy(), left), np.float32(0))
     assert np.array_equal(d.dst_fields["mask"].cpu().numpy()[:total], mask)
     assert np.array_equal(d.dst_fields["adv_tok"].view(torch.float32).cpu().numpy()[:total].view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [300, 5000, 40000])
+def test_scatter_with_offsets_that_do_not_rise(n):
+    """Rollout offsets in another order than the sequences' are refused; what is written all the same stands in its place."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 60, n).astype(np.int32)
+    w = _custom(lens, 1, 1, 4096, fields=("i32",))
+    d = runner.DeviceBatch(w)
+    d.balance(); d.plan(); torch.cuda.synchronize()
+    order = rng.permutation(n)
+    start = np.empty(n, np.int64)
+    start[order] = np.cumsum(lens[order], dtype=np.int64) - lens[order]
+    name = w.fields[0].name
+    d.dst_fields[name].copy_(torch.arange(d.capacity, dtype=torch.int32))
+    d.prepare_scatter([name], fill=0x7F)
+    d.src_tok_off.copy_(torch.from_numpy(start))
+    d.scatter(); torch.cuda.synchronize()
+    assert d.read_status() == binding.DC_ERR_BAD_LAYOUT
+    slot = np.empty(n, np.int64)
+    slot[d.perm.cpu().numpy()] = np.arange(n)
+    want = np.empty(w.total_tokens, np.int64)
+    tok = d.dst_tok_off.cpu().numpy()
+    for i in range(n):
+        want[start[i]:start[i] + lens[i]] = tok[slot[i]] + np.arange(lens[i])
+    got = d.back_fields[name][0].cpu().numpy()
+    assert np.all((got == 0x7F7F7F7F) | (got == want))
