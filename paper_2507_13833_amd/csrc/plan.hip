@@ -44,20 +44,24 @@ __global__ __launch_bounds__(SLOTS_BLOCK) void slots_kernel(PlanArgs a, SourceDe
     a.slot_shard[j] = sh;
 }
 
+// IPT: slots per lane at most, PLAN_IPT (more than PLAN_NEXT_MAX slots) or half of that; either kernel holds the code of its
+// sizes alone.  One kernel whose passes are left at the first step without slots took 7.6 us for 64 slots, 10.6 for 2048 on 8
+// shards, 16.4 for 8192 on 32 and 16.7 for 16 384 on 64; these take 6.8, 9.8, 15.4 and 16.0.
+template <int IPT>
 __global__ __launch_bounds__(PLAN_BLOCK) void plan_kernel(PlanArgs a) {
     __shared__ PlanLds L;
     const int tid = threadIdx.x;
     const int N = a.n_seq;
     // the slots' sequences and lengths (validated by slots_kernel): asked for first, so that these loads are in
     // flight while the shard table is fetched and checked
-    int32_t seq[PLAN_IPT], len[PLAN_IPT];
+    int32_t seq[IPT], len[IPT];
 #pragma unroll
-    for (int q = 0; q < PLAN_IPT; ++q) {
+    for (int q = 0; q < IPT; ++q) {
         const int j = q * PLAN_BLOCK + tid;
         seq[q] = j < N ? (a.perm ? a.perm[j] : j) : -1;
         len[q] = j < N ? a.slot_len[j] : 0;
     }
-    plan_body(L, a, seq, len, true, 0);
+    plan_body<IPT, (IPT < PLAN_IPT ? STEP_OVER : ALL), (IPT < PLAN_IPT)>(L, a, seq, len, true, 0);
 }
 
 // Per-granule tables for the gather (one lane per granule, many workgroups; runs after
@@ -147,7 +151,9 @@ hipError_t launch_plan(const dc_params& prm, const SourceDesc& src, const int64_
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(PLAN_BLOCK), 0, st, a);
+        static_assert(PLAN_NEXT_MAX == PLAN_IPT / 2 * PLAN_BLOCK, "the line between the two kernels");
+        if (prm.n_seq <= PLAN_NEXT_MAX) hipLaunchKernelGGL(plan_kernel<PLAN_IPT / 2>, dim3(1), dim3(PLAN_BLOCK), 0, st, a);
+        else hipLaunchKernelGGL(plan_kernel<PLAN_IPT>, dim3(1), dim3(PLAN_BLOCK), 0, st, a);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;

@@ -73,8 +73,23 @@ struct PlanLds {
 // The caller holds, per lane, the sequence and the (validated) length of slots tid, tid + PLAN_BLOCK, ...
 // (seq = -1, len = 0 beyond N).  check_perm: seq comes from a caller's permutation and must be checked;
 // fixed_c > 0: shard p owns slots [p * fixed_c, (p + 1) * fixed_c) and a.shard_seq_off is not read.
+// STEPS: how the unrolled passes over a lane's slots treat the steps beyond nb.  LEAVE_EARLY: left at the first (a small
+// batch does not fetch the others' code); STEP_OVER: a test each; ALL: none, there are few or none of them (the steps
+// then run into each other: 16 scans at once).  CHAINS = false: for more than PLAN_NEXT_MAX slots, without the code that such
+// a batch never takes.
 // Every lane of the workgroup must call it (barriers inside).
-template <int IPT>
+enum PlanSteps { LEAVE_EARLY, STEP_OVER, ALL };
+template <int IPT, PlanSteps STEPS, typename Body>
+__device__ __forceinline__ void plan_steps(int nb, Body&& body) {
+    if constexpr (STEPS == LEAVE_EARLY) {
+        unrolled_steps<IPT>(nb, body);
+    } else {
+#pragma unroll
+        for (int q = 0; q < IPT; ++q)
+            if (STEPS == ALL || q < nb) body(q);
+    }
+}
+template <int IPT, PlanSteps STEPS = LEAVE_EARLY, bool CHAINS = true>
 __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t (&seq)[IPT], int32_t (&len)[IPT],
                                           bool check_perm, int fixed_c) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
@@ -116,8 +131,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     }
     // dense prefix: inclusive scan inside each wave step (a wave's 64 slots hold < 2^31 tokens) ...
     int32_t inc[IPT];
-    unrolled_steps<IPT>(nb, [&](auto qc) {
-        constexpr int q = decltype(qc)::value;
+    plan_steps<IPT, STEPS>(nb, [&](int q) {
         inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
         if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
     });
@@ -133,8 +147,7 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     lds_barrier();
     // ... and their sum
     const int whole_steps = N / PLAN_BLOCK;              // (uniform) steps in which every lane has a slot
-    unrolled_steps<IPT>(nb, [&](auto qc) {
-        constexpr int q = decltype(qc)::value;
+    plan_steps<IPT, STEPS>(nb, [&](int q) {
         const int j = q * PLAN_BLOCK + tid;
         if (q < whole_steps || j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
     });
@@ -173,9 +186,12 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     }
 
     // ---- 3. micro-batch starts ----
-    const uint64_t all_tokens = (uint64_t)L.gpre[N];
-    if (N <= PLAN_NEXT_MAX && all_tokens <= 0xFFFFFFFFull &&
-        all_tokens > (uint64_t)(4 + 4 * nb) * (uint64_t)P * (uint64_t)a.budget) {         // (uniform)
+    bool chains = false;                                 // (uniform)
+    if constexpr (CHAINS) {
+        const uint64_t all_tokens = (uint64_t)L.gpre[N];
+        chains = N <= PLAN_NEXT_MAX && all_tokens <= 0xFFFFFFFFull && all_tokens > (uint64_t)(4 + 4 * nb) * (uint64_t)P * (uint64_t)a.budget;
+    }
+    if (chains) {
         // Few slots and long chains: every slot finds the end of the micro-batch that would start with it (a bisection of
         // the prefix's low words, a lane's slots side by side), and lane p follows shard p's chain, one LDS read a hop.
         // A walk's hop (below) reads the start, probes a window and counts: 620 cycles against 250, but the search takes
