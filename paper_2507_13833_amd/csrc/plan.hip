@@ -45,8 +45,8 @@ __global__ __launch_bounds__(SLOTS_BLOCK) void slots_kernel(PlanArgs a, SourceDe
 }
 
 // IPT: slots per lane at most, PLAN_IPT (more than PLAN_NEXT_MAX slots) or half of that; either kernel holds the code of its
-// sizes alone.  One kernel whose passes are left at the first step without slots took 7.6 us for 64 slots, 10.6 for 2048 on 8
-// shards, 16.4 for 8192 on 32 and 16.7 for 16 384 on 64; these take 6.8, 9.8, 15.4 and 16.0.
+// sizes alone.  One kernel whose passes are left at the first step without slots took 7.6 us for 64 slots, 10.9 for 2048 on 8
+// shards, 16.4 for 8192 on 32 and 16.8 for 16 384 on 64; these take 6.7, 9.8, 15.5 and 15.9.
 template <int IPT>
 __global__ __launch_bounds__(PLAN_BLOCK) void plan_kernel(PlanArgs a) {
     __shared__ PlanLds L;
