@@ -96,18 +96,22 @@ def test_sort_of_few_sequences(n, kind):
     check_step(_custom(lens, 1, 1, 1 << 17, fields=()), label=f"{n} sequences, {kind}", two_calls=True)
 
 
-@pytest.mark.parametrize("tokens", [1024, 2032 * 1024, 2032 * 1024 + 1])
+@pytest.mark.parametrize("entries", [17, 1023, 1024, 1025, 2047, 2048, 2049])
 @pytest.mark.parametrize("align", [1, 48])
-def test_granule_tables_of_a_small_batch(tokens, align):
-    """Up to 2048 table entries the balance workgroup makes them itself, behind that a launch does."""
+def test_granule_tables_of_a_small_batch(entries, align):
+    """Up to 2048 table entries (the arena's granules and 16 more) the balance workgroup makes them itself, a lane one or two
+    of them, behind that a launch does; the arena ends with the last granule and one token into it."""
     n, shards = 256, 4
-    room = tokens - shards * (align - 1)
-    lens = np.random.default_rng(tokens).integers(1, 2 * room // n, n)
-    lens = np.maximum(1, lens * (room // n) // max(1, int(lens.mean())))
-    lens[0] += max(0, room - int(lens.sum()))
-    lens = lens.astype(np.int32)
-    check_step(_custom(lens, 4, shards, 1 << 22, n_src=2, fields=()), align=align, label=f"{tokens} tokens of capacity", two_calls=True)
-    check_gather_advantage(_custom(lens, 4, shards, 1 << 22, n_src=2, fields=()), align=align, label=f"{tokens} tokens")
+    for tokens in ((entries - 16) * 1024, (entries - 17) * 1024 + 1):
+        if tokens < n + shards * (align - 1):
+            continue
+        room = tokens - shards * (align - 1)
+        lens = np.random.default_rng(tokens).integers(max(1, room // n // 2), max(2, room // n), n)
+        lens[0] += room - int(lens.sum())
+        w = _custom(lens.astype(np.int32), 4, shards, 1 << 22, n_src=2, seed=entries, fields=("i32", "bf16"))
+        assert w.total_tokens + shards * (align - 1) == tokens and -(-tokens // 1024) + 16 == entries and lens.min() > 0
+        check_step(w, align=align, label=f"{tokens} tokens of capacity", two_calls=True)
+        check_gather_advantage(w, align=align, label=f"{tokens} tokens")
 
 
 @pytest.mark.parametrize("kl", [0.0, 0.05])
