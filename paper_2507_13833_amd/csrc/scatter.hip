@@ -157,7 +157,6 @@ ScatterWorkspace carve_scatter_workspace(void* base, int32_t n_seq, const Source
     const size_t n = (size_t)(n_seq > 0 ? n_seq : 0);
     char* p = static_cast<char*>(base);
     size_t off = 0;
-    off += round_up((n + DC_MAX_SRC_SHARDS) * sizeof(int64_t), 256);      // (not used: callers keep the size they know)
     w.r_src_off = reinterpret_cast<int64_t*>(p + off); off += round_up(n * sizeof(int64_t), 256);
     w.r_len = reinterpret_cast<int32_t*>(p + off);     off += round_up(n * sizeof(int32_t), 256);
     w.note = reinterpret_cast<int32_t*>(p + off);      off += round_up(n * sizeof(int32_t), 256);
