@@ -606,7 +606,8 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
 
 // SKIP: rounds of one length are not sorted (mixed_rounds).  Not in the kernels where such rounds are rare and the code's
 // mere presence costs 0.4 to 3.7 us: up to 2048 sequences, and 64 workers up to DC_MAX_SEQ (a length would have to occur more
-// than 64 times among 16 384); nor where the sort is six steps (8 workers).
+// than 64 times among 16 384); nor, up to DC_MAX_SEQ, for 8 workers, whose sort is six steps.  Every portion of a longer list
+// has it.
 template <int WIDTH, bool PORTION = false, bool SKIP = PORTION>
 __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint32_t* items, int32_t max_len,
                                                  uint32_t* rows, int pitch, uint32_t* spare_word,
