@@ -518,10 +518,11 @@ hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src
     //     39.7 -> 23.9, + 1 55 -> 44; of 699 52.8 -> 38.7; KL 67.7 -> 50.5; 32 768 of 849 102 -> 78).  Where the lines lie, in
     //     us against four waves of 4: 4096 of 299 11.5 / 13.3, of 499 13.1 / 14.2, of 699 17.5 / 16.1; 8192 of 699 25.0 / 27.4,
     //     of 999 33.2 / 31.4; 16 384 of 849 44 / 50, KL of 599 44.6 / 48.4, of 849 60.3 / 56.0.
-    //     Then four waves of 4 (8192 of 1249 39.3 -> 37.3; 16 384 of 1249 KL 95 -> 79, + 1 95 -> 79; of 3499 167 -> 161; from
-    //     2048 tokens on with KL one ahead, 16 384 of 2599 188 -> 184, of 3499 245 / 241 without and with it), or, without
-    //     KL above 8192 sequences, two waves of 8 without a ring (16 384 of 1599 73 -> 66, four of 4 70; of 2599
-    //     108 -> 96, four of 4 107; of 3499 163, four of 4 161).
+    //     Then four waves of 4 (8192 of 1249 39.3 -> 36.3; 16 384 of 1249 KL 95 -> 79, + 1 95 -> 79; of 2599 103 -> 100, of
+    //     2620 under a heavy tail, up to 32 K tokens, 82 -> 76; of 3499 155 -> 152); from 2048 tokens on with KL one ahead
+    //     (16 384 of 2599 188 -> 184, of 3499 245 / 241 without and with it).  Two waves of 8 without a ring are up to 5 %
+    //     faster where no length stands out (16 384 of 1599 66 / 70), but a heavy tail waits for them: of 2620 83 / 76, 9216 of
+    //     2300 61 / 50.
     constexpr integral_constant<int, 0> c0; constexpr integral_constant<int, 1> c1; constexpr integral_constant<int, 2> c2;
     constexpr integral_constant<int, 4> c4; constexpr integral_constant<int, 8> c8;
     constexpr std::true_type many; constexpr std::false_type one;
@@ -531,13 +532,8 @@ hipError_t launch_gae(int32_t n_seq, const SourceDesc& src, const int64_t* d_src
         else if (n_seq <= 2048 && mean <= 1024) launch(kl, one, c2, c8, c2);
         else if (n_seq <= 2048) launch(kl, one, c4, c4, c0);
         else if (mean <= (n_seq <= 4096 ? 384 : KL ? 704 : n_seq <= 8192 ? 768 : 960)) launch(kl, many, c8, c4, c0);
-        else if constexpr (KL) {
-            if (mean <= 2048) launch(kl, one, c4, c4, c0);
-            else launch(kl, one, c4, c4, c1);
-        } else {
-            if (n_seq <= 8192 || mean > 2816) launch(kl, one, c4, c4, c0);
-            else launch(kl, one, c2, c8, c0);
-        }
+        else if (!KL || mean <= 2048) launch(kl, one, c4, c4, c0);
+        else if constexpr (KL) launch(kl, one, c4, c4, c1);
     };
     if (a.use_kl) pick(std::true_type{});
     else pick(std::false_type{});
