@@ -38,10 +38,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 TRAFFIC_SOURCE = "profiles/hbm_traffic_config5_pmc.txt"
 TRAFFIC = {
     # config: (fetch bytes + write bytes per gather launch, digest of csrc/gather.hip + csrc/dc_internal.h)
-    5: (1048347200 + 984399700, "fffa17b6f9e27d77"),
+    5: (1048419400 + 984391000, "35c91ec1d2c0cb9c"),
 }
 TRAFFIC_ADV = {                                          # the same for dc_gather_advantage's kernel
-    5: (868200100 + 983701600, "fffa17b6f9e27d77"),
+    5: (868199900 + 983670800, "35c91ec1d2c0cb9c"),
 }
 
 
