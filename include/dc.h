@@ -207,10 +207,9 @@ dc_status dc_balance_group_advantage(const dc_params* prm, const dc_source* src,
  * steps that come before the data movement in the re-partitioning of Sec. 6 - Algorithm 1 ("Load
  * Balancing"), the advantage stage, and the layout the "Distributed Databuffer" redistributes into.
  * With Algorithm 1 as printed (cap = 0 or cap * P = N) on up to 256 shards and up to DC_MAX_SEQ
- * sequences, the plan runs as the tail of the workgroup that balances: that workgroup holds every output
- * slot's sequence and length when it is done, which is all the plan reads.  Two launches instead of
- * five, and one for a batch of up to 2048 sequences and 2048 granules; dc_gather (or dc_gather_advantage)
- * follows as after dc_plan.  Other shapes: the two calls one after
+ * sequences, a second launch plans by shards, a few workgroups each, from d_perm and d_shard_load; up to 128
+ * sequences and 2048 granules of 1024 tokens the plan runs as the tail of the workgroup that balances.  Two launches (or one) instead
+ * of five; dc_gather (or dc_gather_advantage) follows as after dc_plan.  Other shapes: the two calls one after
  * the other.
  */
 dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,

@@ -21,12 +21,16 @@ Workspace carve_workspace(void* base, int32_t n_seq, int64_t dst_capacity_tokens
     w.plan_ok = reinterpret_cast<int32_t*>(p + off);      off += 256;     // plan_ok, then own_shard_off, in one block
     w.own_shard_off = w.plan_ok + 16;
     static_assert((16 + DC_MAX_SRC_SHARDS + 1) * sizeof(int32_t) <= 256, "both fit the block");
-    w.gpre = nullptr; w.start_bits = nullptr; w.tile_tokens = nullptr;
+    w.gpre = nullptr; w.start_bits = nullptr; w.tile_tokens = nullptr; w.mb_counts = nullptr;
     if (n_seq > DC_MAX_SEQ) {
         const size_t words = n / 32 + 2;
         w.gpre = reinterpret_cast<int64_t*>(p + off);        off += round_up((n + 1) * sizeof(int64_t), 256);
         w.start_bits = reinterpret_cast<int32_t*>(p + off);  off += round_up(words * sizeof(int32_t), 256);
         w.tile_tokens = reinterpret_cast<int64_t*>(p + off); off += round_up(words * sizeof(int32_t), 256);
+    }
+    else {
+        w.mb_counts = reinterpret_cast<uint32_t*>(p + off);      // (the last 256 bytes, which nothing else uses)
+        static_assert(MB_COUNT_BYTES <= 256, "they fit");
     }
     w.bytes = off + 256;
     return w;
@@ -237,11 +241,12 @@ dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source*
     if (ws_bytes < ws.bytes) return DC_ERR_WORKSPACE;
     if (ws.n_gran > 0x7FFFFFFFLL) return DC_ERR_UNSUPPORTED_SIZE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    // the printed algorithm on up to 256 workers (what the packed rounds serve): the plan runs as the tail of the
-    // balance workgroup
-    const bool one_launch = prm->n_seq > 0 && prm->n_shards <= BAL_PLAN_MAX_SHARDS &&
-                            (int64_t)cap_eff * prm->n_shards == prm->n_seq;
-    if (!one_launch) {
+    // the printed algorithm on up to 256 workers (what the packed rounds serve): one launch for a very small batch, whose plan
+    // and tables are the tail of the balance workgroup (both sides of the line: small_records), two for others
+    const bool printed = prm->n_seq > 0 && prm->n_shards <= BAL_PLAN_MAX_SHARDS &&
+                         (int64_t)cap_eff * prm->n_shards == prm->n_seq;
+    const bool one_launch = printed && prm->n_seq <= SMALL_REC_SLOTS && ws.n_gran <= SMALL_REC_GRANS;
+    if (!one_launch && !(printed && plan_shards_serves(prm->n_seq, prm->n_shards, dst_capacity_tokens))) {
         rc = dc_balance_group_advantage(prm, src, d_seq_len, d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, d_reward,
                                         d_group_off, n_groups, mask_src_base, d_adv_seq, adv_tok_src_base, d_status, hip_stream);
         if (rc != DC_OK) return rc;
@@ -253,13 +258,16 @@ dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source*
     PlanArgs plan = make_plan_args(*prm, src->d_src_tok_off, d_seq_len, d_perm, d_shard_seq_off, dst_capacity_tokens,
                                    d_dst_tok_off, d_shard_tok_off, d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb,
                                    ws, d_status);
-    if (prm->n_seq <= SMALL_REC_SLOTS && ws.n_gran <= SMALL_REC_GRANS) {
+    hipError_t e;
+    if (one_launch) {
         plan.gran_first = ws.gran_first; plan.gran_rec = ws.gran_rec; plan.n_gran = ws.n_gran;
+        e = launch_balance_plan_advantage(prm->n_seq, prm->n_shards, cap_eff, d_seq_len, d_perm, d_shard_seq_off,
+                                          d_shard_of_seq, d_shard_load, plan, adv, sd, n_groups, d_status, st);
+    } else {
+        e = launch_balance_advantage_perm(prm->n_seq, prm->n_shards, cap_eff, d_seq_len, d_perm, d_shard_seq_off,
+                                          d_shard_load, ws.mb_counts, adv, sd, n_groups, d_status, st);
+        if (e == hipSuccess) e = launch_plan_shards(plan, sd, ws, d_shard_load, d_shard_of_seq, st);
     }
-    hipError_t e = launch_balance_plan_advantage(prm->n_seq, prm->n_shards, cap_eff, d_seq_len, d_perm, d_shard_seq_off,
-                                                 d_shard_of_seq, d_shard_load, plan, adv, sd, n_groups, d_status, st);
-    if (e != hipSuccess) return DC_ERR_HIP;
-    e = launch_records_slots(plan, sd, ws, st);
     return e == hipSuccess ? DC_OK : DC_ERR_HIP;
 }
 

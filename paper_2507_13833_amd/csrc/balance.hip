@@ -79,37 +79,39 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_advantage_kernel(BalanceArg
 static_assert(BAL_BLOCK == PLAN_BLOCK && BAL_ROUNDS == PLAN_IPT, "one lane handles the same slots in both");
 constexpr size_t BAL_PLAN_LDS = sizeof(BalLds) > sizeof(PlanLds) ? sizeof(BalLds) : sizeof(PlanLds);
 
-// MANY: 33 .. 63 or 65 .. 256 workers; else up to 32 or 64.  IPT: see balance_body_t.  (Four kernels, each with the code of
-// its shapes alone.)
-template <bool MANY, int IPT>
+// MANY: 33 .. 63 or 65 .. 256 workers; else up to 32 or 64.  IPT: see balance_body_t.  (A kernel with the code of its shapes
+// alone for each.)
+template <bool MANY>
 __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(BalanceArgs b, PlanArgs p, AdvArgs a, SourceDesc sd) {
     __shared__ __align__(16) unsigned char lds[BAL_PLAN_LDS];
     if (blockIdx.x != 0) {
         advantage_wave(a, sd, (int64_t)(blockIdx.x - 1) * BAL_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
         return;
     }
+    constexpr int IPT = SMALL_REC_IPT;
     SlotRegs<IPT> s;
-    balance_body_t<true, !MANY, MANY, IPT>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq,
-                         b.shard_load, b.status, s);
-    unrolled_steps<IPT>((b.N + PLAN_BLOCK - 1) / PLAN_BLOCK, [&](auto qc) {      // the slots' lengths, for the launch that
-        constexpr int q = decltype(qc)::value;                                        // builds the granule tables
-        const int j = q * PLAN_BLOCK + (int)threadIdx.x;
-        if (j < b.N) p.slot_len[j] = s.len[q];
-    });
+    balance_body_t<BAL_SLOTS, !MANY, MANY, IPT>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off,
+                                                b.shard_of_seq, b.shard_load, b.status, s);
     int64_t src_off[SMALL_REC_IPT];                               // (asked for here: they come while the plan runs)
-    if constexpr (IPT == SMALL_IPT) {
-        static_assert(SMALL_IPT == SMALL_REC_IPT, "the lane's slots");
 #pragma unroll
-        for (int q = 0; q < SMALL_REC_IPT; ++q) {
-            src_off[q] = 0;
-            if (p.gran_rec) src_off[q] = p.src_tok_off[min(max(s.seq[q], 0), b.N - 1)];      // (uniform)
-        }
-    }
+    for (int q = 0; q < SMALL_REC_IPT; ++q) src_off[q] = p.src_tok_off[min(max(s.seq[q], 0), b.N - 1)];
     lds_barrier();                                                // Algorithm 1's tables have been read for the last time
     plan_body(*reinterpret_cast<PlanLds*>(lds), p, s.seq, s.len, false, b.C);
-    if constexpr (IPT == SMALL_IPT) {
-        if (p.gran_rec) small_records(*reinterpret_cast<PlanLds*>(lds), p, sd, s.seq, s.len, src_off, b.C);      // (uniform)
+    small_records(*reinterpret_cast<PlanLds*>(lds), p, sd, s.seq, s.len, src_off, b.C);
+}
+
+// Balance and advantage for launch_plan_shards, which makes everything that follows from perm by many workgroups.
+template <bool MANY, int IPT>
+__global__ __launch_bounds__(BAL_BLOCK) void balance_perm_advantage_kernel(BalanceArgs b, uint32_t* mb_counts, AdvArgs a, SourceDesc sd) {
+    __shared__ BalLds L;
+    if (blockIdx.x != 0) {
+        advantage_wave(a, sd, (int64_t)(blockIdx.x - 1) * BAL_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
+        return;
     }
+    if (threadIdx.x < MB_COUNT_BYTES / sizeof(uint32_t)) mb_counts[threadIdx.x] = 0;
+    SlotRegs<IPT> unused;
+    balance_body_t<BAL_PERM, !MANY, MANY, IPT>(L, b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, nullptr, b.shard_load, b.status,
+                                               unused);
 }
 
 hipError_t launch_balance(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
@@ -132,23 +134,40 @@ hipError_t launch_balance_advantage(int32_t n_seq, int32_t n_shards, int32_t cap
     return hipGetLastError();
 }
 
+// Which of a pair of kernels serves so many workers.
+static bool many_workers(int32_t n_shards) { return n_shards > 32 && n_shards != WAVE; }
+
 hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
                                          int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
                                          int64_t* d_shard_load, const PlanArgs& plan, const AdvArgs& adv,
                                          const SourceDesc& src, int32_t n_groups, int32_t* d_status, hipStream_t st) {
     // (the kernels hold the code of these shapes only)
-    if (n_shards < 1 || n_shards > BAL_PLAN_MAX_SHARDS || (int64_t)cap_eff * n_shards != n_seq || n_seq <= 0 || n_seq > DC_MAX_SEQ)
+    if (n_shards < 1 || n_shards > BAL_PLAN_MAX_SHARDS || (int64_t)cap_eff * n_shards != n_seq || n_seq <= 0 || n_seq > SMALL_REC_SLOTS)
         return hipErrorInvalidValue;
     static_assert(BAL_PLAN_MAX_SHARDS == MULTI_MAX, "the packed rounds' limit");
-    static_assert(SMALL_REC_SLOTS == SMALL_SORT_MAX, "the small kernels make the tables");
     BalanceArgs b;
     b.N = n_seq; b.P = n_shards; b.C = cap_eff; b.seq_len = d_seq_len; b.perm = d_perm;
     b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = d_shard_of_seq; b.shard_load = d_shard_load; b.status = d_status;
     const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src); };
-    const bool many = n_shards > 32 && n_shards != WAVE;
-    if (n_seq <= SMALL_SORT_MAX) launch(many ? balance_plan_advantage_kernel<true, SMALL_IPT> : balance_plan_advantage_kernel<false, SMALL_IPT>);
-    else launch(many ? balance_plan_advantage_kernel<true, BAL_ROUNDS> : balance_plan_advantage_kernel<false, BAL_ROUNDS>);
+    launch(many_workers(n_shards) ? balance_plan_advantage_kernel<true> : balance_plan_advantage_kernel<false>);
+    return hipGetLastError();
+}
+
+hipError_t launch_balance_advantage_perm(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
+                                         int32_t* d_perm, int32_t* d_shard_seq_off, int64_t* d_shard_load,
+                                         uint32_t* mb_counts, const AdvArgs& adv, const SourceDesc& src, int32_t n_groups,
+                                         int32_t* d_status, hipStream_t st) {
+    if (n_shards < 1 || n_shards > BAL_PLAN_MAX_SHARDS || (int64_t)cap_eff * n_shards != n_seq || n_seq <= 0 || n_seq > DC_MAX_SEQ || !mb_counts)
+        return hipErrorInvalidValue;
+    BalanceArgs b;
+    b.N = n_seq; b.P = n_shards; b.C = cap_eff; b.seq_len = d_seq_len; b.perm = d_perm;
+    b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = nullptr; b.shard_load = d_shard_load; b.status = d_status;
+    const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, mb_counts, adv, src); };
+    const bool many = many_workers(n_shards);
+    if (n_seq <= SMALL_SORT_MAX) launch(many ? balance_perm_advantage_kernel<true, SMALL_IPT> : balance_perm_advantage_kernel<false, SMALL_IPT>);
+    else launch(many ? balance_perm_advantage_kernel<true, BAL_ROUNDS> : balance_perm_advantage_kernel<false, BAL_ROUNDS>);
     return hipGetLastError();
 }
 

@@ -1375,12 +1375,16 @@ struct SlotRegs {
 };
 constexpr int SMALL_IPT = SMALL_SORT_MAX / BAL_BLOCK;
 
-// FEW: the code for up to 32 or 64 workers; MANY: for the other numbers of them.  FILL (only with P * C == N): also
-// fill slots.  What a launch is never made for is left out of its kernel (it is executed once from front to back, most
+// What the workgroup leaves: BAL_ALL: every output.  BAL_SLOTS: also the slots' sequences and lengths in registers, for the
+// plan that follows in this workgroup.  BAL_PERM: everything but shard_of_seq, which the launch that plans by shards writes.
+enum BalTail { BAL_ALL, BAL_SLOTS, BAL_PERM };
+
+// FEW: the code for up to 32 or 64 workers; MANY: for the other numbers of them.  TAIL other than BAL_ALL: only with
+// P * C == N.  What a launch is never made for is left out of its kernel (it is executed once from front to back, most
 // of it straight code that the instruction cache has not seen, and its size shows in its time).
-// IPT: sequences per lane at most, BAL_ROUNDS, or SMALL_IPT for a launch of up to SMALL_SORT_MAX sequences (FILL with
-// BAL_ROUNDS: for more than that).
-template <bool FILL, bool FEW, bool MANY, int IPT>
+// IPT: sequences per lane at most, BAL_ROUNDS, SMALL_IPT for a launch of up to SMALL_SORT_MAX sequences, or 1 (TAIL other than
+// BAL_ALL with BAL_ROUNDS: for more than SMALL_SORT_MAX).
+template <BalTail TAIL, bool FEW, bool MANY, int IPT>
 __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, int32_t C,
                                                const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                                int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
@@ -1392,7 +1396,8 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const int pitch = (P <= WAVE && equal) ? place_pitch(C) : 0;
     const bool tight = equal && P <= MULTI_MAX;                             // what the packed rounds serve
     const bool exact = pitch != 0 && (P == 16 || P == 32 || P == 64);      // a worker in every lane of a 16-, 32- or 64-lane sort
-    const bool small = IPT == SMALL_IPT || (!FILL && N <= SMALL_SORT_MAX);      // (uniform)
+    constexpr bool FILL = TAIL == BAL_SLOTS;
+    const bool small = IPT <= SMALL_IPT || (TAIL == BAL_ALL && N <= SMALL_SORT_MAX);      // (uniform)
     if (tight && !small) bin_sort_clear(L);                       // (the barrier below stands between this and the bins' use)
 
     // ---- load lengths, range (register q of a thread: sequence bal_item(q, rounds)) ----
@@ -1449,8 +1454,8 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         uint32_t* dst = reinterpret_cast<uint32_t*>(L.idx_a);
         bool sorted_to_dst = false;
         if (small) {                                              // (uniform)
-            if (rounds <= 1) small_sort_packed<1>(L, N, mine_len, dst);
-            else small_sort_packed<2>(L, N, mine_len, dst);
+            if (IPT == 1 || rounds <= 1) small_sort_packed<1>(L, N, mine_len, dst);
+            else if constexpr (IPT >= 2) small_sort_packed<2>(L, N, mine_len, dst);
             sorted_to_dst = true;
         } else if constexpr (IPT == BAL_ROUNDS) {
             sorted_to_dst = range != 0u && range <= BIN_RANGE_MAX && bin_sort_packed(L, N, (uint32_t)mx, range, mine_len, dst);     // (uniform)
@@ -1516,15 +1521,17 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                 const uint32_t e = rows[k * rpitch + r];
                 const uint32_t u = min(e & 0xFFFFu, (uint32_t)(N - 1));      // (no index leaves the arrays whatever a word holds)
                 perm[q] = (int32_t)u;
-                worker_of[u] = (uint32_t)k;
+                if constexpr (TAIL != BAL_PERM) worker_of[u] = (uint32_t)k;
                 if constexpr (FILL) { slots.seq[qq] = (int32_t)u; slots.len[qq] = (int32_t)(e >> 16); }
             }
             k += step_k;
             r += step_r;
             if (r >= C) { r -= C; k += 1; }
         });
-        lds_barrier();
-        for (int i = tid; i < N; i += BAL_BLOCK) shard_of_seq[i] = (int32_t)worker_of[i];
+        if constexpr (TAIL != BAL_PERM) {
+            lds_barrier();
+            for (int i = tid; i < N; i += BAL_BLOCK) shard_of_seq[i] = (int32_t)worker_of[i];
+        }
         return;
     }
 
@@ -1589,7 +1596,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             if (q < N) {
                 const int u = min((int)step_slot[k * pitch + r], N - 1);
                 perm[q] = u;
-                shard_of_seq[q] = L.keys[q];
+                if constexpr (TAIL != BAL_PERM) shard_of_seq[q] = L.keys[q];
                 if constexpr (FILL) {                             // (lengths of 2^16 and more: they are in global memory only)
                     const int32_t s = seq_len[u];
                     slots.seq[qq] = u;
@@ -1605,7 +1612,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     for (int t = tid; t < n_placed; t += BAL_BLOCK) {
         const int u = sorted[t];
         const int k = L.keys[u];                                  // the worker that took it
-        shard_of_seq[u] = k;
+        if constexpr (TAIL != BAL_PERM) shard_of_seq[u] = k;
         perm[part_off[k] + step_slot[t]] = u;
     }
     if constexpr (FILL && MANY) {                                 // (more than 64 workers, lengths of 2^16 and more)
@@ -1631,7 +1638,7 @@ __device__ __forceinline__ void balance_body(BalLds& L, int32_t N, int32_t P, in
                                              int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
                                              int64_t* __restrict__ shard_load, int32_t* status) {
     SlotRegs<BAL_ROUNDS> unused;
-    balance_body_t<false, true, true, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
+    balance_body_t<BAL_ALL, true, true, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
 }
 
 }  // namespace dc

@@ -48,9 +48,12 @@ struct Workspace {
     int64_t* gpre;           // [N + 1]  } only above DC_MAX_SEQ slots (else null): prefix of the slot lengths inside every tile of slots,
     int32_t* start_bits;     // [N / 32 + 2] slots that open a micro-batch, one bit each,
     int64_t* tile_tokens;    // [N / 64 + 1] tokens of every tile of slots
+    uint32_t* mb_counts;     // MB_COUNT_BYTES, only up to DC_MAX_SEQ slots (else null): micro-batches of every shard, on their way
+                             // between the workgroups of the plan by shards
     int64_t  n_gran;         // ceil(capacity / GATHER_GRAN) + GRAN_TABLE_PAD; entries past the arena hold N / no slot
     size_t   bytes;
 };
+constexpr int MB_COUNT_BYTES = 256;
 Workspace carve_workspace(void* base, int32_t n_seq, int64_t dst_capacity_tokens);
 
 struct SourceDesc {                       // by-value kernel argument
@@ -122,12 +125,12 @@ struct PlanArgs {
     int64_t* gpre;
     int32_t* start_bits;
     int64_t* tile_tokens;
-    // not null: the launch that balances and plans also builds the granule tables (small batches)
+    // the launch that balances and plans also builds the granule tables
     int32_t* gran_first;
     GranRec* gran_rec;
     int64_t  n_gran;
 };
-constexpr int SMALL_REC_SLOTS = 2048;
+constexpr int SMALL_REC_SLOTS = 128;           // (the line: see small_records)
 constexpr int64_t SMALL_REC_GRANS = 2048;
 
 PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, const int32_t* d_seq_len,
@@ -136,17 +139,28 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
                         int32_t* d_mb_seq_off, int32_t* d_cu_seqlens, int32_t* d_n_mb, const Workspace& ws,
                         int32_t* d_status);
 
-// Granule tables and per-slot source descriptors behind a plan that ran as the balance workgroup's tail
-// (p.slot_len holds the slots' lengths, nothing else of the per-slot arrays is filled yet).
-hipError_t launch_records_slots(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, hipStream_t st);
+// The whole plan behind launch_balance_advantage_perm (plan_shards.hip): every output of dc_plan, shard_of_seq, and the
+// workspace's tables.  Needs what launch_balance_plan_advantage needs, and plan_shards_serves.
+constexpr int PLAN_SHARDS_STAGED = 2048;         // slots of a shard up to which its slots' sources are staged in the LDS
+bool plan_shards_serves(int32_t n_seq, int32_t n_shards, int64_t dst_capacity);
+hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, const int64_t* d_shard_load,
+                              int32_t* d_shard_of_seq, hipStream_t st);
 
-// Balance, group advantage and the plan in one launch (workgroup 0: Algorithm 1, then the plan as its tail;
-// the other workgroups: the advantage stage).  Needs n_shards <= BAL_PLAN_MAX_SHARDS, cap_eff * n_shards == n_seq.
+// Balance, group advantage and the plan in one launch (workgroup 0: Algorithm 1, then the plan and the granule tables as its
+// tail; the other workgroups: the advantage stage).  Needs n_shards <= BAL_PLAN_MAX_SHARDS, cap_eff * n_shards == n_seq,
+// n_seq <= SMALL_REC_SLOTS.
 constexpr int BAL_PLAN_MAX_SHARDS = 256;
 hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
                                          int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
                                          int64_t* d_shard_load, const PlanArgs& plan, const AdvArgs& adv,
                                          const SourceDesc& src, int32_t n_groups, int32_t* d_status, hipStream_t st);
+
+// Balance and group advantage in one launch, for launch_plan_shards behind it: everything but shard_of_seq, and mb_counts
+// zeroed.  Needs n_shards <= BAL_PLAN_MAX_SHARDS, cap_eff * n_shards == n_seq.
+hipError_t launch_balance_advantage_perm(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
+                                         int32_t* d_perm, int32_t* d_shard_seq_off, int64_t* d_shard_load,
+                                         uint32_t* mb_counts, const AdvArgs& adv, const SourceDesc& src, int32_t n_groups,
+                                         int32_t* d_status, hipStream_t st);
 
 // The work of slots_kernel and plan_kernel for DC_MAX_SEQ < n_seq <= DC_MAX_SEQ_LARGE: many workgroups, the prefix and
 // the per-word tables in the workspace instead of the LDS.

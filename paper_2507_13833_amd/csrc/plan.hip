@@ -5,7 +5,8 @@
 // reaching into it and the record of the slots that do).
 //
 // O(N) integer work on at most DC_MAX_SEQ slots: latency-bound, so the plan proper runs as
-// ONE workgroup of 1024 lanes with everything staged in LDS.  Lane t handles slots t,
+// ONE workgroup of 1024 lanes with everything staged in LDS (behind Algorithm 1 as printed, whose shards are all alike:
+// plan_shards.hip).  Lane t handles slots t,
 // t + 1024, ... (every global access is coalesced):
 //   0. (slots_kernel, many workgroups) len = seq_len[perm[j]] and the rollout offset of every
 //      slot, validated: random gathers, which need more loads in flight than one CU has;
@@ -102,36 +103,6 @@ __global__ __launch_bounds__(REC_BLOCK) void records_kernel(RecArgs a) {
                  a.gran_first + g, a.gran_rec + g, found);
 }
 
-// The granule tables straight behind a launch that planned without slots_kernel (the plan as the balance
-// workgroup's tail, which leaves the slots' lengths in the workspace): the first workgroups build the records,
-// taking every slot's source through perm on the way; the others do slots_kernel's work for all slots (the
-// gather reads those arrays only for tiles with many short sequences).  Both validate alike, so a record
-// never depends on what the other workgroups have written yet.
-__global__ __launch_bounds__(REC_BLOCK) void records_slots_kernel(RecArgs a, PlanArgs p, SourceDesc sd, uint32_t rec_blocks) {
-    if (blockIdx.x < rec_blocks) {                               // (uniform)
-        __shared__ RecLds L;
-        const int64_t g = (int64_t)blockIdx.x * REC_BLOCK + threadIdx.x;
-        const bool usable = *a.plan_ok != 0;
-        int found = -1;
-        if (usable && a.n_seq > 0)
-            found = first_slot_after(L, a.n_seq, [&](int j) { return a.dst_tok_off[j]; }, min(g, a.n_gran - 1) * GATHER_GRAN);
-        if (g >= a.n_gran) return;
-        build_record(a.n_seq, usable, [&](int j) { return a.dst_tok_off[j]; },
-                     [&](int j, int32_t* ln, int64_t* so, int32_t* sh) { slot_source(p, sd, j, max(p.slot_len[j], 0), ln, so, sh); },
-                     g, a.gran_first + g, a.gran_rec + g, found);
-        return;
-    }
-    const int j = (int)(blockIdx.x - rec_blocks) * REC_BLOCK + (int)threadIdx.x;
-    if (j >= p.n_seq) return;
-    int32_t ln, sh;
-    int64_t so;
-    const int32_t had = p.slot_len[j];
-    slot_source(p, sd, j, max(had, 0), &ln, &so, &sh);
-    p.slot_src_off[j] = so;
-    p.slot_shard[j] = sh;
-    if (ln != had) p.slot_len[j] = ln;
-}
-
 hipError_t launch_plan(const dc_params& prm, const SourceDesc& src, const int64_t* d_src_tok_off,
                        const int32_t* d_seq_len, const int32_t* d_perm, const int32_t* d_shard_seq_off,
                        int64_t dst_capacity, int64_t* d_dst_tok_off, int64_t* d_shard_tok_off,
@@ -166,18 +137,6 @@ hipError_t launch_records(int32_t n_seq, const int64_t* d_dst_tok_off, const Wor
     r.slot_src_off = ws.slot_src_off; r.slot_len = ws.slot_len; r.slot_shard = ws.slot_shard;
     r.plan_ok = ws.plan_ok; r.gran_first = ws.gran_first; r.gran_rec = ws.gran_rec;
     hipLaunchKernelGGL(records_kernel, dim3((unsigned)((ws.n_gran + REC_BLOCK - 1) / REC_BLOCK)), dim3(REC_BLOCK), 0, st, r);
-    return hipGetLastError();
-}
-
-hipError_t launch_records_slots(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, hipStream_t st) {
-    RecArgs r;
-    r.n_seq = p.n_seq; r.n_gran = ws.n_gran; r.dst_tok_off = p.dst_tok_off;
-    r.slot_src_off = ws.slot_src_off; r.slot_len = ws.slot_len; r.slot_shard = ws.slot_shard;
-    r.plan_ok = ws.plan_ok; r.gran_first = ws.gran_first; r.gran_rec = ws.gran_rec;
-    if (p.gran_rec) return hipSuccess;                           // (built by the launch before, see small_records)
-    const unsigned rec_blocks = (unsigned)((ws.n_gran + REC_BLOCK - 1) / REC_BLOCK);
-    const unsigned slot_blocks = (unsigned)((p.n_seq + REC_BLOCK - 1) / REC_BLOCK);
-    hipLaunchKernelGGL(records_slots_kernel, dim3(rec_blocks + slot_blocks), dim3(REC_BLOCK), 0, st, r, p, src, rec_blocks);
     return hipGetLastError();
 }
 

@@ -493,14 +493,15 @@ __device__ __forceinline__ void build_record(int N, bool usable, Starts starts, 
 // behind plan_body), for a batch small enough that one workgroup is quicker with them than a launch of its own is started:
 // up to SMALL_REC_SLOTS slots and SMALL_REC_GRANS granules, the slots' starts and sources in the LDS behind the prefix.
 // src_off[q]: d_src_tok_off of the slots' sequences, asked for before the plan.
-// A launch of its own takes 5 to 7.5 us: steps of 64 and 512 sequences 26.8 -> 21.4 and 34.6 -> 29.7 us.  With 3200 granules
-// (2048 sequences of 1600 tokens) the two are level.
+// The line: a step of 48 / 64 / 128 sequences takes 17.7 / 19.8 / 22.5 us this way and 19.2 / 20.1 / 22.8 with the plan by shards
+// behind it (plan_shards.hip); at 256 the two are level, and 512 / 1024 / 2048 on 8 shards take 29.6 / 33.9 / 50.1 against
+// 28.5 / 31.7 / 44.5.
 struct SmallRecLds {
     int64_t start[SMALL_REC_SLOTS + 1];     // d_dst_tok_off
     int64_t src_off[SMALL_REC_SLOTS];
     int32_t lensh[SMALL_REC_SLOTS];         // length | rollout shard << LENSH_SHIFT
 };
-constexpr int SMALL_REC_IPT = SMALL_REC_SLOTS / PLAN_BLOCK;
+constexpr int SMALL_REC_IPT = (SMALL_REC_SLOTS + PLAN_BLOCK - 1) / PLAN_BLOCK;
 static_assert(sizeof(SmallRecLds) <= sizeof(int64_t) * (DC_MAX_SEQ - SMALL_REC_SLOTS), "it fits behind the prefix of as many slots");
 __device__ __forceinline__ void small_records(PlanLds& L, const PlanArgs& a, const SourceDesc& sd, const int32_t (&seq)[SMALL_REC_IPT],
                                               const int32_t (&len)[SMALL_REC_IPT], const int64_t (&src_off)[SMALL_REC_IPT], int fixed_c) {

@@ -1,0 +1,364 @@
+// The plan, the granule tables and the slots' sources behind a launch that has made perm with Algorithm 1 as printed (every
+// shard holds C slots), by a few workgroups per shard.
+//
+// Bound by latency: three trips to memory in a row (perm; the sequences' lengths and offsets; the outputs), whatever the
+// batch.  A shard's slots, its micro-batches and its stretch of the token axis concern nobody else, but for two sums over
+// the shards: where a shard's tokens start (the loads are known before this launch) and how many micro-batches the shards
+// before it hold.  So workgroup p walks shard p's micro-batches, P + slice * P + p writes a part of its slots and granules;
+// each of them makes the prefix of the shard's lengths for itself, and the only thing that travels between workgroups
+// is one count per shard.
+// 8.2 to 11 us (rocprofv3) on 8 to 128 shards of 64 to 640 slots, 3 M to 42 M tokens.  With the plan as the tail of the
+// balance workgroup (12 to 13 us, and 2 to 6 for shard_of_seq and the slots' lengths) and the tables in a launch behind it
+// (7.4 to 9.8) the two launches took: 2048 sequences on 8 shards 41 us, now 35; 15 360 on 24 112, now 95; 8192 on 32 72, now
+// 59; 16 384 on 64 106, now 90; 8192 on 128 66, now 50.
+#include "plan_device.h"
+
+namespace dc {
+
+struct ShardPlanArgs {
+    int32_t        C, slices;
+    const int64_t* shard_load;
+    int32_t*       shard_of_seq;
+    uint32_t*      mb_counts;        // zeroed by the launch before; see publish_count
+    int32_t*       gran_first;
+    GranRec*       gran_rec;
+    int64_t        n_gran;
+};
+
+// A shard's number of micro-batches, left where the others look for it: a word each up to 64 shards, above that a byte (a
+// shard then holds at most DC_MAX_SEQ / 65 slots).  Zero: not there yet.
+__device__ __forceinline__ int count_shift(int P, int p) { return P <= WAVE ? 0 : 8 * (p & 3); }
+__device__ __forceinline__ uint32_t* count_word(uint32_t* counts, int P, int p) { return counts + (P <= WAVE ? p : p >> 2); }
+__device__ __forceinline__ void publish_count(uint32_t* counts, int P, int p, int n) {
+    __hip_atomic_fetch_or(count_word(counts, P, p), (uint32_t)n << count_shift(P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// (Workgroups start in the order of their numbers, a walker's comes before that of any workgroup that waits for it, and it
+// leaves its count without waiting for anything itself: the loop ends.)
+__device__ __forceinline__ int wait_count(uint32_t* counts, int P, int p) {
+    const uint32_t mask = P <= WAVE ? 0xFFFFFFFFu : 0xFFu;
+    uint32_t n = 0;
+    while (true) {
+        n = (__hip_atomic_load(count_word(counts, P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> count_shift(P, p)) & mask;
+        if (n != 0) return (int)n;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+static_assert(DC_MAX_SEQ / (WAVE + 1) < 256, "a count of more than 64 shards fits a byte");
+static_assert(MB_COUNT_BYTES >= WAVE * 4 && MB_COUNT_BYTES >= BAL_PLAN_MAX_SHARDS, "a word or a byte per shard");
+
+constexpr int TAIL_SLOTS = 8;                // slots behind the shard's last one kept at hand (its last granule reaches into them)
+static_assert(TAIL_SLOTS > REC_SLOTS, "a record's slots");
+
+// BLOCK * IPT: slots of a shard at most.  STAGE: the slots' sources stand in the LDS too.
+template <int BLOCK, int IPT, bool STAGE, typename Pre>
+struct ShardPlanLds {
+    static constexpr int CAP = BLOCK * IPT, STEPS = IPT * (BLOCK / WAVE);
+    Pre pre[CAP + 1];                        // exclusive prefix of the slots' lengths inside the shard
+    union {
+        struct { uint16_t next[2][CAP + 1]; uint8_t opens[CAP]; } walk;
+        struct { int64_t src_off[STAGE ? CAP : 1]; int32_t lensh[STAGE ? CAP : 1]; } src;
+    };
+    int64_t base[BAL_PLAN_MAX_SHARDS + 1];   // aligned token offset of every shard
+    Pre     step_sum[STEPS];
+    int32_t step_count[STEPS];
+    int64_t tmp64[BLOCK / WAVE];
+    int32_t tmp32[BLOCK / WAVE];
+    int64_t tail_start[TAIL_SLOTS], tail_src[TAIL_SLOTS];
+    int32_t tail_len[TAIL_SLOTS], tail_lensh[TAIL_SLOTS];
+};
+
+// sum[q]: what the 64 slots of this wave's step q add up to (the same in every lane, or right in the last one); before[q]
+// gets the sum of everything in front of them (slots q * BLOCK + tid, so steps in (q, wave) order).  part: IPT * waves words.
+template <int BLOCK, int IPT, typename T>
+__device__ __forceinline__ T steps_before(const T (&sum)[IPT], T* part, T* tmp, T (&before)[IPT]) {
+    constexpr int WAVES = BLOCK / WAVE, STEPS = IPT * WAVES;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
+#pragma unroll
+    for (int q = 0; q < IPT; ++q)
+        if (lane == WAVE - 1) part[q * WAVES + w] = sum[q];
+    lds_barrier();
+    T total;
+    if constexpr (STEPS <= WAVE) {                                // every wave scans them for itself
+        const T v = lane < STEPS ? part[lane] : T(0);
+        const T upto = wave_incl_scan_add(v);
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) before[q] = wave_read_lane((T)(upto - v), q * WAVES + w);
+        total = wave_read_lane(upto, WAVE - 1);
+    } else {
+        static_assert(STEPS <= BLOCK, "a thread per step");
+        const T ex = block_excl_scan_add<T>(tid < STEPS ? part[tid] : T(0), tmp, &total);
+        if (tid < STEPS) part[tid] = ex;
+        lds_barrier();
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) before[q] = part[q * WAVES + w];
+    }
+    return total;
+}
+
+__device__ __forceinline__ int32_t sane_len(int32_t s) { return s > 0 && s <= DC_MAX_SEQ_LEN ? s : 1; }      // (the balance's own rule)
+
+template <int BLOCK, int IPT, bool STAGE, typename Pre>
+__global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDesc sd, ShardPlanArgs s) {
+    using Lds = ShardPlanLds<BLOCK, IPT, STAGE, Pre>;
+    __shared__ Lds L;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int N = a.n_seq, P = a.n_shards, C = s.C;
+    const bool walker = (int)blockIdx.x < P;
+    const int slice = walker ? -1 : ((int)blockIdx.x - P) / P;
+    const int p = (int)blockIdx.x - (slice + 1) * P;
+    const int j0 = p * C, j_end = j0 + C;
+    const int nq = (C + BLOCK - 1) / BLOCK;                       // (uniform) steps with slots at all, <= IPT
+
+    // ---- the shard's slots, and what a slice needs of the next ones ----
+    int32_t seq[IPT], len[IPT];
+    int64_t src[IPT];
+    const int64_t my_load = tid < P ? s.shard_load[tid] : 0;
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) seq[q] = q < nq ? a.perm[j0 + min(q * BLOCK + tid, C - 1)] : 0;
+    const int tail_j = j_end + tid;
+    const bool has_tail = !walker && tid < TAIL_SLOTS && tail_j < N;
+    int32_t tail_seq = has_tail ? a.perm[tail_j] : 0;
+    tail_seq = min(max(tail_seq, 0), N - 1);
+    const int32_t tail_len = has_tail ? sane_len(a.seq_len[tail_seq]) : 0;
+    const int64_t tail_src = has_tail ? a.src_tok_off[tail_seq] : 0;
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+        len[q] = 0;
+        src[q] = 0;
+        if (q < nq) {
+            seq[q] = min(max(seq[q], 0), N - 1);
+            len[q] = a.seq_len[seq[q]];
+            if (STAGE && !walker) src[q] = a.src_tok_off[seq[q]];
+        }
+    }
+    // ---- shard bases: exclusive scan of the loads, each rounded up to the alignment ----
+    {
+        const int64_t padded = a.align == 1 ? my_load : (my_load + a.align - 1) / a.align * a.align;      // (uniform)
+        int64_t end;
+        const int64_t b = block_excl_scan_add<int64_t>(padded, L.tmp64, &end);
+        if (tid < P) L.base[tid] = b;
+        if (tid == 0) L.base[P] = end;
+    }
+    // ---- prefix of the lengths ----
+    {
+        Pre inc[IPT], before[IPT];
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) {
+            len[q] = q < nq && q * BLOCK + tid < C ? sane_len(len[q]) : 0;
+            inc[q] = (Pre)wave_incl_scan_add_u32((uint32_t)len[q]);      // (64 lengths stay below 2^31)
+        }
+        const Pre total = steps_before<BLOCK, IPT, Pre>(inc, L.step_sum, reinterpret_cast<Pre*>(L.tmp64), before);
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) {
+            const int r = q * BLOCK + tid;
+            if (r < C) L.pre[r] = before[q] + inc[q] - (Pre)len[q];
+        }
+        if (tid == 0) L.pre[C] = total;
+    }
+
+    if (walker) {
+        // Every slot finds the end of the micro-batch that would open with it (a bisection, a lane's slots side by side).
+        // Then the hops are doubled, slots known to open one naming those 1, 2, 4, ... hops on, until a hop from the first
+        // slot leaves the shard: log2 of the number of micro-batches in rounds of two LDS reads, where following the
+        // chain takes a read (~130 cycles) for each.
+        lds_barrier();
+        const int first_step = 1 << (31 - __clz(C));
+        {
+            int lo[IPT];
+            Pre limit[IPT];
+#pragma unroll
+            for (int q = 0; q < IPT; ++q) {
+                const int r = min(q * BLOCK + tid, C - 1);
+                lo[q] = r + 1;
+                const uint64_t lim = (uint64_t)L.pre[r] + (uint64_t)a.budget;
+                limit[q] = sizeof(Pre) == 4 ? (Pre)min(lim, (uint64_t)0xFFFFFFFFull) : (Pre)lim;
+            }
+            for (int step = first_step; step >= 1; step >>= 1) {      // the last e in (r, C] that fits, or r + 1
+#pragma unroll
+                for (int q = 0; q < IPT; ++q) {
+                    if (q < nq) {                                 // (uniform)
+                        const int c = lo[q] + step;
+                        if (L.pre[min(c, C)] <= limit[q] && c <= C) lo[q] = c;
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < IPT; ++q) {
+                const int r = q * BLOCK + tid;
+                if (r < C) { L.walk.next[0][r] = (uint16_t)lo[q]; L.walk.opens[r] = r == 0; }
+            }
+            if (tid == 0) { L.walk.next[0][C] = (uint16_t)C; L.walk.next[1][C] = (uint16_t)C; }
+        }
+        int cur = 0;
+        for (;; cur ^= 1) {                                       // (at most log2(C) + 1 rounds: a hop moves on by a slot at least)
+            lds_barrier();
+            if ((int)L.walk.next[cur][0] >= C) break;             // (uniform)
+#pragma unroll
+            for (int q = 0; q < IPT; ++q) {
+                const int r = q * BLOCK + tid;
+                if (q < nq && r < C) {
+                    const int e = L.walk.next[cur][r];
+                    if (L.walk.opens[r] && e < C) L.walk.opens[e] = 1;      // (one that another lane has just named names a true one too)
+                    L.walk.next[cur ^ 1][r] = L.walk.next[cur][e];
+                }
+            }
+        }
+        // ---- micro-batch of every slot ----
+        uint16_t* const first_of = L.walk.next[cur ^ 1];          // (its last reader is a barrier behind)
+        int32_t mb[IPT], n_here[IPT], before[IPT];
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) {
+            const int r = q * BLOCK + tid;
+            const uint64_t opens = __ballot(q < nq && r < C && L.walk.opens[min(r, C - 1)] != 0);
+            n_here[q] = (int32_t)__popcll(opens);
+            mb[q] = (int32_t)__popcll(opens & (~0ull >> (WAVE - 1 - lane))) - 1;
+            len[q] = (int32_t)((opens >> lane) & 1ull);           // (the lengths are done with: does the slot open one)
+        }
+        const int32_t n_mb = steps_before<BLOCK, IPT, int32_t>(n_here, L.step_count, L.tmp32, before);
+        if (tid == 0) publish_count(s.mb_counts, P, p, n_mb);
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) {
+            mb[q] += before[q];
+            if (len[q]) first_of[mb[q]] = (uint16_t)(q * BLOCK + tid);
+        }
+        // ---- the micro-batches of the shards before this one ----
+        const int32_t theirs = tid < p ? wait_count(s.mb_counts, P, tid) : 0;
+        int32_t mb0;
+        block_excl_scan_add<int32_t>(theirs, L.tmp32, &mb0);
+        // ---- outputs (see plan_body: a slot stores the entry behind its own as well) ----
+#pragma unroll
+        for (int q = 0; q < IPT; ++q) {
+            const int r = q * BLOCK + tid, j = j0 + r;
+            if (q < nq && r < C) {
+                const int first = first_of[mb[q]];
+                const uint32_t g_first = (uint32_t)L.pre[first];  // (differences inside a micro-batch fit 32 bits)
+                const uint32_t m = (uint32_t)(mb0 + mb[q]);
+                a.mb_seq_off[m] = j0 + first;
+                a.cu_seqlens[(uint32_t)j + m] = (int32_t)((uint32_t)L.pre[r] - g_first);
+                a.cu_seqlens[(uint32_t)j + m + 1u] = (int32_t)((uint32_t)L.pre[r + 1] - g_first);
+            }
+        }
+        if (tid == 0) {
+            a.shard_mb_off[p] = mb0;
+            a.shard_tok_off[p] = L.base[p];
+            if (p == 0) *a.plan_ok = 1;
+            if (p == P - 1) {
+                const int64_t end = L.base[P];
+                a.shard_mb_off[P] = mb0 + n_mb;
+                *a.n_mb = mb0 + n_mb;
+                a.mb_seq_off[mb0 + n_mb] = N;
+                a.shard_tok_off[P] = end;
+                a.dst_tok_off[N] = end;
+                if (end > a.capacity) set_status(a.status, DC_ERR_OVERFLOW);
+            }
+        }
+        return;
+    }
+
+    // ---- the slots' sources ----
+    if (has_tail) {
+        int32_t ln, sh;
+        int64_t so;
+        slot_source_of(a, sd, tail_seq, true, tail_len, tail_src, &ln, &so, &sh);
+        L.tail_len[tid] = tail_len;
+        L.tail_lensh[tid] = ln | (sh << LENSH_SHIFT);
+        L.tail_src[tid] = so;
+    }
+    lds_barrier();
+    const int64_t base = L.base[p];
+    if (has_tail) {
+        const int k = tail_j / C;                                 // its shard, whose first slot (behind j_end) is here too
+        int64_t at = L.base[k];
+        for (int u = k * C - j_end; u < tid; ++u) at += L.tail_len[u];
+        L.tail_start[tid] = at;
+    }
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+        const int r = q * BLOCK + tid, j = j0 + r;
+        const bool mine = q % s.slices == slice;                  // (uniform) this workgroup writes the step's slots
+        if (q < nq && r < C && (STAGE || mine)) {
+            int32_t ln, sh;
+            int64_t so;
+            slot_source_of(a, sd, seq[q], true, len[q], STAGE ? src[q] : a.src_tok_off[seq[q]], &ln, &so, &sh);
+            if constexpr (STAGE) {
+                L.src.src_off[r] = so;
+                L.src.lensh[r] = ln | (sh << LENSH_SHIFT);
+            }
+            if (mine) {
+                a.dst_tok_off[j] = base + (int64_t)L.pre[r];
+                s.shard_of_seq[seq[q]] = p;
+                a.slot_src_off[j] = so;
+                a.slot_len[j] = ln;
+                a.slot_shard[j] = sh;
+            }
+        }
+    }
+    lds_barrier();
+    // ---- the granules whose first token lies in the shard's stretch ----
+    auto far_len = [&](int j) { return sane_len(a.seq_len[min(max(a.perm[j], 0), N - 1)]); };
+    auto starts = [&](int j) -> int64_t {                         // (j < N)
+        if (j < j_end) return base + (int64_t)L.pre[j - j0];
+        if (j - j_end < TAIL_SLOTS) return L.tail_start[j - j_end];
+        const int k = j / C;                                      // (only behind slots that fail a check)
+        int64_t at = L.base[k];
+        for (int u = k * C; u < j; ++u) at += far_len(u);
+        return at;
+    };
+    auto desc = [&](int j, int32_t* ln, int64_t* so, int32_t* sh) {
+        int32_t ls;
+        if (STAGE && j < j_end) {
+            ls = L.src.lensh[j - j0];
+            *so = L.src.src_off[j - j0];
+        } else if (j >= j_end && j - j_end < TAIL_SLOTS) {
+            ls = L.tail_lensh[j - j_end];
+            *so = L.tail_src[j - j_end];
+        } else {
+            slot_source(a, sd, j, far_len(j), ln, so, sh);
+            return;
+        }
+        *ln = ls & ((1 << LENSH_SHIFT) - 1);
+        *sh = ls >> LENSH_SHIFT;
+    };
+    const int64_t ga = (base + GATHER_GRAN - 1) / GATHER_GRAN;
+    const int64_t gb = min(s.n_gran, (L.base[p + 1] + GATHER_GRAN - 1) / GATHER_GRAN);
+    for (int64_t g = ga + slice * BLOCK + tid; g < gb; g += s.slices * BLOCK) {
+        const int64_t rel = g * GATHER_GRAN - base;
+        int lo = 0, hi = C;                                       // the first slot whose end lies behind the granule's first token
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if ((int64_t)L.pre[mid + 1] > rel) hi = mid; else lo = mid + 1;
+        }
+        build_record(N, true, starts, desc, g, s.gran_first + g, s.gran_rec + g, j0 + lo);
+    }
+    // ---- and the table's end, which no token reaches ----
+    const int64_t ge = (L.base[P] + GATHER_GRAN - 1) / GATHER_GRAN;
+    for (int64_t g = ge + ((int64_t)blockIdx.x - P) * BLOCK + tid; g < s.n_gran; g += (int64_t)P * s.slices * BLOCK)
+        build_record(N, false, starts, desc, g, s.gran_first + g, s.gran_rec + g);
+}
+
+bool plan_shards_serves(int32_t n_seq, int32_t n_shards, int64_t dst_capacity) {
+    // (above PLAN_SHARDS_STAGED slots the prefix has 32 bits)
+    return n_seq / n_shards <= PLAN_SHARDS_STAGED || dst_capacity < (int64_t)1 << 32;
+}
+
+hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, const int64_t* d_shard_load,
+                              int32_t* d_shard_of_seq, hipStream_t st) {
+    const int P = p.n_shards, C = p.n_seq / P;
+    if (P < 1 || P > BAL_PLAN_MAX_SHARDS || C < 1 || C * P != p.n_seq || p.n_seq > DC_MAX_SEQ || !ws.mb_counts)
+        return hipErrorInvalidValue;
+    ShardPlanArgs s;
+    s.C = C; s.shard_load = d_shard_load; s.shard_of_seq = d_shard_of_seq; s.mb_counts = ws.mb_counts;
+    s.gran_first = ws.gran_first; s.gran_rec = ws.gran_rec; s.n_gran = ws.n_gran;
+    auto launch = [&](auto kernel, int block) {
+        // a granule per thread, up to 1024 workgroups
+        const int64_t want = (ws.n_gran + (int64_t)P * block - 1) / ((int64_t)P * block);
+        s.slices = (int32_t)max((int64_t)1, min(want, (int64_t)(1024 / P)));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(P * (1 + s.slices))), dim3(block), 0, st, p, src, s);
+        return hipGetLastError();
+    };
+    static_assert(512 * 4 == PLAN_SHARDS_STAGED && 1024 * 16 == DC_MAX_SEQ, "what the two kernels hold");
+    if (C <= PLAN_SHARDS_STAGED) return launch(plan_shards_kernel<512, 4, true, int64_t>, 512);
+    return launch(plan_shards_kernel<1024, 16, false, uint32_t>, 1024);
+}
+
+}  // namespace dc

@@ -457,3 +457,84 @@ def test_scatter_with_offsets_that_do_not_rise(n):
         want[start[i]:start[i] + lens[i]] = tok[slot[i]] + np.arange(lens[i])
     got = d.back_fields[name][0].cpu().numpy()
     assert np.all((got == 0x7F7F7F7F) | (got == want))
+
+
+@pytest.mark.parametrize("n,shards,budget,align", [
+    (2049, 3, 41, 1), (2560, 5, 4096, 1),                # 512 slots of a shard and more: one and two steps of the workgroup
+    (2044, 4, 97, 9000), (2048, 4, 97, 9000), (2052, 4, 97, 9000),
+    (4094, 2, 1000, 6), (4096, 2, 41, 1), (4098, 2, 41, 1),      # the last whose sources are staged, and the first beyond
+    (16384, 1, 77, 1), (16384, 1, 1 << 20, 1), (16383, 3, 300, 16), (16384, 4, 5000, 1),
+    (16384, 64, 41, 1), (16320, 64, 2000, 16), (16380, 65, 41, 1), (16320, 255, 60, 3), (16384, 256, 2000, 1),
+])
+def test_plan_by_shards(n, shards, budget, align):
+    """Two launches: Algorithm 1, then workgroups that each plan a shard; shards of one slot to all of them, budgets from one
+    slot to a whole shard, a word and a byte for a shard's number of micro-batches."""
+    lens = np.random.default_rng(n + budget).integers(1, 41, n).astype(np.int32)
+    w = _custom(lens, 1, shards, budget, n_src=3 if n % 3 == 0 else 1, seed=n, fields=("i32",))
+    check_step(w, align=align, two_calls=True, label=f"{n} slots on {shards} shards, budget {budget}")
+
+
+@pytest.mark.parametrize("shards,per", [(256, 1), (256, 2), (200, 3), (128, 5), (100, 9), (64, 17)])
+@pytest.mark.parametrize("longest", [60000, 70000])
+def test_granules_that_many_small_shards_share(shards, per, longest):
+    """Granules whose record holds slots of the next shards, of which one granule holds dozens, beside long sequences."""
+    n = shards * per
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 12, n)
+    at = rng.permutation(n)[: 3200000 // longest]
+    lens[at] = rng.integers(longest - 2000, longest, len(at))
+    w = _custom(lens.astype(np.int32), 1, shards, 1 << 20, n_src=2 if n % 2 == 0 else 1, seed=n, fields=("i32",))
+    check_step(w, align=1 if per % 2 else 5, two_calls=True, label=f"{shards} shards of {per}")
+    check_gather_advantage(w, label=f"{shards} shards of {per}")
+
+
+@pytest.mark.parametrize("n,shards", [(4096, 64), (2560, 256), (12288, 3)])
+def test_plan_by_shards_with_slots_that_fail_a_check(n, shards):
+    """Sequences whose place in the rollout layout is refused take their tokens' room but move nothing, however many of them
+    stand in a row at a shard's end; all others are moved whole."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    w = _custom(rng.integers(1, 90, n).astype(np.int32), 1, shards, 4096, seed=n, fields=("i32",))
+    bal = oracle.balance(w.seq_len, shards)
+    bad = np.zeros(n, bool)                                      # (by slot)
+    per = n // shards
+    for k in range(1, shards, 3):
+        bad[k * per - rng.integers(0, per): k * per + rng.integers(0, 40)] = True
+    bad[-5:] = True
+    d = runner.DeviceBatch(w, align_tokens=3, poison=True)
+    d.adv_tok_src = None
+    grown = d.capacity + 3000 * 1024                             # (an arena above the single launch's limit)
+    d.capacity = grown
+    d.ws_bytes = binding.dc_workspace_bytes(d.prm, grown)
+    d.ws = torch.full((d.ws_bytes,), 0x7F, dtype=torch.uint8, device=d.dev)
+    dst = torch.full((grown,), 0x5A5A5A5A, dtype=torch.int32, device=d.dev)
+    name = w.fields[0].name
+    d.src_tok_off[torch.from_numpy(bal.perm[bad].astype(np.int64)).to(d.dev)] = -1
+    binding.dc_balance_plan_group_advantage(
+        d.prm, d.source, d.seq_len, d.perm, d.shard_seq_off, d.shard_of_seq, d.shard_load, d.reward, d.group_off, w.n_groups,
+        None, d.adv_seq, None, grown, d.dst_tok_off, d.shard_tok_off, d.shard_mb_off, d.mb_seq_off, d.cu_seqlens, d.n_mb,
+        d.ws, d.ws_bytes, d.status)
+    binding.dc_gather(d.prm, d.source, binding.Fields([(d.src_fields[name], dst, 4)]), grown, d.dst_tok_off, d.ws, d.ws_bytes,
+                      d.status)
+    torch.cuda.synchronize()
+    assert d.read_status() == binding.DC_ERR_BAD_LAYOUT
+    pl = oracle.plan(w.seq_len, bal.perm, bal.shard_seq_off, w.token_budget, 3)
+    assert np.array_equal(d.perm.cpu().numpy(), bal.perm) and np.array_equal(d.dst_tok_off.cpu().numpy(), pl.dst_tok_off)
+    assert np.array_equal(d.shard_mb_off.cpu().numpy(), pl.shard_mb_off)
+    want = np.full(grown, 0x5A5A5A5A, np.int32)
+    for j in np.flatnonzero(~bad):
+        i = bal.perm[j]
+        want[pl.dst_tok_off[j]:pl.dst_tok_off[j] + w.seq_len[i]] = w.fields[0].shards[0][w.src_tok_off[i]:][:w.seq_len[i]]
+    assert np.array_equal(dst.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,shards", [(1, 1), (64, 4), (127, 127), (128, 2), (128, 128), (129, 3)])
+@pytest.mark.parametrize("entries", [17, 1040, 2048, 2049])
+def test_single_launch_of_a_very_small_batch(n, shards, entries):
+    """Up to 128 sequences and 2048 table entries in one launch; one sequence and one entry more in two."""
+    tokens = (entries - 16) * 1024
+    rng = np.random.default_rng(n + entries)
+    lens = rng.integers(max(1, tokens // n // 3), max(2, tokens // n), n)
+    lens[n // 2] += tokens - int(lens.sum())
+    w = _custom(lens.astype(np.int32), 1, shards, 1 << 22, n_src=3 if n % 3 == 0 else 1, seed=n, fields=("i32",))
+    check_step(w, two_calls=True, label=f"{n} sequences, {entries} entries")
