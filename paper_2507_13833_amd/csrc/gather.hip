@@ -33,7 +33,10 @@ namespace dc {
 
 constexpr int GATHER_BLOCK = 256;
 static_assert(GRAN_PER_TILE == GATHER_BLOCK / WAVE, "one granule per wave");
-constexpr int64_t GATHER_RIDE_MIN_WGS = 8192;                         // ~4 workgroups per wave slot of the chip
+// Carrier workgroups from which the narrow fields ride (the chip holds 1792).  Steps of 6 M tokens with 2, 3 and
+// 5 carriers (3000, 4500 and 7500 workgroups): 66.3 -> 65.4 us, 65.2 -> 64.1, 82.7 -> 80.2; of 2 M with 5 and 3.2 M with 2
+// (2500, 1600): 40.9 -> 41.3, 53.5 -> 55.2.
+constexpr int64_t GATHER_RIDE_MIN_WGS = 3000;
 constexpr int32_t LEN_MASK = (1 << LENSH_SHIFT) - 1;
 static_assert(GATHER_GRAN == WAVE * 16, "a wave covers its granule with 1, 2 or 4 chunks per lane");
 static_assert(GRAN_PER_TILE + 1 <= 8, "the tile's slice of the granule table is one 8-dword scalar load");
@@ -133,153 +136,163 @@ struct SlotS {
     int64_t ad;
 };
 
-// The elements of one 16-byte chunk that does not lie inside one slot, on their way.
-struct BoundaryChunk {
-    uint32_t val[16];
-    uint32_t ok;             // bit r: element r exists (belongs to a slot, inside the arena) and was loaded
-    int32_t  c0;             // the chunk's first token inside the granule
+// The 16-byte chunks of a granule that do not lie inside one slot: those that a slot's end (or the arena's) falls into and,
+// where slots do not follow each other without a gap, those that a slot's start falls into.  Eight at most, known from the
+// record alone, and moved one element per lane, eight, or four chunks of 1-byte elements, at a time.
+// (c: an edge's chunk, its first token / 4, one byte each; there: which of the eight exist.  Slots' ends first.)
+struct Edges {
+    uint64_t c;
+    uint32_t there;
 };
-
-template <int LG>
-__device__ __forceinline__ void boundary_load(const SlotS (&e)[REC_SLOTS], bool mine, int32_t limit, BoundaryChunk& bc) {
-#pragma unroll
-    for (int r = 0; r < (16 >> LG); ++r) {
-        const int32_t t = bc.c0 + r;
-        int32_t e_sel = INT32_MIN;
-        int64_t a_sel = 0;
-#pragma unroll
-        for (int k = 0; k < REC_SLOTS; ++k)
-            if (t >= e[k].st) { e_sel = e[k].en; a_sel = e[k].ad; }
-        bc.val[r] = 0;
-        if (mine && t < e_sel && t < limit) {
-            bc.ok |= 1u << r;
-            bc.val[r] = load_elem(LG, reinterpret_cast<gptr>(a_sel + ((int64_t)t << LG)));
-        }
-    }
-}
-
-template <int LG>
-__device__ __forceinline__ void boundary_store(gptr_w dst, const BoundaryChunk& bc) {
-#pragma unroll
-    for (int r = 0; r < (16 >> LG); ++r)
-        if (bc.ok & (1u << r)) store_elem(LG, dst + ((int64_t)(bc.c0 + r) << LG), bc.val[r]);
-}
-
-// The wave's granule (1024 tokens: es chunks per lane) of one tile, served from the granule's
-// record.  `limit` = tokens of the granule that exist in the arena (> 0).
-// BACK: destination and only source are given (back_dst, back_src) instead of fd's.
-template <bool BACK>
-__device__ __forceinline__ void move_wave_sparse(const FieldDesc& fd, int n_src, char* back_dst, const char* back_src,
-                                                 int lg, const u32x16& rec, int64_t wave_begin, int32_t limit) {
-    const int es = 1 << lg;
-    const int tpc = 16 >> lg;                              // tokens per 16-byte chunk
-    const int tpi = WAVE * tpc;                            // tokens one wave instruction covers
-    int lane = threadIdx.x & (WAVE - 1);
-    gptr_w dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(BACK ? back_dst : fd.dst) + (wave_begin << lg));
-
-    SlotS e[REC_SLOTS];
+__device__ __forceinline__ Edges granule_edges(const SlotS (&e)[REC_SLOTS], int tpc, int32_t limit) {
+    Edges d;
+    d.c = 0;
+    d.there = 0;
+    int32_t before = INT32_MIN;                            // end of the slot before
 #pragma unroll
     for (int k = 0; k < REC_SLOTS; ++k) {
-        const int32_t st = (int32_t)rec[4 * k], ls = (int32_t)rec[4 * k + 1];
-        const int64_t so = (int64_t)((uint64_t)rec[4 * k + 2] | ((uint64_t)rec[4 * k + 3] << 32));
-        const char* base = BACK ? back_src : fd.src[0];
-        if (!BACK && n_src > 1) base = fd.src[(ls >> LENSH_SHIFT) & (DC_MAX_SRC_SHARDS - 1)];
-        e[k].st = st;
-        e[k].en = st + (ls & LEN_MASK);
-        e[k].ad = reinterpret_cast<int64_t>(base) + ((so - st) << lg);
+        const int32_t en = min(e[k].en, limit), st = e[k].st;
+        if (en > 0 && en < GATHER_GRAN && (en & (tpc - 1)) != 0) d.there |= 1u << k;
+        if (st > 0 && st < limit && st != before && (st & (tpc - 1)) != 0) d.there |= 16u << k;
+        d.c |= (uint64_t)((uint32_t)(en & -tpc) >> 2 & 0xFFu) << (8 * k);
+        d.c |= (uint64_t)((uint32_t)(st & -tpc) >> 2 & 0xFFu) << (8 * (REC_SLOTS + k));
+        before = e[k].en;
+    }
+    return d;
+}
+
+// One element of the edges, per lane: edges from_edge + lane / tpc.
+struct EdgeElem {
+    uint32_t val;
+    int32_t  tok;            // the element's token inside the granule, -1: nothing there
+};
+// (select(t): the record's slot at token t)
+__device__ __forceinline__ int32_t edge_token(const Edges& d, int lg_tpc, int lane, int from_edge) {
+    const int q = from_edge + (lane >> lg_tpc);
+    const int32_t t = (int32_t)((uint32_t)(d.c >> (8 * (q & 7))) & 0xFFu) * 4 + (lane & ((1 << lg_tpc) - 1));
+    return q < 2 * REC_SLOTS && ((d.there >> q) & 1u) ? t : -1;
+}
+__device__ __forceinline__ EdgeElem edge_load(const SlotS (&e)[REC_SLOTS], const Edges& d, int lg, int lane, int from_edge, int32_t limit) {
+    EdgeElem x;
+    const int32_t t = edge_token(d, 4 - lg, lane, from_edge);
+    int32_t e_sel = INT32_MIN;
+    int64_t a_sel = 0;
+#pragma unroll
+    for (int k = 0; k < REC_SLOTS; ++k)
+        if (t >= e[k].st) { e_sel = e[k].en; a_sel = e[k].ad; }
+    x.tok = t >= 0 && t < e_sel && t < limit ? t : -1;
+    x.val = 0;
+    if (x.tok >= 0) x.val = load_elem(lg, reinterpret_cast<gptr>(a_sel + ((int64_t)t << lg)));
+    return x;
+}
+__device__ __forceinline__ void edge_store(gptr_w dst, int lg, const EdgeElem& x) {
+    if (x.tok >= 0) store_elem(lg, dst + ((int64_t)x.tok << lg), x.val);
+}
+
+// The wave's granule (1024 tokens: es chunks per lane) of one field, on its way from the granule's slots (its record) to
+// its place.  MAXU: chunks per lane at most, 4, or 2 for fields of 1- and 2-byte elements.
+template <int MAXU>
+struct SparseMove {
+    static constexpr int NARROWU = 2;                      // chunks per lane of 1- and 2-byte elements
+    u32x4    v[MAXU];
+    uint32_t x[NARROWU], shift[NARROWU];                   // (4-byte sources are 4-byte aligned)
+    uint32_t in_mask;                                      // bit u: chunk u is inside one slot
+    bool     part;                                         // (uniform) not every chunk is
+    EdgeElem edge;
+    gptr_w   dst;
+
+    // `limit` = tokens of the granule that exist in the arena (> 0).  BACK: destination and only source are given (back_dst,
+    // back_src) instead of fd's.
+    template <bool BACK>
+    __device__ __forceinline__ void slots(SlotS (&e)[REC_SLOTS], const FieldDesc& fd, int n_src, const char* back_src, int lg,
+                                          const u32x16& rec) const {
+#pragma unroll
+        for (int k = 0; k < REC_SLOTS; ++k) {
+            const int32_t st = (int32_t)rec[4 * k], ls = (int32_t)rec[4 * k + 1];
+            const int64_t so = (int64_t)((uint64_t)rec[4 * k + 2] | ((uint64_t)rec[4 * k + 3] << 32));
+            const char* base = BACK ? back_src : fd.src[0];
+            if (!BACK && n_src > 1) base = fd.src[(ls >> LENSH_SHIFT) & (DC_MAX_SRC_SHARDS - 1)];
+            e[k].st = st;
+            e[k].en = st + (ls & LEN_MASK);
+            e[k].ad = reinterpret_cast<int64_t>(base) + ((so - st) << lg);
+        }
     }
 
-    constexpr int MAXU = 4;                                // chunks per lane: es of them are used
-    uint32_t in_mask = 0, bnd_mask = 0;                    // bit u: chunk u is inside one slot / needs the element path
-    gptr from[MAXU];
+    template <bool BACK>
+    __device__ __forceinline__ void load(const FieldDesc& fd, int n_src, char* back_dst, const char* back_src, int lg,
+                                         const u32x16& rec, int64_t wave_begin, int32_t limit) {
+        const int es = 1 << lg;
+        const int tpc = 16 >> lg;                          // tokens per 16-byte chunk
+        const int tpi = WAVE * tpc;                        // tokens one wave instruction covers
+        const int lane = threadIdx.x & (WAVE - 1);
+        dst = reinterpret_cast<gptr_w>(reinterpret_cast<uintptr_t>(BACK ? back_dst : fd.dst) + (wave_begin << lg));
+        SlotS e[REC_SLOTS];
+        slots<BACK>(e, fd, n_src, back_src, lg, rec);
+        in_mask = 0;
+        part = false;
+        gptr from[MAXU];
 #pragma unroll
-    for (int u = 0; u < MAXU; ++u) {
-        from[u] = nullptr;
-        if (u < es) {                                      // uniform
-            const int32_t lo = u * tpi;                    // the instruction's first token inside the granule
-            const int32_t c0 = lo + lane * tpc;            // my chunk's first token
-            // scalar: the slot of the instruction's first token; does it cover all 64 chunks?
-            int32_t s_en = INT32_MIN;
-            int64_t s_ad = 0;
-#pragma unroll
-            for (int k = 0; k < REC_SLOTS; ++k)
-                if (lo >= e[k].st) { s_en = e[k].en; s_ad = e[k].ad; }
-            if (s_en >= lo + tpi && lo + tpi <= limit) {   // uniform: one slot, no search per lane
-                in_mask |= 1u << u;
-                from[u] = reinterpret_cast<gptr>(s_ad + ((int64_t)c0 << lg));
-            } else {
-                int32_t e_sel = INT32_MIN;
-                int64_t a_sel = 0;
-#pragma unroll
-                for (int k = 0; k < REC_SLOTS; ++k)
-                    if (c0 >= e[k].st) { e_sel = e[k].en; a_sel = e[k].ad; }
-                const bool in = c0 + tpc <= e_sel && c0 + tpc <= limit;
-                if (in) in_mask |= 1u << u;
-                else if (c0 < limit) bnd_mask |= 1u << u;
-                from[u] = reinterpret_cast<gptr>(a_sel + ((int64_t)c0 << lg));
-            }
-        }
-    }
-    // ---- chunks inside one slot: loads ----
-    u32x4 v[MAXU];
-    uint32_t x[MAXU];
-#pragma unroll
-    for (int u = 0; u < MAXU; ++u)
-        if (in_mask & (1u << u)) load_chunk(from[u], v[u], x[u]);
-    // ---- a chunk that touches a slot boundary, padding or the arena end is moved element by
-    // element; the loads of a lane's first such chunk go out with the loads above, so a wave
-    // with a sequence boundary in its granule (two waves in five) pays no second round trip
-    const bool any_bnd = __ballot(bnd_mask != 0) != 0ull;                   // uniform
-    BoundaryChunk bc;
-    bc.ok = 0; bc.c0 = 0;
-    if (any_bnd) {
-        bc.c0 = (bnd_mask ? __builtin_ctz(bnd_mask) : 0) * tpi + lane * tpc;
-        if (lg == 2) boundary_load<2>(e, bnd_mask != 0, limit, bc);
-        else if (lg == 1) boundary_load<1>(e, bnd_mask != 0, limit, bc);
-        else boundary_load<0>(e, bnd_mask != 0, limit, bc);
-    }
-    // ---- stores ----
-#pragma unroll
-    for (int u = 0; u < MAXU; ++u)
-        if (in_mask & (1u << u)) {
-            const uint32_t sh = (uint32_t)reinterpret_cast<uintptr_t>(from[u]) & 3u;
-            gstore16(dst + (u * WAVE + lane) * 16, realign(v[u], x[u], sh));
-        }
-    if (!any_bnd) return;
-    if (lg == 2) boundary_store<2>(dst, bc);
-    else if (lg == 1) boundary_store<1>(dst, bc);
-    else boundary_store<0>(dst, bc);
-    // ---- further boundary chunks of the same lane (sequences shorter than a wave instruction) ----
-    const uint32_t rest = bnd_mask & (bnd_mask - 1);
-    if (__ballot(rest != 0) == 0ull) return;                                // uniform
-#pragma unroll 1
-    for (int u = 1; u < es; ++u) {
-        const bool mine = (rest >> u) & 1u;
-        if (__ballot(mine) == 0ull) continue;                               // uniform
-        const int32_t c0 = u * tpi + lane * tpc;
-        constexpr int EB = 4;                                               // elements in flight; divides 4, 8, 16
-#pragma unroll 1
-        for (int e0 = 0; e0 < tpc; e0 += EB) {
-            uint32_t val[EB];
-            bool ok[EB];
-#pragma unroll
-            for (int r = 0; r < EB; ++r) {
-                const int32_t t = c0 + e0 + r;
-                int32_t e_sel = INT32_MIN;
-                int64_t a_sel = 0;
+        for (int u = 0; u < MAXU; ++u) {
+            from[u] = nullptr;
+            if (u < es) {                                  // uniform
+                const int32_t lo = u * tpi;                // the instruction's first token inside the granule
+                const int32_t c0 = lo + lane * tpc;        // my chunk's first token
+                // scalar: the slot of the instruction's first token; does it cover all 64 chunks?
+                int32_t s_en = INT32_MIN;
+                int64_t s_ad = 0;
 #pragma unroll
                 for (int k = 0; k < REC_SLOTS; ++k)
-                    if (t >= e[k].st) { e_sel = e[k].en; a_sel = e[k].ad; }
-                ok[r] = mine && t < e_sel && t < limit;
-                val[r] = 0;
-                if (ok[r]) val[r] = load_elem(lg, reinterpret_cast<gptr>(a_sel + ((int64_t)t << lg)));
-            }
+                    if (lo >= e[k].st) { s_en = e[k].en; s_ad = e[k].ad; }
+                if (s_en >= lo + tpi && lo + tpi <= limit) {   // uniform: one slot, no search per lane
+                    in_mask |= 1u << u;
+                    from[u] = reinterpret_cast<gptr>(s_ad + ((int64_t)c0 << lg));
+                } else {
+                    part = true;
+                    int32_t e_sel = INT32_MIN;
+                    int64_t a_sel = 0;
 #pragma unroll
-            for (int r = 0; r < EB; ++r)
-                if (ok[r]) store_elem(lg, dst + ((int64_t)(c0 + e0 + r) << lg), val[r]);
+                    for (int k = 0; k < REC_SLOTS; ++k)
+                        if (c0 >= e[k].st) { e_sel = e[k].en; a_sel = e[k].ad; }
+                    if (c0 + tpc <= e_sel && c0 + tpc <= limit) in_mask |= 1u << u;
+                    from[u] = reinterpret_cast<gptr>(a_sel + ((int64_t)c0 << lg));
+                }
+            }
         }
+#pragma unroll
+        for (int u = 0; u < MAXU; ++u)
+            if (in_mask & (1u << u)) {
+                if (u < NARROWU) {
+                    shift[u] = (uint32_t)reinterpret_cast<uintptr_t>(from[u]) & 3u;
+                    load_chunk(from[u], v[u], x[u]);
+                } else {
+                    v[u] = gload16_a4(from[u]);
+                }
+            }
+        // the edges' elements go out with the loads above, so a wave with a sequence boundary in its granule (two waves in
+        // five, or all of them) pays no second round trip
+        edge.tok = -1;
+        edge.val = 0;
+        if (part) edge = edge_load(e, granule_edges(e, tpc, limit), lg, lane, 0, limit);
     }
-}
+
+    template <bool BACK>
+    __device__ __forceinline__ void store(const FieldDesc& fd, int n_src, const char* back_src, int lg, const u32x16& rec,
+                                          int32_t limit) const {
+        const int lane = threadIdx.x & (WAVE - 1);
+#pragma unroll
+        for (int u = 0; u < MAXU; ++u)
+            if (in_mask & (1u << u)) gstore16(dst + (u * WAVE + lane) * 16, u < NARROWU ? realign(v[u], x[u], shift[u]) : v[u]);
+        if (!part) return;                                 // (uniform)
+        edge_store(dst, lg, edge);
+        if (lg != 0) return;
+        // (1-byte elements: four chunks took the 64 lanes; slots' starts behind a gap are left)
+        SlotS e[REC_SLOTS];
+        slots<BACK>(e, fd, n_src, back_src, lg, rec);
+        const Edges d = granule_edges(e, 16, limit);
+        if ((d.there >> REC_SLOTS) == 0u) return;
+        edge_store(dst, lg, edge_load(e, d, lg, lane, REC_SLOTS, limit));
+    }
+};
 
 // ---------------------------------------------------------------- dense granules: one wave, LDS words of its own
 // The slots that reach into a granule, relative to its first token, DENSE_SLOTS at a time.  A pass serves the tokens
@@ -336,7 +349,7 @@ __device__ __forceinline__ int dense_first_step(int n) {
     return 1 << (31 - __builtin_clz((uint32_t)max(n, 1)));
 }
 
-// The wave's granule of one field, slots first .. last reaching into it (same arguments as move_wave_sparse otherwise).
+// The wave's granule of one field, slots first .. last reaching into it (same arguments as SparseMove::load otherwise).
 template <bool BACK>
 __device__ __forceinline__ void move_wave_dense(const GatherArgs& a, WaveSlots& sg, const FieldDesc& fd, int n_src,
                                                 char* back_dst, const char* back_src, int lg, int first, int last,
@@ -719,10 +732,29 @@ __device__ __forceinline__ void move_tile(const GatherArgs& a, const FieldTable&
     auto next_field = [&](uint32_t f) { return f < a.n_carriers ? a.n_carriers + f : f + a.n_carriers; };
     auto lg_of = [&](const FieldDesc& fd) { return fd.elem_bytes == 4 ? 2 : (fd.elem_bytes == 2 ? 1 : 0); };
     if (g.last - g.first < REC_SLOTS) {
-        for (uint32_t f = fc; f < n; f = next_field(f)) {
-            const FieldDesc& fd = ft.f[f];
-            move_wave_sparse<BACK>(fd, ft.n_src, BACK ? const_cast<char*>(fd.src[seg]) : nullptr, BACK ? fd.dst : nullptr, lg_of(fd),
-                                   g.rec, wave_begin, g.limit);
+        // (a wave's loads and stores retire in one order, so a field's loads issued behind another's stores wait for those:
+        //  the first rider's go out in front of the carrier's stores)
+        auto load = [&](auto& m, const FieldDesc& fd) {
+            m.template load<BACK>(fd, ft.n_src, BACK ? const_cast<char*>(fd.src[seg]) : nullptr, BACK ? fd.dst : nullptr, lg_of(fd), g.rec,
+                                  wave_begin, g.limit);
+        };
+        auto store = [&](auto& m, const FieldDesc& fd) {
+            m.template store<BACK>(fd, ft.n_src, BACK ? fd.dst : nullptr, lg_of(fd), g.rec, g.limit);
+        };
+        SparseMove<4> m;
+        load(m, ft.f[fc]);
+        uint32_t f = next_field(fc);
+        if (f < n) {                                              // (uniform)
+            SparseMove<2> r;
+            load(r, ft.f[f]);
+            store(m, ft.f[fc]);
+            store(r, ft.f[f]);
+            for (f = next_field(f); f < n; f = next_field(f)) {
+                load(r, ft.f[f]);
+                store(r, ft.f[f]);
+            }
+        } else {
+            store(m, ft.f[fc]);
         }
     } else {
         for (uint32_t f = fc; f < n; f = next_field(f)) {

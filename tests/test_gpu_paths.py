@@ -538,3 +538,18 @@ def test_single_launch_of_a_very_small_batch(n, shards, entries):
     lens[n // 2] += tokens - int(lens.sum())
     w = _custom(lens.astype(np.int32), 1, shards, 1 << 22, n_src=3 if n % 3 == 0 else 1, seed=n, fields=("i32",))
     check_step(w, two_calls=True, label=f"{n} sequences, {entries} entries")
+
+
+@pytest.mark.parametrize("align", [1, 7, 16])
+@pytest.mark.parametrize("lo,hi", [(300, 900), (900, 5000)])
+def test_edges_of_granules_with_riders(lo, hi, align):
+    """Up to four slots to a granule, their ends and starts anywhere in a 16-byte chunk, with and without padding between
+    shards, in an arena large enough that the narrow fields ride on the 4-byte fields' waves; both directions."""
+    rng = np.random.default_rng(lo + align)
+    n = 12 * (6400000 // 12 // ((lo + hi) // 2))
+    lens = rng.integers(lo, hi, n).astype(np.int32)
+    w = _custom(lens, 4, 12, 1 << 15, n_src=3, seed=lo + align)
+    check_step(w, align=align, label=f"{n} sequences, riders", two_calls=n <= 16384)
+    if align == 7:
+        check_gather_advantage(w, align=align, label=f"{n} sequences, riders")
+        check_scatter(w, label=f"{n} sequences, riders")
