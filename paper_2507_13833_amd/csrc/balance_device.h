@@ -616,7 +616,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     const uint32_t lane = threadIdx.x;
     const uint32_t G = (uint32_t)__builtin_amdgcn_readfirstlane(max_len) << 6;    // see lpt_rounds for the rebasing
     const uint32_t fit = (3u << 30) / max(G, 1u);
-    const int check_every = (int)min(64u, fit - 2u);
+    const int check_every = (int)min(256u, fit - 2u);
     int until_check = 1;
     const uint32_t full = KEY_FULL | lane;
     const bool mine_exists = (int)lane < P;                       // lane k keeps worker k ...
