@@ -219,7 +219,7 @@ hipError_t launch_balance_large(int32_t n_seq, int32_t n_shards, int32_t cap_eff
     int32_t* idx_b = idx_a + n;
     int32_t* sorted_len = idx_b + n;
     uint32_t* counts = reinterpret_cast<uint32_t*>(sorted_len + n);
-    hipError_t e = launch_sort_large(n_seq, d_seq_len, idx_a, idx_b, sorted_len, counts, d_status, st);
+    hipError_t e = launch_sort_large(n_seq, d_seq_len, idx_a, idx_b, sorted_len, d_shard_of_seq, counts, d_status, st);
     if (e != hipSuccess) return e;
     BalanceLargeWs ws;
     ws.sorted = idx_b;

@@ -87,7 +87,7 @@ hipError_t launch_balance_large(int32_t n_seq, int32_t n_shards, int32_t cap_eff
 // Indices by descending length (stable), by many workgroups (sort_large.hip).
 size_t sort_large_table_bytes(int32_t n_seq);
 hipError_t launch_sort_large(int32_t n_seq, const int32_t* d_seq_len, int32_t* d_idx_a, int32_t* d_idx_b,
-                             int32_t* d_sorted_len, uint32_t* d_counts, int32_t* d_status, hipStream_t st);
+                             int32_t* d_sorted_len, int32_t* d_spare, uint32_t* d_counts, int32_t* d_status, hipStream_t st);
 
 struct AdvArgs;
 hipError_t launch_balance_advantage(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,

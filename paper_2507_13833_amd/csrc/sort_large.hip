@@ -7,8 +7,12 @@
 //            by wave, lanes with equal digits matched by ballots), and moves the indices; the last pass also
 //            writes the lengths in sorted order.
 // No workgroup ever waits for another inside a launch; the launches of a pass order them.
-#include "dc_device.h"
-#include "dc_internal.h"
+//
+// Up to SORT_PORTIONS * SORT_PORTION sequences two launches take the place of the nine: a workgroup sorts a portion of the
+// sequences in its LDS (as dc_balance sorts its own), then every element counts, in each other portion, the elements that
+// come before it.  Bound by latency: the nine take 4 to 7 us each whatever they do, 47 us for 65 536 sequences; these two
+// take 22 (12 + 10).  A portion more costs every element a search more, a larger one its workgroup a longer sort.
+#include "balance_device.h"
 
 namespace dc {
 
@@ -137,16 +141,190 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_scatter_kernel(SortArgs a) {
     }
 }
 
+constexpr int SORT_PORTION = 8192;
+constexpr int SORT_PORTIONS = 16;
+static_assert(SORT_PORTION <= DC_MAX_SEQ && SORT_PORTION <= 0x10000, "a portion fits the LDS, a place in it 16 bits");
+
+// Workgroup b: portion b by descending length, equal lengths in index order: lengths to len_out, indices to idx_out.
+__global__ __launch_bounds__(BAL_BLOCK) void sort_portions_kernel(int32_t n_all, const int32_t* __restrict__ seq_len,
+                                                                  int32_t* __restrict__ len_out, int32_t* __restrict__ idx_out,
+                                                                  int32_t* status) {
+    __shared__ BalLds L;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
+    const int first = blockIdx.x * SORT_PORTION, N = min(SORT_PORTION, n_all - first);
+    const int rounds = (N + BAL_BLOCK - 1) / BAL_BLOCK;
+    constexpr int USED = SORT_PORTION / BAL_BLOCK;
+    bin_sort_clear(L);                                            // (the barrier below stands between this and the bins' use)
+    int32_t len[BAL_ROUNDS];
+#pragma unroll
+    for (int q = 0; q < BAL_ROUNDS; ++q) len[q] = q < USED ? seq_len[first + min(bal_item(q, rounds), N - 1)] : 1;
+    int32_t mx = 0, mn = INT32_MAX;
+#pragma unroll
+    for (int q = 0; q < USED; ++q) {
+        const bool mine = q < rounds && bal_item(q, rounds) < N;
+        const int32_t s = sort_len(len[q]);
+        if (mine && s != len[q]) set_status(status, DC_ERR_ZERO_LENGTH_SEQ);
+        len[q] = mine ? s : 1;
+        mx = max(mx, mine ? s : 0);
+        mn = min(mn, mine ? s : INT32_MAX);
+    }
+    wave_all_reduce([&](auto j) {
+        constexpr int J = decltype(j)::value;
+        const uint32_t hi = lane_xor<J>((uint32_t)mx), lo = lane_xor<J>((uint32_t)mn);
+        mx = max(mx, (int32_t)hi);
+        mn = min(mn, (int32_t)lo);
+    });
+    if (lane == 0) { L.red[w] = mx; L.red[BAL_WAVES + w] = mn; }
+    lds_barrier();
+    mx = 0; mn = INT32_MAX;
+    for (int i = 0; i < BAL_WAVES; ++i) { mx = max(mx, L.red[i]); mn = min(mn, L.red[BAL_WAVES + i]); }
+    const uint32_t range = (uint32_t)(mx - mn);
+    const int passes = range == 0 ? 0 : (32 - __clz(range) + 7) / 8;
+    if ((uint32_t)mx <= PACKED_MAX_LEN) {                         // (uniform) words of length << 16 | place in the portion
+        uint32_t* src = reinterpret_cast<uint32_t*>(L.keys);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(L.idx_a);
+        if (range != 0u && range <= BIN_RANGE_MAX && bin_sort_packed(L, N, (uint32_t)mx, range, len, dst)) {
+            src = dst;
+        } else {
+            lds_barrier();
+#pragma unroll
+            for (int q = 0; q < USED; ++q) {
+                const int i = bal_item(q, rounds);
+                if (q < rounds && i < N) src[i] = ((uint32_t)len[q] << 16) | (uint32_t)i;
+            }
+            lds_barrier();
+            for (int pass = 0; pass < passes; ++pass) {
+                const int shift = pass * 8;
+                counting_pass(L, N, rounds,
+                              [&](int pos) { return ((uint32_t)mx - (src[pos] >> 16)) >> shift; },
+                              [&](int pos, int out) { dst[out] = src[pos]; });
+                uint32_t* t = src; src = dst; dst = t;
+            }
+        }
+        for (int i = tid; i < N; i += BAL_BLOCK) {
+            const uint32_t e = src[i];
+            len_out[first + i] = (int32_t)(e >> 16);
+            idx_out[first + i] = first + (int32_t)(e & 0xFFFFu);
+        }
+        return;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < USED; ++q) {
+        const int i = bal_item(q, rounds);
+        if (q < rounds && i < N) { L.keys[i] = len[q]; L.idx_a[i] = (uint16_t)i; }
+    }
+    uint16_t* src = L.idx_a;
+    uint16_t* dst = L.idx_b;
+    lds_barrier();
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = pass * 8;
+        counting_pass(L, N, rounds,
+                      [&](int pos) { return ((uint32_t)(mx - L.keys[src[pos]])) >> shift; },
+                      [&](int pos, int out) { dst[out] = src[pos]; });
+        uint16_t* t = src; src = dst; dst = t;
+    }
+    for (int i = tid; i < N; i += BAL_BLOCK) {
+        len_out[first + i] = L.keys[src[i]];
+        idx_out[first + i] = first + (int32_t)src[i];
+    }
+}
+
+// Every element's place among all portions: its place in its own, and in each other one the elements before it, which
+// are those that are longer, and of an earlier portion those of its length too.  512 evenly spaced lengths of every portion
+// stand in the LDS (one read of memory), what lies between two of them is bisected where it is.  PORTIONS: at most; up to eight
+// side by side.
+template <int PORTIONS>
+__global__ __launch_bounds__(SORT_BLOCK) void sort_merge_kernel(int32_t n_all, const int32_t* __restrict__ len_in,
+                                                                const int32_t* __restrict__ idx_in, int32_t* __restrict__ len_out,
+                                                                int32_t* __restrict__ idx_out) {
+    constexpr int SAMPLES = 512, STRIDE = SORT_PORTION / SAMPLES, SIDE = PORTIONS < 8 ? PORTIONS : 8;
+    __shared__ int32_t sample[PORTIONS][SAMPLES];
+    static_assert(STRIDE * SAMPLES == SORT_PORTION && SAMPLES % SORT_BLOCK == 0 && (STRIDE & (STRIDE - 1)) == 0, "whole stretches");
+    const int tid = threadIdx.x;
+    const int n_portions = (n_all + SORT_PORTION - 1) / SORT_PORTION;
+    {
+        int32_t x[PORTIONS][SAMPLES / SORT_BLOCK];                // (every load is issued before the first is looked at)
+#pragma unroll
+        for (int b = 0; b < PORTIONS; ++b)
+#pragma unroll
+            for (int s = 0; s < SAMPLES / SORT_BLOCK; ++s)
+                x[b][s] = len_in[min(b * SORT_PORTION + (s * SORT_BLOCK + tid) * STRIDE, n_all - 1)];
+#pragma unroll
+        for (int b = 0; b < PORTIONS; ++b)
+#pragma unroll
+            for (int s = 0; s < SAMPLES / SORT_BLOCK; ++s)        // (behind the last element: shorter than any)
+                sample[b][s * SORT_BLOCK + tid] = b * SORT_PORTION + (s * SORT_BLOCK + tid) * STRIDE < n_all ? x[b][s] : 0;
+    }
+    const int t = blockIdx.x * SORT_BLOCK + tid;
+    const int32_t mine = len_in[min(t, n_all - 1)], idx = idx_in[min(t, n_all - 1)];
+    const int own = (int)(blockIdx.x * SORT_BLOCK) / SORT_PORTION;        // (uniform)
+    __syncthreads();
+    int place = min(t, n_all - 1) - own * SORT_PORTION;
+    for (int b0 = 0; b0 < n_portions; b0 += SIDE) {               // (uniform)
+        int lo[SIDE], hi[SIDE], size[SIDE];
+        int32_t limit[SIDE];                                      // an element comes before mine if it is longer than this
+#pragma unroll
+        for (int k = 0; k < SIDE; ++k) {
+            const int b = min(b0 + k, n_portions - 1);
+            limit[k] = b < own ? mine - 1 : mine;
+            size[k] = min(SORT_PORTION, n_all - b * SORT_PORTION);
+            lo[k] = 0;
+        }
+#pragma unroll
+        for (int step = SAMPLES / 2; step >= 1; step >>= 1) {     // samples before mine, all but the last looked at
+#pragma unroll
+            for (int k = 0; k < SIDE; ++k)
+                if (sample[min(b0 + k, n_portions - 1)][lo[k] + step - 1] > limit[k]) lo[k] += step;
+        }
+#pragma unroll
+        for (int k = 0; k < SIDE; ++k) {
+            if (sample[min(b0 + k, n_portions - 1)][lo[k]] > limit[k]) lo[k] += 1;
+            hi[k] = min(lo[k] * STRIDE, size[k]);
+            lo[k] = min(max(lo[k] * STRIDE - STRIDE + 1, 0), hi[k]);
+        }
+#pragma unroll
+        for (int step = STRIDE; step >= 1; step >>= 1) {          // STRIDE + 1 places at most are left
+#pragma unroll
+            for (int k = 0; k < SIDE; ++k) {
+                const int mid = (lo[k] + hi[k]) >> 1;
+                const int32_t x = len_in[min(min(b0 + k, n_portions - 1) * SORT_PORTION + mid, n_all - 1)];
+                if (lo[k] < hi[k]) { if (x > limit[k]) lo[k] = mid + 1; else hi[k] = mid; }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < SIDE; ++k)
+            if (b0 + k < n_portions && b0 + k != own) place += lo[k];
+    }
+    if (t < n_all) {
+        place = min(place, n_all - 1);
+        len_out[place] = mine;
+        idx_out[place] = idx;
+    }
+}
+
 // Bytes of the (digit, tile) table for n sequences.
 size_t sort_large_table_bytes(int32_t n_seq) {
     const size_t tiles = ((size_t)n_seq + SORT_TILE - 1) / SORT_TILE;
     return 256 * (tiles + 1) * sizeof(uint32_t);                  // the (digit, tile) counts, then the digits' totals
 }
 
-// d_idx_a, d_idx_b, d_sorted_len: arrays of n_seq int32; d_counts: sort_large_table_bytes(n_seq).  The passes go
-// identity -> b, b -> a, a -> b: the sorted indices end in d_idx_b, their lengths in d_sorted_len, d_idx_a is free again.
+// d_idx_a, d_idx_b, d_sorted_len, d_spare: arrays of n_seq int32; d_counts: sort_large_table_bytes(n_seq).  The passes go
+// identity -> b, b -> a, a -> b: the sorted indices end in d_idx_b, their lengths in d_sorted_len, the others are free again.
 hipError_t launch_sort_large(int32_t n_seq, const int32_t* d_seq_len, int32_t* d_idx_a, int32_t* d_idx_b,
-                             int32_t* d_sorted_len, uint32_t* d_counts, int32_t* d_status, hipStream_t st) {
+                             int32_t* d_sorted_len, int32_t* d_spare, uint32_t* d_counts, int32_t* d_status, hipStream_t st) {
+    if (n_seq <= SORT_PORTIONS * SORT_PORTION) {
+        hipLaunchKernelGGL(sort_portions_kernel, dim3((unsigned)((n_seq + SORT_PORTION - 1) / SORT_PORTION)), dim3(BAL_BLOCK), 0, st,
+                           n_seq, d_seq_len, d_spare, d_idx_a, d_status);
+        auto merge = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((n_seq + SORT_BLOCK - 1) / SORT_BLOCK)), dim3(SORT_BLOCK), 0, st, n_seq, d_spare,
+                               d_idx_a, d_sorted_len, d_idx_b);
+        };
+        if (n_seq <= 4 * SORT_PORTION) merge(sort_merge_kernel<4>);
+        else if (n_seq <= 8 * SORT_PORTION) merge(sort_merge_kernel<8>);
+        else merge(sort_merge_kernel<SORT_PORTIONS>);
+        return hipGetLastError();
+    }
     SortArgs a;
     a.n = n_seq;
     a.n_tiles = (n_seq + SORT_TILE - 1) / SORT_TILE;

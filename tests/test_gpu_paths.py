@@ -553,3 +553,13 @@ def test_edges_of_granules_with_riders(lo, hi, align):
     if align == 7:
         check_gather_advantage(w, align=align, label=f"{n} sequences, riders")
         check_scatter(w, label=f"{n} sequences, riders")
+
+
+@pytest.mark.parametrize("kind", ["geometric", "equal", "long", "rising", "few"])
+@pytest.mark.parametrize("n", [16385, 24576, 24577, 32769, 65536, 65537, 131072, 131073])
+def test_sort_by_portions(n, kind):
+    """Portions of 8192 sequences, sorted each and merged by counting: the last portion of one sequence and a whole one, four,
+    eight and sixteen portions and one more, lengths that many sequences of every portion share, and lengths of 2^16 and more."""
+    rng = np.random.default_rng(n)
+    lens = np.arange(n) % 40000 + 1 if kind == "rising" else rng.integers(5, 9, n) if kind == "few" else _lengths(kind, n, rng)
+    _check_balance_ws(lens.astype(np.int32), 8, cap=-(-n // 8) if n % 8 else 0, label=f"{n} sequences, {kind}")
