@@ -20,12 +20,14 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_kernel(AdvArgs a, SourceD
     advantage_wave(a, sd, (int64_t)blockIdx.x * ADV_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));   // one wave per sequence
 }
 
-// The stage for many short sequences: a wave takes ADV_SEQS consecutive ones, lane k finds sequence k's place, group and
+// The stage for many short sequences: a wave takes SEQS consecutive ones, lane k finds sequence k's place, group and
 // advantage by itself (the same sums in the same order), and the wave then streams their tokens, four sequences' mask
 // words in flight at a time, the first four's asked for ahead of the statistics.
 // With a wave per sequence every lane of it works out the same statistics, ~350 vector instructions in float64 for a
 // sequence whose tokens take ten, and 65 536 of those are the stage's time: 69.0 us for 28 M tokens in 65 536 sequences,
-// 43.3 with eight to a wave (four and sixteen: 7 to 10 % more).  Below 16 384 sequences there are not enough waves left (8192
+// 44.1 with eight to a wave (four: 46.2; 32 768 of 600 take 30.1 and 30.3, 24 576 of 500 23.2 and 20.9, 16 384 of 300 15.3 and
+// 13.0).  A wave waits for nothing but its groups' loads: while the ragged heads and tails, three tokens each, were read where
+// they are written, each such read waited for the stores in front of it (48.0).  Below 16 384 sequences there are not enough waves left (8192
 // of 57 tokens 10.4 -> 11.4), and longer ones want their tokens spread over more waves; the line is the mean above which
 // the stage with a quarter of its sequences past the four steps is slower so (16 384 of 326 18.3 / 18.4, of 469 20.6 / 22.9;
 // 24 576 of 416 27.1 / 27.8, of 678 32.2 / 34.8; 32 768 of 792 44.0 / 41.3; 49 152 of 998 69.3 / 68.5).
@@ -33,7 +35,6 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_kernel(AdvArgs a, SourceD
 // neighbours, as the answers to one prompt are, every one in another set), and take them with all their waves and
 // ADV_UNROLL steps in flight.  16 384 sequences of 190 tokens, 64 of 32 K among them: 28.9 us with a wave per sequence, 17.9
 // here (64 at a stretch: 22.4 and 17.2), where the wave that met them took 98 and 450.
-constexpr int ADV_SEQS = 8;                            // sequences of a wave
 constexpr int ADV_GROUP = 4;                           // sequences in flight
 constexpr int ADV_STEPS = 4;                           // 4-token chunks per lane of one of them in flight
 constexpr int ADV_REST = 8;                            // the same of a longer one's rest
@@ -43,12 +44,14 @@ constexpr int ADV_SETS = 509;                          // (half as many: a Paret
 constexpr int ADV_BRIEF_MIN_SEQ = 16384;               // a wave per sequence fills the chip's wave slots twice
 constexpr int ADV_BRIEF_MAX_MEAN = ADV_STEPS * WAVE * 4;       // (what the four steps take)
 constexpr int ADV_BRIEF_SEQ_PER_TOKEN = 48;            // sequences per token of the mean length, at least
-static_assert(ADV_SEQS % ADV_GROUP == 0 && ADV_SEQS <= WAVE, "a lane per sequence");
+constexpr int ADV_EIGHT_MIN_SEQ = 32768;               // eight sequences to a wave from here on, four below
 
 __device__ __forceinline__ bool adv_long(int32_t ln) { return ln >= ADV_LONG && ln <= DC_MAX_SEQ_LEN; }
 
 // (bounded to eight waves to a SIMD: the long ones' code alone would take the scalar registers of one of them)
+template <int SEQS>
 __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a, SourceDesc sd) {
+    static_assert(SEQS % ADV_GROUP == 0 && SEQS <= WAVE, "a lane per sequence");
     const int lane = threadIdx.x & (WAVE - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int N = a.n_seq;
@@ -68,8 +71,8 @@ __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a
         }
         return;
     }
-    const int64_t first = ((int64_t)(blockIdx.x - ADV_SETS) * ADV_WAVES + w) * ADV_SEQS;
-    if (lane < ADV_SEQS && first + lane <= a.n_groups) {             // group table: [0] = 0, non-decreasing, last = N
+    const int64_t first = ((int64_t)(blockIdx.x - ADV_SETS) * ADV_WAVES + w) * SEQS;
+    if (lane < SEQS && first + lane <= a.n_groups) {             // group table: [0] = 0, non-decreasing, last = N
         const int g = (int)first + lane;
         const int32_t v = a.group_off[g];
         bool bad = v < 0 || v > N || (g == 0 && v != 0) || (g == a.n_groups && v != N);
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a
     }
     if (first >= N) return;
     // ---- lane k: sequence first + k (lanes beyond the last one repeat it and store nothing) ----
-    const int n = (int)min((int64_t)ADV_SEQS, N - first);            // (uniform)
+    const int n = (int)min((int64_t)SEQS, N - first);            // (uniform)
     const int i = (int)first + min(lane, n - 1);
     const int64_t so = a.src_tok_off[i], so_next = a.src_tok_off[min(i + 1, N - 1)];
     const int32_t ln = a.seq_len[i];
@@ -109,23 +112,30 @@ __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a
     const int64_t begin = so, end = none ? so : so + ln;
 
     // ---- the wave's view of sequence k ----
+    // (all of it uniform; lanes add 32-bit offsets, so an access costs no address arithmetic of its own)
     struct Seq {
-        const uint8_t* mask;
+        const uint8_t* mask;                                          // of its first token
         float* out;
-        int64_t begin, a4, e4, end;                                   // ragged head up to a4, 4-aligned body, ragged tail from e4
+        int32_t a4, e4, end;                                          // ragged head up to a4, body in whole 16-byte chunks, ragged tail from e4
     };
     auto seq = [&](int k) {
         Seq q;
         const int sh = __builtin_amdgcn_readlane(s, k);
-        q.mask = a.mask[sh];
-        q.out = a.adv_tok[sh];
-        q.begin = wave_read_lane(begin, k);
-        q.end = wave_read_lane(end, k);
-        q.a4 = min(q.end, (q.begin + 3) & ~int64_t(3));
-        q.e4 = max(q.a4, q.end & ~int64_t(3));
+        const int64_t at = wave_read_lane(begin, k);
+        q.mask = a.mask[sh] + at;
+        q.out = a.adv_tok[sh] + at;
+        q.end = (int32_t)(wave_read_lane(end, k) - at);
+        const int32_t head = (int32_t)(-at) & 3;
+        q.a4 = min(q.end, head);
+        q.e4 = max(q.a4, ((q.end - head) & ~3) + head);
         return q;
     };
     uint32_t mk[ADV_GROUP][ADV_STEPS];
+    uint32_t ends[ADV_GROUP];                                        // lanes 0 .. 2: the head's mask bytes, 32 .. 34: the tail's
+    auto end_token = [&](const Seq& q) {                             // (-1: none)
+        const int32_t t = lane < 32 ? lane : q.e4 + (lane - 32);
+        return (lane & 31) < 3 && t < (lane < 32 ? q.a4 : q.end) ? t : -1;
+    };
     auto load_group = [&](int k0) {
 #pragma unroll
         for (int k = 0; k < ADV_GROUP; ++k) {
@@ -133,9 +143,12 @@ __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a
             const Seq q = seq(k0 + k);
 #pragma unroll
             for (int u = 0; u < ADV_STEPS; ++u) {
-                const int64_t c = q.a4 + (u * WAVE + lane) * 4;
-                mk[k][u] = c < q.e4 ? load4(q.mask + c) : 0u;
+                const uint32_t c = (uint32_t)(u * WAVE + lane) * 4u;
+                mk[k][u] = (int32_t)c < q.e4 - q.a4 ? load4(q.mask + q.a4 + c) : 0u;
             }
+            const int32_t t = end_token(q);
+            ends[k] = 0;
+            if (t >= 0) ends[k] = q.mask[(uint32_t)t];
         }
     };
     load_group(0);
@@ -166,7 +179,7 @@ __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a
 
     // ---- the tokens ----
 #pragma unroll
-    for (int k0 = 0; k0 < ADV_SEQS; k0 += ADV_GROUP) {
+    for (int k0 = 0; k0 < SEQS; k0 += ADV_GROUP) {
         if (k0 >= n) break;                                           // (uniform)
         if (k0 > 0) load_group(k0);
 #pragma unroll
@@ -174,25 +187,24 @@ __global__ __launch_bounds__(ADV_BLOCK, 8) void advantage_brief_kernel(AdvArgs a
             if (k0 + k >= n) continue;                               // (uniform)
             const Seq q = seq(k0 + k);
             const uint32_t av = (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(adv), k0 + k);
-            const float af = __uint_as_float(av);
-            if (lane < 3 && q.begin + lane < q.a4) q.out[q.begin + lane] = q.mask[q.begin + lane] ? af : 0.0f;
-            if (lane >= 32 && lane < 35 && q.e4 + (lane - 32) < q.end) q.out[q.e4 + lane - 32] = q.mask[q.e4 + lane - 32] ? af : 0.0f;
+            const int32_t t = end_token(q);
+            if (t >= 0) q.out[(uint32_t)t] = ends[k] ? __uint_as_float(av) : 0.0f;
 #pragma unroll
             for (int u = 0; u < ADV_STEPS; ++u) {
-                const int64_t c = q.a4 + (u * WAVE + lane) * 4;
-                if (c < q.e4) store16(q.out + c, select_by_mask(mk[k][u], av));
+                const uint32_t c = (uint32_t)(u * WAVE + lane) * 4u;
+                if ((int32_t)c < q.e4 - q.a4) store16(q.out + q.a4 + c, select_by_mask(mk[k][u], av));
             }
-            for (int64_t c0 = q.a4 + ADV_STEPS * WAVE * 4; c0 < q.e4; c0 += ADV_REST * WAVE * 4) {       // (uniform) a longer one's rest
+            for (int32_t c0 = q.a4 + ADV_STEPS * WAVE * 4; c0 < q.e4; c0 += ADV_REST * WAVE * 4) {       // (uniform) a longer one's rest
                 uint32_t more[ADV_REST];
 #pragma unroll
                 for (int u = 0; u < ADV_REST; ++u) {
-                    const int64_t c = c0 + (u * WAVE + lane) * 4;
-                    more[u] = c < q.e4 ? load4(q.mask + c) : 0u;
+                    const uint32_t c = (uint32_t)(u * WAVE + lane) * 4u;
+                    more[u] = (int32_t)c < q.e4 - c0 ? load4(q.mask + c0 + c) : 0u;
                 }
 #pragma unroll
                 for (int u = 0; u < ADV_REST; ++u) {
-                    const int64_t c = c0 + (u * WAVE + lane) * 4;
-                    if (c < q.e4) store16(q.out + c, select_by_mask(more[u], av));
+                    const uint32_t c = (uint32_t)(u * WAVE + lane) * 4u;
+                    if ((int32_t)c < q.e4 - c0) store16(q.out + c0 + c, select_by_mask(more[u], av));
                 }
             }
         }
@@ -224,8 +236,12 @@ hipError_t launch_advantage(int32_t n_seq, const SourceDesc& src, const int64_t*
     int64_t tokens = 0;
     for (int s = 0; s < src.n_src; ++s) tokens += src.tokens[s];
     if (a.per_token && n_seq >= ADV_BRIEF_MIN_SEQ && tokens / n_seq <= std::min(ADV_BRIEF_MAX_MEAN, n_seq / ADV_BRIEF_SEQ_PER_TOKEN)) {
-        const int64_t blocks = (adv_waves(n_seq, n_groups) + ADV_WAVES * ADV_SEQS - 1) / (ADV_WAVES * ADV_SEQS);
-        hipLaunchKernelGGL(advantage_brief_kernel, dim3((unsigned)blocks + ADV_SETS), dim3(ADV_BLOCK), 0, st, a, src);
+        auto launch = [&](auto kernel, int seqs) {
+            const int64_t blocks = (adv_waves(n_seq, n_groups) + ADV_WAVES * seqs - 1) / (ADV_WAVES * seqs);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)blocks + ADV_SETS), dim3(ADV_BLOCK), 0, st, a, src);
+        };
+        if (n_seq >= ADV_EIGHT_MIN_SEQ) launch(advantage_brief_kernel<8>, 8);
+        else launch(advantage_brief_kernel<4>, 4);
         return hipGetLastError();
     }
     const int64_t grid = (adv_waves(n_seq, n_groups) + ADV_WAVES - 1) / ADV_WAVES;
