@@ -38,10 +38,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 TRAFFIC_SOURCE = "profiles/hbm_traffic_config5_pmc.txt"
 TRAFFIC = {
     # config: (fetch bytes + write bytes per gather launch, digest of csrc/gather.hip + csrc/dc_internal.h)
-    5: (1048419400 + 984391000, "35c91ec1d2c0cb9c"),
+    5: (1040842000 + 983683000, "6383be69c7a7e02a"),
 }
 TRAFFIC_ADV = {                                          # the same for dc_gather_advantage's kernel
-    5: (868199900 + 983670800, "35c91ec1d2c0cb9c"),
+    5: (866161100 + 983153000, "6383be69c7a7e02a"),
 }
 
 
