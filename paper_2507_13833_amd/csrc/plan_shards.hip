@@ -32,16 +32,18 @@ __device__ __forceinline__ uint32_t* count_word(uint32_t* counts, int P, int p) 
 __device__ __forceinline__ void publish_count(uint32_t* counts, int P, int p, int n) {
     __hip_atomic_fetch_or(count_word(counts, P, p), (uint32_t)n << count_shift(P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// (Workgroups start in the order of their numbers, a walker's comes before that of any workgroup that waits for it, and it
-// leaves its count without waiting for anything itself: the loop ends.)
+// The count, or 0 if it has not come after WAIT_LOOKS looks (a few hundred us; it comes within one or two).
+// Nothing says that all walkers are on the chip at once, so nobody waits for another without an end: a walker whose look
+// stays empty counts that shard itself (with WAIT_LOOKS = 0 every walker counts all shards before its own: same outputs).
+constexpr int WAIT_LOOKS = 512;
 __device__ __forceinline__ int wait_count(uint32_t* counts, int P, int p) {
     const uint32_t mask = P <= WAVE ? 0xFFFFFFFFu : 0xFFu;
-    uint32_t n = 0;
-    while (true) {
-        n = (__hip_atomic_load(count_word(counts, P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> count_shift(P, p)) & mask;
+    for (int look = 0; look < WAIT_LOOKS; ++look) {
+        const uint32_t n = (__hip_atomic_load(count_word(counts, P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> count_shift(P, p)) & mask;
         if (n != 0) return (int)n;
         __builtin_amdgcn_s_sleep(1);
     }
+    return 0;
 }
 static_assert(DC_MAX_SEQ / (WAVE + 1) < 256, "a count of more than 64 shards fits a byte");
 static_assert(MB_COUNT_BYTES >= WAVE * 4 && MB_COUNT_BYTES >= BAL_PLAN_MAX_SHARDS, "a word or a byte per shard");
@@ -63,6 +65,7 @@ struct ShardPlanLds {
     int32_t step_count[STEPS];
     int64_t tmp64[BLOCK / WAVE];
     int32_t tmp32[BLOCK / WAVE];
+    int32_t missing;                         // the first shard whose count has not come
     int64_t tail_start[TAIL_SLOTS], tail_src[TAIL_SLOTS];
     int32_t tail_len[TAIL_SLOTS], tail_lensh[TAIL_SLOTS];
 };
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
         if (tid == 0) L.base[P] = end;
     }
     // ---- prefix of the lengths ----
-    {
+    auto prefix = [&]() {
         Pre inc[IPT], before[IPT];
 #pragma unroll
         for (int q = 0; q < IPT; ++q) {
@@ -154,77 +157,107 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
             if (r < C) L.pre[r] = before[q] + inc[q] - (Pre)len[q];
         }
         if (tid == 0) L.pre[C] = total;
-    }
+    };
+    prefix();
 
     if (walker) {
         // Every slot finds the end of the micro-batch that would open with it (a bisection, a lane's slots side by side).
         // Then the hops are doubled, slots known to open one naming those 1, 2, 4, ... hops on, until a hop from the first
         // slot leaves the shard: log2 of the number of micro-batches in rounds of two LDS reads, where following the
         // chain takes a read (~130 cycles) for each.
-        lds_barrier();
         const int first_step = 1 << (31 - __clz(C));
-        {
-            int lo[IPT];
-            Pre limit[IPT];
-#pragma unroll
-            for (int q = 0; q < IPT; ++q) {
-                const int r = min(q * BLOCK + tid, C - 1);
-                lo[q] = r + 1;
-                const uint64_t lim = (uint64_t)L.pre[r] + (uint64_t)a.budget;
-                limit[q] = sizeof(Pre) == 4 ? (Pre)min(lim, (uint64_t)0xFFFFFFFFull) : (Pre)lim;
-            }
-            for (int step = first_step; step >= 1; step >>= 1) {      // the last e in (r, C] that fits, or r + 1
+        int target = p;                                           // the shard that is walked: the workgroup's own, unless
+        bool published = false;                                   // another's count does not come
+        int32_t theirs = 0, mb0 = 0, n_mb = 0;                    // thread k < p: shard k's count
+        int32_t mb[IPT];
+        uint16_t* first_of = nullptr;
+        for (;;) {
+            lds_barrier();
+            {
+                int lo[IPT];
+                Pre limit[IPT];
 #pragma unroll
                 for (int q = 0; q < IPT; ++q) {
-                    if (q < nq) {                                 // (uniform)
-                        const int c = lo[q] + step;
-                        if (L.pre[min(c, C)] <= limit[q] && c <= C) lo[q] = c;
+                    const int r = min(q * BLOCK + tid, C - 1);
+                    lo[q] = r + 1;
+                    const uint64_t lim = (uint64_t)L.pre[r] + (uint64_t)a.budget;
+                    limit[q] = sizeof(Pre) == 4 ? (Pre)min(lim, (uint64_t)0xFFFFFFFFull) : (Pre)lim;
+                }
+                for (int step = first_step; step >= 1; step >>= 1) {      // the last e in (r, C] that fits, or r + 1
+#pragma unroll
+                    for (int q = 0; q < IPT; ++q) {
+                        if (q < nq) {                                 // (uniform)
+                            const int c = lo[q] + step;
+                            if (L.pre[min(c, C)] <= limit[q] && c <= C) lo[q] = c;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < IPT; ++q) {
+                    const int r = q * BLOCK + tid;
+                    if (r < C) { L.walk.next[0][r] = (uint16_t)lo[q]; L.walk.opens[r] = r == 0; }
+                }
+                if (tid == 0) { L.walk.next[0][C] = (uint16_t)C; L.walk.next[1][C] = (uint16_t)C; }
+            }
+            int cur = 0;
+            for (;; cur ^= 1) {                                       // (at most log2(C) + 1 rounds: a hop moves on by a slot at least)
+                lds_barrier();
+                if ((int)L.walk.next[cur][0] >= C) break;             // (uniform)
+#pragma unroll
+                for (int q = 0; q < IPT; ++q) {
+                    const int r = q * BLOCK + tid;
+                    if (q < nq && r < C) {
+                        const int e = L.walk.next[cur][r];
+                        if (L.walk.opens[r] && e < C) L.walk.opens[e] = 1;      // (one that another lane has just named names a true one too)
+                        L.walk.next[cur ^ 1][r] = L.walk.next[cur][e];
                     }
                 }
             }
+            // ---- micro-batch of every slot ----
+            first_of = L.walk.next[cur ^ 1];                          // (its last reader is a barrier behind)
+            int32_t n_here[IPT], before[IPT];
 #pragma unroll
             for (int q = 0; q < IPT; ++q) {
                 const int r = q * BLOCK + tid;
-                if (r < C) { L.walk.next[0][r] = (uint16_t)lo[q]; L.walk.opens[r] = r == 0; }
+                const uint64_t opens = __ballot(q < nq && r < C && L.walk.opens[min(r, C - 1)] != 0);
+                n_here[q] = (int32_t)__popcll(opens);
+                mb[q] = (int32_t)__popcll(opens & (~0ull >> (WAVE - 1 - lane))) - 1;
+                len[q] = (int32_t)((opens >> lane) & 1ull);           // (the lengths are done with: does the slot open one)
             }
-            if (tid == 0) { L.walk.next[0][C] = (uint16_t)C; L.walk.next[1][C] = (uint16_t)C; }
-        }
-        int cur = 0;
-        for (;; cur ^= 1) {                                       // (at most log2(C) + 1 rounds: a hop moves on by a slot at least)
+            n_mb = steps_before<BLOCK, IPT, int32_t>(n_here, L.step_count, L.tmp32, before);
+            if (!published && tid == 0) publish_count(s.mb_counts, P, p, n_mb);
+#pragma unroll
+            for (int q = 0; q < IPT; ++q) {
+                mb[q] += before[q];
+                if (len[q]) first_of[mb[q]] = (uint16_t)(q * BLOCK + tid);
+            }
+            // ---- the micro-batches of the shards before this one ----
+            if (!published) theirs = tid < p ? wait_count(s.mb_counts, P, tid) : 0;
+            else if (tid == target && target != p) theirs = n_mb;
+            published = true;
+            const bool missing = tid < p && theirs == 0;
+            int32_t sum;                                              // (the missing ones ride the sum's high bits)
+            block_excl_scan_add<int32_t>(missing ? 1 << 20 : theirs, L.tmp32, &sum);
+            static_assert(DC_MAX_SEQ < (1 << 20) && BAL_PLAN_MAX_SHARDS <= (1 << 11), "both parts fit");
+            if ((sum >> 20) == 0) {                                   // (uniform)
+                mb0 = sum;
+                if (target == p) break;
+                target = p;                                           // (its walk was overwritten)
+            } else {
+                if (tid == 0) L.missing = P;
+                lds_barrier();
+                if (missing) atomicMin(&L.missing, tid);
+                lds_barrier();
+                target = L.missing;
+            }
             lds_barrier();
-            if ((int)L.walk.next[cur][0] >= C) break;             // (uniform)
 #pragma unroll
             for (int q = 0; q < IPT; ++q) {
-                const int r = q * BLOCK + tid;
-                if (q < nq && r < C) {
-                    const int e = L.walk.next[cur][r];
-                    if (L.walk.opens[r] && e < C) L.walk.opens[e] = 1;      // (one that another lane has just named names a true one too)
-                    L.walk.next[cur ^ 1][r] = L.walk.next[cur][e];
-                }
+                len[q] = 0;
+                if (q < nq) len[q] = a.seq_len[min(max(a.perm[target * C + min(q * BLOCK + tid, C - 1)], 0), N - 1)];
             }
+            prefix();
         }
-        // ---- micro-batch of every slot ----
-        uint16_t* const first_of = L.walk.next[cur ^ 1];          // (its last reader is a barrier behind)
-        int32_t mb[IPT], n_here[IPT], before[IPT];
-#pragma unroll
-        for (int q = 0; q < IPT; ++q) {
-            const int r = q * BLOCK + tid;
-            const uint64_t opens = __ballot(q < nq && r < C && L.walk.opens[min(r, C - 1)] != 0);
-            n_here[q] = (int32_t)__popcll(opens);
-            mb[q] = (int32_t)__popcll(opens & (~0ull >> (WAVE - 1 - lane))) - 1;
-            len[q] = (int32_t)((opens >> lane) & 1ull);           // (the lengths are done with: does the slot open one)
-        }
-        const int32_t n_mb = steps_before<BLOCK, IPT, int32_t>(n_here, L.step_count, L.tmp32, before);
-        if (tid == 0) publish_count(s.mb_counts, P, p, n_mb);
-#pragma unroll
-        for (int q = 0; q < IPT; ++q) {
-            mb[q] += before[q];
-            if (len[q]) first_of[mb[q]] = (uint16_t)(q * BLOCK + tid);
-        }
-        // ---- the micro-batches of the shards before this one ----
-        const int32_t theirs = tid < p ? wait_count(s.mb_counts, P, tid) : 0;
-        int32_t mb0;
-        block_excl_scan_add<int32_t>(theirs, L.tmp32, &mb0);
         // ---- outputs (see plan_body: a slot stores the entry behind its own as well) ----
 #pragma unroll
         for (int q = 0; q < IPT; ++q) {
