@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
-from test_gpu_parity import _check_balance_ws, _custom, _gpu, _with_ppo_fields, check_gae, check_gather_advantage, check_scatter, check_step
+from test_gpu_parity import _check_balance_ws, _custom, _gpu, _with_ppo_fields, check_gae, check_gather_advantage, check_scatter, check_step, compare_step
 
 pytestmark = pytest.mark.gpu
 
@@ -574,3 +574,37 @@ def test_heads_and_tails_of_short_sequences(n, n_src):
     lens[::11] = rng.integers(250, 262, len(lens[::11]))
     lens[5::1001] = rng.integers(1020, 1030, len(lens[5::1001]))
     check_step(_custom(lens.astype(np.int32), 1 if n % 2 else 2, 1, 1 << 16, n_src=n_src, seed=n, fields=()), label=f"{n} sequences")
+
+
+@pytest.mark.parametrize("n,shards", [(3072, 24), (2560, 160)])
+def test_plan_by_shards_replayed_and_on_two_streams(n, shards):
+    """The shards' counts travel through words of the workspace that the launch before clears: a captured step gives the same
+    whatever the workspace holds before a replay, and steps of two buffer sets on two streams do not see each other's."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    ws = [_custom(rng.integers(1, 400, n).astype(np.int32), 8, shards, b, n_src=2, seed=b, fields=("i32",)) for b in (512, 4096)]
+    ds = [runner.DeviceBatch(w, poison=True) for w in ws]
+    for d in ds:
+        d.step_two_calls()
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        ds[0].step_two_calls()
+    for rep in range(3):
+        ds[0].ws.fill_(0x7F if rep else 0)
+        for t in (ds[0].perm, ds[0].cu_seqlens, ds[0].dst_tok_off, ds[0].shard_mb_off, ds[0].shard_of_seq):
+            t.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        compare_step(ds[0], ws[0])
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream())
+    for rep in range(6):
+        with torch.cuda.stream(streams[rep % 2]):
+            ds[rep % 2].step_two_calls()
+    torch.cuda.synchronize()
+    for d, w in zip(ds, ws):
+        compare_step(d, w)
