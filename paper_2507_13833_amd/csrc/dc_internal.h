@@ -140,9 +140,8 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
                         int32_t* d_status);
 
 // The whole plan behind launch_balance_advantage_perm (plan_shards.hip): every output of dc_plan, shard_of_seq, and the
-// workspace's tables.  Needs what launch_balance_plan_advantage needs, and plan_shards_serves.
+// workspace's tables.  Needs n_shards <= BAL_PLAN_MAX_SHARDS and equal shards.
 constexpr int PLAN_SHARDS_STAGED = 2048;         // slots of a shard up to which its slots' sources are staged in the LDS
-bool plan_shards_serves(int32_t n_seq, int32_t n_shards, int64_t dst_capacity);
 hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, const int64_t* d_shard_load,
                               int32_t* d_shard_of_seq, hipStream_t st);
 

@@ -11,6 +11,10 @@
 // balance workgroup (12 to 13 us, and 2 to 6 for shard_of_seq and the slots' lengths) and the tables in a launch behind it
 // (7.4 to 9.8) the two launches took: 2048 sequences on 8 shards 41 us, now 35; 15 360 on 24 112, now 95; 8192 on 32 72, now
 // 59; 16 384 on 64 106, now 90; 8192 on 128 66, now 50.
+// Shards of more than 2048 slots (up to sixteen to a lane, in loops that keep nothing in registers from one pass to the next:
+// unrolled, the walk spilled 94 of them and took 8 to 12 us more), both launches: 16 384 sequences on 4 shards 302 us with
+// 4096 tokens to a micro-batch and 296 with 65 536, as the balance workgroup's tail 352 and 316; 8190 on 3 210 and 205, so
+// 224 and 215.
 #include "plan_device.h"
 
 namespace dc {
@@ -51,17 +55,76 @@ static_assert(MB_COUNT_BYTES >= WAVE * 4 && MB_COUNT_BYTES >= BAL_PLAN_MAX_SHARD
 constexpr int TAIL_SLOTS = 8;                // slots behind the shard's last one kept at hand (its last granule reaches into them)
 static_assert(TAIL_SLOTS > REC_SLOTS, "a record's slots");
 
-// BLOCK * IPT: slots of a shard at most.  STAGE: the slots' sources stand in the LDS too.
-template <int BLOCK, int IPT, bool STAGE, typename Pre>
+// Exclusive prefix of the lengths of a shard's slots, in 64 bits (16 384 slots can hold 2^38 tokens, in an arena of any size).
+// last_within: e[k] is the last e in [from[k], C] with at(e) <= limit[k] (from[k] is one), a lane's slots side by side.
+template <int CAP, bool SPLIT>
+struct ShardPrefix {
+    int64_t v[CAP + 1];
+    __device__ __forceinline__ int64_t at(int r) const { return v[r]; }
+    __device__ __forceinline__ uint32_t low(int r) const { return (uint32_t)v[r]; }
+    template <int SIDE>
+    __device__ __forceinline__ void last_within(int C, const int (&from)[SIDE], const int64_t (&limit)[SIDE], int (&e)[SIDE]) const {
+#pragma unroll
+        for (int k = 0; k < SIDE; ++k) e[k] = from[k];
+        for (int hop = 1 << (31 - __clz(C)); hop >= 1; hop >>= 1) {      // (uniform)
+#pragma unroll
+            for (int k = 0; k < SIDE; ++k) {
+                const int c = e[k] + hop;
+                if (v[min(c, C)] <= limit[k] && c <= C) e[k] = c;
+            }
+        }
+    }
+};
+// SPLIT: the tokens before every 64 slots in 64 bits, those of the slots in front inside the 64 in 32 (below 2^30): 64 for
+// every slot of a large shard leave no room for its walk, and 32 alone would make falling sums of 2^32 tokens and more.
+template <int CAP>
+struct ShardPrefix<CAP, true> {
+    int64_t  step[CAP / WAVE + 1];
+    uint32_t in[CAP + 1];
+    __device__ __forceinline__ int64_t at(int r) const { return step[r / WAVE] + (int64_t)in[r]; }
+    __device__ __forceinline__ uint32_t low(int r) const { return (uint32_t)step[r / WAVE] + in[r]; }
+    // (the 64 it stands in, then its place there)
+    template <int SIDE>
+    __device__ __forceinline__ void last_within(int C, const int (&from)[SIDE], const int64_t (&limit)[SIDE], int (&e)[SIDE]) const {
+        const int last = C / WAVE;
+        int s[SIDE];
+        uint32_t left[SIDE];
+#pragma unroll
+        for (int k = 0; k < SIDE; ++k) s[k] = from[k] / WAVE;
+        for (int hop = last > 0 ? 1 << (31 - __clz(last)) : 0; hop >= 1; hop >>= 1) {      // (uniform)
+#pragma unroll
+            for (int k = 0; k < SIDE; ++k) {
+                const int c = s[k] + hop;
+                if (step[min(c, last)] <= limit[k] && c <= last) s[k] = c;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < SIDE; ++k) {
+            left[k] = (uint32_t)min(limit[k] - step[s[k]], (int64_t)0x7FFFFFFF);
+            e[k] = s[k] * WAVE;
+        }
+#pragma unroll
+        for (int hop = WAVE / 2; hop >= 1; hop >>= 1) {
+#pragma unroll
+            for (int k = 0; k < SIDE; ++k) {
+                const int c = e[k] + hop;
+                if (in[min(c, C)] <= left[k] && c <= C) e[k] = c;
+            }
+        }
+    }
+};
+
+// BLOCK * IPT: slots of a shard at most.  STAGE: the slots' sources and a word of 64 bits for each stand in the LDS too.
+template <int BLOCK, int IPT, bool STAGE>
 struct ShardPlanLds {
-    static constexpr int CAP = BLOCK * IPT, STEPS = IPT * (BLOCK / WAVE);
-    Pre pre[CAP + 1];                        // exclusive prefix of the slots' lengths inside the shard
+    static constexpr int CAP = BLOCK * IPT, STEPS = CAP / WAVE;
+    ShardPrefix<CAP, !STAGE> pre;
     union {
         struct { uint16_t next[2][CAP + 1]; uint8_t opens[CAP]; } walk;
         struct { int64_t src_off[STAGE ? CAP : 1]; int32_t lensh[STAGE ? CAP : 1]; } src;
     };
     int64_t base[BAL_PLAN_MAX_SHARDS + 1];   // aligned token offset of every shard
-    Pre     step_sum[STEPS];
+    uint32_t step_sum[STEPS];
     int32_t step_count[STEPS];
     int64_t tmp64[BLOCK / WAVE];
     int32_t tmp32[BLOCK / WAVE];
@@ -70,41 +133,14 @@ struct ShardPlanLds {
     int32_t tail_len[TAIL_SLOTS], tail_lensh[TAIL_SLOTS];
 };
 
-// sum[q]: what the 64 slots of this wave's step q add up to (the same in every lane, or right in the last one); before[q]
-// gets the sum of everything in front of them (slots q * BLOCK + tid, so steps in (q, wave) order).  part: IPT * waves words.
-template <int BLOCK, int IPT, typename T>
-__device__ __forceinline__ T steps_before(const T (&sum)[IPT], T* part, T* tmp, T (&before)[IPT]) {
-    constexpr int WAVES = BLOCK / WAVE, STEPS = IPT * WAVES;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
-#pragma unroll
-    for (int q = 0; q < IPT; ++q)
-        if (lane == WAVE - 1) part[q * WAVES + w] = sum[q];
-    lds_barrier();
-    T total;
-    if constexpr (STEPS <= WAVE) {                                // every wave scans them for itself
-        const T v = lane < STEPS ? part[lane] : T(0);
-        const T upto = wave_incl_scan_add(v);
-#pragma unroll
-        for (int q = 0; q < IPT; ++q) before[q] = wave_read_lane((T)(upto - v), q * WAVES + w);
-        total = wave_read_lane(upto, WAVE - 1);
-    } else {
-        static_assert(STEPS <= BLOCK, "a thread per step");
-        const T ex = block_excl_scan_add<T>(tid < STEPS ? part[tid] : T(0), tmp, &total);
-        if (tid < STEPS) part[tid] = ex;
-        lds_barrier();
-#pragma unroll
-        for (int q = 0; q < IPT; ++q) before[q] = part[q * WAVES + w];
-    }
-    return total;
-}
-
 __device__ __forceinline__ int32_t sane_len(int32_t s) { return s > 0 && s <= DC_MAX_SEQ_LEN ? s : 1; }      // (the balance's own rule)
 
-template <int BLOCK, int IPT, bool STAGE, typename Pre>
+template <int BLOCK, int IPT, bool STAGE>
 __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDesc sd, ShardPlanArgs s) {
-    using Lds = ShardPlanLds<BLOCK, IPT, STAGE, Pre>;
+    using Lds = ShardPlanLds<BLOCK, IPT, STAGE>;
     __shared__ Lds L;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    constexpr int WAVES = BLOCK / WAVE, UNROLL = IPT < 4 ? IPT : 4;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int N = a.n_seq, P = a.n_shards, C = s.C;
     const bool walker = (int)blockIdx.x < P;
     const int slice = walker ? -1 : ((int)blockIdx.x - P) / P;
@@ -142,21 +178,39 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
         if (tid < P) L.base[tid] = b;
         if (tid == 0) L.base[P] = end;
     }
-    // ---- prefix of the lengths ----
+    // ---- prefix of the lengths (whole behind the next barrier) ----
     auto prefix = [&]() {
-        Pre inc[IPT], before[IPT];
-#pragma unroll
-        for (int q = 0; q < IPT; ++q) {
-            len[q] = q < nq && q * BLOCK + tid < C ? sane_len(len[q]) : 0;
-            inc[q] = (Pre)wave_incl_scan_add_u32((uint32_t)len[q]);      // (64 lengths stay below 2^31)
-        }
-        const Pre total = steps_before<BLOCK, IPT, Pre>(inc, L.step_sum, reinterpret_cast<Pre*>(L.tmp64), before);
+        uint32_t inc[IPT];
 #pragma unroll
         for (int q = 0; q < IPT; ++q) {
             const int r = q * BLOCK + tid;
-            if (r < C) L.pre[r] = before[q] + inc[q] - (Pre)len[q];
+            len[q] = q < nq && r < C ? sane_len(len[q]) : 0;
+            inc[q] = wave_incl_scan_add_u32((uint32_t)len[q]);    // (64 lengths stay below 2^31)
+            if (lane == WAVE - 1) L.step_sum[r / WAVE] = inc[q];
+            if constexpr (!STAGE)
+                if (r <= C) L.pre.in[r] = inc[q] - (uint32_t)len[q];
         }
-        if (tid == 0) L.pre[C] = total;
+        lds_barrier();
+        if constexpr (STAGE) {
+            static_assert(Lds::STEPS <= WAVE, "every wave scans them for itself");
+            const int64_t n = lane < Lds::STEPS ? (int64_t)L.step_sum[lane] : 0;
+            const int64_t upto = wave_incl_scan_add(n);
+#pragma unroll
+            for (int q = 0; q < IPT; ++q) {
+                const int r = q * BLOCK + tid;
+                if (r < C) L.pre.v[r] = wave_read_lane((int64_t)(upto - n), q * WAVES + w) + (int64_t)(inc[q] - (uint32_t)len[q]);
+            }
+            if (tid == 0) L.pre.v[C] = wave_read_lane(upto, WAVE - 1);
+        } else {
+            static_assert(Lds::STEPS <= BLOCK, "a thread per step");
+            int64_t total;
+            const int64_t ex = block_excl_scan_add<int64_t>(tid < Lds::STEPS ? (int64_t)L.step_sum[tid] : 0, L.tmp64, &total);
+            if (tid < Lds::STEPS) L.pre.step[tid] = ex;
+            if (tid == 0) {
+                L.pre.step[Lds::STEPS] = total;
+                if (C == Lds::CAP) L.pre.in[Lds::CAP] = 0;
+            }
+        }
     };
     prefix();
 
@@ -165,45 +219,44 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
         // Then the hops are doubled, slots known to open one naming those 1, 2, 4, ... hops on, until a hop from the first
         // slot leaves the shard: log2 of the number of micro-batches in rounds of two LDS reads, where following the
         // chain takes a read (~130 cycles) for each.
-        const int first_step = 1 << (31 - __clz(C));
         int target = p;                                           // the shard that is walked: the workgroup's own, unless
         bool published = false;                                   // another's count does not come
         int32_t theirs = 0, mb0 = 0, n_mb = 0;                    // thread k < p: shard k's count
-        int32_t mb[IPT];
+        int32_t opened = 0;
         uint16_t* first_of = nullptr;
+        auto opening = [&](int q) {                               // lanes whose slot of step q opens a micro-batch
+            const int r = q * BLOCK + tid;
+            return __ballot(q < nq && r < C && L.walk.opens[min(r, C - 1)] != 0);
+        };
+        auto micro_batch = [&](int q, uint64_t opens) {           // the lane's slot's
+            const int32_t in_front = Lds::STEPS <= WAVE ? wave_read_lane(opened, q * WAVES + w) : L.step_count[q * WAVES + w];
+            return in_front + (int32_t)__popcll(opens & (~0ull >> (WAVE - 1 - lane))) - 1;
+        };
         for (;;) {
             lds_barrier();
-            {
-                int lo[IPT];
-                Pre limit[IPT];
+            constexpr int SIDE = UNROLL;
+#pragma unroll 1
+            for (int q0 = 0; q0 < nq; q0 += SIDE) {                   // (uniform)
+                int from[SIDE], e[SIDE];
+                int64_t limit[SIDE];
 #pragma unroll
-                for (int q = 0; q < IPT; ++q) {
-                    const int r = min(q * BLOCK + tid, C - 1);
-                    lo[q] = r + 1;
-                    const uint64_t lim = (uint64_t)L.pre[r] + (uint64_t)a.budget;
-                    limit[q] = sizeof(Pre) == 4 ? (Pre)min(lim, (uint64_t)0xFFFFFFFFull) : (Pre)lim;
+                for (int k = 0; k < SIDE; ++k) {
+                    from[k] = min((q0 + k) * BLOCK + tid, C - 1);
+                    limit[k] = L.pre.at(from[k]) + a.budget;
                 }
-                for (int step = first_step; step >= 1; step >>= 1) {      // the last e in (r, C] that fits, or r + 1
+                L.pre.last_within(C, from, limit, e);
 #pragma unroll
-                    for (int q = 0; q < IPT; ++q) {
-                        if (q < nq) {                                 // (uniform)
-                            const int c = lo[q] + step;
-                            if (L.pre[min(c, C)] <= limit[q] && c <= C) lo[q] = c;
-                        }
-                    }
+                for (int k = 0; k < SIDE; ++k) {                      // (a sequence above the budget is alone in its micro-batch)
+                    const int r = (q0 + k) * BLOCK + tid;
+                    if (r < C) { L.walk.next[0][r] = (uint16_t)max(e[k], r + 1); L.walk.opens[r] = r == 0; }
                 }
-#pragma unroll
-                for (int q = 0; q < IPT; ++q) {
-                    const int r = q * BLOCK + tid;
-                    if (r < C) { L.walk.next[0][r] = (uint16_t)lo[q]; L.walk.opens[r] = r == 0; }
-                }
-                if (tid == 0) { L.walk.next[0][C] = (uint16_t)C; L.walk.next[1][C] = (uint16_t)C; }
             }
+            if (tid == 0) { L.walk.next[0][C] = (uint16_t)C; L.walk.next[1][C] = (uint16_t)C; }
             int cur = 0;
             for (;; cur ^= 1) {                                       // (at most log2(C) + 1 rounds: a hop moves on by a slot at least)
                 lds_barrier();
                 if ((int)L.walk.next[cur][0] >= C) break;             // (uniform)
-#pragma unroll
+#pragma unroll UNROLL
                 for (int q = 0; q < IPT; ++q) {
                     const int r = q * BLOCK + tid;
                     if (q < nq && r < C) {
@@ -213,23 +266,29 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
                     }
                 }
             }
-            // ---- micro-batch of every slot ----
-            first_of = L.walk.next[cur ^ 1];                          // (its last reader is a barrier behind)
-            int32_t n_here[IPT], before[IPT];
-#pragma unroll
+            // ---- micro-batches that open in front of every 64 slots ----
+#pragma unroll UNROLL
             for (int q = 0; q < IPT; ++q) {
-                const int r = q * BLOCK + tid;
-                const uint64_t opens = __ballot(q < nq && r < C && L.walk.opens[min(r, C - 1)] != 0);
-                n_here[q] = (int32_t)__popcll(opens);
-                mb[q] = (int32_t)__popcll(opens & (~0ull >> (WAVE - 1 - lane))) - 1;
-                len[q] = (int32_t)((opens >> lane) & 1ull);           // (the lengths are done with: does the slot open one)
+                const uint64_t opens = opening(q);
+                if (lane == 0) L.step_count[q * WAVES + w] = (int32_t)__popcll(opens);
             }
-            n_mb = steps_before<BLOCK, IPT, int32_t>(n_here, L.step_count, L.tmp32, before);
+            lds_barrier();
+            if constexpr (Lds::STEPS <= WAVE) {                       // every wave scans them for itself, lane k keeps step k's
+                const int32_t n = lane < Lds::STEPS ? L.step_count[lane] : 0;
+                const int32_t upto = wave_incl_scan_add(n);
+                opened = upto - n;
+                n_mb = wave_read_lane(upto, WAVE - 1);
+            } else {
+                opened = block_excl_scan_add<int32_t>(tid < Lds::STEPS ? L.step_count[tid] : 0, L.tmp32, &n_mb);
+                if (tid < Lds::STEPS) L.step_count[tid] = opened;
+                lds_barrier();
+            }
             if (!published && tid == 0) publish_count(s.mb_counts, P, p, n_mb);
-#pragma unroll
+            first_of = L.walk.next[cur ^ 1];                          // (its last reader is a barrier behind)
+#pragma unroll UNROLL
             for (int q = 0; q < IPT; ++q) {
-                mb[q] += before[q];
-                if (len[q]) first_of[mb[q]] = (uint16_t)(q * BLOCK + tid);
+                const uint64_t opens = opening(q);
+                if ((opens >> lane) & 1ull) first_of[micro_batch(q, opens)] = (uint16_t)(q * BLOCK + tid);
             }
             // ---- the micro-batches of the shards before this one ----
             if (!published) theirs = tid < p ? wait_count(s.mb_counts, P, tid) : 0;
@@ -259,16 +318,17 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
             prefix();
         }
         // ---- outputs (see plan_body: a slot stores the entry behind its own as well) ----
-#pragma unroll
+#pragma unroll UNROLL
         for (int q = 0; q < IPT; ++q) {
             const int r = q * BLOCK + tid, j = j0 + r;
+            const int32_t mine = micro_batch(q, opening(q));
             if (q < nq && r < C) {
-                const int first = first_of[mb[q]];
-                const uint32_t g_first = (uint32_t)L.pre[first];  // (differences inside a micro-batch fit 32 bits)
-                const uint32_t m = (uint32_t)(mb0 + mb[q]);
+                const int first = first_of[mine];
+                const uint32_t g_first = L.pre.low(first);        // (differences inside a micro-batch fit 32 bits)
+                const uint32_t m = (uint32_t)(mb0 + mine);
                 a.mb_seq_off[m] = j0 + first;
-                a.cu_seqlens[(uint32_t)j + m] = (int32_t)((uint32_t)L.pre[r] - g_first);
-                a.cu_seqlens[(uint32_t)j + m + 1u] = (int32_t)((uint32_t)L.pre[r + 1] - g_first);
+                a.cu_seqlens[(uint32_t)j + m] = (int32_t)(L.pre.low(r) - g_first);
+                a.cu_seqlens[(uint32_t)j + m + 1u] = (int32_t)(L.pre.low(r + 1) - g_first);
             }
         }
         if (tid == 0) {
@@ -318,7 +378,7 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
                 L.src.lensh[r] = ln | (sh << LENSH_SHIFT);
             }
             if (mine) {
-                a.dst_tok_off[j] = base + (int64_t)L.pre[r];
+                a.dst_tok_off[j] = base + L.pre.at(r);
                 s.shard_of_seq[seq[q]] = p;
                 a.slot_src_off[j] = so;
                 a.slot_len[j] = ln;
@@ -330,7 +390,7 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
     // ---- the granules whose first token lies in the shard's stretch ----
     auto far_len = [&](int j) { return sane_len(a.seq_len[min(max(a.perm[j], 0), N - 1)]); };
     auto starts = [&](int j) -> int64_t {                         // (j < N)
-        if (j < j_end) return base + (int64_t)L.pre[j - j0];
+        if (j < j_end) return base + L.pre.at(j - j0);
         if (j - j_end < TAIL_SLOTS) return L.tail_start[j - j_end];
         const int k = j / C;                                      // (only behind slots that fail a check)
         int64_t at = L.base[k];
@@ -355,23 +415,16 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
     const int64_t ga = (base + GATHER_GRAN - 1) / GATHER_GRAN;
     const int64_t gb = min(s.n_gran, (L.base[p + 1] + GATHER_GRAN - 1) / GATHER_GRAN);
     for (int64_t g = ga + slice * BLOCK + tid; g < gb; g += s.slices * BLOCK) {
-        const int64_t rel = g * GATHER_GRAN - base;
-        int lo = 0, hi = C;                                       // the first slot whose end lies behind the granule's first token
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if ((int64_t)L.pre[mid + 1] > rel) hi = mid; else lo = mid + 1;
-        }
-        build_record(N, true, starts, desc, g, s.gran_first + g, s.gran_rec + g, j0 + lo);
+        const int from[1] = {0};
+        const int64_t rel[1] = {g * GATHER_GRAN - base};
+        int found[1];                                             // the first slot whose end lies behind the granule's first token
+        L.pre.last_within(C, from, rel, found);
+        build_record(N, true, starts, desc, g, s.gran_first + g, s.gran_rec + g, j0 + found[0]);
     }
     // ---- and the table's end, which no token reaches ----
     const int64_t ge = (L.base[P] + GATHER_GRAN - 1) / GATHER_GRAN;
     for (int64_t g = ge + ((int64_t)blockIdx.x - P) * BLOCK + tid; g < s.n_gran; g += (int64_t)P * s.slices * BLOCK)
         build_record(N, false, starts, desc, g, s.gran_first + g, s.gran_rec + g);
-}
-
-bool plan_shards_serves(int32_t n_seq, int32_t n_shards, int64_t dst_capacity) {
-    // (above PLAN_SHARDS_STAGED slots the prefix has 32 bits)
-    return n_seq / n_shards <= PLAN_SHARDS_STAGED || dst_capacity < (int64_t)1 << 32;
 }
 
 hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, const int64_t* d_shard_load,
@@ -390,8 +443,8 @@ hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Wo
         return hipGetLastError();
     };
     static_assert(512 * 4 == PLAN_SHARDS_STAGED && 1024 * 16 == DC_MAX_SEQ, "what the two kernels hold");
-    if (C <= PLAN_SHARDS_STAGED) return launch(plan_shards_kernel<512, 4, true, int64_t>, 512);
-    return launch(plan_shards_kernel<1024, 16, false, uint32_t>, 1024);
+    if (C <= PLAN_SHARDS_STAGED) return launch(plan_shards_kernel<512, 4, true>, 512);
+    return launch(plan_shards_kernel<1024, 16, false>, 1024);
 }
 
 }  // namespace dc

@@ -608,3 +608,52 @@ def test_plan_by_shards_replayed_and_on_two_streams(n, shards):
     torch.cuda.synchronize()
     for d, w in zip(ds, ws):
         compare_step(d, w)
+
+
+@pytest.mark.parametrize("n,shards,budget,longest,whole", [
+    (2049, 1, 1 << 25, 1 << 24, False), (4100, 2, (1 << 31) - 1, 1 << 24, False), (16384, 4, 1 << 24, 1 << 24, False),
+    (16384, 1, (1 << 31) - 1, 1 << 24, False), (2112, 1, 100_000_000, 1 << 22, True),
+])
+def test_plan_by_shards_of_more_than_32_bits_of_tokens(n, shards, budget, longest, whole):
+    """Shards of 2^32 tokens and more, in an arena that ends early (the overflow is reported, and every table is still what dc_plan
+    makes of the same batch) and in one that takes them all."""
+    torch, binding, _ = _gpu()
+    rng = np.random.default_rng(n)
+    lens = rng.integers(longest - longest // 8, longest + 1, n).astype(np.int32)
+    off = np.cumsum(lens, dtype=np.int64) - lens
+    total = int(lens.sum(dtype=np.int64))
+    assert total // shards > 1 << 32
+    capacity = total if whole else 1 << 20
+    dev = "cuda:0"
+
+    def ints(k, dtype=torch.int32):
+        return torch.zeros(k, dtype=dtype, device=dev)
+
+    prm = binding.make_params(n, shards, budget)
+    seq_len = torch.from_numpy(lens).to(dev)
+    src = binding.Source([0, n], [total], torch.from_numpy(off).to(dev))
+    reward, adv_seq = torch.zeros(n, device=dev), torch.zeros(n, device=dev)
+    group_off = torch.arange(n + 1, dtype=torch.int32, device=dev)
+    perm, seq_off, shard_of, load = ints(n), ints(shards + 1), ints(n), ints(shards, torch.int64)
+    ws_bytes = binding.dc_workspace_bytes(prm, capacity)
+    got = []
+    for separate in (False, True):
+        out = [ints(n + 1, torch.int64), ints(shards + 1, torch.int64), ints(shards + 1), ints(n + 1), ints(2 * n), ints(1)]
+        ws, status = torch.full((ws_bytes,), 0x7F, dtype=torch.uint8, device=dev), ints(1)
+        if separate:
+            binding.dc_plan(prm, src, seq_len, perm, seq_off, capacity, *out, ws, ws_bytes, status)
+        else:
+            binding.dc_balance_plan_group_advantage(prm, src, seq_len, perm, seq_off, shard_of, load, reward, group_off, n, None,
+                                                    adv_seq, None, capacity, *out, ws, ws_bytes, status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == (binding.DC_OK if whole else binding.DC_ERR_OVERFLOW)
+        got.append((out, ws[:ws_bytes - 512]))                    # (behind the tables: the plan's own words)
+    bal = oracle.balance(lens, shards)
+    assert np.array_equal(perm.cpu().numpy(), bal.perm) and np.array_equal(load.cpu().numpy(), bal.shard_load)
+    pl = oracle.plan(lens, bal.perm, bal.shard_seq_off, budget)
+    for out, _ in got:
+        tok, shard_tok, shard_mb, mb, cu, n_mb = (t.cpu().numpy() for t in out)
+        assert n_mb[0] == pl.n_mb and np.array_equal(tok, pl.dst_tok_off) and np.array_equal(shard_tok, pl.shard_tok_off)
+        assert np.array_equal(shard_mb, pl.shard_mb_off) and np.array_equal(mb[:pl.n_mb + 1], pl.mb_seq_off)
+        assert np.array_equal(cu[:n + pl.n_mb], pl.cu_seqlens)
+    assert torch.equal(got[0][1], got[1][1])                      # the granule tables and the slots' sources
