@@ -217,14 +217,14 @@ dc_status dc_balance_group_advantage(const dc_params* prm, const dc_source* src,
     return e == hipSuccess ? DC_OK : DC_ERR_HIP;
 }
 
-dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,
-                                          int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
-                                          int64_t* d_shard_load, const float* d_reward, const int32_t* d_group_off,
-                                          int32_t n_groups, const uint8_t* const* mask_src_base, float* d_adv_seq,
-                                          float* const* adv_tok_src_base, int64_t dst_capacity_tokens,
-                                          int64_t* d_dst_tok_off, int64_t* d_shard_tok_off, int32_t* d_shard_mb_off,
-                                          int32_t* d_mb_seq_off, int32_t* d_cu_seqlens, int32_t* d_n_mb,
-                                          void* d_ws, size_t ws_bytes, int32_t* d_status, void* hip_stream) {
+static dc_status balance_plan_group_advantage(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,
+                                              int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
+                                              int64_t* d_shard_load, const float* d_reward, const int32_t* d_group_off,
+                                              int32_t n_groups, const uint8_t* const* mask_src_base, float* d_adv_seq,
+                                              float* const* adv_tok_src_base, int64_t dst_capacity_tokens,
+                                              int64_t* d_dst_tok_off, int64_t* d_shard_tok_off, int32_t* d_shard_mb_off,
+                                              int32_t* d_mb_seq_off, int32_t* d_cu_seqlens, int32_t* d_n_mb,
+                                              void* d_ws, size_t ws_bytes, int32_t* d_status, void* hip_stream, int looks) {
     // every argument is checked before anything is enqueued
     int32_t cap_eff;
     dc_status rc = check_balance(prm, d_seq_len, d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, &cap_eff);
@@ -266,9 +266,39 @@ dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source*
     } else {
         e = launch_balance_advantage_perm(prm->n_seq, prm->n_shards, cap_eff, d_seq_len, d_perm, d_shard_seq_off,
                                           d_shard_load, ws.mb_counts, adv, sd, n_groups, d_status, st);
-        if (e == hipSuccess) e = launch_plan_shards(plan, sd, ws, d_shard_load, d_shard_of_seq, st);
+        if (e == hipSuccess) e = launch_plan_shards(plan, sd, ws, d_shard_load, d_shard_of_seq, looks, st);
     }
     return e == hipSuccess ? DC_OK : DC_ERR_HIP;
+}
+
+dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,
+                                          int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
+                                          int64_t* d_shard_load, const float* d_reward, const int32_t* d_group_off,
+                                          int32_t n_groups, const uint8_t* const* mask_src_base, float* d_adv_seq,
+                                          float* const* adv_tok_src_base, int64_t dst_capacity_tokens,
+                                          int64_t* d_dst_tok_off, int64_t* d_shard_tok_off, int32_t* d_shard_mb_off,
+                                          int32_t* d_mb_seq_off, int32_t* d_cu_seqlens, int32_t* d_n_mb,
+                                          void* d_ws, size_t ws_bytes, int32_t* d_status, void* hip_stream) {
+    return balance_plan_group_advantage(
+        prm, src, d_seq_len, d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, d_reward,
+        d_group_off, n_groups, mask_src_base, d_adv_seq, adv_tok_src_base, dst_capacity_tokens, d_dst_tok_off, d_shard_tok_off,
+        d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb, d_ws, ws_bytes, d_status, hip_stream, PLAN_SHARDS_LOOKS);
+}
+
+// For the tests alone (in no header): the same call whose walkers look `looks` times at another shard's count, so that they also
+// count shards for themselves.
+dc_status dc_test_balance_plan_looks(int32_t looks, const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,
+                                     int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
+                                     int64_t* d_shard_load, const float* d_reward, const int32_t* d_group_off,
+                                     int32_t n_groups, const uint8_t* const* mask_src_base, float* d_adv_seq,
+                                     float* const* adv_tok_src_base, int64_t dst_capacity_tokens,
+                                     int64_t* d_dst_tok_off, int64_t* d_shard_tok_off, int32_t* d_shard_mb_off,
+                                     int32_t* d_mb_seq_off, int32_t* d_cu_seqlens, int32_t* d_n_mb,
+                                     void* d_ws, size_t ws_bytes, int32_t* d_status, void* hip_stream) {
+    return balance_plan_group_advantage(
+        prm, src, d_seq_len, d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, d_reward,
+        d_group_off, n_groups, mask_src_base, d_adv_seq, adv_tok_src_base, dst_capacity_tokens, d_dst_tok_off, d_shard_tok_off,
+        d_shard_mb_off, d_mb_seq_off, d_cu_seqlens, d_n_mb, d_ws, ws_bytes, d_status, hip_stream, looks);
 }
 
 dc_status dc_gae(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len, const float* d_reward,

@@ -142,8 +142,9 @@ PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, cons
 // The whole plan behind launch_balance_advantage_perm (plan_shards.hip): every output of dc_plan, shard_of_seq, and the
 // workspace's tables.  Needs n_shards <= BAL_PLAN_MAX_SHARDS and equal shards.
 constexpr int PLAN_SHARDS_STAGED = 2048;         // slots of a shard up to which its slots' sources are staged in the LDS
+constexpr int PLAN_SHARDS_LOOKS = 512;           // at another shard's count, before a walker counts that shard itself
 hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, const int64_t* d_shard_load,
-                              int32_t* d_shard_of_seq, hipStream_t st);
+                              int32_t* d_shard_of_seq, int looks, hipStream_t st);
 
 // Balance, group advantage and the plan in one launch (workgroup 0: Algorithm 1, then the plan and the granule tables as its
 // tail; the other workgroups: the advantage stage).  Needs n_shards <= BAL_PLAN_MAX_SHARDS, cap_eff * n_shards == n_seq,

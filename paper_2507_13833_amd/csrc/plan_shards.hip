@@ -27,6 +27,7 @@ struct ShardPlanArgs {
     int32_t*       gran_first;
     GranRec*       gran_rec;
     int64_t        n_gran;
+    int32_t        looks;            // at another shard's count
 };
 
 // A shard's number of micro-batches, left where the others look for it: a word each up to 64 shards, above that a byte (a
@@ -36,13 +37,12 @@ __device__ __forceinline__ uint32_t* count_word(uint32_t* counts, int P, int p) 
 __device__ __forceinline__ void publish_count(uint32_t* counts, int P, int p, int n) {
     __hip_atomic_fetch_or(count_word(counts, P, p), (uint32_t)n << count_shift(P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The count, or 0 if it has not come after WAIT_LOOKS looks (a few hundred us; it comes within one or two).
+// The count, or 0 if it has not come after so many looks (PLAN_SHARDS_LOOKS take a few hundred us; it comes within one or two).
 // Nothing says that all walkers are on the chip at once, so nobody waits for another without an end: a walker whose look
-// stays empty counts that shard itself (with WAIT_LOOKS = 0 every walker counts all shards before its own: same outputs).
-constexpr int WAIT_LOOKS = 512;
-__device__ __forceinline__ int wait_count(uint32_t* counts, int P, int p) {
+// stays empty counts that shard itself (with no looks every walker counts all shards before its own: same outputs).
+__device__ __forceinline__ int wait_count(uint32_t* counts, int P, int p, int looks) {
     const uint32_t mask = P <= WAVE ? 0xFFFFFFFFu : 0xFFu;
-    for (int look = 0; look < WAIT_LOOKS; ++look) {
+    for (int look = 0; look < looks; ++look) {
         const uint32_t n = (__hip_atomic_load(count_word(counts, P, p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> count_shift(P, p)) & mask;
         if (n != 0) return (int)n;
         __builtin_amdgcn_s_sleep(1);
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
                 if ((opens >> lane) & 1ull) first_of[micro_batch(q, opens)] = (uint16_t)(q * BLOCK + tid);
             }
             // ---- the micro-batches of the shards before this one ----
-            if (!published) theirs = tid < p ? wait_count(s.mb_counts, P, tid) : 0;
+            if (!published) theirs = tid < p ? wait_count(s.mb_counts, P, tid, s.looks) : 0;
             else if (tid == target && target != p) theirs = n_mb;
             published = true;
             const bool missing = tid < p && theirs == 0;
@@ -428,13 +428,13 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
 }
 
 hipError_t launch_plan_shards(const PlanArgs& p, const SourceDesc& src, const Workspace& ws, const int64_t* d_shard_load,
-                              int32_t* d_shard_of_seq, hipStream_t st) {
+                              int32_t* d_shard_of_seq, int looks, hipStream_t st) {
     const int P = p.n_shards, C = p.n_seq / P;
     if (P < 1 || P > BAL_PLAN_MAX_SHARDS || C < 1 || C * P != p.n_seq || p.n_seq > DC_MAX_SEQ || !ws.mb_counts)
         return hipErrorInvalidValue;
     ShardPlanArgs s;
     s.C = C; s.shard_load = d_shard_load; s.shard_of_seq = d_shard_of_seq; s.mb_counts = ws.mb_counts;
-    s.gran_first = ws.gran_first; s.gran_rec = ws.gran_rec; s.n_gran = ws.n_gran;
+    s.gran_first = ws.gran_first; s.gran_rec = ws.gran_rec; s.n_gran = ws.n_gran; s.looks = looks;
     auto launch = [&](auto kernel, int block) {
         // a granule per thread, up to 1024 workgroups
         const int64_t want = (ws.n_gran + (int64_t)P * block - 1) / ((int64_t)P * block);

@@ -657,3 +657,20 @@ def test_plan_by_shards_of_more_than_32_bits_of_tokens(n, shards, budget, longes
         assert np.array_equal(shard_mb, pl.shard_mb_off) and np.array_equal(mb[:pl.n_mb + 1], pl.mb_seq_off)
         assert np.array_equal(cu[:n + pl.n_mb], pl.cu_seqlens)
     assert torch.equal(got[0][1], got[1][1])                      # the granule tables and the slots' sources
+
+
+@pytest.mark.parametrize("looks", [0, 1, 3])
+@pytest.mark.parametrize("n,shards,budget,align", [(2048, 2, 41, 1), (3072, 24, 300, 6), (4096, 64, 97, 1), (2600, 65, 97, 8), (2560, 256, 60, 1),
+                                                   (4098, 2, 41, 1), (12288, 4, 5000, 3), (16383, 3, 300, 1)])
+def test_plan_by_shards_whose_counts_do_not_come(n, shards, budget, align, looks, monkeypatch):
+    """Walkers that do not find another shard's count count that shard themselves and walk their own again: with no looks at all
+    shards before their own, with one or three at those that come late."""
+    import ctypes
+    _, binding, _ = _gpu()
+    lib = binding.load()
+    call = lib.dc_test_balance_plan_looks
+    call.restype, call.argtypes = ctypes.c_int, [ctypes.c_int32] + lib.dc_balance_plan_group_advantage.argtypes
+    monkeypatch.setattr(lib, "dc_balance_plan_group_advantage", lambda *a: call(looks, *a))
+    lens = np.random.default_rng(n + budget).integers(1, 41, n).astype(np.int32)
+    w = _custom(lens, 1, shards, budget, n_src=3 if n % 3 == 0 else 1, seed=n, fields=("i32",))
+    check_step(w, align=align, two_calls=True, label=f"{n} slots on {shards} shards, {looks} looks")
