@@ -73,13 +73,12 @@ struct PlanLds {
 // The caller holds, per lane, the sequence and the (validated) length of slots tid, tid + PLAN_BLOCK, ...
 // (seq = -1, len = 0 beyond N).  check_perm: seq comes from a caller's permutation and must be checked;
 // fixed_c > 0: shard p owns slots [p * fixed_c, (p + 1) * fixed_c) and a.shard_seq_off is not read.
-// STEPS: how the unrolled passes over a lane's slots treat the steps beyond nb.  LEAVE_EARLY: left at the first (a small
-// batch does not fetch the others' code); STEP_OVER: a test each; ALL: none, there are few or none of them (the steps
-// then run into each other: 16 scans at once).  CHAINS = false: for more than PLAN_NEXT_MAX slots, without the code that such
-// a batch never takes.
+// STEPS: how the unrolled passes over a lane's slots treat the steps beyond nb.  STEP_OVER: a test each; ALL: none, there are
+// few or none of them (the steps then run into each other: 16 scans at once).  CHAINS = false: for more than PLAN_NEXT_MAX slots,
+// without the code that such a batch never takes.
 // Every lane of the workgroup must call it (barriers inside).
-enum PlanSteps { LEAVE_EARLY, STEP_OVER, ALL };
-template <int IPT, PlanSteps STEPS = LEAVE_EARLY, bool CHAINS = true>
+enum PlanSteps { STEP_OVER, ALL };
+template <int IPT, PlanSteps STEPS = ALL, bool CHAINS = true>
 __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t (&seq)[IPT], int32_t (&len)[IPT],
                                           bool check_perm, int fixed_c) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
@@ -122,20 +121,12 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     // dense prefix: inclusive scan inside each wave step (a wave's 64 slots hold < 2^31 tokens) ...
     int32_t inc[IPT];
     // (the loops' bodies stand in them, not in lambdas: 15.9 us for 16 384 slots in plan_kernel instead of 16.4)
-    if constexpr (STEPS == LEAVE_EARLY) {
-        unrolled_steps<IPT>(nb, [&](auto qc) {
-            constexpr int q = decltype(qc)::value;
+#pragma unroll
+    for (int q = 0; q < IPT; ++q)
+        if (STEPS == ALL || q < nb) {
             inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
             if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
-        });
-    } else {
-#pragma unroll
-        for (int q = 0; q < IPT; ++q)
-            if (STEPS == ALL || q < nb) {
-                inc[q] = (int32_t)wave_incl_scan_add_u32((uint32_t)len[q]);
-                if (lane == WAVE - 1) L.wave_pref[q * PLAN_WAVES + w] = inc[q];
-            }
-    }
+        }
     lds_barrier();
     // ... an exclusive scan of the 256 step totals in slot order (step q, wave w) ...
     {
@@ -148,18 +139,10 @@ __device__ __forceinline__ void plan_body(PlanLds& L, const PlanArgs& a, int32_t
     lds_barrier();
     // ... and their sum
     const int whole_steps = N / PLAN_BLOCK;              // (uniform) steps in which every lane has a slot
-    if constexpr (STEPS == LEAVE_EARLY) {
-        unrolled_steps<IPT>(nb, [&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            const int j = q * PLAN_BLOCK + tid;
-            if (q < whole_steps || j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
-        });
-    } else {
 #pragma unroll
-        for (int q = 0; q < IPT; ++q) {
-            const int j = q * PLAN_BLOCK + tid;
-            if (j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
-        }
+    for (int q = 0; q < IPT; ++q) {
+        const int j = q * PLAN_BLOCK + tid;
+        if (j < N) L.gpre[j] = L.wave_pref[q * PLAN_WAVES + w] + (inc[q] - len[q]);
     }
     lds_barrier();
 

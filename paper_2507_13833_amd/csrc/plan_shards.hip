@@ -52,8 +52,10 @@ __device__ __forceinline__ int wait_count(uint32_t* counts, int P, int p, int lo
 static_assert(DC_MAX_SEQ / (WAVE + 1) < 256, "a count of more than 64 shards fits a byte");
 static_assert(MB_COUNT_BYTES >= WAVE * 4 && MB_COUNT_BYTES >= BAL_PLAN_MAX_SHARDS, "a word or a byte per shard");
 
-constexpr int TAIL_SLOTS = 8;                // slots behind the shard's last one kept at hand (its last granule reaches into them)
-static_assert(TAIL_SLOTS > REC_SLOTS, "a record's slots");
+// Slots behind the shard's last one kept at hand, for the records of its last granules.  A granule that starts in front of the
+// next shard's first token has no later first slot than that shard's first: the slot behind the one found starts behind the
+// granule's start, whether it passes the checks or not.
+constexpr int TAIL_SLOTS = REC_SLOTS;
 
 // Exclusive prefix of the lengths of a shard's slots, in 64 bits (16 384 slots can hold 2^38 tokens, in an arena of any size).
 // last_within: e[k] is the last e in [from[k], C] with at(e) <= limit[k] (from[k] is one), a lane's slots side by side.
@@ -388,25 +390,17 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
     }
     lds_barrier();
     // ---- the granules whose first token lies in the shard's stretch ----
-    auto far_len = [&](int j) { return sane_len(a.seq_len[min(max(a.perm[j], 0), N - 1)]); };
-    auto starts = [&](int j) -> int64_t {                         // (j < N)
-        if (j < j_end) return base + L.pre.at(j - j0);
-        if (j - j_end < TAIL_SLOTS) return L.tail_start[j - j_end];
-        const int k = j / C;                                      // (only behind slots that fail a check)
-        int64_t at = L.base[k];
-        for (int u = k * C; u < j; ++u) at += far_len(u);
-        return at;
-    };
+    auto starts = [&](int j) { return j < j_end ? base + L.pre.at(j - j0) : L.tail_start[j - j_end]; };      // (j < N)
     auto desc = [&](int j, int32_t* ln, int64_t* so, int32_t* sh) {
         int32_t ls;
-        if (STAGE && j < j_end) {
-            ls = L.src.lensh[j - j0];
-            *so = L.src.src_off[j - j0];
-        } else if (j >= j_end && j - j_end < TAIL_SLOTS) {
+        if (j >= j_end) {
             ls = L.tail_lensh[j - j_end];
             *so = L.tail_src[j - j_end];
+        } else if constexpr (STAGE) {
+            ls = L.src.lensh[j - j0];
+            *so = L.src.src_off[j - j0];
         } else {
-            slot_source(a, sd, j, far_len(j), ln, so, sh);
+            slot_source(a, sd, j, (int32_t)(L.pre.low(j - j0 + 1) - L.pre.low(j - j0)), ln, so, sh);
             return;
         }
         *ln = ls & ((1 << LENSH_SHIFT) - 1);
