@@ -208,9 +208,9 @@ dc_status dc_balance_group_advantage(const dc_params* prm, const dc_source* src,
  * Balancing"), the advantage stage, and the layout the "Distributed Databuffer" redistributes into.
  * With Algorithm 1 as printed (cap = 0 or cap * P = N) on up to 256 shards and up to DC_MAX_SEQ
  * sequences, a second launch plans by shards, a few workgroups each, from d_perm and d_shard_load; up to 128
- * sequences and 2048 granules of 1024 tokens the plan runs as the tail of the workgroup that balances.  Two launches (or one) instead
- * of five; dc_gather (or dc_gather_advantage) follows as after dc_plan.  Other shapes: the two calls one after
- * the other.
+ * sequences (256 on shards of up to 64) and 2048 granules of 1024 tokens the plan runs as the tail of the workgroup
+ * that balances.  Two launches (or one) instead of five; dc_gather (or dc_gather_advantage) follows as after dc_plan.
+ * Other shapes: the two calls one after the other.
  */
 dc_status dc_balance_plan_group_advantage(const dc_params* prm, const dc_source* src, const int32_t* d_seq_len,
                                           int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,

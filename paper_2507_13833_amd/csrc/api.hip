@@ -245,7 +245,7 @@ static dc_status balance_plan_group_advantage(const dc_params* prm, const dc_sou
     // and tables are the tail of the balance workgroup (both sides of the line: small_records), two for others
     const bool printed = prm->n_seq > 0 && prm->n_shards <= BAL_PLAN_MAX_SHARDS &&
                          (int64_t)cap_eff * prm->n_shards == prm->n_seq;
-    const bool one_launch = printed && prm->n_seq <= SMALL_REC_SLOTS && ws.n_gran <= SMALL_REC_GRANS;
+    const bool one_launch = printed && plans_in_one_launch(prm->n_seq, prm->n_shards, ws.n_gran);
     if (!printed) {
         rc = dc_balance_group_advantage(prm, src, d_seq_len, d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, d_reward,
                                         d_group_off, n_groups, mask_src_base, d_adv_seq, adv_tok_src_base, d_status, hip_stream);

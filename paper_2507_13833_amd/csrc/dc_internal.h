@@ -130,8 +130,12 @@ struct PlanArgs {
     GranRec* gran_rec;
     int64_t  n_gran;
 };
-constexpr int SMALL_REC_SLOTS = 128;           // (the line: see small_records)
+constexpr int SMALL_REC_SLOTS = 256;
 constexpr int64_t SMALL_REC_GRANS = 2048;
+// Which batches on equal shards are planned by the workgroup that balances (the line: see small_records).
+inline bool plans_in_one_launch(int32_t n_seq, int32_t n_shards, int64_t n_gran) {
+    return n_gran <= SMALL_REC_GRANS && (n_seq <= 128 || (n_seq <= SMALL_REC_SLOTS && n_seq <= 64 * (int64_t)n_shards));
+}
 
 PlanArgs make_plan_args(const dc_params& prm, const int64_t* d_src_tok_off, const int32_t* d_seq_len,
                         const int32_t* d_perm, const int32_t* d_shard_seq_off, int64_t dst_capacity,

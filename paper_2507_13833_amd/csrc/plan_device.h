@@ -476,9 +476,12 @@ __device__ __forceinline__ void build_record(int N, bool usable, Starts starts, 
 // behind plan_body), for a batch small enough that one workgroup is quicker with them than a launch of its own is started:
 // up to SMALL_REC_SLOTS slots and SMALL_REC_GRANS granules, the slots' starts and sources in the LDS behind the prefix.
 // src_off[q]: d_src_tok_off of the slots' sequences, asked for before the plan.
-// The line: a step of 48 / 64 / 128 sequences takes 17.7 / 19.8 / 22.5 us this way and 19.2 / 20.1 / 22.8 with the plan by shards
-// behind it (plan_shards.hip); at 256 the two are level, and 512 / 1024 / 2048 on 8 shards take 29.6 / 33.9 / 50.1 against
-// 28.5 / 31.7 / 44.5.
+// The line (steps in us, this way against the plan by shards behind it, plan_shards.hip): 48 / 64 / 128 sequences 17.7 / 19.8 /
+// 22.5 against 19.2 / 20.1 / 22.8.  Above 128 a shard's walk is what the other way waits for: 192 and 256 on 8 shards 21.5 and
+// 22.8 against 22.3 and 23.6, on 4 21.3 and 24.1 against 21.9 and 24.6, on 2 25.2 and 28.2 against 25.4 and 27.8, on one 31.5 and
+// 36.3 against 30.7 and 35.0.  Above 256 the two are within 0.8 of each other up to 512 (of 450 tokens; of 1500 the other way
+// is up to 0.9 quicker), and 1024 on 8 shards take 31.8 against 30.9, 2048 50.1 against 44.5.  A call between other kernels,
+// its code not in the caches, shows the same line (192 and 256 on 8 shards 30.7 and 32.1 against 30.5 and 32.4).
 struct SmallRecLds {
     int64_t start[SMALL_REC_SLOTS + 1];     // d_dst_tok_off
     int64_t src_off[SMALL_REC_SLOTS];

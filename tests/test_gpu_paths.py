@@ -528,10 +528,11 @@ def test_plan_by_shards_with_slots_that_fail_a_check(n, shards):
     assert np.array_equal(dst.cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("n,shards", [(1, 1), (64, 4), (127, 127), (128, 2), (128, 128), (129, 3)])
+@pytest.mark.parametrize("n,shards", [(1, 1), (64, 4), (127, 127), (128, 2), (128, 128), (129, 3), (130, 2), (192, 3), (256, 4), (256, 256),
+                                      (195, 3), (260, 5)])
 @pytest.mark.parametrize("entries", [17, 1040, 2048, 2049])
 def test_single_launch_of_a_very_small_batch(n, shards, entries):
-    """Up to 128 sequences and 2048 table entries in one launch; one sequence and one entry more in two."""
+    """Up to 128 sequences, 256 on shards of up to 64, and 2048 table entries in one launch; a little more of any in two."""
     tokens = (entries - 16) * 1024
     rng = np.random.default_rng(n + entries)
     lens = rng.integers(max(1, tokens // n // 3), max(2, tokens // n), n)
