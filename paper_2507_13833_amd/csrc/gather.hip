@@ -137,53 +137,39 @@ struct SlotS {
 };
 
 // The 16-byte chunks of a granule that do not lie inside one slot: those that a slot's end (or the arena's) falls into and,
-// where slots do not follow each other without a gap, those that a slot's start falls into.  Eight at most, known from the
-// record alone, and moved one element per lane, eight, or four chunks of 1-byte elements, at a time.
-// (c: an edge's chunk, its first token / 4, one byte each; there: which of the eight exist.  Slots' ends first.)
-struct Edges {
-    uint64_t c;
-    uint32_t there;
-};
-__device__ __forceinline__ Edges granule_edges(const SlotS (&e)[REC_SLOTS], int tpc, int32_t limit) {
-    Edges d;
-    d.c = 0;
-    d.there = 0;
-    int32_t before = INT32_MIN;                            // end of the slot before
-#pragma unroll
-    for (int k = 0; k < REC_SLOTS; ++k) {
-        const int32_t en = min(e[k].en, limit), st = e[k].st;
-        if (en > 0 && en < GATHER_GRAN && (en & (tpc - 1)) != 0) d.there |= 1u << k;
-        if (st > 0 && st < limit && st != before && (st & (tpc - 1)) != 0) d.there |= 16u << k;
-        d.c |= (uint64_t)((uint32_t)(en & -tpc) >> 2 & 0xFFu) << (8 * k);
-        d.c |= (uint64_t)((uint32_t)(st & -tpc) >> 2 & 0xFFu) << (8 * (REC_SLOTS + k));
-        before = e[k].en;
-    }
-    return d;
-}
-
-// One element of the edges, per lane: edges from_edge + lane / tpc.
+// where slots do not follow each other without a gap, those that a slot's start falls into.  Four of each at most, known from
+// the record alone, and moved one element per lane: lane q * (tokens of a chunk) + r picks the end (start) of slot q out of the
+// record by itself.  (In scalar registers, eight edges packed into words, the kernels ran out of those, 10 to 48 spilled: 1.8 M
+// tokens of four fields in 2048 sequences took 11.2 us instead of 10.7, 22.6 instead of 21.4 back.)
 struct EdgeElem {
     uint32_t val;
     int32_t  tok;            // the element's token inside the granule, -1: nothing there
 };
-// (select(t): the record's slot at token t)
-__device__ __forceinline__ int32_t edge_token(const Edges& d, int lg_tpc, int lane, int from_edge) {
-    const int q = from_edge + (lane >> lg_tpc);
-    const int32_t t = (int32_t)((uint32_t)(d.c >> (8 * (q & 7))) & 0xFFu) * 4 + (lane & ((1 << lg_tpc) - 1));
-    return q < 2 * REC_SLOTS && ((d.there >> q) & 1u) ? t : -1;
-}
-__device__ __forceinline__ EdgeElem edge_load(const SlotS (&e)[REC_SLOTS], const Edges& d, int lg, int lane, int from_edge, int32_t limit) {
-    EdgeElem x;
-    const int32_t t = edge_token(d, 4 - lg, lane, from_edge);
+template <bool STARTS>
+__device__ __forceinline__ EdgeElem edge_load(const SlotS (&e)[REC_SLOTS], int lg, int lane, int32_t limit) {
+    const int lg_tpc = 4 - lg, in_chunk = (1 << lg_tpc) - 1, q = lane >> lg_tpc;
+    int32_t at = STARTS ? e[0].st : min(e[0].en, limit);
+#pragma unroll
+    for (int k = 1; k < REC_SLOTS; ++k) at = q == k ? (STARTS ? e[k].st : min(e[k].en, limit)) : at;
+    const bool there = q < REC_SLOTS && at > 0 && at < (STARTS ? limit : GATHER_GRAN) && (at & in_chunk) != 0;
+    const int32_t t = (at & ~in_chunk) + (lane & in_chunk);
     int32_t e_sel = INT32_MIN;
     int64_t a_sel = 0;
 #pragma unroll
     for (int k = 0; k < REC_SLOTS; ++k)
         if (t >= e[k].st) { e_sel = e[k].en; a_sel = e[k].ad; }
-    x.tok = t >= 0 && t < e_sel && t < limit ? t : -1;
+    EdgeElem x;
+    x.tok = there && t < e_sel && t < limit ? t : -1;
     x.val = 0;
     if (x.tok >= 0) x.val = load_elem(lg, reinterpret_cast<gptr>(a_sel + ((int64_t)t << lg)));
     return x;
+}
+// (uniform) Whether a slot starts inside the granule behind a gap (else its start is another's end).
+__device__ __forceinline__ bool starts_behind_gap(const SlotS (&e)[REC_SLOTS], int32_t limit) {
+    bool gap = e[0].st > 0 && e[0].st < limit;
+#pragma unroll
+    for (int k = 1; k < REC_SLOTS; ++k) gap = gap || (e[k].st != e[k - 1].en && e[k].st < limit);
+    return gap;
 }
 __device__ __forceinline__ void edge_store(gptr_w dst, int lg, const EdgeElem& x) {
     if (x.tok >= 0) store_elem(lg, dst + ((int64_t)x.tok << lg), x.val);
@@ -197,7 +183,7 @@ struct SparseMove {
     u32x4    v[MAXU];
     uint32_t x[NARROWU], shift[NARROWU];                   // (4-byte sources are 4-byte aligned)
     uint32_t in_mask;                                      // bit u: chunk u is inside one slot
-    bool     part;                                         // (uniform) not every chunk is
+    bool     part, gap;                                    // (uniform) not every chunk is; a slot starts behind a gap
     EdgeElem edge;
     gptr_w   dst;
 
@@ -272,25 +258,28 @@ struct SparseMove {
         // five, or all of them) pays no second round trip
         edge.tok = -1;
         edge.val = 0;
-        if (part) edge = edge_load(e, granule_edges(e, tpc, limit), lg, lane, 0, limit);
+        gap = false;
+        if (part) {
+            edge = edge_load<false>(e, lg, lane, limit);
+            gap = starts_behind_gap(e, limit);
+        }
     }
 
+    // The edges in front of the whole chunks, where they wait for the last load: beside the chunks next to them they fill their
+    // lines at once.  31 M tokens in 65 536 sequences 146 -> 139 us, 158 -> 150 back; 24 M of two 4-byte fields and a 2-byte one
+    // 100.5 -> 98.2 back.
     template <bool BACK>
     __device__ __forceinline__ void store(const FieldDesc& fd, int n_src, const char* back_src, int lg, const u32x16& rec,
                                           int32_t limit) const {
         const int lane = threadIdx.x & (WAVE - 1);
+        if (part) edge_store(dst, lg, edge);               // (uniform)
 #pragma unroll
         for (int u = 0; u < MAXU; ++u)
             if (in_mask & (1u << u)) gstore16(dst + (u * WAVE + lane) * 16, u < NARROWU ? realign(v[u], x[u], shift[u]) : v[u]);
-        if (!part) return;                                 // (uniform)
-        edge_store(dst, lg, edge);
-        if (lg != 0) return;
-        // (1-byte elements: four chunks took the 64 lanes; slots' starts behind a gap are left)
+        if (!gap) return;                                  // (uniform)
         SlotS e[REC_SLOTS];
         slots<BACK>(e, fd, n_src, back_src, lg, rec);
-        const Edges d = granule_edges(e, 16, limit);
-        if ((d.there >> REC_SLOTS) == 0u) return;
-        edge_store(dst, lg, edge_load(e, d, lg, lane, REC_SLOTS, limit));
+        edge_store(dst, lg, edge_load<true>(e, lg, lane, limit));
     }
 };
 
