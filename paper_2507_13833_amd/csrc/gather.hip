@@ -25,6 +25,7 @@
 // and a byte funnel shift for 1- and 2-byte fields) and one aligned 16-byte store;
 // a chunk that touches a slot boundary, padding or the arena end is copied element
 // by element, all its elements in flight together.
+#include <algorithm>
 #include <hip/hip_ext.h>
 #include "dc_device.h"
 #include "dc_internal.h"
@@ -33,10 +34,18 @@ namespace dc {
 
 constexpr int GATHER_BLOCK = 256;
 static_assert(GRAN_PER_TILE == GATHER_BLOCK / WAVE, "one granule per wave");
-// Carrier workgroups from which the narrow fields ride (the chip holds 1792).  Steps of 6 M tokens with 2, 3 and
-// 5 carriers (3000, 4500 and 7500 workgroups): 66.3 -> 65.4 us, 65.2 -> 64.1, 82.7 -> 80.2; of 2 M with 5 and 3.2 M with 2
-// (2500, 1600): 40.9 -> 41.3, 53.5 -> 55.2.
-constexpr int64_t GATHER_RIDE_MIN_WGS = 3000;
+// Carrier workgroups from which the narrow fields ride (the chip holds 2048).  A 1-byte field gains by it from about 3000 on, a
+// 2-byte one, with half as much in flight as a 4-byte field itself, loses unless there are many workgroups or the others make up
+// for it; the line rises with twice the 2-byte fields less the 4-byte and the 1-byte ones.  Us with workgroups of their own ->
+// riding, of both directions: one 1-byte field beside one 4-byte one 36.8 -> 35.5 at 3200 workgroups, 53.9 -> 49.8 at 5000, 76.3 ->
+// 70.4 at 8000; three 51.6 -> 47.3, 79.5 -> 70.7 and 115.4 -> 99.4; one 2-byte field 31.5 -> 33.5, 58.3 -> 57.6 and 83.3 -> 82.4;
+// two 41.2 -> 46.0, 61.8 -> 65.8 and 95.6 -> 97.1; two and a 1-byte one 48.5 -> 54.7, 72.9 -> 76.9 and 128.3 -> 123.4; two 2-byte
+// fields beside two 4-byte ones 32.9 -> 34.8, 47.4 -> 50.0 and 85.4 -> 83.1.
+constexpr int64_t GATHER_RIDE_MIN_WGS = 3000, GATHER_RIDE_MAX_WGS = 8192, GATHER_RIDE_STEP_WGS = 1700;
+static int64_t ride_min_workgroups(int n_four, int n_two, int n_one) {
+    const int64_t line = GATHER_RIDE_MIN_WGS + GATHER_RIDE_STEP_WGS * (2 * n_two - n_four - n_one);
+    return std::min(std::max(line, GATHER_RIDE_MIN_WGS), GATHER_RIDE_MAX_WGS);
+}
 constexpr int32_t LEN_MASK = (1 << LENSH_SHIFT) - 1;
 static_assert(GATHER_GRAN == WAVE * 16, "a wave covers its granule with 1, 2 or 4 chunks per lane");
 static_assert(GRAN_PER_TILE + 1 <= 8, "the tile's slice of the granule table is one 8-dword scalar load");
@@ -843,7 +852,9 @@ static int order_fields(const FieldTable& ft, int64_t tiles, FieldTable* sorted,
     if (skip >= 0) sorted->f[n] = ft.f[skip];
     // riding pays when the carriers alone give the chip several rounds of workgroups; a small
     // batch needs every workgroup it can get
-    const bool ride = n_wide > 0 && tiles * n_wide >= GATHER_RIDE_MIN_WGS;
+    int n_two = 0;
+    for (int f = n_wide; f < n_moved; ++f) n_two += sorted->f[f].elem_bytes == 2 ? 1 : 0;
+    const bool ride = n_wide > 0 && tiles * n_wide >= ride_min_workgroups(n_wide, n_two, n_moved - n_wide - n_two);
     a->n_carriers = (uint32_t)(ride ? n_wide : n_moved);
     a->n_riders = (uint32_t)n_moved - a->n_carriers;
     a->tiles = (uint32_t)tiles;

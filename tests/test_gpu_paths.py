@@ -556,6 +556,16 @@ def test_edges_of_granules_with_riders(lo, hi, align):
         check_scatter(w, label=f"{n} sequences, riders")
 
 
+@pytest.mark.parametrize("n_src", [1, 3])
+def test_two_byte_field_beside_one_four_byte_field(n_src):
+    """3000 workgroups of one 4-byte field, where a 2-byte field has its own, and 6000 of two, where it rides with a 1-byte field."""
+    lens = np.random.default_rng(n_src).integers(1000, 5000, 4200).astype(np.int32)
+    w = _custom(lens, 4, 12, 1 << 15, n_src=n_src, seed=n_src)
+    assert 3000 <= w.total_tokens // 4096 < 8192
+    check_gather_advantage(w, align=7, label="one 4-byte and one 2-byte carrier")
+    check_scatter(w, label="the same, back")
+
+
 @pytest.mark.parametrize("kind", ["geometric", "equal", "long", "rising", "few"])
 @pytest.mark.parametrize("n", [16385, 24576, 24577, 32769, 65536, 65537, 131072, 131073])
 def test_sort_by_portions(n, kind):
