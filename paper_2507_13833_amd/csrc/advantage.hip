@@ -24,13 +24,17 @@ __global__ __launch_bounds__(ADV_BLOCK) void advantage_kernel(AdvArgs a, SourceD
 // advantage by itself (the same sums in the same order), and the wave then streams their tokens, four sequences' mask
 // words in flight at a time, the first four's asked for ahead of the statistics.
 // With a wave per sequence every lane of it works out the same statistics, ~350 vector instructions in float64 for a
-// sequence whose tokens take ten, and 65 536 of those are the stage's time: 69.0 us for 28 M tokens in 65 536 sequences,
-// 44.1 with eight to a wave (four: 46.2; 32 768 of 600 take 30.1 and 30.3, 24 576 of 500 23.2 and 20.9, 16 384 of 300 15.3 and
-// 13.0).  A wave waits for nothing but its groups' loads: while the ragged heads and tails, three tokens each, were read where
-// they are written, each such read waited for the stores in front of it (48.0).  Below 16 384 sequences there are not enough waves left (8192
+// sequence whose tokens take ten, and 65 536 of those are the stage's time: 69.0 us for 28 M tokens in 65 536 sequences, 43.3
+// with eight to a wave.  A wave waits for nothing but its groups' loads: while the ragged heads and tails, three tokens each,
+// were read where they are written, each such read waited for the stores in front of it (31 M tokens in 65 536 sequences 48.0
+// us, now 44.1; sequences that all have one length, and no ragged ends, lose 1 to 5 %: 32 768 of 300 18.4, now 19.3).  Below 16 384 sequences there are not enough waves left (8192
 // of 57 tokens 10.4 -> 11.4), and longer ones want their tokens spread over more waves; the line is the mean above which
 // the stage with a quarter of its sequences past the four steps is slower so (16 384 of 326 18.3 / 18.4, of 469 20.6 / 22.9;
 // 24 576 of 416 27.1 / 27.8, of 678 32.2 / 34.8; 32 768 of 792 44.0 / 41.3; 49 152 of 998 69.3 / 68.5).
+// Four to a wave where eight leave too few waves (us with eight and with four, groups of 8): 16 384 of 20 tokens 11.3 / 10.4, of
+// 300 14.4 / 13.1; 20 480 of 20 12.1 / 11.5, of 300 16.1 / 14.5; 24 576 of 20 12.1 / 12.7, of 300 19.1 / 16.4; 32 760 of 20
+// 13.7 / 15.5, of 200 17.2 / 17.8, of 300 21.2 / 20.0; 40 000 of 300 24.0 / 25.3.  Every wave works its groups out for itself, so
+// not with large groups: 20 480 of 200 in groups of 16 14.9 / 15.1, of 64 21.7 / 23.8, of 1024 168 / 204.
 // Long sequences are not a single wave's: the first ADV_SETS workgroups look for them, each in a set of its own (of
 // neighbours, as the answers to one prompt are, every one in another set), and take them with all their waves and
 // ADV_UNROLL steps in flight.  16 384 sequences of 190 tokens, 64 of 32 K among them: 28.9 us with a wave per sequence, 17.9
@@ -44,7 +48,11 @@ constexpr int ADV_SETS = 509;                          // (half as many: a Paret
 constexpr int ADV_BRIEF_MIN_SEQ = 16384;               // a wave per sequence fills the chip's wave slots twice
 constexpr int ADV_BRIEF_MAX_MEAN = ADV_STEPS * WAVE * 4;       // (what the four steps take)
 constexpr int ADV_BRIEF_SEQ_PER_TOKEN = 48;            // sequences per token of the mean length, at least
-constexpr int ADV_EIGHT_MIN_SEQ = 32768;               // eight sequences to a wave from here on, four below
+// Four sequences to a wave instead of eight: below the first line, or below the second if the sequences are not very short;
+// not where the groups are large, as every wave works out its groups' sums.
+constexpr int ADV_FOUR_MAX_SEQ = 22528, ADV_FOUR_LONGER_MAX_SEQ = 32768;
+constexpr int ADV_FOUR_LONGER_MIN_MEAN = 225;
+constexpr int ADV_FOUR_MAX_GROUP = 16;                 // responses to a prompt, on average
 
 __device__ __forceinline__ bool adv_long(int32_t ln) { return ln >= ADV_LONG && ln <= DC_MAX_SEQ_LEN; }
 
@@ -240,8 +248,10 @@ hipError_t launch_advantage(int32_t n_seq, const SourceDesc& src, const int64_t*
             const int64_t blocks = (adv_waves(n_seq, n_groups) + ADV_WAVES * seqs - 1) / (ADV_WAVES * seqs);
             hipLaunchKernelGGL(kernel, dim3((unsigned)blocks + ADV_SETS), dim3(ADV_BLOCK), 0, st, a, src);
         };
-        if (n_seq >= ADV_EIGHT_MIN_SEQ) launch(advantage_brief_kernel<8>, 8);
-        else launch(advantage_brief_kernel<4>, 4);
+        const bool four = (int64_t)n_groups * ADV_FOUR_MAX_GROUP >= n_seq &&
+                          (n_seq < ADV_FOUR_MAX_SEQ || (n_seq < ADV_FOUR_LONGER_MAX_SEQ && tokens / n_seq >= ADV_FOUR_LONGER_MIN_MEAN));
+        if (four) launch(advantage_brief_kernel<4>, 4);
+        else launch(advantage_brief_kernel<8>, 8);
         return hipGetLastError();
     }
     const int64_t grid = (adv_waves(n_seq, n_groups) + ADV_WAVES - 1) / ADV_WAVES;

@@ -576,12 +576,13 @@ def test_sort_by_portions(n, kind):
     _check_balance_ws(lens.astype(np.int32), 8, cap=-(-n // 8) if n % 8 else 0, label=f"{n} sequences, {kind}")
 
 
-@pytest.mark.parametrize("n,n_src", [(16384, 1), (16390, 2), (32767, 1), (32768, 4), (32772, 3)])
-def test_heads_and_tails_of_short_sequences(n, n_src):
+@pytest.mark.parametrize("n,n_src,longest", [(16384, 1, 14), (16390, 2, 14), (32767, 1, 14), (32768, 4, 14), (32772, 3, 14), (22527, 1, 14),
+                                             (22528, 2, 14), (22528, 4, 470), (32767, 1, 470), (32768, 1, 470)])
+def test_heads_and_tails_of_short_sequences(n, n_src, longest):
     """Four and eight short sequences to a wave, each starting and ending anywhere in a 16-byte chunk: sequences inside one
     chunk, of one chunk, and without a whole one."""
     rng = np.random.default_rng(n)
-    lens = rng.integers(1, 14, n)
+    lens = rng.integers(1, longest, n)
     lens[::11] = rng.integers(250, 262, len(lens[::11]))
     lens[5::1001] = rng.integers(1020, 1030, len(lens[5::1001]))
     check_step(_custom(lens.astype(np.int32), 1 if n % 2 else 2, 1, 1 << 16, n_src=n_src, seed=n, fields=()), label=f"{n} sequences")
