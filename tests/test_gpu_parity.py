@@ -133,8 +133,8 @@ def test_full_config_as_benchmarked(cfg):
 
 @pytest.mark.parametrize("cfg", [1, 2, 3, 4, 5])
 def test_full_config_balance_and_plan_in_one_call(cfg):
-    """dc_balance_plan_group_advantage + dc_gather (what bench.py times): on configs 3-5 the plan runs as the tail
-    of the balance workgroup, on configs 1 and 2 (4 and 8 shards) the call issues the separate kernels."""
+    """dc_balance_plan_group_advantage + dc_gather (what bench.py times): two launches and the gather, the second launch
+    plans by shards."""
     import torch
     d = check_step(workloads.make_workload(cfg), label=f"config {cfg}, balance + plan in one call", two_calls=True)
     first = {k: v.clone() for k, v in d.dst_fields.items()}

@@ -98,10 +98,11 @@ def test_sort_of_few_sequences(n, kind):
 
 @pytest.mark.parametrize("entries", [17, 1023, 1024, 1025, 2047, 2048, 2049])
 @pytest.mark.parametrize("align", [1, 48])
-def test_granule_tables_of_a_small_batch(entries, align):
-    """Up to 2048 table entries (the arena's granules and 16 more) the balance workgroup makes them itself, a lane one or two
-    of them, behind that a launch does; the arena ends with the last granule and one token into it."""
-    n, shards = 256, 4
+@pytest.mark.parametrize("n,shards", [(128, 4), (256, 4), (512, 4)])
+def test_granule_tables_of_a_small_batch(entries, align, n, shards):
+    """Up to 256 sequences on shards of 64 and 2048 table entries (the arena's granules and 16 more) the balance workgroup makes
+    them itself, a lane one or two of them, beyond either the launch that plans by shards does; the arena ends with the last
+    granule and one token into it."""
     for tokens in ((entries - 16) * 1024, (entries - 17) * 1024 + 1):
         if tokens < n + shards * (align - 1):
             continue
@@ -686,3 +687,44 @@ def test_plan_by_shards_whose_counts_do_not_come(n, shards, budget, align, looks
     lens = np.random.default_rng(n + budget).integers(1, 41, n).astype(np.int32)
     w = _custom(lens, 1, shards, budget, n_src=3 if n % 3 == 0 else 1, seed=n, fields=("i32",))
     check_step(w, align=align, two_calls=True, label=f"{n} slots on {shards} shards, {looks} looks")
+
+
+@pytest.mark.parametrize("n,shards", [(64, 16), (256, 4), (512, 4), (2560, 256), (4096, 64), (4100, 2), (16384, 4)])
+def test_status_codes_of_balance_and_plan_in_one_call(n, shards):
+    """What the call refuses on the device, in one launch, planned by shards, and with shards of more than 2048 slots; what a
+    refusal leaves whole is right."""
+    torch, binding, runner = _gpu()
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 60, n).astype(np.int32)
+    lens[n // 3] = 200
+    w = _custom(lens, 1, shards, 100, n_src=2, seed=n, fields=("i32",))
+    d = runner.DeviceBatch(w)
+    d.step_two_calls(); torch.cuda.synchronize()
+    assert d.read_status() == binding.DC_ERR_SEQ_EXCEEDS_BUDGET        # 200 > budget 100: alone in its micro-batch
+    bal = oracle.balance(w.seq_len, shards)
+    assert np.array_equal(d.perm.cpu().numpy(), bal.perm) and np.array_equal(d.shard_of_seq.cpu().numpy(), bal.shard_of_seq)
+    assert np.array_equal(d.dst_tok_off.cpu().numpy(), oracle.plan(w.seq_len, bal.perm, bal.shard_seq_off, 1 << 20).dst_tok_off)
+
+    w = _custom(lens, 1, shards, 4096, n_src=2, seed=n, fields=("i32",))
+    for at in (0, n // 2, n - 1):
+        for bad in (0, -7, (1 << 24) + 1):
+            d = runner.DeviceBatch(w)
+            d.seq_len[at] = bad
+            d.capacity = 1 << 17                                       # (what its arenas do not have is not gathered)
+            d.ws_bytes = binding.dc_workspace_bytes(d.prm, d.capacity)
+            d.ws = torch.zeros(d.ws_bytes, dtype=torch.uint8, device=d.dev)
+            d.balance_plan_group_advantage(); torch.cuda.synchronize()
+            assert d.read_status() == binding.DC_ERR_ZERO_LENGTH_SEQ
+    for align in (1, 5):
+        d = runner.DeviceBatch(w, align_tokens=align)
+        pl = oracle.plan(w.seq_len, bal.perm, bal.shard_seq_off, w.token_budget, align)
+        d.capacity = int(pl.dst_tok_off[-1]) - 1                       # arena one token short
+        d.step_two_calls(); torch.cuda.synchronize()
+        assert d.read_status() == binding.DC_ERR_OVERFLOW
+        assert np.array_equal(d.dst_tok_off.cpu().numpy(), pl.dst_tok_off) and int(d.n_mb.item()) == pl.n_mb
+        assert np.array_equal(d.cu_seqlens.cpu().numpy()[:n + pl.n_mb], pl.cu_seqlens)
+    for at in (1, n - 1):
+        d = runner.DeviceBatch(w)
+        d.src_tok_off[at] = int(w.src_shard_tokens[at // (n // 2)])    # a sequence that would start beyond its buffer
+        d.step_two_calls(); torch.cuda.synchronize()
+        assert d.read_status() == binding.DC_ERR_BAD_LAYOUT
