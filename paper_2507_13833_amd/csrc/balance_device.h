@@ -914,9 +914,8 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
 //   sure     the bound of lpt_rounds_packed says that the round places one item on every worker: nothing is tested;
 //   general  the longest accepted prefix of the ranks takes its items; full workers have sorted behind the open ones.
 // Bound by the chain of sorts, of which one wave runs a step in about 20 cycles whether it carries one or two chains.
-// Up to 256 workers: 8192 sequences on 128 workers take 66 us with the plan in the same launch, where the rounds that the
-// whole workgroup runs (lpt_rounds_wide32_portion: five barriers and a bisection per 64 workers in each) took 175 and
-// slots and plan 23 more; 25 472 sequences on 128 workers: 95 us for the assignment, a step of 632 us takes 285.  With
+// Up to 256 workers: 8192 sequences on 128 workers take 41 us up to perm, where with the rounds that the whole workgroup runs
+// (lpt_rounds_wide32_portion: five barriers and a bisection per 64 workers in each) the launch took 175; 25 472 sequences on 128 workers: 95 us for the assignment, a step of 632 us takes 285.  With
 // eight keys to a lane a sort is four times the work and a step of the network is no longer hidden by its neighbours.
 //
 // items, rows, pitch: as for lpt_rounds_packed.  The call returns, before all N items are placed, when a row holds

@@ -297,9 +297,9 @@ struct SparseMove {
 // before the slot behind its last one, whose start the last entry holds ("no slot" if there is none); a chunk that this
 // start falls into is served by both passes, each its own tokens.  Lane k stages slot k.
 // Bound by latency: the granule's table entries, the slots' descriptors and the payload are each one trip to memory for
-// the whole granule.  The gather kernel takes 6.6 us for 15 550 tokens in 64 sequences, 34 us for 3.3 M tokens in 15 360
-// and 261 us for 31.5 M tokens in 65 536 (5 fields).  With the slots staged per tile by the workgroup, one chunk per lane
-// at a time and an edge chunk's elements one after the other it took 14.7, 70 and 307 us.
+// the whole granule.  The gather kernel takes 6.2 us for 15 550 tokens in 64 sequences and 34 us for 3.3 M tokens in 15 360 (5
+// fields).  With the slots staged per tile by the workgroup, one chunk per lane at a time and an edge chunk's elements one
+// after the other it took 14.7 and 70 us.
 constexpr int DENSE_SLOTS = WAVE - 1;
 constexpr int DENSE_CHUNKS = GATHER_GRAN / 4;                  // chunks of a granule of 4-byte elements, the most there are
 struct WaveSlots {

@@ -1,16 +1,18 @@
 // The plan, the granule tables and the slots' sources behind a launch that has made perm with Algorithm 1 as printed (every
 // shard holds C slots), by a few workgroups per shard.
 //
-// Bound by latency: three trips to memory in a row (perm; the sequences' lengths and offsets; the outputs), whatever the
-// batch.  A shard's slots, its micro-batches and its stretch of the token axis concern nobody else, but for two sums over
+// Bound by latency: two trips to memory (perm; the sequences' lengths and offsets), then a chain of reads of the LDS.  Clocks of
+// the last walker on 32 shards of 256 slots (2.4 GHz): lengths and bases 1.3 us, prefix 0.6, every slot's end 1.8, hops 1.3,
+// counts 0.6, the others' counts 1.2, outputs 0.6; of a slice: 1.3, 0.6, sources 1.0, granules 1.7.
+// A shard's slots, its micro-batches and its stretch of the token axis concern nobody else, but for two sums over
 // the shards: where a shard's tokens start (the loads are known before this launch) and how many micro-batches the shards
 // before it hold.  So workgroup p walks shard p's micro-batches, P + slice * P + p writes a part of its slots and granules;
 // each of them makes the prefix of the shard's lengths for itself, and the only thing that travels between workgroups
 // is one count per shard.
-// 8.2 to 11 us (rocprofv3) on 8 to 128 shards of 64 to 640 slots, 3 M to 42 M tokens.  With the plan as the tail of the
+// 7.4 to 10.1 us (rocprofv3) on 4 to 128 shards of 64 to 640 slots, 0.2 M to 42 M tokens.  With the plan as the tail of the
 // balance workgroup (12 to 13 us, and 2 to 6 for shard_of_seq and the slots' lengths) and the tables in a launch behind it
-// (7.4 to 9.8) the two launches took: 2048 sequences on 8 shards 41 us, now 35; 15 360 on 24 112, now 95; 8192 on 32 72, now
-// 59; 16 384 on 64 106, now 90; 8192 on 128 66, now 50.
+// (7.4 to 9.8) the two launches took: 2048 sequences on 8 shards 41 us, now 34; 15 360 on 24 112, now 91; 8192 on 32 72, now
+// 57; 16 384 on 64 106, now 88; 8192 on 128 66, now 50.
 // Shards of more than 2048 slots (up to sixteen to a lane, in loops that keep nothing in registers from one pass to the next:
 // unrolled, the walk spilled 94 of them and took 8 to 12 us more), both launches: 16 384 sequences on 4 shards 302 us with
 // 4096 tokens to a micro-batch and 296 with 65 536, as the balance workgroup's tail 352 and 316; 8190 on 3 210 and 205, so
