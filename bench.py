@@ -38,10 +38,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 TRAFFIC_SOURCE = "profiles/hbm_traffic_config5_pmc.txt"
 TRAFFIC = {
     # config: (fetch bytes + write bytes per gather launch, digest of csrc/gather.hip + csrc/dc_internal.h)
-    5: (1040842000 + 983683000, "6383be69c7a7e02a"),
+    5: (1039640900 + 977283600, "b8beb8f3a880185d"),
 }
 TRAFFIC_ADV = {                                          # the same for dc_gather_advantage's kernel
-    5: (866161100 + 983153000, "6383be69c7a7e02a"),
+    5: (865335500 + 978360300, "b8beb8f3a880185d"),
 }
 
 
