@@ -295,7 +295,8 @@ __global__ __launch_bounds__(BLOCK) void plan_shards_kernel(PlanArgs a, SourceDe
                 if ((opens >> lane) & 1ull) first_of[micro_batch(q, opens)] = (uint16_t)(q * BLOCK + tid);
             }
             // ---- the micro-batches of the shards before this one ----
-            if (!published) theirs = tid < p ? wait_count(s.mb_counts, P, tid, s.looks) : 0;
+            // (readfirstlane: without it the compiler sets scratch memory aside that the kernel never touches)
+            if (!published) theirs = tid < p ? wait_count(s.mb_counts, P, tid, __builtin_amdgcn_readfirstlane(s.looks)) : 0;
             else if (tid == target && target != p) theirs = n_mb;
             published = true;
             const bool missing = tid < p && theirs == 0;
