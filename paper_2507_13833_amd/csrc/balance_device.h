@@ -553,7 +553,7 @@ __device__ __forceinline__ int lpt_rounds(int N, int P, int C, int32_t* keys, co
 }
 
 // ---------------------------------------------------------------------------------------------------
-// The rounds once more for the printed algorithm on up to 32 or on 64 workers (P <= WIDTH = 16 or 32, or P = 64; N == P * C) with
+// The rounds once more for the printed algorithm on up to 32 or on 64 workers (P <= WIDTH = 2, 4, 8, 16 or 32, or P = 64; N == P * C) with
 // lengths below 2^16: the common case, and the one in which the rounds are most of the kernel's time.
 //
 // A round of one wave is the sort of the 64 updated keys, a chain of dependent instructions with idle
@@ -604,6 +604,10 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
     return c;
 }
 
+// WIDTH 2 and 4: the sort of 8 lanes is six steps, that of 4 is three, of 2 one, and the list on few workers is many rounds: a
+// sure round takes 151 cycles on 8 lanes, 92 on 4; whole steps: 512 sequences on 4 shards 28.9 -> 26.8 us, 1104 on 3 47.9 -> 42.1,
+// 5352 on 3 145 -> 117.
+//
 // SKIP: rounds of one length are not sorted (mixed_rounds).  Not in the kernels where such rounds are rare and the code's
 // mere presence costs 0.4 to 3.7 us: up to 2048 sequences, and 64 workers up to DC_MAX_SEQ (a length would have to occur more
 // than 64 times among 16 384); nor, up to DC_MAX_SEQ, for 8 workers, whose sort is six steps.  Every portion of a longer list
@@ -631,8 +635,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     const uint64_t everyone = P == WAVE ? ~0ull : (1ull << P) - 1ull;
     constexpr bool EVERY_LANE = WIDTH == WAVE;
     constexpr int NS = net_steps(WIDTH);
-    constexpr int LAST = NS - 1;                                  // the last gap of the sort (what an 8-lane sort has no later gap for goes there)
-    static_assert(LAST >= 5, "the rounds' side work is laid out over six gaps at least");
+    constexpr int LAST = NS - 1;                                  // the last gap of the sort (what a narrow sort has no later gap for goes there)
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     uint32_t key = (mine_exists && C > 0) ? lane : full;
     int32_t count = 0;
@@ -691,16 +694,16 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                 int32_t before4 = 0;
                 v = wave_sort_steps<WIDTH, 0, NS>(v, [&](auto slot) {
                     constexpr int S = decltype(slot)::value;
-                    constexpr int STORE = LEVEL ? 3 : (LAST < 9 ? LAST : 9);      // (!LEVEL: the cross-lane read has come back)
-                    if constexpr (S == 0) { e1 = *next_item; id = sk & 63u; }
-                    if constexpr (S == 1) { at = __umul24(id, pitch4); next_item += stride; }
-                    if constexpr (S == 2 && !LEVEL) before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4);
-                    if constexpr (S == (LEVEL ? 2 : STORE)) {
+                    auto in_gap = [](int want) { return S == (want < LAST ? want : LAST); };
+                    if constexpr (in_gap(0)) { e1 = *next_item; id = sk & 63u; }
+                    if constexpr (in_gap(1)) { at = __umul24(id, pitch4); next_item += stride; }
+                    if constexpr (in_gap(2) && !LEVEL) before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4);
+                    if constexpr (in_gap(LEVEL ? 2 : 9)) {        // (!LEVEL: the cross-lane read has come back)
                         at += row_at;
                         if constexpr (!LEVEL) at += (uint32_t)before4;
                         if constexpr (!EVERY_LANE) at = offers ? at : spare_at;
                     }
-                    if constexpr (S == STORE) *reinterpret_cast<uint32_t*>(rows_b + at) = e;      // filed with its worker
+                    if constexpr (in_gap(LEVEL ? 3 : 9)) *reinterpret_cast<uint32_t*>(rows_b + at) = e;      // filed with its worker
                     if constexpr (S == LAST) { e = e1; len = e1 >> 16; }
                 });
                 sk = v;
@@ -743,16 +746,19 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                 int32_t before4 = 0;
                 v = wave_sort_steps<WIDTH, 0, NS>(v, [&](auto slot) {
                     constexpr int S = decltype(slot)::value;
-                    constexpr int STORE = LAST < 9 ? LAST : 9;
-                    if constexpr (S == 0) { e1 = *next_item; m = net_swap_order(m); }
-                    if constexpr (S == 1) { id = sk & 63u; m = umin32(m, dpp_mov<DPP_ROW_SHR1>(NONE, m)); }
-                    if constexpr (S == 2) { before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4); m = umin32(m, dpp_mov<DPP_ROW_SHR2>(NONE, m)); }
-                    if constexpr (S == 3) { at = __umul24(id, pitch4); m = umin32(m, dpp_mov<DPP_ROW_SHR4>(NONE, m)); }
-                    if constexpr (S == 4 && WIDTH > 8) m = umin32(m, dpp_mov<DPP_ROW_SHR8>(NONE, m));
-                    if constexpr (S == 5 && WIDTH > 16) m = umin32(m, dpp_mov<DPP_ROW_BCAST15, 0xA>(NONE, m));
-                    if constexpr (S == 6 && WIDTH > 32) m = umin32(m, dpp_mov<DPP_ROW_BCAST31, 0xC>(NONE, m));
-                    if constexpr (S == (LAST < 7 ? LAST : 7)) { m = dpp_mov<DPP_WAVE_SHR1>(NONE, m); sk_by_rank = net_swap_order(sk_in); }
-                    if constexpr (S == STORE) {
+                    auto in_gap = [](int want) { return S == (want < LAST ? want : LAST); };
+                    if constexpr (in_gap(0)) { e1 = *next_item; m = net_swap_order(m); }
+                    if constexpr (in_gap(1)) { id = sk & 63u; m = umin32(m, dpp_mov<DPP_ROW_SHR1>(NONE, m)); }
+                    if constexpr (in_gap(2)) {
+                        before4 = __builtin_amdgcn_ds_bpermute((int)(id << 2), count4);
+                        if constexpr (WIDTH > 2) m = umin32(m, dpp_mov<DPP_ROW_SHR2>(NONE, m));
+                    }
+                    if constexpr (in_gap(3)) { at = __umul24(id, pitch4); if constexpr (WIDTH > 4) m = umin32(m, dpp_mov<DPP_ROW_SHR4>(NONE, m)); }
+                    if constexpr (in_gap(4) && WIDTH > 8) m = umin32(m, dpp_mov<DPP_ROW_SHR8>(NONE, m));
+                    if constexpr (in_gap(5) && WIDTH > 16) m = umin32(m, dpp_mov<DPP_ROW_BCAST15, 0xA>(NONE, m));
+                    if constexpr (in_gap(6) && WIDTH > 32) m = umin32(m, dpp_mov<DPP_ROW_BCAST31, 0xC>(NONE, m));
+                    if constexpr (in_gap(7)) { m = dpp_mov<DPP_WAVE_SHR1>(NONE, m); sk_by_rank = net_swap_order(sk_in); }
+                    if constexpr (in_gap(9)) {
                         at += (uint32_t)before4 + 4u * (uint32_t)r;
                         if constexpr (!EVERY_LANE) at = offers ? at : spare_at;
                         *reinterpret_cast<uint32_t*>(rows_b + at) = e;
@@ -780,7 +786,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                 v = wave_sort_steps<WIDTH, 0, NS>(v, [&](auto slot) {
                     constexpr int S = decltype(slot)::value;
                     if constexpr (S == 0) e1 = *at;
-                    if constexpr (S == 1) behind4 = __builtin_amdgcn_ds_permute((int)(to << 2), take ? 0 : 4);
+                    if constexpr (S == (LAST < 1 ? LAST : 1)) behind4 = __builtin_amdgcn_ds_permute((int)(to << 2), take ? 0 : 4);
                     if constexpr (S == LAST) { count4 -= behind4; e = e1; len = e1 >> 16; }
                 });
                 sk = v;
@@ -825,7 +831,15 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                         mixed_rounds(sure * FAST_BATCH);
                         rounds += sure * FAST_BATCH;
                     } else if (level) {
-                        for (int b = 0; b < sure; ++b) {
+                        int b = sure;
+                        if constexpr (WIDTH <= 8) {
+                            for (; b >= 2; b -= 2) {              // (the loop's own branch: ten cycles a round of 90 to 150)
+#pragma unroll
+                                for (int u = 0; u < 2 * FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
+                                rounds += 2 * FAST_BATCH;
+                            }
+                        }
+                        for (; b > 0; --b) {
 #pragma unroll
                             for (int u = 0; u < FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
                             rounds += FAST_BATCH;
@@ -1378,12 +1392,12 @@ constexpr int SMALL_IPT = SMALL_SORT_MAX / BAL_BLOCK;
 // plan that follows in this workgroup.  BAL_PERM: everything but shard_of_seq, which the launch that plans by shards writes.
 enum BalTail { BAL_ALL, BAL_SLOTS, BAL_PERM };
 
-// FEW: the code for up to 32 or 64 workers; MANY: for the other numbers of them.  TAIL other than BAL_ALL: only with
+// NARROW: the code for up to 4 workers; FEW: for 5 to 32, or 64; MANY: for the other numbers of them.  TAIL other than BAL_ALL: only with
 // P * C == N.  What a launch is never made for is left out of its kernel (it is executed once from front to back, most
 // of it straight code that the instruction cache has not seen, and its size shows in its time).
 // IPT: sequences per lane at most, BAL_ROUNDS, SMALL_IPT for a launch of up to SMALL_SORT_MAX sequences, or 1 (TAIL other than
 // BAL_ALL with BAL_ROUNDS: for more than SMALL_SORT_MAX).
-template <BalTail TAIL, bool FEW, bool MANY, int IPT>
+template <BalTail TAIL, bool NARROW, bool FEW, bool MANY, int IPT>
 __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, int32_t C,
                                                const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                                int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
@@ -1490,22 +1504,43 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                 lds_barrier();
                 if (w == 0) lpt_rounds_multi_any(N, P, items, rows, rpitch, C + 1, spare, m, shard_load);     // (a row takes a whole partition)
             }
+        } else if (NARROW && P == 1) {                            // (uniform) one partition: the list is its row (1888
+            // sequences, a whole step: 146 us with a round for each, 32.6 so)
+            uint32_t sum = 0;                                     // (at most DC_MAX_SEQ lengths below 2^16)
+            for (int i = tid; i < N; i += BAL_BLOCK) sum += items[i] >> 16;
+            sum = wave_incl_scan_add_u32(sum);
+            if (lane == WAVE - 1) L.red[w] = (int32_t)sum;
+            lds_barrier();
+            if (tid == 0) {
+                int64_t total = 0;
+                for (int i = 0; i < BAL_WAVES; ++i) total += L.red[i];
+                shard_load[0] = total;
+                shard_seq_off[0] = 0;
+                shard_seq_off[1] = N;
+            }
         } else if (w == 0) {
-            if constexpr (FEW) {
-                int32_t* worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;
+            int32_t* worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;
+            if (NARROW && P <= 4) {
+                if constexpr (NARROW) {
+                    if (P <= 2) lpt_rounds_packed<2>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                    else lpt_rounds_packed<4>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                }
+            } else if constexpr (FEW) {
                 if (P <= 8) lpt_rounds_packed<8>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else if (P <= 16) lpt_rounds_packed<16, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else if (P <= 32) lpt_rounds_packed<32, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else lpt_rounds_packed<64>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-                if (lane < P) shard_seq_off[lane] = lane * C;     // (every partition ends with C items)
-                if (lane == 0) shard_seq_off[P] = N;
             }
+            if (lane < P) shard_seq_off[lane] = lane * C;         // (every partition ends with C items)
+            if (lane == 0) shard_seq_off[P] = N;
         }
         lds_barrier();
         // ---- P_0, P_1, ... are the rows; the worker of a sequence is the row it stands in ----
         // (gathered by sequence in the LDS, where the sorted items were, so that both outputs leave in index
         // order: 16 384 scattered 4-byte stores take longer to drain than the rounds save)
-        uint32_t* const worker_of = items;
+        const bool one_row = NARROW && P == 1;                    // (then the sorted items are the row)
+        const uint32_t* const row_of = one_row ? items : rows;
+        uint32_t* const worker_of = one_row ? rows : items;
         // (slot q = worker q / C, place q mod C: one division per lane, then steps of BAL_BLOCK slots)
         const int step_k = BAL_BLOCK / C, step_r = BAL_BLOCK - step_k * C;
         int k = tid / C, r = tid - k * C;
@@ -1517,7 +1552,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             constexpr int qq = decltype(qc)::value;
             const int q = qq * BAL_BLOCK + tid;
             if (q < N) {
-                const uint32_t e = rows[k * rpitch + r];
+                const uint32_t e = row_of[k * rpitch + r];
                 const uint32_t u = min(e & 0xFFFFu, (uint32_t)(N - 1));      // (no index leaves the arrays whatever a word holds)
                 perm[q] = (int32_t)u;
                 if constexpr (TAIL != BAL_PERM) worker_of[u] = (uint32_t)k;
@@ -1564,7 +1599,9 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         int32_t* spare = L.spare;
         LptCarry fresh = lpt_fresh(P, C);
         int n_placed = 0;
-        if constexpr (FEW) {
+        if constexpr (NARROW && !FEW) {
+            n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+        } else if constexpr (FEW) {
             if (exact && P == 16) n_placed = lpt_rounds<16, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (exact && P == 32) n_placed = lpt_rounds<32, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (exact) n_placed = lpt_rounds<64, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
@@ -1637,7 +1674,7 @@ __device__ __forceinline__ void balance_body(BalLds& L, int32_t N, int32_t P, in
                                              int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
                                              int64_t* __restrict__ shard_load, int32_t* status) {
     SlotRegs<BAL_ROUNDS> unused;
-    balance_body_t<BAL_ALL, true, true, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
+    balance_body_t<BAL_ALL, true, true, true, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
 }
 
 }  // namespace dc

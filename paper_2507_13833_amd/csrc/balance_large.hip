@@ -149,6 +149,7 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_large_kernel(int32_t N, int
 
     if (packed_rounds_apply(N, P, C, mx)) {                       // (uniform)
         if (multi_serves(P)) packed_portions_many(L, N, P, C, shard_seq_off, shard_load, ws);
+        else if (P <= 4) packed_portions_few<4>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else if (P <= 8) packed_portions_few<8>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else if (P <= 16) packed_portions_few<16>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else if (P <= 32) packed_portions_few<32>(L, N, P, C, mx, shard_seq_off, shard_load, ws);

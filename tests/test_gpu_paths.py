@@ -728,3 +728,14 @@ def test_status_codes_of_balance_and_plan_in_one_call(n, shards):
         d.src_tok_off[at] = int(w.src_shard_tokens[at // (n // 2)])    # a sequence that would start beyond its buffer
         d.step_two_calls(); torch.cuda.synchronize()
         assert d.read_status() == binding.DC_ERR_BAD_LAYOUT
+
+
+@pytest.mark.parametrize("kind", ["geometric", "equal", "tail", "long"])
+@pytest.mark.parametrize("n,shards", [(1, 1), (63, 1), (129, 1), (2048, 1), (2049, 1), (16384, 1), (2, 2), (6, 2), (130, 2), (2050, 2), (16384, 2),
+                                      (3, 3), (21, 3), (387, 3), (2052, 3), (16383, 3), (4, 4), (12, 4), (128, 4), (260, 4), (2052, 4), (16384, 4)])
+def test_up_to_four_workers(n, shards, kind):
+    """Sorts of two and four lanes, and the one partition that needs none: the ends of the kernels' ranges, rounds left over."""
+    lens = _lengths(kind, n, np.random.default_rng(n + 31 * shards)).astype(np.int32)
+    w = _custom(np.minimum(lens, 2000) if kind == "tail" and n > 1000 else lens, 1, shards, 1 << 17, fields=())
+    check_step(w, align=7, label=f"{n} on {shards}, {kind}, one call", two_calls=True)
+    check_step(w, align=7, label=f"{n} on {shards}, {kind}")
