@@ -21,7 +21,7 @@
 //      total load (the minimum grows by at most one longest sequence per round, so
 //      the check runs every so many rounds, not in each);
 //      Up to 256 workers with N = P * C and lengths below 2^16 the wave keeps length and index of an
-//      item in one word and one, two or four keys to a lane (lpt_rounds_packed, lpt_rounds_multi);
+//      item in one word and one, two or four keys to a lane (lpt_rounds_packed, above 64 lpt_rounds_multi);
 //      otherwise, with more than 64 workers, the same rounds run on the whole workgroup, thread k =
 //      worker k: the accepted prefix comes from a workgroup-wide min-scan, and keys travel between
 //      rank order and worker order through LDS;

@@ -553,7 +553,7 @@ __device__ __forceinline__ int lpt_rounds(int N, int P, int C, int32_t* keys, co
 }
 
 // ---------------------------------------------------------------------------------------------------
-// The rounds once more for the printed algorithm on up to 32 or on 64 workers (P <= WIDTH = 2, 4, 8, 16 or 32, or P = 64; N == P * C) with
+// The rounds once more for the printed algorithm on up to 64 workers (P <= WIDTH = 2, 4, 8, 16, 32 or 64; N == P * C) with
 // lengths below 2^16: the common case, and the one in which the rounds are most of the kernel's time.
 //
 // A round of one wave is the sort of the 64 updated keys, a chain of dependent instructions with idle
@@ -612,7 +612,11 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
 // mere presence costs 0.4 to 3.7 us: up to 2048 sequences, and 64 workers up to DC_MAX_SEQ (a length would have to occur more
 // than 64 times among 16 384); nor, up to DC_MAX_SEQ, for 8 workers, whose sort is six steps.  Every portion of a longer list
 // has it.
-template <int WIDTH, bool PORTION = false, bool SKIP = PORTION>
+//
+// ALL: a worker in every lane (64 of them); otherwise any P <= WIDTH.  (33 to 63 workers, whole steps: 990 sequences on 33 36.5 -> 31.4
+// us, 9600 on 48 98.0 -> 90.2, 36 000 on 40 347 -> 303 against the rounds below with one key to a lane, which loop over single
+// rounds and leave the sort's waits empty.)
+template <int WIDTH, bool PORTION = false, bool SKIP = PORTION, bool ALL = WIDTH == WAVE>
 __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint32_t* items, int32_t max_len,
                                                  uint32_t* rows, int pitch, uint32_t* spare_word,
                                                  int32_t* worker_count, int64_t* __restrict__ shard_load,
@@ -626,14 +630,14 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
     const bool mine_exists = (int)lane < P;                       // lane k keeps worker k ...
     const uint32_t rank = net_lane(lane);                         // ... and plays this rank of the sorted order (in the general
                                                                   // rounds: rank k)
-    // WIDTH 64: P == 64.  WIDTH 8, 16 and 32: any P <= WIDTH; the keys of the lanes without a worker sort behind the
+    // Lanes without a worker: their keys sort behind the
     // workers' and must stay where they are, so what is offered to their ranks is nothing: those lanes read the
     // zero word behind the last item, round after round (a stride of their own, no instruction more per round).
-    constexpr bool SOME = WIDTH != WAVE;
+    constexpr bool SOME = !ALL;
     const bool offers = !SOME || (int)rank < P;
     const int stride = offers ? P : 0;                            // from a rank's item of one round to its item of the next
     const uint64_t everyone = P == WAVE ? ~0ull : (1ull << P) - 1ull;
-    constexpr bool EVERY_LANE = WIDTH == WAVE;
+    constexpr bool EVERY_LANE = ALL;
     constexpr int NS = net_steps(WIDTH);
     constexpr int LAST = NS - 1;                                  // the last gap of the sort (what a narrow sort has no later gap for goes there)
     constexpr uint32_t NONE = 0xFFFFFFFFu;
@@ -921,14 +925,14 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
 }
 
 // ---------------------------------------------------------------- rounds of one wave that keeps up to 256 workers
-// The packed rounds for 33 .. 63 and 65 .. 256 workers: wave 0 keeps K = 1, 2 or 4 of the sorted keys in a lane (rank
+// The packed rounds for 65 .. 256 workers: wave 0 keeps K = 2 or 4 of the sorted keys in a lane (rank
 // r * 64 + net_lane(lane) in register r; key = load << 8 | worker, rebased as above), sorts them with wave_sort_multi, and never
 // goes back from ranks to workers: a worker's number of items stands in the LDS (not at all while every worker holds the
 // same number), its load goes out when it is full or at the end.  Two kinds of round:
 //   sure     the bound of lpt_rounds_packed says that the round places one item on every worker: nothing is tested;
 //   general  the longest accepted prefix of the ranks takes its items; full workers have sorted behind the open ones.
 // Bound by the chain of sorts, of which one wave runs a step in about 20 cycles whether it carries one or two chains.
-// Up to 256 workers: 8192 sequences on 128 workers take 41 us up to perm, where with the rounds that the whole workgroup runs
+// 65 to 256 workers: 8192 sequences on 128 workers take 41 us up to perm, where with the rounds that the whole workgroup runs
 // (lpt_rounds_wide32_portion: five barriers and a bisection per 64 workers in each) the launch took 175; 25 472 sequences on 128 workers: 95 us for the assignment, a step of 632 us takes 285.  With
 // eight keys to a lane a sort is four times the work and a step of the network is no longer hidden by its neighbours.
 //
@@ -1146,11 +1150,9 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
     return pos;
 }
 
-// The rounds that serve P workers with equal partitions and lengths up to PACKED_MAX_LEN.
-__device__ __forceinline__ bool multi_serves(int P) { return (P > 32 && P < WAVE) || (P > WAVE && P <= MULTI_MAX); }
+// More than WAVE workers.
 __device__ __forceinline__ int lpt_rounds_multi_any(int N, int P, const uint32_t* items, uint32_t* rows, int pitch, int row_cap,
                                                     uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
-    if (P <= WAVE) return lpt_rounds_multi<1>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
     if (P <= 2 * WAVE) return lpt_rounds_multi<2>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
     return lpt_rounds_multi<4>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
 }
@@ -1496,7 +1498,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         lds_barrier();
         const int rpitch = row_pitch(C);
         uint32_t* const spare = reinterpret_cast<uint32_t*>(L.spare);
-        if (MANY && multi_serves(P)) {                            // (uniform)
+        if (MANY && P > WAVE) {                                   // (uniform)
             if constexpr (MANY) {
                 MultiLds& m = multi_lds(L);
                 multi_fresh(m, P, C);
@@ -1525,6 +1527,9 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                     if (P <= 2) lpt_rounds_packed<2>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                     else lpt_rounds_packed<4>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 }
+            } else if (MANY && P > 32 && P < WAVE) {
+                if constexpr (MANY)
+                    lpt_rounds_packed<64, false, false, false>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
             } else if constexpr (FEW) {
                 if (P <= 8) lpt_rounds_packed<8>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else if (P <= 16) lpt_rounds_packed<16, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);

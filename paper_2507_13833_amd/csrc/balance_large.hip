@@ -79,8 +79,8 @@ __device__ __forceinline__ void packed_portions(BalLds& L, int32_t N, int32_t P,
     for (int k = tid; k <= P; k += BAL_BLOCK) shard_seq_off[k] = k * C;
 }
 
-// Up to 32 or 64 workers: wave 0, lane k = worker k.
-template <int WIDTH>
+// Up to 64 workers: wave 0, lane k = worker k.
+template <int WIDTH, bool ALL = WIDTH == WAVE>
 __device__ __forceinline__ void packed_portions_few(BalLds& L, int32_t N, int32_t P, int32_t C, int32_t mx,
                                                     int32_t* __restrict__ shard_seq_off, int64_t* __restrict__ shard_load,
                                                     const BalanceLargeWs& ws) {
@@ -93,7 +93,7 @@ __device__ __forceinline__ void packed_portions_few(BalLds& L, int32_t N, int32_
                     [&](int n, const uint32_t* items, uint32_t* rows, int pitch, auto meanwhile) {
         if (w == 0) {
             count_before[lane] = carry.count;
-            const int done = lpt_rounds_packed<WIDTH, true>(n, P, C, items, mx, rows, pitch, reinterpret_cast<uint32_t*>(L.spare),
+            const int done = lpt_rounds_packed<WIDTH, true, true, ALL>(n, P, C, items, mx, rows, pitch, reinterpret_cast<uint32_t*>(L.spare),
                                                             worker_count, shard_load, &carry, pitch);
             if (lane == 0) *placed = done;
         } else {
@@ -104,7 +104,7 @@ __device__ __forceinline__ void packed_portions_few(BalLds& L, int32_t N, int32_
     });
 }
 
-// The other numbers of workers, up to 256: wave 0, the workers' state in the LDS.
+// 65 to 256 workers: wave 0, the workers' state in the LDS.
 __device__ __forceinline__ void packed_portions_many(BalLds& L, int32_t N, int32_t P, int32_t C,
                                                      int32_t* __restrict__ shard_seq_off, int64_t* __restrict__ shard_load,
                                                      const BalanceLargeWs& ws) {
@@ -148,11 +148,12 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_large_kernel(int32_t N, int
     const int32_t mx = ws.sorted_len[0];                          // the longest sequence comes first
 
     if (packed_rounds_apply(N, P, C, mx)) {                       // (uniform)
-        if (multi_serves(P)) packed_portions_many(L, N, P, C, shard_seq_off, shard_load, ws);
+        if (P > WAVE) packed_portions_many(L, N, P, C, shard_seq_off, shard_load, ws);
         else if (P <= 4) packed_portions_few<4>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else if (P <= 8) packed_portions_few<8>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else if (P <= 16) packed_portions_few<16>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else if (P <= 32) packed_portions_few<32>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
+        else if (P < WAVE) packed_portions_few<64, false>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         else packed_portions_few<64>(L, N, P, C, mx, shard_seq_off, shard_load, ws);
         return;
     }
