@@ -936,8 +936,8 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
 // (lpt_rounds_wide32_portion: five barriers and a bisection per 64 workers in each) the launch took 175; 25 472 sequences on 128 workers: 95 us for the assignment, a step of 632 us takes 285.  With
 // eight keys to a lane a sort is four times the work and a step of the network is no longer hidden by its neighbours.
 //
-// items, rows, pitch: as for lpt_rounds_packed.  The call returns, before all N items are placed, when a row holds
-// row_cap items.
+// items, rows, pitch: as for lpt_rounds_packed.  PORTION: the call returns, before all N items are placed, when a row holds
+// row_cap items, and the next call goes on with the rest and the workers as they are in m.
 constexpr int MULTI_MAX = 4 * WAVE;                      // workers
 constexpr int MULTI_ID_BITS = 8;
 constexpr uint32_t MULTI_ID_MASK = (1u << MULTI_ID_BITS) - 1u;
@@ -968,7 +968,7 @@ __device__ __forceinline__ void multi_fresh(MultiLds& m, int P, int C) {
     if (tid == 0) m.taken = 0;
 }
 
-template <int K>
+template <int K, bool PORTION>
 __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* items, uint32_t* rows, int pitch, int row_cap,
                                                 uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
     constexpr uint32_t NONE = 0xFFFFFFFFu;
@@ -984,9 +984,9 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
     }
     int64_t taken = m.taken;
     int pos = 0;
-    // level: every row holds c_row items; else the LDS says.  slack: items until the first worker is full (0: one is);
-    // c_hi: items of the fullest row
-    bool level = false, fresh = false;                            // fresh: slack and c_hi are as the LDS says
+    // level: every row holds c_row items; else the LDS says.  slack: items until the first worker is full, at least (0: one
+    // may be); c_hi: items of the fullest row, at most
+    bool level = false, fresh = false;                            // fresh: slack and c_hi are good enough (a count takes ~700 cycles)
     int c_row = 0, slack = 0, c_hi = 0;
     auto count_rows = [&]() {
         uint32_t hi = 0, room = NONE, room_hi = 0;
@@ -1057,6 +1057,39 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
             for (int r = 0; r < K; ++r)
                 if (sk[r] < MULTI_FULL) sk[r] -= sub;
             taken += (int64_t)(sub >> MULTI_ID_BITS);
+        }
+        // The last items: what is left goes to as many of the smallest keys at most, so one register of them is enough, and no
+        // round here is a sure one: ~1000 cycles a round instead of 4500 for four registers (1280 sequences on 256 shards end with ten
+        // such rounds, of 21 items to one).
+        if constexpr (!PORTION) {
+            if (N - pos <= WAVE) {                                // (uniform)
+                if (level) {
+#pragma unroll
+                    for (int r = 0; r < K; ++r) m.cnt[sk[r] & MULTI_ID_MASK] = c_row;
+                    level = false;
+                }
+                while (pos < N) {
+                    const bool valid = sk[0] < MULTI_FULL && pos + rl < N;
+                    const uint32_t newk = valid ? sk[0] + ((e[0] >> 16) << MULTI_ID_BITS) : NONE;
+                    const uint32_t pm = wave_excl_scan_umin(net_swap_order(newk));        // (by rank)
+                    const uint64_t acc = __ballot(net_swap_order(valid ? sk[0] : NONE) < pm);
+                    const int took = (~acc == 0ull) ? WAVE : (__ffsll((long long)~acc) - 1);
+                    if (took == 0) break;                         // cannot happen: an open worker always takes an item
+                    if (rl < took) {
+                        const uint32_t id = sk[0] & MULTI_ID_MASK;
+                        const int32_t c = m.cnt[id];
+                        rows[(int)id * pitch + c] = e[0];
+                        m.cnt[id] = c + 1;
+                        sk[0] = close_if_full(newk, c + 1);
+                    }
+                    pos += took;
+                    e[0] = items[pos + rl];                       // (zeros behind the last item)
+                    uint32_t v[1] = {sk[0]};
+                    wave_sort_multi<1>(v);
+                    sk[0] = v[0];
+                }
+                break;
+            }
         }
         if (!fresh) count_rows();
         if (c_hi >= row_cap) break;                               // a row is full: the caller empties them all
@@ -1133,7 +1166,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         c_row += 1;                                               // (if level)
         c_hi += 1;
         slack -= 1;
-        fresh = still;
+        fresh = still || (slack > 0 && c_hi < row_cap);           // (nobody took more than one)
 #pragma unroll
         for (int r = 0; r < K; ++r) e[r] = items[offers[r] ? pos + r * WAVE + rl : N];        // (zeros behind the last item)
         wave_sort_multi<K>(sk);
@@ -1151,10 +1184,11 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
 }
 
 // More than WAVE workers.
+template <bool PORTION>
 __device__ __forceinline__ int lpt_rounds_multi_any(int N, int P, const uint32_t* items, uint32_t* rows, int pitch, int row_cap,
                                                     uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
-    if (P <= 2 * WAVE) return lpt_rounds_multi<2>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
-    return lpt_rounds_multi<4>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
+    if (P <= 2 * WAVE) return lpt_rounds_multi<2, PORTION>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
+    return lpt_rounds_multi<4, PORTION>(N, P, items, rows, pitch, row_cap, spare_word, m, shard_load);
 }
 
 // The same rounds for 64 < P <= DC_MAX_SHARDS workers, run by the whole workgroup: thread k keeps
@@ -1504,7 +1538,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
                 multi_fresh(m, P, C);
                 if (tid <= P) shard_seq_off[tid] = tid * C;
                 lds_barrier();
-                if (w == 0) lpt_rounds_multi_any(N, P, items, rows, rpitch, C + 1, spare, m, shard_load);     // (a row takes a whole partition)
+                if (w == 0) lpt_rounds_multi_any<false>(N, P, items, rows, rpitch, C + 1, spare, m, shard_load);     // (a row takes a whole partition)
             }
         } else if (NARROW && P == 1) {                            // (uniform) one partition: the list is its row (1888
             // sequences, a whole step: 146 us with a round for each, 32.6 so)

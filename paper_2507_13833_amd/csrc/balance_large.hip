@@ -127,7 +127,7 @@ __device__ __forceinline__ void packed_portions_many(BalLds& L, int32_t N, int32
         }
         lds_barrier();
         if (w == 0) {
-            const int done = lpt_rounds_multi_any(n, P, items, rows, pitch, pitch, reinterpret_cast<uint32_t*>(L.spare), m, shard_load);
+            const int done = lpt_rounds_multi_any<true>(n, P, items, rows, pitch, pitch, reinterpret_cast<uint32_t*>(L.spare), m, shard_load);
             if (tid == 0) *placed = done;
         } else {
             meanwhile();

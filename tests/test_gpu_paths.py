@@ -739,3 +739,12 @@ def test_up_to_four_workers(n, shards, kind):
     w = _custom(np.minimum(lens, 2000) if kind == "tail" and n > 1000 else lens, 1, shards, 1 << 17, fields=())
     check_step(w, align=7, label=f"{n} on {shards}, {kind}, one call", two_calls=True)
     check_step(w, align=7, label=f"{n} on {shards}, {kind}")
+
+
+@pytest.mark.parametrize("kind", ["geometric", "equal", "tail"])
+@pytest.mark.parametrize("shards,per", [(65, 1), (65, 2), (66, 3), (100, 2), (127, 3), (128, 2), (129, 2), (200, 3), (255, 4), (256, 2), (256, 5), (96, 40)])
+def test_last_items_of_many_workers(shards, per, kind):
+    """More than 64 workers: the last 64 items are placed by the 64 smallest keys alone, whichever rounds come before them."""
+    lens = _lengths(kind, shards * per, np.random.default_rng(shards * per)).astype(np.int32)
+    w = _custom(lens, 1, shards, 1 << 17, fields=())
+    check_step(w, label=f"{shards} shards of {per}, {kind}", two_calls=True)
