@@ -606,7 +606,9 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
 
 // WIDTH 2 and 4: the sort of 8 lanes is six steps, that of 4 is three, of 2 one, and the list on few workers is many rounds: a
 // sure round takes 151 cycles on 8 lanes, 92 on 4; whole steps: 512 sequences on 4 shards 28.9 -> 26.8 us, 1104 on 3 47.9 -> 42.1,
-// 5352 on 3 145 -> 117.
+// 5352 on 3 145 -> 117.  Up to 8 lanes eight sure rounds make an iteration, since its branch is a larger part of them: 15 360
+// sequences on 2 shards 374.7 -> 365.1 us up to the plan, on 4 234.7 -> 223.2, on 8 151.3 -> 150.0 (512 on 4 20.2 -> 20.6, on 8
+// 24.0 -> 24.3: the first pass through the code).
 //
 // SKIP: rounds of one length are not sorted (mixed_rounds).  Not in the kernels where such rounds are rare and the code's
 // mere presence costs 0.4 to 3.7 us: up to 2048 sequences, and 64 workers up to DC_MAX_SEQ (a length would have to occur more
@@ -835,15 +837,19 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                         mixed_rounds(sure * FAST_BATCH);
                         rounds += sure * FAST_BATCH;
                     } else if (level) {
-                        int b = sure;
+                        // (b counts upwards in all of these loops: counted down, the compiler kept another counter in the
+                        // loops of every width, the code behind them moved by an instruction, and the loop of mixed_rounds on
+                        // 32 lanes began with the last instruction of a 64-byte line instead of the first: 25 cycles an
+                        // iteration, 15 360 short answers on 24 shards 84.5 -> 85.1 us up to the plan)
+                        int b = 0;
                         if constexpr (WIDTH <= 8) {
-                            for (; b >= 2; b -= 2) {              // (the loop's own branch: ten cycles a round of 90 to 150)
+                            for (; b + 2 <= sure; b += 2) {       // (the loop's own branch, see the widths above)
 #pragma unroll
                                 for (int u = 0; u < 2 * FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
                                 rounds += 2 * FAST_BATCH;
                             }
                         }
-                        for (; b > 0; --b) {
+                        for (; b < sure; ++b) {
 #pragma unroll
                             for (int u = 0; u < FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
                             rounds += FAST_BATCH;
