@@ -36,6 +36,7 @@
 
 namespace dc {
 
+template <BalWorkers W>
 __global__ __launch_bounds__(BAL_BLOCK) void balance_kernel(int32_t N, int32_t P, int32_t C,
                                                             const int32_t* __restrict__ seq_len,
                                                             int32_t* __restrict__ perm,
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_kernel(int32_t N, int32_t P
                                                             int64_t* __restrict__ shard_load,
                                                             int32_t* status) {
     __shared__ BalLds L;
-    balance_body(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status);
+    balance_body<W>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status);
 }
 
 // Balance and the group-relative advantage in ONE launch: workgroup 0 is the balance workgroup, every
@@ -64,10 +65,11 @@ struct BalanceArgs {
     int32_t* status;
 };
 
+template <BalWorkers W>
 __global__ __launch_bounds__(BAL_BLOCK) void balance_advantage_kernel(BalanceArgs b, AdvArgs a, SourceDesc sd) {
     __shared__ BalLds L;
     if (blockIdx.x == 0)
-        balance_body(L, b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq, b.shard_load, b.status);
+        balance_body<W>(L, b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq, b.shard_load, b.status);
     else
         advantage_wave(a, sd, (int64_t)(blockIdx.x - 1) * BAL_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)));
 }
@@ -79,9 +81,6 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_advantage_kernel(BalanceArg
 static_assert(BAL_BLOCK == PLAN_BLOCK && BAL_ROUNDS == PLAN_IPT, "one lane handles the same slots in both");
 constexpr size_t BAL_PLAN_LDS = sizeof(BalLds) > sizeof(PlanLds) ? sizeof(BalLds) : sizeof(PlanLds);
 
-// Which numbers of workers a kernel holds the code of, and no other's (see balance_body_t): up to 4; up to 32, or 64; 33 .. 63 or
-// 65 .. 256.  IPT: see balance_body_t.
-enum BalWorkers { WORKERS_NARROW, WORKERS_FEW, WORKERS_MANY };
 template <BalWorkers W>
 __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(BalanceArgs b, PlanArgs p, AdvArgs a, SourceDesc sd) {
     __shared__ __align__(16) unsigned char lds[BAL_PLAN_LDS];
@@ -91,8 +90,8 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_plan_advantage_kernel(Balan
     }
     constexpr int IPT = SMALL_REC_IPT;
     SlotRegs<IPT> s;
-    balance_body_t<BAL_SLOTS, W == WORKERS_NARROW, W == WORKERS_FEW, W == WORKERS_MANY, IPT>(
-        *reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, b.shard_of_seq, b.shard_load, b.status, s);
+    balance_body_t<BAL_SLOTS, W, IPT>(*reinterpret_cast<BalLds*>(lds), b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off,
+                                      b.shard_of_seq, b.shard_load, b.status, s);
     int64_t src_off[SMALL_REC_IPT];                               // (asked for here: they come while the plan runs)
 #pragma unroll
     for (int q = 0; q < SMALL_REC_IPT; ++q) src_off[q] = p.src_tok_off[min(max(s.seq[q], 0), b.N - 1)];
@@ -111,15 +110,16 @@ __global__ __launch_bounds__(BAL_BLOCK) void balance_perm_advantage_kernel(Balan
     }
     if (threadIdx.x < MB_COUNT_BYTES / sizeof(uint32_t)) mb_counts[threadIdx.x] = 0;
     SlotRegs<IPT> unused;
-    balance_body_t<BAL_PERM, W == WORKERS_NARROW, W == WORKERS_FEW, W == WORKERS_MANY, IPT>(
-        L, b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, nullptr, b.shard_load, b.status, unused);
+    balance_body_t<BAL_PERM, W, IPT>(L, b.N, b.P, b.C, b.seq_len, b.perm, b.shard_seq_off, nullptr, b.shard_load, b.status, unused);
 }
 
 hipError_t launch_balance(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
                           int32_t* d_perm, int32_t* d_shard_seq_off, int32_t* d_shard_of_seq,
                           int64_t* d_shard_load, int32_t* d_status, hipStream_t st) {
-    hipLaunchKernelGGL(balance_kernel, dim3(1), dim3(BAL_BLOCK), 0, st, n_seq, n_shards, cap_eff, d_seq_len,
-                       d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, d_status);
+    by_workers(n_seq, n_shards, cap_eff, [&](auto workers) {
+        hipLaunchKernelGGL(balance_kernel<decltype(workers)::value>, dim3(1), dim3(BAL_BLOCK), 0, st, n_seq, n_shards, cap_eff, d_seq_len,
+                           d_perm, d_shard_seq_off, d_shard_of_seq, d_shard_load, d_status);
+    });
     return hipGetLastError();
 }
 
@@ -131,17 +131,10 @@ hipError_t launch_balance_advantage(int32_t n_seq, int32_t n_shards, int32_t cap
     b.N = n_seq; b.P = n_shards; b.C = cap_eff; b.seq_len = d_seq_len; b.perm = d_perm;
     b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = d_shard_of_seq; b.shard_load = d_shard_load; b.status = d_status;
     const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
-    hipLaunchKernelGGL(balance_advantage_kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, adv, src);
+    by_workers(n_seq, n_shards, cap_eff, [&](auto workers) {
+        hipLaunchKernelGGL(balance_advantage_kernel<decltype(workers)::value>, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, adv, src);
+    });
     return hipGetLastError();
-}
-
-// Calls launch with the kind of workers there are.  (A kernel of their own for up to 4: with their rounds beside the others' in one
-// kernel the others took up to 0.6 % longer, 242.5 -> 244 us for a step of 8192 sequences on 16 shards.)
-template <typename Launch>
-static void by_workers(int32_t n_shards, Launch launch) {
-    if (n_shards <= 4) launch(std::integral_constant<BalWorkers, WORKERS_NARROW>{});
-    else if (n_shards <= 32 || n_shards == WAVE) launch(std::integral_constant<BalWorkers, WORKERS_FEW>{});
-    else launch(std::integral_constant<BalWorkers, WORKERS_MANY>{});
 }
 
 hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_t cap_eff, const int32_t* d_seq_len,
@@ -157,7 +150,7 @@ hipError_t launch_balance_plan_advantage(int32_t n_seq, int32_t n_shards, int32_
     b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = d_shard_of_seq; b.shard_load = d_shard_load; b.status = d_status;
     const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, plan, adv, src); };
-    by_workers(n_shards, [&](auto workers) { launch(balance_plan_advantage_kernel<decltype(workers)::value>); });
+    by_workers(n_seq, n_shards, cap_eff, [&](auto workers) { launch(balance_plan_advantage_kernel<decltype(workers)::value>); });
     return hipGetLastError();
 }
 
@@ -172,7 +165,7 @@ hipError_t launch_balance_advantage_perm(int32_t n_seq, int32_t n_shards, int32_
     b.shard_seq_off = d_shard_seq_off; b.shard_of_seq = nullptr; b.shard_load = d_shard_load; b.status = d_status;
     const int64_t grid = 1 + (adv_waves(n_seq, n_groups) + BAL_WAVES - 1) / BAL_WAVES;
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(BAL_BLOCK), 0, st, b, mb_counts, adv, src); };
-    by_workers(n_shards, [&](auto workers) {
+    by_workers(n_seq, n_shards, cap_eff, [&](auto workers) {
         constexpr BalWorkers W = decltype(workers)::value;
         if (n_seq <= SMALL_SORT_MAX) launch(balance_perm_advantage_kernel<W, SMALL_IPT>);
         else launch(balance_perm_advantage_kernel<W, BAL_ROUNDS>);

@@ -1434,16 +1434,30 @@ constexpr int SMALL_IPT = SMALL_SORT_MAX / BAL_BLOCK;
 // plan that follows in this workgroup.  BAL_PERM: everything but shard_of_seq, which the launch that plans by shards writes.
 enum BalTail { BAL_ALL, BAL_SLOTS, BAL_PERM };
 
-// NARROW: the code for up to 4 workers; FEW: for 5 to 32, or 64; MANY: for the other numbers of them.  TAIL other than BAL_ALL: only with
-// P * C == N.  What a launch is never made for is left out of its kernel (it is executed once from front to back, most
-// of it straight code that the instruction cache has not seen, and its size shows in its time).
+// Which numbers of workers a kernel holds the code of, and no other's: up to 4; 5 to 32, or 64 with equal partitions; the other
+// numbers of them.  (A kernel is executed once from front to back, most of it straight code that the instruction cache has not
+// seen, and its size shows in its time: beside the code for up to 4 workers a step of 8192 sequences on 16 shards took 244 us
+// instead of 242.5; with everything in one kernel dc_balance_group_advantage of 512 sequences on 32 shards 11.39 instead of 10.97,
+// dc_balance of 4097 on 2 455 instead of 423.)
+enum BalWorkers { WORKERS_NARROW, WORKERS_FEW, WORKERS_MANY };
+
+// Calls launch with the kind of workers there are.
+template <typename Launch>
+inline void by_workers(int32_t N, int32_t P, int32_t C, Launch launch) {
+    if (P <= 4) launch(std::integral_constant<BalWorkers, WORKERS_NARROW>{});
+    else if (P <= 32 || (P == WAVE && (int64_t)P * C == N)) launch(std::integral_constant<BalWorkers, WORKERS_FEW>{});
+    else launch(std::integral_constant<BalWorkers, WORKERS_MANY>{});
+}
+
+// TAIL other than BAL_ALL: only with P * C == N.  What a launch is never made for is left out of its kernel.
 // IPT: sequences per lane at most, BAL_ROUNDS, SMALL_IPT for a launch of up to SMALL_SORT_MAX sequences, or 1 (TAIL other than
 // BAL_ALL with BAL_ROUNDS: for more than SMALL_SORT_MAX).
-template <BalTail TAIL, bool NARROW, bool FEW, bool MANY, int IPT>
+template <BalTail TAIL, BalWorkers W, int IPT>
 __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, int32_t C,
                                                const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                                int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
                                                int64_t* __restrict__ shard_load, int32_t* status, SlotRegs<IPT>& slots) {
+    constexpr bool NARROW = W == WORKERS_NARROW, FEW = W == WORKERS_FEW, MANY = W == WORKERS_MANY;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
 
     // every partition ends with exactly C items (Algorithm 1 as printed: C = N / K): rows per worker
@@ -1644,17 +1658,16 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         int32_t* spare = L.spare;
         LptCarry fresh = lpt_fresh(P, C);
         int n_placed = 0;
-        if constexpr (NARROW && !FEW) {
+        if constexpr (NARROW) {
             n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
         } else if constexpr (FEW) {
             if (exact && P == 16) n_placed = lpt_rounds<16, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (exact && P == 32) n_placed = lpt_rounds<32, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (exact) n_placed = lpt_rounds<64, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (P <= 16) n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-            else if (P <= 32) n_placed = lpt_rounds<32>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        }
-        if constexpr (MANY) {
-            if (P > 32 && !(FEW && exact)) n_placed = lpt_rounds<64>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else n_placed = lpt_rounds<32>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+        } else {
+            n_placed = lpt_rounds<64>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
         }
         // start of every P_k inside perm
         const int32_t c = worker_count[lane];
@@ -1714,12 +1727,13 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     }
 }
 
+template <BalWorkers W>
 __device__ __forceinline__ void balance_body(BalLds& L, int32_t N, int32_t P, int32_t C,
                                              const int32_t* __restrict__ seq_len, int32_t* __restrict__ perm,
                                              int32_t* __restrict__ shard_seq_off, int32_t* __restrict__ shard_of_seq,
                                              int64_t* __restrict__ shard_load, int32_t* status) {
     SlotRegs<BAL_ROUNDS> unused;
-    balance_body_t<BAL_ALL, true, true, true, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
+    balance_body_t<BAL_ALL, W, BAL_ROUNDS>(L, N, P, C, seq_len, perm, shard_seq_off, shard_of_seq, shard_load, status, unused);
 }
 
 }  // namespace dc

@@ -748,3 +748,15 @@ def test_last_items_of_many_workers(shards, per, kind):
     lens = _lengths(kind, shards * per, np.random.default_rng(shards * per)).astype(np.int32)
     w = _custom(lens, 1, shards, 1 << 17, fields=())
     check_step(w, label=f"{shards} shards of {per}, {kind}", two_calls=True)
+
+
+@pytest.mark.parametrize("kind", ["geometric", "long"])
+@pytest.mark.parametrize("shards", [1, 4, 5, 16, 17, 32, 33, 63, 64, 65, 256])
+def test_balance_calls_of_their_own(shards, kind):
+    """dc_balance and dc_balance_group_advantage at the ends of their kernels' ranges of workers, equal partitions and unequal ones
+    (64 workers: two kernels)."""
+    rng = np.random.default_rng(7 * shards)
+    for n, cap in ((shards * 7, 0), (2048 // shards * shards, 0), (2049 // shards * shards + (shards > 1), 2049 // shards + 3)):
+        lens = _lengths(kind, n, rng).astype(np.int32)
+        _check_balance_ws(lens, shards, cap=cap, label=f"{n} on {shards}, {kind}, cap {cap}")
+        check_step(_custom(lens, 1, shards, 1 << 17, fields=()), cap=cap, align=7, fused=True, label=f"{n} on {shards}, {kind}, cap {cap}")
