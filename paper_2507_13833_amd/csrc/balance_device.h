@@ -368,6 +368,17 @@ __device__ __forceinline__ void small_sort_packed(BalLds& L, int N, const int32_
     }
 }
 
+// What follows begins at a multiple of 32 bytes, so that a loop's place in the blocks in which instructions are fetched does not
+// depend on the code in front of it: a loop of rounds with only an instruction or two of its own in its first block takes ten to
+// twenty cycles a round more, and changes to the rounds of other widths had moved it there.  Used where a loop's place showed, in the
+// kernels of dc_balance, dc_balance_group_advantage and dc_balance_ws; not in those that plan as well: general rounds are rare there
+// (lengths of 2^16 and more), and the bytes cost the packed rounds what they gave (15 360 short answers on 24 shards, up to the plan:
+// 100.6 -> 101.4 us).
+template <bool PIN>
+__device__ __forceinline__ void pin_code() {
+    if constexpr (PIN) asm volatile(".p2align 5");
+}
+
 // The assignment rounds (wave 0 only).  WIDTH = 16, 32 or 64 >= P lanes take part in the sort.
 // pitch == 0: step_slot[t] = place of item I[t] inside its worker's partition; pitch > 0 (every
 // partition will hold exactly C items): step_slot[k * pitch + c] = the c-th item of worker k.
@@ -395,7 +406,11 @@ __device__ __forceinline__ LptCarry lpt_fresh(int P, int C) {
 
 // TIGHT: P == WIDTH and pitch > 0 (the printed algorithm on 16, 32 or 64 workers): the rounds in which every
 // worker takes an item drop the selects that the general case needs.
-template <int WIDTH, bool TIGHT = false>
+//
+// PIN: see pin_code.  4097 sequences on 2 shards, unequal partitions: 455.2 us with the loop of the rounds in which everyone takes an
+// item 24 bytes behind a multiple of 32, 445.0 at 16, 437.6 at 20, 434.8 at 8, where it stands pinned (with a kernel of their own for
+// up to 4 workers: 423.4, pinned 399.7).
+template <int WIDTH, bool PIN, bool TIGHT = false>
 __device__ __forceinline__ int lpt_rounds(int N, int P, int C, int32_t* keys, const uint16_t* sorted,
                                           int32_t max_len, uint16_t* step_slot, int pitch, int32_t* spare_word,
                                           int32_t* worker_count, int64_t* __restrict__ shard_load, LptCarry& carry) {
@@ -440,7 +455,7 @@ __device__ __forceinline__ int lpt_rounds(int N, int P, int C, int32_t* keys, co
             uint32_t idx1 = sorted[min(pos + P + (int)lane, N - 1)];
             // every LDS read issued so far is waited for here, outside the loop: a wait left to the loop's
             // first use would sit in the loop and also wait, every round, for the stores of the round before
-            asm volatile("" : "+v"(idx1), "+v"(s), "+v"(idx));
+            if constexpr (!PIN) asm volatile("" : "+v"(idx1), "+v"(s), "+v"(idx));
             // The two LDS stores that record a round's placements are issued at the top of the NEXT round,
             // behind that round's reads.  LDS operations retire through one in-order counter and the compiler
             // waits for "everything" at the loop's joins, so a round's first wait also waits for the stores
@@ -449,6 +464,7 @@ __device__ __forceinline__ int lpt_rounds(int N, int P, int C, int32_t* keys, co
             uint32_t st_slot = DC_MAX_SEQ + PLACE_PAD - 1, st_val = 0, st_id = 0;      // nothing to record yet
             int32_t* st_key = spare_word;
             const int n_rounds = min(avail, (N - pos) / P);       // >= 1: until a worker is full or the items run out
+            if constexpr (PIN) asm volatile(".p2align 5" : "+v"(idx1), "+v"(s), "+v"(idx));
             while (rounds < n_rounds) {
                 if (__builtin_expect(--until_check == 0, 0)) {    // uniform; first, so that the rest of the round is one
                     until_check = check_every;                    // straight run of instructions for the scheduler
@@ -615,10 +631,13 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
 // than 64 times among 16 384); nor, up to DC_MAX_SEQ, for 8 workers, whose sort is six steps.  Every portion of a longer list
 // has it.
 //
+// PIN: see pin_code (dc_balance_group_advantage, 15 360 sequences on 4 shards 200.3 -> 197.4 us, dc_balance on 2 329.0 -> 325.6, on 16
+// 97.2 -> 96.8).
+//
 // ALL: a worker in every lane (64 of them); otherwise any P <= WIDTH.  (33 to 63 workers, whole steps: 990 sequences on 33 36.5 -> 31.4
 // us, 9600 on 48 98.0 -> 90.2, 36 000 on 40 347 -> 303 against the rounds below with one key to a lane, which loop over single
 // rounds and leave the sort's waits empty.)
-template <int WIDTH, bool PORTION = false, bool SKIP = PORTION, bool ALL = WIDTH == WAVE>
+template <int WIDTH, bool PORTION = false, bool SKIP = PORTION, bool ALL = WIDTH == WAVE, bool PIN = false>
 __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint32_t* items, int32_t max_len,
                                                  uint32_t* rows, int pitch, uint32_t* spare_word,
                                                  int32_t* worker_count, int64_t* __restrict__ shard_load,
@@ -725,6 +744,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                     const int m = min(n - done, WAVE);            // (a multiple of FAST_BATCH)
                     const int at = min(pos + (done + (int)lane) * P, N - P);      // (lane i: the i-th round of these)
                     uint64_t one_length = __ballot((items[at] ^ items[at + P - 1]) < 0x10000u);
+                    pin_code<PIN>();
                     for (int r = rounds + done; r < rounds + done + m; r += FAST_BATCH, one_length >>= FAST_BATCH) {
 #pragma unroll
                         for (int u = 0; u < FAST_BATCH; ++u) {
@@ -843,6 +863,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                         // iteration, 15 360 short answers on 24 shards 84.5 -> 85.1 us up to the plan)
                         int b = 0;
                         if constexpr (WIDTH <= 8) {
+                            pin_code<PIN>();
                             for (; b + 2 <= sure; b += 2) {       // (the loop's own branch, see the widths above)
 #pragma unroll
                                 for (int u = 0; u < 2 * FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
@@ -978,6 +999,9 @@ template <int K, bool PORTION>
 __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* items, uint32_t* rows, int pitch, int row_cap,
                                                 uint32_t* spare_word, MultiLds& m, int64_t* __restrict__ shard_load) {
     constexpr uint32_t NONE = 0xFFFFFFFFu;
+    // The loops of sure rounds are pinned (see pin_code): 65 520 sequences on 65 shards 467.3 us, 470.5 at 16
+    // or 24 behind it.  Four registers' loops are twice as long and show nothing, and in one launch the bytes cost what they gave.
+    constexpr bool PIN = PORTION && K == 2;
     const int lane = threadIdx.x;                                 // (wave 0)
     const int rl = (int)net_lane(lane);                           // register r of this lane holds rank r * 64 + rl
     uint32_t sk[K], e[K];
@@ -1025,6 +1049,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         constexpr bool LEVEL = decltype(level_c)::value;
         uint32_t v[K], e1[K];
         int32_t c[K];
+        if constexpr (PIN) asm("" : "+v"(e[0]), "+v"(e[K - 1]));  // (one wait for both)
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             v[r] = sk[r] + ((e[r] >> 16) << MULTI_ID_BITS);
@@ -1117,8 +1142,10 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
         }
         if (sure > 0) {
             if (level) {
+                pin_code<PIN>();
                 for (int b = 0; b < sure; ++b) sure_round(std::true_type{});
             } else {
+                pin_code<PIN>();
                 for (int b = 0; b < sure; ++b) sure_round(std::false_type{});
                 if (slack == 0) {                                 // (level: everyone is full together, behind the last item)
 #pragma unroll
@@ -1223,7 +1250,9 @@ __device__ __forceinline__ WideCarry wide_fresh(int P, int C) {
     return c;
 }
 
-// The rounds over the N items of one portion.  Returns the number of items placed.
+// The rounds over the N items of one portion.  Returns the number of items placed.  PIN: see pin_code (20 000 sequences on 200
+// shards, one of 70 000 tokens: 1409 us with the loop over the keys 24 bytes behind a multiple of 32, 1370 with it up to 16).
+template <bool PIN>
 __device__ __forceinline__ int lpt_rounds_wide_portion(BalLds& L, int N, int P, int C, const uint16_t* sorted,
                                                        uint16_t* step_slot, WideCarry& carry) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
@@ -1240,6 +1269,7 @@ __device__ __forceinline__ int lpt_rounds_wide_portion(BalLds& L, int N, int P, 
         // my rank = keys below mine (keys are distinct: the worker id sits in the low bits)
         if (tid < P) {
             int rank = 0;
+            pin_code<PIN>();
             for (int j = 0; j < P; ++j) rank += kbuf[j] < key ? 1 : 0;
             sbuf[rank] = key;
         }
@@ -1410,12 +1440,13 @@ __device__ __forceinline__ void lpt_wide_finish(BalLds& L, int N, int P, const W
     if (tid == 0) { part_off[P] = total; shard_seq_off[P] = N; }
 }
 
+template <bool PIN>
 __device__ __forceinline__ int lpt_rounds_wide(BalLds& L, int N, int P, int C, const uint16_t* sorted, uint16_t* step_slot,
                                                int32_t max_len, int32_t* __restrict__ shard_seq_off,
                                                int64_t* __restrict__ shard_load) {
     WideCarry carry = wide_fresh(P, C);
     const int placed = (uint32_t)max_len <= PACKED_MAX_LEN ? lpt_rounds_wide32_portion(L, N, P, C, sorted, step_slot, carry)
-                                                           : lpt_rounds_wide_portion(L, N, P, C, sorted, step_slot, carry);
+                                                           : lpt_rounds_wide_portion<PIN>(L, N, P, C, sorted, step_slot, carry);
     lpt_wide_finish(L, N, P, carry, shard_seq_off, shard_load);
     return placed;
 }
@@ -1466,6 +1497,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     const bool tight = equal && P <= MULTI_MAX;                             // what the packed rounds serve
     const bool exact = pitch != 0 && (P == 16 || P == 32 || P == 64);      // a worker in every lane of a 16-, 32- or 64-lane sort
     constexpr bool FILL = TAIL == BAL_SLOTS;
+    constexpr bool PIN = TAIL == BAL_ALL;
     const bool small = IPT <= SMALL_IPT || (TAIL == BAL_ALL && N <= SMALL_SORT_MAX);      // (uniform)
     if (tight && !small) bin_sort_clear(L);                       // (the barrier below stands between this and the bins' use)
 
@@ -1578,15 +1610,15 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             int32_t* worker_count = reinterpret_cast<int32_t*>(L.cnt) + WCOUNT_AT;
             if (NARROW && P <= 4) {
                 if constexpr (NARROW) {
-                    if (P <= 2) lpt_rounds_packed<2>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-                    else lpt_rounds_packed<4>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                    if (P <= 2) lpt_rounds_packed<2, false, false, false, PIN>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                    else lpt_rounds_packed<4, false, false, false, PIN>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 }
             } else if (MANY && P > 32 && P < WAVE) {
                 if constexpr (MANY)
                     lpt_rounds_packed<64, false, false, false>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
             } else if constexpr (FEW) {
                 if (P <= 8) lpt_rounds_packed<8>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
-                else if (P <= 16) lpt_rounds_packed<16, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
+                else if (P <= 16) lpt_rounds_packed<16, false, (IPT > 2), false, PIN>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else if (P <= 32) lpt_rounds_packed<32, false, (IPT > 2)>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
                 else lpt_rounds_packed<64>(N, P, C, items, mx, rows, rpitch, spare, worker_count, shard_load);
             }
@@ -1650,7 +1682,7 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
     // ---- b) assignment rounds: wave 0 for up to 64 workers, else the whole workgroup ----
     if (MANY && P > WAVE) {
         if constexpr (MANY) {
-            const int n_placed = lpt_rounds_wide(L, N, P, C, sorted, step_slot, mx, shard_seq_off, shard_load);
+            const int n_placed = lpt_rounds_wide<PIN>(L, N, P, C, sorted, step_slot, mx, shard_seq_off, shard_load);
             if (tid == 0) *placed = n_placed;
         }
     } else if (w == 0) {
@@ -1659,15 +1691,15 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
         LptCarry fresh = lpt_fresh(P, C);
         int n_placed = 0;
         if constexpr (NARROW) {
-            n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            n_placed = lpt_rounds<16, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
         } else if constexpr (FEW) {
-            if (exact && P == 16) n_placed = lpt_rounds<16, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-            else if (exact && P == 32) n_placed = lpt_rounds<32, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-            else if (exact) n_placed = lpt_rounds<64, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-            else if (P <= 16) n_placed = lpt_rounds<16>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-            else n_placed = lpt_rounds<32>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            if (exact && P == 16) n_placed = lpt_rounds<16, PIN, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (exact && P == 32) n_placed = lpt_rounds<32, PIN, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (exact) n_placed = lpt_rounds<64, PIN, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (P <= 16) n_placed = lpt_rounds<16, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else n_placed = lpt_rounds<32, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
         } else {
-            n_placed = lpt_rounds<64>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            n_placed = lpt_rounds<64, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
         }
         // start of every P_k inside perm
         const int32_t c = worker_count[lane];

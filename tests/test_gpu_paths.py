@@ -760,3 +760,24 @@ def test_balance_calls_of_their_own(shards, kind):
         lens = _lengths(kind, n, rng).astype(np.int32)
         _check_balance_ws(lens, shards, cap=cap, label=f"{n} on {shards}, {kind}, cap {cap}")
         check_step(_custom(lens, 1, shards, 1 << 17, fields=()), cap=cap, align=7, fused=True, label=f"{n} on {shards}, {kind}, cap {cap}")
+
+
+@pytest.mark.parametrize("shards", [2, 3, 4, 33, 40, 63])
+def test_packed_keys_rebased_at_the_narrow_widths_and_with_idle_lanes(shards):
+    """More than 2^24 tokens to a worker, so that its key passes 2^30 inside the packed rounds: sorts of two and four lanes, and 64 lanes
+    of which some keep no worker, whose keys must stay where they are; in one launch and in portions."""
+    rng = np.random.default_rng(shards)
+    for per in (16384 // shards, 33000 // shards + 1):
+        _check_balance_ws(rng.integers(40000, 65536, shards * per), shards, label=f"{shards} workers, {per} long sequences each")
+
+
+@pytest.mark.parametrize("shards", [33, 40, 63])
+@pytest.mark.parametrize("copies", [1.5, 70.0])
+def test_rounds_of_one_length_with_idle_lanes(shards, copies):
+    """33 to 63 workers: rounds that need no sort, which only the kernel that works in portions leaves unsorted."""
+    rng = np.random.default_rng(int(10 * copies) + shards)
+    for n in (2049, 16384, 33000):
+        per = n // shards + (n != 16384)
+        values = max(1, int(per / copies))
+        lens = (40 + rng.integers(0, values, per * shards)).astype(np.int32)
+        _check_balance_ws(lens, shards, label=f"{per * shards} on {shards} shards, {values} lengths")
