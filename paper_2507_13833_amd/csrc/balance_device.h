@@ -632,7 +632,7 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
 // has it.
 //
 // PIN: see pin_code (dc_balance_group_advantage, 15 360 sequences on 4 shards 200.3 -> 197.4 us, dc_balance on 2 329.0 -> 325.6, on 16
-// 97.2 -> 96.8).
+// 97.2 -> 96.8; portions: 65 535 on 5 985.3 -> 970.1, 65 536 on 16 290.6 -> 288.2).
 //
 // ALL: a worker in every lane (64 of them); otherwise any P <= WIDTH.  (33 to 63 workers, whole steps: 990 sequences on 33 36.5 -> 31.4
 // us, 9600 on 48 98.0 -> 90.2, 36 000 on 40 347 -> 303 against the rounds below with one key to a lane, which loop over single

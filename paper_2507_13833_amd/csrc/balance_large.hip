@@ -93,7 +93,7 @@ __device__ __forceinline__ void packed_portions_few(BalLds& L, int32_t N, int32_
                     [&](int n, const uint32_t* items, uint32_t* rows, int pitch, auto meanwhile) {
         if (w == 0) {
             count_before[lane] = carry.count;
-            const int done = lpt_rounds_packed<WIDTH, true, true, ALL>(n, P, C, items, mx, rows, pitch, reinterpret_cast<uint32_t*>(L.spare),
+            const int done = lpt_rounds_packed<WIDTH, true, true, ALL, true>(n, P, C, items, mx, rows, pitch, reinterpret_cast<uint32_t*>(L.spare),
                                                             worker_count, shard_load, &carry, pitch);
             if (lane == 0) *placed = done;
         } else {
