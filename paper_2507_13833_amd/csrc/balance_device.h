@@ -628,8 +628,9 @@ __device__ __forceinline__ PackedCarry packed_fresh(int P, int C) {
 //
 // SKIP: rounds of one length are not sorted (mixed_rounds).  Not in the kernels where such rounds are rare and the code's
 // mere presence costs 0.4 to 3.7 us: up to 2048 sequences, and 64 workers up to DC_MAX_SEQ (a length would have to occur more
-// than 64 times among 16 384); nor, up to DC_MAX_SEQ, for 8 workers, whose sort is six steps.  Every portion of a longer list
-// has it.
+// than 64 times among 16 384); nor, up to DC_MAX_SEQ, for 2 to 8 workers, whose sort is one, three or six steps, and for 33 to 63,
+// which run as 64 do (above 2048 sequences not timed: a length would have to occur more than 33 to 63 times).  Every portion
+// of a longer list has it.
 //
 // PIN: see pin_code (dc_balance_group_advantage, 15 360 sequences on 4 shards 200.3 -> 197.4 us, dc_balance on 2 329.0 -> 325.6, on 16
 // 97.2 -> 96.8; portions: 65 535 on 5 985.3 -> 970.1, 65 536 on 16 290.6 -> 288.2).
@@ -744,6 +745,10 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                     const int m = min(n - done, WAVE);            // (a multiple of FAST_BATCH)
                     const int at = min(pos + (done + (int)lane) * P, N - P);      // (lane i: the i-th round of these)
                     uint64_t one_length = __ballot((items[at] ^ items[at + P - 1]) < 0x10000u);
+                    // (32 lanes: 4 bytes in front of the loop and 28 behind it.  Without them the loop begins with the last instruction
+                    // of a 32-byte block, 25 cycles an iteration: 15 360 short answers on 24 shards, up to the plan, 101.9 us instead
+                    // of 101.1; with the code behind moved by the 4 alone 16 lanes took 105.4 to 105.9 instead of 105.2.)
+                    if constexpr (WIDTH == 32) asm volatile("s_nop 0");
                     pin_code<PIN>();
                     for (int r = rounds + done; r < rounds + done + m; r += FAST_BATCH, one_length >>= FAST_BATCH) {
 #pragma unroll
@@ -760,6 +765,7 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                         }
                     }
                 }
+                if constexpr (WIDTH == 32) asm volatile("s_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0");
             };
             // One round with the exact test (every rank's key below the smallest updated key of the ranks before
             // it); false, and nothing changed but refused_acc, if it does not stand.  The row entry is written before
@@ -857,20 +863,16 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
                         mixed_rounds(sure * FAST_BATCH);
                         rounds += sure * FAST_BATCH;
                     } else if (level) {
-                        // (b counts upwards in all of these loops: counted down, the compiler kept another counter in the
-                        // loops of every width, the code behind them moved by an instruction, and the loop of mixed_rounds on
-                        // 32 lanes began with the last instruction of a 64-byte line instead of the first: 25 cycles an
-                        // iteration, 15 360 short answers on 24 shards 84.5 -> 85.1 us up to the plan)
-                        int b = 0;
+                        int b = sure;
                         if constexpr (WIDTH <= 8) {
                             pin_code<PIN>();
-                            for (; b + 2 <= sure; b += 2) {       // (the loop's own branch, see the widths above)
+                            for (; b >= 2; b -= 2) {              // (the loop's own branch, see the widths above)
 #pragma unroll
                                 for (int u = 0; u < 2 * FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
                                 rounds += 2 * FAST_BATCH;
                             }
                         }
-                        for (; b < sure; ++b) {
+                        for (; b > 0; --b) {
 #pragma unroll
                             for (int u = 0; u < FAST_BATCH; ++u) sure_round(rounds + u, std::true_type{});
                             rounds += FAST_BATCH;
@@ -963,8 +965,9 @@ __device__ __forceinline__ int lpt_rounds_packed(int N, int P, int C, const uint
 // (lpt_rounds_wide32_portion: five barriers and a bisection per 64 workers in each) the launch took 175; 25 472 sequences on 128 workers: 95 us for the assignment, a step of 632 us takes 285.  With
 // eight keys to a lane a sort is four times the work and a step of the network is no longer hidden by its neighbours.
 //
-// items, rows, pitch: as for lpt_rounds_packed.  PORTION: the call returns, before all N items are placed, when a row holds
-// row_cap items, and the next call goes on with the rest and the workers as they are in m.
+// items, rows, pitch: as for lpt_rounds_packed.  PORTION: the call returns, before all N items are placed, when a row may hold
+// row_cap items (it goes by a bound that can be a few too high after general rounds: a portion then ends a little early, which no
+// batch tried has shown), and the next call goes on with the rest and the workers as they are in m.
 constexpr int MULTI_MAX = 4 * WAVE;                      // workers
 constexpr int MULTI_ID_BITS = 8;
 constexpr uint32_t MULTI_ID_MASK = (1u << MULTI_ID_BITS) - 1u;
@@ -1123,7 +1126,7 @@ __device__ __forceinline__ int lpt_rounds_multi(int N, int P, const uint32_t* it
             }
         }
         if (!fresh) count_rows();
-        if (c_hi >= row_cap) break;                               // a row is full: the caller empties them all
+        if (c_hi >= row_cap) break;                               // a row may be full: the caller empties them all
         // how many rounds does the bound cover?  Lane i looks at the last item of the (i + 1)-th round from here.
         const int may = min(min(slack, row_cap - c_hi), (N - pos) / P);
         int sure = 0;
@@ -1697,9 +1700,10 @@ __device__ __forceinline__ void balance_body_t(BalLds& L, int32_t N, int32_t P, 
             else if (exact && P == 32) n_placed = lpt_rounds<32, PIN, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (exact) n_placed = lpt_rounds<64, PIN, true>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
             else if (P <= 16) n_placed = lpt_rounds<16, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-            else n_placed = lpt_rounds<32, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
-        } else {
-            n_placed = lpt_rounds<64, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+            else if (P <= 32) n_placed = lpt_rounds<32, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
+        }
+        if constexpr (MANY) {
+            if (P > 32) n_placed = lpt_rounds<64, PIN>(N, P, C, L.keys, sorted, mx, step_slot, pitch, spare, worker_count, shard_load, fresh);
         }
         // start of every P_k inside perm
         const int32_t c = worker_count[lane];

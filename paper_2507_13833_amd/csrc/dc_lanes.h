@@ -123,7 +123,7 @@ __device__ __forceinline__ uint32_t bitonic_sort_levels(uint32_t v) {
     return v;
 }
 
-// Bitonic sort of each aligned group of WIDTH lanes (WIDTH = 16, 32, 64): even groups
+// Bitonic sort of each aligned group of WIDTH lanes (WIDTH = 2, 4, ... 64): even groups
 // come out ascending (lane r of group 0 ends with the r-th smallest of lanes
 // 0..WIDTH-1), odd groups descending.  Keys need not be distinct.
 template <int WIDTH>
