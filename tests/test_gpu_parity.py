@@ -674,8 +674,8 @@ def test_seeded_random_shapes_of_the_balance():
 
 
 def test_seeded_random_shapes_with_fewer_workers_than_lanes():
-    """Twenty-five drawn batches of Algorithm 1 as printed on 1 to 32 workers: the packed rounds on an 8-, 16- or
-    32-lane sort whose upper lanes have no worker, batches from one item per worker to the LDS limit, heavy ties,
+    """Twenty-five drawn batches of Algorithm 1 as printed on 1 to 32 workers: the packed rounds on a sort
+    of 2 to 32 lanes whose upper lanes have no worker, batches from one item per worker to the LDS limit, heavy ties,
     long tails, and a length of 2^16 or more (the general rounds with the same layout)."""
     torch, binding, runner = _gpu()
     rng = np.random.default_rng(2026)

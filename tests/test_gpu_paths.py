@@ -41,7 +41,8 @@ def _lengths(kind, n, rng):
 @pytest.mark.parametrize("kind", ["geometric", "tail", "equal", "long"])
 @pytest.mark.parametrize("shards", [33, 48, 63, 65, 96, 127, 128, 129, 200, 255, 256, 257])
 def test_one_wave_with_up_to_256_workers(shards, kind):
-    """One, two and four keys to a lane, with and without lanes that keep no worker, plan in the same launch up to 256."""
+    """33 to 63 workers on a sort of 64 lanes, above 64 two and four keys to a lane, with and without lanes that keep no worker, plan in
+    the same launch up to 256."""
     rng = np.random.default_rng(shards)
     for per in (1, 2, 21) if kind != "tail" else (3, 16384 // shards):
         lens = _lengths(kind, shards * per, rng).astype(np.int32)
